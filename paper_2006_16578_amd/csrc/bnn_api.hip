@@ -444,9 +444,7 @@ int bnn_bmm_general_f32(const float* A, const float* B, float* C, int M, int N, 
     uint32_t* Ab = static_cast<uint32_t*>(workspace);
     uint32_t* Bb = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + align256((size_t)M * ldw * 4));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    int rc = launch_sign_pack_f32(A, Ab, M, K, lda, ldw, s);
-    if (rc != BNN_OK) return rc;
-    rc = launch_sign_pack_f32(B, Bb, N, K, ldb, ldw, s);
+    const int rc = launch_sign_pack2_f32(A, Ab, M, lda, B, Bb, N, ldb, K, ldw, s);
     if (rc != BNN_OK) return rc;
     return bmm_common(Ab, Bb, reinterpret_cast<int32_t*>(C), nullptr, nullptr, M, N, K, ldw, ldw, ldc, 0, BNN_PATH_AUTO, stream, true);
 }
@@ -468,9 +466,7 @@ int bnn_bconv_general_f32(const float* in, const float* filt, float* out, int N,
     uint32_t* xb = static_cast<uint32_t*>(workspace);
     uint32_t* fb = reinterpret_cast<uint32_t*>(static_cast<char*>(workspace) + align256((size_t)N * H * W * cw * 4));
     hipStream_t s = static_cast<hipStream_t>(stream);
-    int rc = launch_sign_pack_f32(in, xb, (long long)N * H * W, C, C, cw, s);
-    if (rc != BNN_OK) return rc;
-    rc = launch_sign_pack_f32(filt, fb, (long long)O * k * k, C, C, cw, s);
+    const int rc = launch_sign_pack2_f32(in, xb, (long long)N * H * W, C, filt, fb, (long long)O * k * k, C, C, cw, s);
     if (rc != BNN_OK) return rc;
     return bconv_common(xb, fb, reinterpret_cast<int32_t*>(out), nullptr, nullptr, nullptr, N, H, W, C, O, k, stride, pad, pad_mode,
                         BNN_PATH_AUTO, stream, nullptr, nullptr, nullptr, 0, 0, 0, 1, false, true);

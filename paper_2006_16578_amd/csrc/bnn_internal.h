@@ -150,6 +150,8 @@ int launch_threshold_pack(const int32_t* X, const int32_t* thr, uint32_t* bits, 
                           int ldx, int ldb_w, hipStream_t s);
 int launch_pack_u8(const uint8_t* x, int thr, uint32_t* bits, long long rows, int cols, int ldb_w, hipStream_t s);
 int launch_sign_pack_f32(const float* x, uint32_t* bits, long long rows, int cols, int ldx, int ldb_w, hipStream_t s);
+int launch_sign_pack2_f32(const float* x0, uint32_t* bits0, long long rows0, int ldx0, const float* x1, uint32_t* bits1, long long rows1,
+                          int ldx1, int cols, int ldb_w, hipStream_t s);
 int launch_tile_b(const uint32_t* B, uint32_t* Bt, int N, int ldb_w, hipStream_t s);
 int launch_panels_from_rows(const uint32_t* X, uint32_t* Xp, long long rows, int K, int ldx_w, hipStream_t s);
 int launch_rows_from_panels(const uint32_t* Xp, uint32_t* X, long long rows, int K, int ldx_w, hipStream_t s);

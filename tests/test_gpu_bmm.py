@@ -215,6 +215,22 @@ def test_threshold_pack_and_packs(bnn, orc):
         assert np.array_equal(host(bnn.unpack_i32(to_dev(bits), cols)), orc.unpack_pm1(bits, cols).astype(np.int32))
 
 
+@pytest.mark.parametrize("rows,cols,ld", [(7, 3, 1), (9, 4, 2), (3, 16, 1), (5, 17, 3), (70, 33, 2), (66, 127, 4), (65, 784, 28),
+                                          (4201, 1000, 32), (1100, 4096, 128), (131075, 29, 1)])
+def test_packs_at_row_ends(bnn, orc, rows, cols, ld):
+    # rows shorter than a load, rows that end inside one, pad words, and the form with many loads in flight (from 131072 words)
+    rng = np.random.default_rng(rows + cols)
+    X = rng.integers(-50, 51, size=(rows, cols)).astype(np.int32)
+    tau = rng.integers(-20, 21, size=cols).astype(np.int32)
+    assert np.array_equal(words(bnn.threshold_pack(to_dev(X), to_dev(tau), ldb_w=ld)), orc.threshold_pack(X, tau, ldb_w=ld))
+    x8 = rng.integers(0, 256, size=(rows, cols)).astype(np.uint8)
+    assert np.array_equal(words(bnn.pack_u8(to_dev(x8), 127, ldb_w=ld)), orc.pack_u8(x8, 127, ldb_w=ld))
+    xf = rng.normal(size=(rows, cols)).astype(np.float32)
+    xf[0, 0], xf[rows - 1, cols - 1] = np.nan, np.inf        # NaN compares false
+    ref = orc.pack_f32(np.nan_to_num(xf, nan=-1.0), np.zeros(cols, np.float32), ldb_w=ld)
+    assert np.array_equal(words(bnn.sign_pack_f32(to_dev(xf), ldb_w=ld)), ref)
+
+
 def test_error_codes(bnn):
     A = torch.zeros((4, 4), dtype=torch.int32, device="cuda")
     with pytest.raises(bnn.BnnError) as e:
