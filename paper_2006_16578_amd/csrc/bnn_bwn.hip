@@ -17,7 +17,7 @@
 // (caller's workspace); every workgroup copies its channel tile to LDS with plain 16-byte loads and reads
 // one 16-byte unit per MFMA operand.
 //
-// Two kernels:
+// Three kernels; small windows of 3-channel images take the one of bnn_bwn_pixel.hip.  Here:
 //  * LDS-staged (default).  A workgroup owns a rectangle of output pixels of one image.  It loads the
 //    input patch under that rectangle once with coalesced loads, splits every value once, and keeps the
 //    three bf16 planes in LDS ([plane][patch row][pixel][Cp], Cp = C padded so that a pixel step is a
@@ -663,10 +663,9 @@ bool staged_geom(int MT, int NT, int WAVES, int N, int H, int W, int C, int O, i
 
 template <int MT, int NT, int WAVES, int CIN, bool WANT_Y>
 int launch_bwn_staged_v(const float* x, const uint32_t* wbits, const float* thr, float* y, uint32_t* bits, int N, int C, int O,
-                      int k, const BwnTile& g, size_t lds_bytes, void* workspace, size_t workspace_bytes, hipStream_t s) {
+                      int k, const BwnTile& g, size_t lds_bytes, void* workspace, hipStream_t s) {
     constexpr int COLS = NT * 32;
     const int col_tiles = (int)cdiv(O, COLS);
-    if (workspace_bytes < (size_t)g.wbytes * col_tiles) return BNN_ERR_WORKSPACE;
     if (lds_bytes > 64 * 1024) {
         static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bwn_staged_kernel<MT, NT, WAVES, CIN, WANT_Y>),
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
@@ -684,12 +683,15 @@ int launch_bwn_staged_v(const float* x, const uint32_t* wbits, const float* thr,
 template <int MT, int NT, int WAVES>
 int launch_bwn_staged(const float* x, const uint32_t* wbits, const float* thr, float* y, uint32_t* bits, int N, int C, int O,
                       int k, const BwnTile& g, size_t lds_bytes, void* workspace, size_t workspace_bytes, hipStream_t s) {
+    if (workspace_bytes < (size_t)g.wbytes * cdiv(O, NT * 32)) return BNN_ERR_WORKSPACE;
+    int rc = BNN_OK;
+    if (try_bwn_pixel(x, wbits, thr, y, bits, N, g.H, g.W, C, O, k, g.stride, g.pad, g.P, g.Q, s, &rc)) return rc;
     // the fp32 sums are a test / debugging output: only the generic-channel variant carries them
     if (y != nullptr)
-        return launch_bwn_staged_v<MT, NT, WAVES, 0, true>(x, wbits, thr, y, bits, N, C, O, k, g, lds_bytes, workspace, workspace_bytes, s);
+        return launch_bwn_staged_v<MT, NT, WAVES, 0, true>(x, wbits, thr, y, bits, N, C, O, k, g, lds_bytes, workspace, s);
     if (C == 3)
-        return launch_bwn_staged_v<MT, NT, WAVES, 3, false>(x, wbits, thr, y, bits, N, C, O, k, g, lds_bytes, workspace, workspace_bytes, s);
-    return launch_bwn_staged_v<MT, NT, WAVES, 0, false>(x, wbits, thr, y, bits, N, C, O, k, g, lds_bytes, workspace, workspace_bytes, s);
+        return launch_bwn_staged_v<MT, NT, WAVES, 3, false>(x, wbits, thr, y, bits, N, C, O, k, g, lds_bytes, workspace, s);
+    return launch_bwn_staged_v<MT, NT, WAVES, 0, false>(x, wbits, thr, y, bits, N, C, O, k, g, lds_bytes, workspace, s);
 }
 
 }  // namespace

@@ -313,6 +313,38 @@ def test_bwn_first_layer_11x11_wave_kernel(bnn, orc, shape):
     assert np.array_equal(host(yi), orc.bwn_conv_f32(xi, wb, C, st, pad))
 
 
+# 3x3 and 5x5 first layers of 3-channel images (one LDS record per pixel): every fragment shape (8, 16, 32 columns), one and two
+# 64-channel groups and ragged ones, stride 2, no and large padding, images smaller than a tile; integer inputs are exact in any
+# order, so the sums equal the oracle's bit for bit; thresholds of +-infinity; a NaN pixel changes no output that does not cover it
+@pytest.mark.parametrize("shape", [(3, 33, 65, 3, 64, 3, 1, 1), (2, 17, 7, 3, 33, 3, 1, 2), (2, 70, 13, 3, 130, 3, 1, 0),
+                                   (5, 64, 61, 3, 65, 3, 2, 1), (1, 3, 3, 3, 1, 3, 2, 0), (40, 50, 24, 3, 100, 3, 2, 2),
+                                   (2, 37, 40, 3, 64, 5, 1, 2), (3, 19, 30, 3, 128, 5, 1, 4), (2, 66, 35, 3, 40, 5, 2, 2),
+                                   (7, 41, 14, 3, 192, 5, 2, 0), (70, 96, 96, 3, 32, 3, 1, 1)])
+def test_bwn_first_layer_pixel_records(bnn, orc, shape):
+    N, H, W, C, O, k, st, pad = shape
+    rng = np.random.default_rng(sum(shape) + 7)
+    wb = wl.random_bits(rng, (O, k, k), C)
+    thr = rng.normal(0, 600.0, size=O).astype(np.float32)
+    thr[0] = np.inf
+    thr[O // 2] = -np.inf
+    x = rng.integers(-2000, 2001, size=(N, H, W, C)).astype(np.float32)
+    bits, y = bnn.bwn_conv_thr(to_dev(x), to_dev(wb), to_dev(thr), C, st, pad, want_f32=True)
+    ref = orc.bwn_conv_f32(x, wb, C, st, pad)
+    assert np.array_equal(host(y), ref)
+    assert np.array_equal(words(bits), orc.pack_f32(ref, thr))
+    only = words(bnn.bwn_conv_thr(to_dev(x), to_dev(wb), to_dev(thr), C, st, pad))
+    assert np.array_equal(only, words(bits))
+    h, w = H // 2, W // 3
+    x[0, h, w, 2] = np.nan
+    got = words(bnn.bwn_conv_thr(to_dev(x), to_dev(wb), to_dev(thr), C, st, pad))
+    P, Q = only.shape[1:3]
+    covers = np.zeros((N, P, Q), bool)
+    for p in range(P):
+        for q in range(Q):
+            covers[0, p, q] = 0 <= h - (p * st - pad) < k and 0 <= w - (q * st - pad) < k
+    assert np.array_equal(got[~covers], only[~covers]) and not got[covers].any()
+
+
 def test_bwn_exact_cases(bnn, orc):
     # (a) integer inputs: the three-way bf16 split is exact and sums below 2^24 never round, so the fp32
     # result equals the oracle's bit for bit; (b) isolated values with all 24 significand bits set (at most
