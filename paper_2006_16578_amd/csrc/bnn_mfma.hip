@@ -40,6 +40,7 @@ int launch_mfma(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
         return mfma::launch_shape<4, false, true>(A, B, g, e, s);
     }
     if (mfma_conv_patch_takes(g, e)) return launch_mfma_conv_patch(A, B, g, e, s);
+    if (mfma_conv_xlds_takes(g, e)) return launch_mfma_conv_xlds(A, B, g, e, s);
     // (blocked 16-bit sums are implemented by the direct kernels only)
     if (!e.sums_tiled && staged_ok(g, tile)) return launch_mfma_conv_staged(A, B, g, e, s);
     if (!mfma::offsets_fit(g)) return BNN_ERR_UNSUPPORTED;
@@ -59,6 +60,7 @@ const char* describe_mfma(const Geom& g, bool int32_out) {
     const int tile = mfma::pick_tile(g, &e);
     if (tile == 0 && mfma_wide_takes(g, e)) return "mfma_fp4_bmm_xlds_wg256x256";
     if (mfma_conv_patch_takes(g, e)) return describe_mfma_conv_patch(g);
+    if (mfma_conv_xlds_takes(g, e)) return describe_mfma_conv_xlds(g);
     const bool st = !g.b_tiled && staged_ok(g, tile);
     switch (tile) {
         case 0: return g.conv ? (st ? "mfma_fp4_conv_lds_wg256x128" : "mfma_fp4_conv_wg256x128")

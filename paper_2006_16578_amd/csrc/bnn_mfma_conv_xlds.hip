@@ -1,0 +1,406 @@
+// Convolutions of any window, stride, channel count and padding convention on the matrix cores: the input patch under a
+// workgroup's output pixels is expanded to E2M1 ONCE, on its way into LDS, and the waves read finished pixel operands; the
+// filters stay packed in global memory / L2 and every wave expands its own two filter fragments a K-step ahead.
+//
+// What bounds the direct kernel (bnn_mfma_kernel.h) at windows and channel counts it has no unrolled form for: every K-step gathers
+// its words with 4-byte loads, masks them per tap, and expands both operands -- 25 vector instructions per MFMA at 96 channels and
+// a 5x5 window, a third of the K slots spent on rounding each tap up to whole K-steps, the matrix pipe busy 18 % of the time.  Here:
+//  * LDS holds one 16-byte unit per pixel and 32-channel word (the four operand registers of a lane), in planes [word][pixel]:
+//    the 32 pixels of a fragment read 32 consecutive units (two-way conflicts at stride 2).  A tap's pixel is a constant offset
+//    away, so K runs over the flattened words of a filter, whatever the channel count: words 8c .. 8c + 3 of chunk c go to the
+//    lower half-wave, 8c + 4 .. 8c + 7 to the upper one; only the last chunk of a filter can be partly empty (its missing words are units of zeros).
+//  * Padding is data: an out-of-frame pixel is the unit of -1 bits, or with excluded padding a unit of zeros, and the bits past the
+//    last channel are zeros too, so that no K slot needs a mask and no sum needs a correction in either convention.
+//  * A K-step of a wave (128 pixels x 64 channels) is eight MFMAs, four 16-byte LDS reads and about twenty vector instructions
+//    (expansion of two filter words, four addresses): below what the issue slots beside the MFMAs hold.
+//  * Bits only: the filters are the MFMA's row operand, with channels dealt to its rows so that a half-wave owns 32 consecutive
+//    ones; packing is a compare and an add-with-carry per accumulator register, and a lane stores whole words of its pixel.
+//    Everything else keeps pixels as rows and the shared epilogue (32 consecutive channels per store instruction).
+// Measured (graph replay, old kernels -> this one): 64 x 27x27x96 -> 200, 5x5, excluded padding 47.5 -> 19.8 us; 128 x 56x56x48 -> 48,
+// 3x3, excluded padding 48.4 -> 18.1; 128 x 28x28x96 -> 192, 3x3 26.5 -> 19.7; 100 x 9x9x300 -> 300 18.6 -> 11.8.  Of the 19.8 us, the
+// K loop is 12.8 (20 % above what its MFMAs take where a SIMD has two waves), staging 1.5, launch and epilogue the rest.
+// The patch covers whole padded rows of the images a tile of consecutive output pixels touches, so small images pack several to a
+// tile.  Two workgroups per compute unit: one stages while the other multiplies.
+#include <type_traits>
+
+#include "bnn_mfma_kernel.h"
+
+namespace bnn {
+namespace {
+
+using mfma::v16f;
+using mfma::v8i;
+
+struct XArgs {
+    int HP, PCW;            // rows of an image's padded frame that windows reach; pixels of a patch row
+    int plane;              // units from word plane to word plane (odd)
+    int px_max;             // pixels of the largest patch
+    int kwords;             // words of one filter
+    int vw, groups;         // words per staging load, loads per pixel
+    int table_bytes, thr_at;    // bytes of the offset table; where the thresholds lie
+    uint32_t last_mask;     // valid bits of a pixel's last word
+    FastDiv div_pcw, div_hp, div_groups, div_tw;
+};
+
+__device__ __forceinline__ uint4 expand_unit(uint32_t w, uint32_t c2) {
+    return make_uint4(((w << 3) & 0x88888888u) | c2, ((w << 2) & 0x88888888u) | c2, ((w << 1) & 0x88888888u) | c2,
+                      (w & 0x88888888u) | c2);
+}
+
+__device__ __forceinline__ v8i as_operand(const uint4& u) {
+    v8i r;
+    r[0] = (int)u.x; r[1] = (int)u.y; r[2] = (int)u.z; r[3] = (int)u.w;
+    r[4] = 0; r[5] = 0; r[6] = 0; r[7] = 0;         // the upper half is not read for 4-bit formats
+    return r;
+}
+
+// 1 nibble of ones for every set bit of w, in the layout of expand_unit.
+__device__ __forceinline__ uint4 nibble_mask(uint32_t w) {
+    return make_uint4((w & 0x11111111u) * 15u, ((w >> 1) & 0x11111111u) * 15u, ((w >> 2) & 0x11111111u) * 15u,
+                      ((w >> 3) & 0x11111111u) * 15u);
+}
+
+// w = 2 w + bit for four compare results, the first becoming the highest bit.  The s_nop covers the two wait states between a
+// vector compare that writes an SGPR pair and a vector instruction that reads it: the compiler does not look into the block.
+__device__ __forceinline__ void push4(uint32_t& w, unsigned long long a, unsigned long long b, unsigned long long c, unsigned long long d) {
+    asm("s_nop 1\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %1\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %2\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %3\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %4"
+        : "+v"(w) : "s"(a), "s"(b), "s"(c), "s"(d) : "vcc");
+}
+
+typedef uint32_t word4 __attribute__((ext_vector_type(4), aligned(4)));      // filters of odd word counts start at any word
+
+// MT x NT accumulators of 32 x 32 per wave, WM x WN waves.  SWAP: filters are the MFMA's row operand (bits only).
+template <int MT, int NT, int WM, int WN, bool SWAP>
+__global__ __launch_bounds__(WM * WN * 64, 2) void conv_xlds_kernel(const uint32_t* __restrict__ A, const uint32_t* __restrict__ B, Geom g,
+                                                                   Epi e, XArgs x, int gx, int gy) {
+    static_assert(NT == 2, "a wave owns 64 channels, a half-wave 32 of them");
+    constexpr int NTHR = WM * WN * 64, ROWS = WM * MT * 32, COLS = WN * NT * 32;
+    extern __shared__ uint4 smem[];
+    char* lds = reinterpret_cast<char*>(smem);          // offsets of the K words (int each), then the units
+    mfma::accumulators_in_agprs();
+    int bx, by;
+    if (!mfma::tile_coords(gx, gy, bx, by)) return;     // uniform for the workgroup
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int m_base = bx * ROWS;                       // rows < 2^31
+    const int m0 = m_base + wm * (MT * 32), n0 = (by * WN + wn) * (NT * 32);
+    const int rows = (int)g.rows;
+
+    uint32_t c2;
+    asm volatile("v_mov_b32 %0, 0x22222222" : "=v"(c2));
+
+    // ---- patch rows: padded rows Y = n * HP + p * stride + r, from the first output pixel's first to the last one's last
+    const int first_n = fast_div(m_base, g.div_pq), first_p = fast_div(m_base - first_n * (g.P * g.Q), g.div_q);
+    const int last = min(m_base + ROWS, rows) - 1;
+    const int last_n = fast_div(last, g.div_pq), last_p = fast_div(last - last_n * (g.P * g.Q), g.div_q);
+    const int Ya = first_n * x.HP + first_p * g.stride;
+    const int npx = (last_n * x.HP + last_p * g.stride + g.k - Ya) * x.PCW;              // <= px_max
+
+    // ---- this lane's pixels (byte offset of their first tap's unit) and filters
+    uint32_t pbase[MT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+        const int row = min(m0 + 32 * i + l32, rows - 1);                               // past the end: dropped by the epilogue
+        const int n = fast_div(row, g.div_pq), rem = row - n * (g.P * g.Q);
+        const int p = fast_div(rem, g.div_q), q = rem - p * g.Q;
+        pbase[i] = (uint32_t)(x.table_bytes + ((n * x.HP + p * g.stride - Ya) * x.PCW + q * g.stride) * 16);
+    }
+    uint32_t boff[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const int ch = SWAP ? n0 + 32 * ((l32 >> 2) & 1) + 16 * j + 4 * (l32 >> 3) + (l32 & 3) : n0 + 32 * j + l32;
+        boff[j] = (uint32_t)(min(ch, g.cols - 1) * g.ldb_w + 4 * half) * 4u;            // < 2^31 (checked on the host)
+    }
+    const int nfull = x.kwords >> 3, tail = x.kwords & 7;
+    uint4 bq[NT], bn[NT];
+    auto load_b = [&](int c, uint4 (&b)[NT]) {                                          // words 8 c + 4 half .. + 3 of a whole chunk
+        const char* base = reinterpret_cast<const char*>(B + 8 * c);                     // uniform
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const word4 v = *reinterpret_cast<const word4*>(base + (size_t)boff[j]);
+            b[j] = make_uint4(v[0], v[1], v[2], v[3]);
+        }
+    };
+    auto load_tail = [&](uint4 (&b)[NT]) {              // the last, partly filled chunk; a word past the filter's end repeats its last one
+        const int w0 = 8 * nfull + 4 * half;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const uint32_t* src = B + (boff[j] >> 2) - 4 * half;
+            b[j] = make_uint4(src[min(w0, x.kwords - 1)], src[min(w0 + 1, x.kwords - 1)], src[min(w0 + 2, x.kwords - 1)],
+                              src[min(w0 + 3, x.kwords - 1)]);
+        }
+    };
+    if (nfull > 0) load_b(0, bq);
+    else load_tail(bq);
+
+    // ---- offsets of the K words from a pixel's first unit
+    for (int w = tid; w < ((x.kwords + 7) & ~7); w += NTHR) {
+        const int tap = fast_div(w, x.div_tw), wi = w - tap * g.tw;
+        const int r = (tap * g.kinv) >> 16, s = tap - r * g.k;
+        // a word past the filter's end: the plane of zeros behind the patch (there if the last chunk is partly filled)
+        *reinterpret_cast<int*>(lds + 4 * w) = (w < x.kwords ? wi * x.plane + r * x.PCW + s : g.tw * x.plane) * 16;
+    }
+    if (tail > 0)
+        for (int u = tid; u < npx; u += NTHR)
+            reinterpret_cast<uint4*>(lds + x.table_bytes)[g.tw * x.plane + u] = make_uint4(0u, 0u, 0u, 0u);
+    if (SWAP && tid < COLS) {                           // thresholds of the tile's channels, as the epilogue compares them
+        const int ch = by * COLS + tid;
+        reinterpret_cast<float*>(lds + x.thr_at)[tid] = ch < g.cols ? (float)e.thr[min(ch, g.cols - 1)] : __builtin_inff();
+    }
+    // ---- patch -> LDS: item = vw words of one pixel, consecutive in memory; four loads in flight per thread
+    {
+        const int items = npx * x.groups;
+        for (int base = 0; base < items; base += 4 * NTHR) {
+            uint32_t w[4][4];
+            int px[4], wi0[4];
+            bool in[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int it = min(base + u * NTHR + tid, items - 1);
+                px[u] = fast_div(it, x.div_groups);
+                wi0[u] = (it - px[u] * x.groups) * x.vw;
+                const int yr = fast_div(px[u], x.div_pcw), X = px[u] - yr * x.PCW - g.pad;
+                const int n = fast_div(Ya + yr, x.div_hp), yy = Ya + yr - n * x.HP - g.pad;
+                in[u] = (unsigned)yy < (unsigned)g.H && (unsigned)X < (unsigned)g.W;
+                const uint32_t* src = A + (in[u] ? (((long long)n * g.H + yy) * g.W + X) * g.lda_w + wi0[u] : 0);
+                w[u][0] = src[0];
+                if (x.vw == 4) {                                                        // uniform: lda_w a multiple of 4
+                    const uint4 v = *reinterpret_cast<const uint4*>(src);
+                    w[u][0] = v.x; w[u][1] = v.y; w[u][2] = v.z; w[u][3] = v.w;
+                } else if (x.vw >= 2) {
+                    w[u][1] = src[1];
+                    if (x.vw == 3) w[u][2] = src[2];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (base + u * NTHR + tid >= items) continue;
+                uint4* dst = reinterpret_cast<uint4*>(lds + x.table_bytes) + wi0[u] * x.plane + px[u];
+                const uint32_t keep = (in[u] || !g.excl) ? 0xFFFFFFFFu : 0u;             // excluded padding: zeros
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    if (d >= x.vw) break;                                               // uniform
+                    uint4 v = expand_unit(in[u] ? w[u][d] : 0u, c2);
+                    uint4 m = make_uint4(keep, keep, keep, keep);
+                    if (wi0[u] + d == g.tw - 1 && x.last_mask != 0xFFFFFFFFu) {
+                        const uint4 q = nibble_mask(x.last_mask);
+                        m = make_uint4(m.x & q.x, m.y & q.y, m.z & q.z, m.w & q.w);
+                    }
+                    dst[d * x.plane] = make_uint4(v.x & m.x, v.y & m.y, v.z & m.z, v.w & m.w);
+                }
+            }
+        }
+    }
+    __syncthreads();                                    // the only barrier
+
+    v16f acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    uint4 fa[2][MT], fb[2][NT];
+    auto read_a = [&](int off, int slot) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i) fa[slot][i] = *reinterpret_cast<const uint4*>(lds + (pbase[i] + (uint32_t)off));
+    };
+    auto expand_b = [&](const uint4 (&b)[NT], int v, int slot) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) fb[slot][j] = expand_unit(v == 0 ? b[j].x : v == 1 ? b[j].y : v == 2 ? b[j].z : b[j].w, c2);
+    };
+    auto multiply = [&](int slot) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+                acc[i][j] = SWAP ? __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as_operand(fb[slot][j]), as_operand(fa[slot][i]), acc[i][j], 4,
+                                                                                   4, 0, 0, 0, 0)
+                                 : __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(as_operand(fa[slot][i]), as_operand(fb[slot][j]), acc[i][j], 4,
+                                                                                   4, 0, 0, 0, 0);
+    };
+    auto offsets = [&](int c) { return *reinterpret_cast<const int4*>(lds + (8 * c + 4 * half) * 4); };
+
+    // Pixel units and expanded filter words run one K-step ahead, packed filter words and offsets one chunk.
+    int4 off = offsets(0), offn = off;
+    read_a(off.x, 0); expand_b(bq, 0, 0);
+    const int nchunks = nfull + (tail > 0 ? 1 : 0);
+    for (int c = 0; c < nfull; ++c) {
+        if (c + 1 < nfull) load_b(c + 1, bn);
+        else if (tail > 0) load_tail(bn);
+        offn = offsets(min(c + 1, nchunks - 1));        // past the end: read again and dropped
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            if (v < 3) { read_a(v == 0 ? off.y : v == 1 ? off.z : off.w, (v + 1) & 1); expand_b(bq, v + 1, (v + 1) & 1); }
+            else { read_a(offn.x, 0); expand_b(bn, 0, 0); }
+            multiply(v & 1);
+#pragma unroll
+            for (int q = 0; q < MT * NT; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // an even mix: MFMA, vector ALU, LDS read
+                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int j = 0; j < NT; ++j) bq[j] = bn[j];
+        off = offn;
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {                       // the partly filled chunk: as many K-steps as hold a word
+        if (v < tail) {                                 // uniform
+            if (v < 3) { read_a(v == 0 ? off.y : v == 1 ? off.z : off.w, (v + 1) & 1); expand_b(bq, v + 1, (v + 1) & 1); }
+            multiply(v & 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+
+    int corr = 0;                                       // pad bits of the fused second source only
+    if (g.A2 != nullptr) corr = mfma::extra_source<MT, NT, SWAP>(acc, g, m0, n0, lane, c2) - g.bits2;
+    if constexpr (!SWAP) {
+        mfma::epilogue<MT, NT, true, false>(acc, m0, n0, lane, g, e, corr, 0);
+    } else {
+        // register r of tile j holds channel n0 + 32 * half + 16 * j + r of pixel m0 + 32 * i + l32
+        float th[32];
+        const float4* tl = reinterpret_cast<const float4*>(lds + x.thr_at) + (wn * 64 + 32 * half) / 4;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const float4 v = tl[t];
+            th[4 * t] = v.x + (float)corr; th[4 * t + 1] = v.y + (float)corr; th[4 * t + 2] = v.z + (float)corr; th[4 * t + 3] = v.w + (float)corr;
+        }
+        const int wi = (n0 >> 5) + half;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            uint32_t w = 0u;
+#pragma unroll
+            for (int t = 28; t >= 0; t -= 4) {
+                const v16f& v = acc[i][t >> 4];
+                const int r = t & 15;
+                push4(w, __builtin_amdgcn_ballot_w64(v[r + 3] >= th[t + 3]), __builtin_amdgcn_ballot_w64(v[r + 2] >= th[t + 2]),
+                      __builtin_amdgcn_ballot_w64(v[r + 1] >= th[t + 1]), __builtin_amdgcn_ballot_w64(v[r] >= th[t]));
+            }
+            const int row = m0 + 32 * i + l32;
+            if (row < rows && wi < e.ldbits_w) e.bits[(long long)row * e.ldbits_w + wi] = w;
+        }
+    }
+}
+
+// Largest patch (pixels) of a tile of `tile_rows` consecutive output pixels.
+long long patch_pixels(const Geom& g, int tile_rows) {
+    const long long pq = (long long)g.P * g.Q;
+    const long long out_rows = min((tile_rows - 1 + g.Q - 1) / g.Q + 1LL, (g.rows + g.Q - 1) / g.Q);
+    const long long images = min((tile_rows - 1 + pq - 1) / pq, (g.rows + pq - 1) / pq - 1);      // image boundaries inside a tile
+    return ((out_rows - 1) * g.stride + g.k + images * max(0, g.k - g.stride)) * ((g.Q - 1LL) * g.stride + g.k);
+}
+
+constexpr size_t XLDS_MAX = 80 * 1024;                  // two workgroups per compute unit
+
+bool fill_args(const Geom& g, int tile_rows, int tile_cols, XArgs* x, size_t* lds_bytes) {
+    const long long px = patch_pixels(g, tile_rows);
+    const long long kwords = (long long)g.taps * g.tw;
+    const long long plane = px | 1, table = (kwords + 7) / 8 * 32;
+    const long long thr_at = table + plane * (g.tw + (kwords % 8 ? 1 : 0)) * 16;
+    const long long total = thr_at + tile_cols * 4;
+    if (total > (long long)XLDS_MAX) return false;
+    if ((long long)g.cols * g.ldb_w * 4 >= (1LL << 31)) return false;
+    x->HP = (g.P - 1) * g.stride + g.k;
+    if ((g.rows / ((long long)g.P * g.Q) + 1) * x->HP >= (1LL << 31)) return false;
+    x->PCW = (g.Q - 1) * g.stride + g.k;
+    x->px_max = (int)px; x->plane = (int)plane; x->kwords = (int)kwords;
+    x->vw = g.tw % 4 == 0 ? 4 : g.tw == 3 ? 3 : g.tw % 2 == 0 ? 2 : 1;
+    x->groups = g.tw / x->vw;
+    x->table_bytes = (int)table; x->thr_at = (int)thr_at;
+    x->last_mask = (g.bits_tap & 31) ? (1u << (g.bits_tap & 31)) - 1u : 0xFFFFFFFFu;
+    x->div_pcw = make_fastdiv((uint32_t)x->PCW); x->div_hp = make_fastdiv((uint32_t)x->HP);
+    x->div_groups = make_fastdiv((uint32_t)x->groups); x->div_tw = make_fastdiv((uint32_t)g.tw);
+    *lds_bytes = (size_t)total;
+    return true;
+}
+
+template <int MT, int NT, int WM, int WN>
+int launch_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
+    XArgs x;
+    size_t lds;
+    if (!fill_args(g, WM * MT * 32, WN * NT * 32, &x, &lds)) return BNN_ERR_UNSUPPORTED;
+    const int gx = (int)cdiv(g.rows, WM * MT * 32), gy = (int)cdiv(g.cols, WN * NT * 32);
+    const unsigned nwg = (unsigned)(cdiv((long long)gx * gy, 8) * 8);
+    const bool swap = e.bits != nullptr && e.out == nullptr && e.out16 == nullptr && e.resid == nullptr && e.resid16 == nullptr &&
+                      e.resid_bits == nullptr;
+    static const hipError_t attr0 = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_xlds_kernel<MT, NT, WM, WN, true>),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)XLDS_MAX);
+    static const hipError_t attr1 = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_xlds_kernel<MT, NT, WM, WN, false>),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)XLDS_MAX);
+    if (attr0 != hipSuccess || attr1 != hipSuccess) return BNN_ERR_DEVICE;
+    if (swap) hipLaunchKernelGGL((conv_xlds_kernel<MT, NT, WM, WN, true>), dim3(nwg), dim3(WM * WN * 64), lds, s, A, B, g, e, x, gx, gy);
+    else hipLaunchKernelGGL((conv_xlds_kernel<MT, NT, WM, WN, false>), dim3(nwg), dim3(WM * WN * 64), lds, s, A, B, g, e, x, gx, gy);
+    return check_launch();
+}
+
+struct XTile { int rows, cols, mfmas; };                // mfmas: per wave and K-step
+constexpr XTile XTILES[] = {{0, 0, 0}, {256, 128, 8}, {128, 256, 8}, {512, 64, 8}, {128, 128, 4}, {256, 64, 4}};
+
+// Tile for this geometry, 0: another kernel's.  Among the tiles whose patch fits LDS, the one with the least estimated time: rounds
+// of 512 workgroups times the cycles of one (K-steps, a little more than their MFMAs take where a step has only four; staging;
+// epilogue; the rest).
+int xlds_tile(const Geom& g) {
+    if (!g.conv || g.rows >= (1LL << 31) - 1024) return 0;
+    // What the other kernels do as well or better (measured, this kernel's speed over theirs): 1x1 windows and
+    // filters of less than two chunks, whose patch is used too little (0.7 to 0.9), the unrolled 3x3 forms of 2, 4, 8 and 16 words per pixel (0.85 to 1.06) -- except with excluded
+    // padding and a partly filled last word, where they correct every sum by its pixel (this kernel 2.7); and with
+    // -1 padding what the staged kernel takes (0.98 to 1.19) and pixels of whole 32-byte units, which the direct kernel loads 16
+    // bytes at a time (0.98 to 1.06).
+    if (g.k == 1 || g.taps * g.tw < 16) return 0;
+    const bool pad_bits = g.bits_tap != g.tw * 32;
+    if (g.k == 3 && (g.tw == 2 || g.tw == 4 || g.tw == 8 || g.tw == 16) && !(g.excl && pad_bits)) return 0;
+    if (!g.excl && (mfma::conv_stages_through_lds(g) || g.tw % 8 == 0)) return 0;
+    int best = 0;
+    double best_cost = 0.;
+    const double steps = (g.taps * g.tw + 1) / 2;
+    for (int t = 1; t <= 5; ++t) {
+        XArgs x;
+        size_t lds;
+        const long long gy = cdiv(g.cols, XTILES[t].cols), wgs = cdiv(g.rows, XTILES[t].rows) * gy;
+        // Few workgroups: the 64 x 64 tiles of the direct kernel have four times as many (49 workgroups 0.87 of its speed, 98: 1.04,
+        // 171: 1.3).  Many empty columns: 0.77 at 64 of 128.
+        if (wgs < 96 || (double)(gy * XTILES[t].cols) > 1.5 * g.cols) continue;
+        if (!fill_args(g, XTILES[t].rows, XTILES[t].cols, &x, &lds)) continue;
+        const double m = XTILES[t].mfmas;
+        const double wg = steps * m * (m < 8. ? 44. : 36.) + (double)x.px_max * g.tw / 4. + m * 160. + 1500.;
+        const double cost = (double)cdiv(wgs, 512) * wg;
+        if (best == 0 || cost < best_cost) { best = t; best_cost = cost; }
+    }
+    return best;
+}
+
+}  // namespace
+
+bool mfma_conv_xlds_takes(const Geom& g, const Epi& e) { return !e.sums_tiled && xlds_tile(g) != 0; }
+
+const char* describe_mfma_conv_xlds(const Geom& g) {
+    switch (xlds_tile(g)) {
+        case 1: return "mfma_fp4_conv_xlds_wg256x128";
+        case 2: return "mfma_fp4_conv_xlds_wg128x256";
+        case 3: return "mfma_fp4_conv_xlds_wg512x64";
+        case 4: return "mfma_fp4_conv_xlds_wg128x128";
+        default: return "mfma_fp4_conv_xlds_wg256x64";
+    }
+}
+
+int launch_mfma_conv_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
+    switch (xlds_tile(g)) {
+        case 1: return launch_xlds<4, 2, 2, 2>(A, B, g, e, s);
+        case 2: return launch_xlds<4, 2, 1, 4>(A, B, g, e, s);
+        case 3: return launch_xlds<4, 2, 4, 1>(A, B, g, e, s);
+        case 4: return launch_xlds<2, 2, 2, 2>(A, B, g, e, s);
+        case 5: return launch_xlds<2, 2, 4, 1>(A, B, g, e, s);
+        default: return BNN_ERR_UNSUPPORTED;
+    }
+}
+
+}  // namespace bnn

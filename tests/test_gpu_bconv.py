@@ -76,6 +76,27 @@ def test_ragged_shapes_staged_tiles(bnn, orc, shape):
         run_conv(bnn, orc, case, 0, pad_mode, ref=ref1)
 
 
+# the kernel whose pixels are expanded in LDS, on each of its tiles: partly filled last chunk of K and none,
+# partly filled last word (the bits past it are zeros in both padding conventions), several images per tile, ragged
+# rows and columns, stride 2 and 3, no padding and the largest, loads of 1, 2, 3 and 4 words per pixel
+XLDS = [(16, 27, 27, 96, 200, 5, 1, 2, "mfma_fp4_conv_xlds_wg128x128"), (70, 27, 26, 96, 200, 5, 1, 2, "mfma_fp4_conv_xlds_wg128x256"),
+        (100, 27, 25, 70, 120, 3, 1, 1, "mfma_fp4_conv_xlds_wg256x128"), (150, 30, 31, 33, 64, 5, 1, 4, "mfma_fp4_conv_xlds_wg512x64"),
+        (150, 9, 9, 300, 300, 3, 1, 1, "mfma_fp4_conv_xlds_wg128x128"), (1500, 7, 5, 20, 50, 4, 1, 2, "mfma_fp4_conv_xlds_wg256x64"),
+        (1300, 5, 7, 160, 60, 3, 1, 1, "mfma_fp4_conv_xlds_wg256x64"), (40, 50, 50, 50, 250, 4, 3, 3, "mfma_fp4_conv_xlds_wg128x128"),
+        (400, 33, 17, 90, 96, 7, 2, 0, "mfma_fp4_conv_xlds_wg128x128"), (30, 28, 28, 64, 128, 5, 1, 2, "mfma_fp4_conv_xlds_wg128x128")]
+
+
+@pytest.mark.parametrize("shape", XLDS)
+def test_shapes_expanded_in_lds(bnn, orc, shape):
+    N, H, W, C, O, k, st, pad, kernel = shape
+    if kernel is not None:
+        assert bnn.bconv_kernel_name(N, H, W, C, O, k, st, pad) == kernel
+    case = wl.bconv_case(95, N, H, W, C, O, k, st, pad, index0=C % 83)
+    for pad_mode in (0, 1):
+        ref = orc.bconv(case["x"], case["filt"], C, st, pad, pad_mode, tier=1)
+        run_conv(bnn, orc, case, 0, pad_mode, ref=ref)
+
+
 def test_paper_sweep_shape_c640(bnn, orc):
     # one shape of the paper's BConv sweep (batch 16, 64x64, 3x3, C = O = 640), as bench.py runs it
     case = wl.bconv_case(6, 16, 64, 64, 640, 640, 3, 1, 1, index0=640 % 97)
