@@ -7,6 +7,7 @@ dtypes are checked here, everything else by the library, whose status codes are 
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 
@@ -102,8 +103,19 @@ def _ptr(t):
     return ctypes.c_void_p(0 if t is None else t.data_ptr())
 
 
+# What a call costs on the host counts: a small product runs 4 us on the GPU.  The two helpers below ask torch for the current
+# device and the raw stream only (0.3 us; a device context manager and a Stream object per call took 3.1 of 10 us).
 def _stream(t: torch.Tensor):
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    """The current stream of t's device."""
+    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(t.get_device()))
+
+
+_STAY = contextlib.nullcontext()
+
+
+def _on(t: torch.Tensor):
+    """Context in which t's device is the current one."""
+    return _STAY if torch.cuda.current_device() == t.get_device() else torch.cuda.device(t.device)
 
 
 def _dev(t: torch.Tensor, dtype, ndim=None, name="tensor"):
@@ -127,7 +139,7 @@ def bmm(A, B, K: int, out=None, path: int = PATH_AUTO):
     M, lda = A.shape
     N, ldb = B.shape
     C = torch.empty((M, N), dtype=torch.int32, device=A.device) if out is None else _dev(out, torch.int32, 2, "out")
-    with torch.cuda.device(A.device):
+    with _on(A):
         _check(load().bnn_bmm_ex(_ptr(A), _ptr(B), _ptr(C), M, N, int(K), lda, ldb, C.shape[1], int(path), _stream(A)), "bnn_bmm")
     return C
 
@@ -141,7 +153,7 @@ def bmm_thr(A, B, thr, K: int, ldcb_w: int | None = None, out=None, path: int = 
         raise ValueError("thr must have N entries")
     ldcb_w = round_up(nwords(N), 4) if ldcb_w is None else int(ldcb_w)
     Cb = torch.empty((M, ldcb_w), dtype=_BITS, device=A.device) if out is None else _dev(out, _BITS, 2, "out")
-    with torch.cuda.device(A.device):
+    with _on(A):
         _check(load().bnn_bmm_thr_ex(_ptr(A), _ptr(B), _ptr(thr), _ptr(Cb), M, N, int(K), lda, ldb, Cb.shape[1], int(path),
                                      _stream(A)), "bnn_bmm_thr")
     return Cb
@@ -164,7 +176,7 @@ def bconv(x, filt, C: int, stride: int, pad: int, pad_mode: int = PAD_MINUS_ONE,
     """int32 [N][P][Q][O] = cross-correlation of packed x [N][H][W][cw] with filt [O][k][k][cw]."""
     N, H, W, O, k, P, Q = _conv_dims(x, filt, C, stride, pad)
     y = torch.empty((N, max(P, 0), max(Q, 0), O), dtype=torch.int32, device=x.device) if out is None else out
-    with torch.cuda.device(x.device):
+    with _on(x):
         _check(load().bnn_bconv_ex(_ptr(x), _ptr(filt), _ptr(y), N, H, W, int(C), O, k, int(stride), int(pad),
                                    int(pad_mode), int(path), _stream(x)), "bnn_bconv")
     return y
@@ -182,7 +194,7 @@ def bconv_thr(x, filt, thr, C: int, stride: int, pad: int, pad_mode: int = PAD_M
     if want_sum and sum_out is None:
         sum_out = torch.empty((N, P, Q, O), dtype=torch.int32, device=x.device)
     bits = torch.empty((N, max(P, 0), max(Q, 0), nwords(O)), dtype=_BITS, device=x.device) if out is None else out
-    with torch.cuda.device(x.device):
+    with _on(x):
         _check(load().bnn_bconv_thr_ex(_ptr(x), _ptr(filt), _ptr(residual), _ptr(sum_out), _ptr(thr), _ptr(bits), N, H, W,
                                        int(C), O, k, int(stride), int(pad), int(pad_mode), int(path), _stream(x)),
                "bnn_bconv_thr")
@@ -195,7 +207,7 @@ def threshold_pack(X, thr, ldb_w: int | None = None):
     rows = X.numel() // cols
     ldb_w = nwords(cols) if ldb_w is None else int(ldb_w)
     bits = torch.empty(tuple(X.shape[:-1]) + (ldb_w,), dtype=_BITS, device=X.device)
-    with torch.cuda.device(X.device):
+    with _on(X):
         _check(load().bnn_threshold_pack(_ptr(X), _ptr(thr), _ptr(bits), ctypes.c_int64(rows), cols, cols, ldb_w, _stream(X)),
                "bnn_threshold_pack")
     return bits
@@ -206,7 +218,7 @@ def pack_u8(x, thr: int, ldb_w: int | None = None):
     rows, cols = x.shape
     ldb_w = nwords(cols) if ldb_w is None else int(ldb_w)
     bits = torch.empty((rows, ldb_w), dtype=_BITS, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on(x):
         _check(load().bnn_pack_u8(_ptr(x), int(thr), _ptr(bits), ctypes.c_int64(rows), cols, ldb_w, _stream(x)), "bnn_pack_u8")
     return bits
 
@@ -217,7 +229,7 @@ def pack_f32(x, thr, ldb_w: int | None = None):
     rows = x.numel() // cols
     ldb_w = nwords(cols) if ldb_w is None else int(ldb_w)
     bits = torch.empty(tuple(x.shape[:-1]) + (ldb_w,), dtype=_BITS, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on(x):
         _check(load().bnn_pack_f32(_ptr(x), _ptr(thr), _ptr(bits), ctypes.c_int64(rows), cols, ldb_w, _stream(x)), "bnn_pack_f32")
     return bits
 
@@ -227,7 +239,7 @@ def tile_b(B, K: int):
     _dev(B, _BITS, 2, "B")
     N, ldb = B.shape
     out = torch.empty(((N + 31) // 32 * 32, ldb), dtype=_BITS, device=B.device)
-    with torch.cuda.device(B.device):
+    with _on(B):
         _check(load().bnn_tile_b(_ptr(B), _ptr(out), N, int(K), ldb, _stream(B)), "bnn_tile_b")
     return out
 
@@ -237,7 +249,7 @@ def bmm_tiled(A, Bt, N: int, K: int, out=None):
     M = A.shape[0]
     if out is None:
         out = torch.empty((M, N), dtype=torch.int32, device=A.device)
-    with torch.cuda.device(A.device):
+    with _on(A):
         _check(load().bnn_bmm_tiled(_ptr(A), _ptr(Bt), _ptr(out), M, int(N), int(K), A.shape[1], Bt.shape[1], out.shape[1],
                                     _stream(A)), "bnn_bmm_tiled")
     return out
@@ -249,7 +261,7 @@ def bmm_thr_tiled(A, Bt, thr, N: int, K: int, ldcb_w: int | None = None, out=Non
     ldcb_w = round_up(nwords(N), 4) if ldcb_w is None else ldcb_w
     if out is None:
         out = torch.empty((M, ldcb_w), dtype=_BITS, device=A.device)
-    with torch.cuda.device(A.device):
+    with _on(A):
         _check(load().bnn_bmm_thr_tiled(_ptr(A), _ptr(Bt), _ptr(thr), _ptr(out), M, int(N), int(K), A.shape[1], Bt.shape[1],
                                         out.shape[1], _stream(A)), "bnn_bmm_thr_tiled")
     return out
@@ -260,7 +272,7 @@ def panels_from_rows(X, K: int):
     _dev(X, _BITS, 2, "X")
     rows, ldx = X.shape
     out = torch.empty(((int(K) + 255) // 256, rows, 8), dtype=_BITS, device=X.device)
-    with torch.cuda.device(X.device):
+    with _on(X):
         _check(load().bnn_panels_from_rows(_ptr(X), _ptr(out), ctypes.c_int64(rows), int(K), ldx, _stream(X)), "bnn_panels_from_rows")
     return out
 
@@ -271,7 +283,7 @@ def rows_from_panels(Xp, K: int, ldx_w: int | None = None):
     rows = Xp.shape[1]
     ldx_w = round_up(nwords(K), 4) if ldx_w is None else int(ldx_w)
     out = torch.empty((rows, ldx_w), dtype=_BITS, device=Xp.device)
-    with torch.cuda.device(Xp.device):
+    with _on(Xp):
         _check(load().bnn_rows_from_panels(_ptr(Xp), _ptr(out), ctypes.c_int64(rows), int(K), ldx_w, _stream(Xp)), "bnn_rows_from_panels")
     return out
 
@@ -282,7 +294,7 @@ def bmm_panels(Ap, Bp, K: int, out=None):
     M, N = Ap.shape[1], Bp.shape[1]
     if out is None:
         out = torch.empty((M, N), dtype=torch.int32, device=Ap.device)
-    with torch.cuda.device(Ap.device):
+    with _on(Ap):
         _check(load().bnn_bmm_panels(_ptr(Ap), _ptr(Bp), _ptr(out), M, N, int(K), out.shape[1], _stream(Ap)), "bnn_bmm_panels")
     return out
 
@@ -293,7 +305,7 @@ def bmm_thr_panels(Ap, Bp, thr, K: int, out=None):
     M, N = Ap.shape[1], Bp.shape[1]
     if out is None:
         out = torch.empty(((N + 255) // 256, M, 8), dtype=_BITS, device=Ap.device)
-    with torch.cuda.device(Ap.device):
+    with _on(Ap):
         _check(load().bnn_bmm_thr_panels(_ptr(Ap), _ptr(Bp), _ptr(thr), _ptr(out), M, N, int(K), _stream(Ap)), "bnn_bmm_thr_panels")
     return out
 
@@ -306,7 +318,7 @@ def probe_load_stride(stride_bytes: int, rows: int | None = None, iters: int = 4
         rows = max(32, footprint_bytes // stride_bytes // 32 * 32)
     buf = torch.zeros(rows * stride_bytes // 4, dtype=_BITS, device=device)
     cyc = torch.zeros(2, dtype=torch.int64, device=device)
-    with torch.cuda.device(buf.device):
+    with _on(buf):
         for _ in range(2):                                  # the second run has the buffer in cache
             _check(load().bnn_probe_load_stride(_ptr(buf), _ptr(cyc), int(stride_bytes), int(rows), int(iters),
                                                 1 if dependent else 0, _stream(buf)), "bnn_probe_load_stride")
@@ -323,7 +335,7 @@ def probe_pipeline(which: str, buf, iters: int = 2000, reps: int = 3):
     _dev(buf, torch.uint8, 1, "buf")
     work = ctypes.c_double(0.0)
     best = None
-    with torch.cuda.device(buf.device):
+    with _on(buf):
         for rep in range(reps + 1):
             e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             e0.record()
@@ -341,7 +353,7 @@ def probe_pipeline_enqueue(which: str, buf, iters: int) -> float:
     """Enqueues one launch of a ceiling microbenchmark without waiting for it; returns its work units."""
     _dev(buf, torch.uint8, 1, "buf")
     work = ctypes.c_double(0.0)
-    with torch.cuda.device(buf.device):
+    with _on(buf):
         _check(load().bnn_probe_pipeline(PROBES[which], _ptr(buf), ctypes.c_size_t(buf.numel()), int(iters),
                                          ctypes.byref(work), _stream(buf)), "bnn_probe_pipeline")
     return work.value
@@ -353,7 +365,7 @@ def sign_pack_f32(x, ldb_w: int | None = None):
     rows, cols = x.shape
     ldb_w = nwords(cols) if ldb_w is None else ldb_w
     bits = torch.empty((rows, ldb_w), dtype=_BITS, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on(x):
         _check(load().bnn_sign_pack_f32(_ptr(x), _ptr(bits), ctypes.c_int64(rows), cols, cols, ldb_w, _stream(x)), "bnn_sign_pack_f32")
     return bits
 
@@ -369,7 +381,7 @@ def bmm_general_f32(A, B, out=None, workspace=None):
         out = torch.empty((M, N), dtype=torch.float32, device=A.device)
     if workspace is None:
         workspace = torch.empty(max(int(load().bnn_bmm_general_workspace_bytes(M, N, K)), 256), dtype=torch.uint8, device=A.device)
-    with torch.cuda.device(A.device):
+    with _on(A):
         _check(load().bnn_bmm_general_f32(_ptr(A), _ptr(B), _ptr(out), M, N, K, K, K, N, _ptr(workspace),
                                           ctypes.c_size_t(workspace.numel()), _stream(A)), "bnn_bmm_general_f32")
     return out
@@ -389,7 +401,7 @@ def bconv_general_f32(x, filt, stride: int, pad: int, pad_mode: int = PAD_MINUS_
     if workspace is None:
         workspace = torch.empty(max(int(load().bnn_bconv_general_workspace_bytes(N, H, W, C, O, k)), 256), dtype=torch.uint8,
                                 device=x.device)
-    with torch.cuda.device(x.device):
+    with _on(x):
         _check(load().bnn_bconv_general_f32(_ptr(x), _ptr(filt), _ptr(out), N, H, W, C, O, k, int(stride), int(pad), int(pad_mode),
                                             _ptr(workspace), ctypes.c_size_t(workspace.numel()), _stream(x)), "bnn_bconv_general_f32")
     return out
@@ -400,7 +412,7 @@ def unpack_i32(bits, cols: int):
     ldb_w = bits.shape[-1]
     rows = bits.numel() // ldb_w
     out = torch.empty(tuple(bits.shape[:-1]) + (cols,), dtype=torch.int32, device=bits.device)
-    with torch.cuda.device(bits.device):
+    with _on(bits):
         _check(load().bnn_unpack_i32(_ptr(bits), _ptr(out), ctypes.c_int64(rows), int(cols), ldb_w, int(cols), _stream(bits)),
                "bnn_unpack_i32")
     return out
@@ -413,7 +425,7 @@ def maxpool_or(bits, C: int, win: int, stride: int):
     ok = stride >= 1 and 1 <= win <= min(H, W)          # anything else is left for the library to reject
     P, Q = ((H - win) // stride + 1, (W - win) // stride + 1) if ok else (1, 1)
     out = torch.empty((N, P, Q, cw), dtype=_BITS, device=bits.device)
-    with torch.cuda.device(bits.device):
+    with _on(bits):
         _check(load().bnn_maxpool_or(_ptr(bits), _ptr(out), N, H, W, int(C), int(win), int(stride), _stream(bits)),
                "bnn_maxpool_or")
     return out
@@ -430,7 +442,7 @@ def conv_f32_thr(x, w, thr, stride: int, pad: int, want_f32: bool = False):
     Q = (W + 2 * pad - k) // stride + 1
     bits = torch.empty((N, P, Q, nwords(O)), dtype=_BITS, device=x.device)
     y = torch.empty((N, P, Q, O), dtype=torch.float32, device=x.device) if want_f32 else None
-    with torch.cuda.device(x.device):
+    with _on(x):
         _check(load().bnn_conv_f32_thr(_ptr(x), _ptr(w), _ptr(thr), _ptr(y), _ptr(bits), N, H, W, C, O, k, int(stride), int(pad),
                                        _stream(x)), "bnn_conv_f32_thr")
     return (bits, y) if want_f32 else bits
@@ -450,7 +462,7 @@ def conv_f32_split_thr(x, w, thr, stride: int, pad: int, want_f32: bool = False,
     y = torch.empty((N, P, Q, O), dtype=torch.float32, device=x.device) if want_f32 else None
     if workspace is None:
         workspace = torch.empty(max(int(load().bnn_conv_f32_split_workspace_bytes(C, O, k)), 16), dtype=torch.uint8, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on(x):
         _check(load().bnn_conv_f32_split_thr_ex(_ptr(x), _ptr(w), _ptr(thr), _ptr(y), _ptr(bits), N, H, W, C, O, k, int(stride),
                                                 int(pad), int(products), _ptr(workspace), ctypes.c_size_t(workspace.numel()),
                                                 _stream(x)), "bnn_conv_f32_split_thr_ex")
@@ -470,7 +482,7 @@ def bwn_conv_thr(x, wbits, thr, C: int, stride: int, pad: int, want_f32: bool = 
     y = torch.empty((N, P, Q, O), dtype=torch.float32, device=x.device) if want_f32 else None
     if workspace is None:
         workspace = torch.empty(max(int(load().bnn_bwn_workspace_bytes(C, O, k)), 16), dtype=torch.uint8, device=x.device)
-    with torch.cuda.device(x.device):
+    with _on(x):
         _check(load().bnn_bwn_conv_thr(_ptr(x), _ptr(wbits), _ptr(thr), _ptr(y), _ptr(bits), N, H, W, C, O, k, int(stride), int(pad),
                                        _ptr(workspace), ctypes.c_size_t(workspace.numel()), _stream(x)), "bnn_bwn_conv_thr")
     return (bits, y) if want_f32 else bits
@@ -483,7 +495,7 @@ def head_f32(bits, w, C: int, want_pooled: bool = False):
     J = w.shape[0]
     y = torch.empty((N, J), dtype=torch.float32, device=bits.device)
     pooled = torch.empty((N, C), dtype=torch.int32, device=bits.device) if want_pooled else None
-    with torch.cuda.device(bits.device):
+    with _on(bits):
         _check(load().bnn_head_f32(_ptr(bits), _ptr(w), _ptr(y), _ptr(pooled), N, H * W, int(C), J, _stream(bits)), "bnn_head_f32")
     return (y, pooled) if want_pooled else y
 
@@ -617,7 +629,7 @@ class Net:
             self._ws = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
         if out is None:
             out = torch.empty((batch, self._out_cols), dtype=self._out_kind, device=x.device)
-        with torch.cuda.device(x.device):
+        with _on(x):
             _check(load().bnn_net_forward(self._h, _ptr(x), _ptr(out), batch, _ptr(self._ws), ctypes.c_size_t(self._ws.numel()),
                                           int(path), _stream(x)), "bnn_net_forward")
         return out
@@ -629,7 +641,7 @@ class Net:
         batch = x.shape[0]
         if out is None:
             out = torch.empty((batch, self._out_cols), dtype=self._out_kind, device=x.device)
-        with torch.cuda.device(x.device):
+        with _on(x):
             _check(load().bnn_net_forward_static(self._h, _ptr(x), _ptr(out), batch, int(path), _stream(x)),
                    "bnn_net_forward_static")
         return out
@@ -657,7 +669,7 @@ class Net:
             self._ws = torch.empty(max(need, 256), dtype=torch.uint8, device=x.device)
         if out is None:
             out = torch.empty((batch, self._out_cols), dtype=self._out_kind, device=x.device)
-        with torch.cuda.device(x.device):
+        with _on(x):
             _check(load().bnn_net_forward_persistent(self._h, _ptr(x), _ptr(out), batch, _ptr(self._ws),
                                                      ctypes.c_size_t(self._ws.numel()),
                                                      (1 if no_sync else 0) | (2 if give_up_at_once else 0) | ((int(grid_cap) & 0xFFFF) << 8),
