@@ -459,7 +459,9 @@ __device__ __forceinline__ void epilogue_sums(v16f (&acc)[MT][NT], const long lo
 // generic body).  Bound by its memory traffic -- 8 bytes per output against one bit -- so what counts is that nothing waits for
 // more than it needs: every access has a scalar base (its row) and one 32-bit lane offset, no vector address arithmetic and no
 // per-element tests; the residual of the next 32 rows is requested before this one's sums are formed; and the streams, each
-// byte of which is touched once, bypass the caches.  256 x 28x28x128 -> 128, 3x3, residual in, sum and bits out (209 MB): 68.4 us
+// byte of which is touched once, bypass the caches.  Only for rows of whole 128-byte lines: where rows share lines (100, 250, 511
+// channels) streaming costs 20 to 50 %, and without it this body is 6 to 9 % behind the generic one.
+// 256 x 28x28x128 -> 128, 3x3, residual in, sum and bits out (209 MB): 68.4 us
 // with the generic body (28 vector instructions per MFMA, 3.1 TB/s), 51.5 us with this one (4.1 TB/s).
 template <int MT, int NT>
 __device__ __forceinline__ void epilogue_resid(v16f (&acc)[MT][NT], const long long m0, const int n0, const int lane, const Geom& g,
@@ -532,7 +534,7 @@ __device__ __forceinline__ void epilogue(v16f (&acc)[MT][NT], const long long m0
         case EPI_SUMS: epilogue_sums<MT, NT>(acc, m0, n0, lane, g, e, corr_all); return;
         default: break;
     }
-    if (MT * NT > 1 && e.resid != nullptr && e.out16 == nullptr && !row_corr && m0 + 32 * MT <= g.rows && n0 + 32 * NT <= g.cols) {
+    if (CONV && MT * NT > 1 && e.resid != nullptr && e.out16 == nullptr && !row_corr && (e.ldc & 31) == 0 && m0 + 32 * MT <= g.rows && n0 + 32 * NT <= g.cols) {
         epilogue_resid<MT, NT>(acc, m0, n0, lane, g, e, corr_all, thi);
         return;
     }
