@@ -92,13 +92,15 @@ int conv_shape(int N, int H, int W, int C, int O, int k, int stride, int pad, in
     return BNN_OK;
 }
 
+// pool_bits (internal, used by the layer chain): where the 2x2-pooled bits of the output go if the kernel that serves the call
+// can store them too; *pooled says whether it does.
 // resid_bits (internal, used by the layer chain): a packed [N][P][Q][ceil(O/32)] tensor whose +1/-1
 // values are the residual, instead of an int32 tensor.
 int bconv_common(const uint32_t* in, const uint32_t* filt, int32_t* out, const int32_t* resid,
                  const int32_t* thr, uint32_t* bits, int N, int H, int W, int C, int O, int k, int stride,
                  int pad, int pad_mode, int path, void* stream, const uint32_t* resid_bits = nullptr,
                  const uint32_t* x2 = nullptr, const uint32_t* filt2 = nullptr, int H2 = 0, int W2 = 0, int C2 = 0,
-                 int stride2 = 1, bool sums16 = false, bool out_f32 = false) {
+                 int stride2 = 1, bool sums16 = false, bool out_f32 = false, uint32_t* pool_bits = nullptr, bool* pooled = nullptr) {
     if (!in || !filt) return BNN_ERR_INVALID_ARG;
     if (!out && !bits) return BNN_ERR_INVALID_ARG;
     if (bits && !thr) return BNN_ERR_INVALID_ARG;
@@ -126,6 +128,11 @@ int bconv_common(const uint32_t* in, const uint32_t* filt, int32_t* out, const i
         e.out16 = reinterpret_cast<int16_t*>(out); e.out = nullptr;
         e.resid16 = reinterpret_cast<const int16_t*>(resid); e.resid = nullptr;
         e.sums_tiled = (O % 32 == 0) ? 1 : 0;      // the buffers hold 32 rows more than the tensor (plan())
+    }
+    if (pool_bits != nullptr && path != BNN_PATH_VALU && capture_sink == nullptr && mfma_conv_pools(g, e)) {
+        g.pool2 = 1; g.div_qh = make_fastdiv((uint32_t)(Q / 2));
+        e.pool_bits = pool_bits;
+        *pooled = true;
     }
     return dispatch(in, filt, g, e, path, static_cast<hipStream_t>(stream));
 }
@@ -678,6 +685,7 @@ int forward_impl(bnn_net* net, const void* input, void* output, int batch, char*
     int curH = 1, curW = 1, curC = 0, cur_ld = 0;
     int32_t* R = nullptr;               // running int32 residual (same shape as cur), or null
     int rslot = 0;
+    bool pool_done = false;             // the layer before has stored this pooling layer's bits
     for (size_t i = 0; i < net->layers.size(); ++i) {
         const bnn_net::Layer& L = net->layers[i];
         uint32_t* obits = reinterpret_cast<uint32_t*>(ws + L.bits_off);
@@ -733,14 +741,21 @@ int forward_impl(bnn_net* net, const void* input, void* output, int batch, char*
                 R = nullptr;
                 break;
             }
-            case bnn_net::CONV:
-                rc = bnn_bconv_thr_ex(cur, static_cast<const uint32_t*>(L.w0), nullptr, nullptr,
-                                      static_cast<const int32_t*>(L.t0), obits, batch, curH, curW, curC, L.b, L.k,
-                                      L.stride, L.pad, L.pad_mode, path, stream);
+            case bnn_net::CONV: {
+                // a 2x2 pooling layer behind a convolution is stored by the convolution itself where its kernel can
+                const bool pool_next = i + 1 < net->layers.size() && net->layers[i + 1].kind == bnn_net::POOL &&
+                                       net->layers[i + 1].k == 2 && net->layers[i + 1].stride == 2;
+                pool_done = false;
+                rc = bconv_common(cur, static_cast<const uint32_t*>(L.w0), nullptr, nullptr, static_cast<const int32_t*>(L.t0), obits,
+                                  batch, curH, curW, curC, L.b, L.k, L.stride, L.pad, L.pad_mode, path, stream, nullptr, nullptr,
+                                  nullptr, 0, 0, 0, 1, false, false,
+                                  pool_next ? reinterpret_cast<uint32_t*>(ws + net->layers[i + 1].bits_off) : nullptr, &pool_done);
                 R = nullptr;
                 break;
+            }
             case bnn_net::POOL:
-                rc = bnn_maxpool_or(cur, obits, batch, curH, curW, curC, L.k, L.stride, stream);
+                if (!pool_done) rc = bnn_maxpool_or(cur, obits, batch, curH, curW, curC, L.k, L.stride, stream);
+                pool_done = false;
                 R = nullptr;
                 break;
             case bnn_net::BLOCK: {

@@ -51,6 +51,10 @@ struct Geom {
     FastDiv div_pq, div_q;   // divisions by P*Q and by Q (row -> image, pixel row, pixel column); rows < 2^31
     int kinv;        // ceil(65536 / k): tap / k == (tap * kinv) >> 16 for every tap < k*k + 64 (checked for k <= 42; k <= 32 accepted)
     int excl;        // 1: out-of-frame taps contribute nothing; 0: they count as -1
+    // 1: the GEMM rows of an image run over its 2x2 pooling windows, four pixels each (P and Q even; unrolled 3x3 direct kernels only), so that the
+    // epilogue can also store the pooled bits (Epi::pool_bits).  pool_row_pixel() gives a row's pixel.
+    int pool2;
+    FastDiv div_qh;  // division by Q / 2
     int b_tiled;     // BMM only: B is stored in tiles of 32 rows x 16 bytes (bnn_tile_b), ldb_w words per row as before
     // Optional second source, accumulated into the same sums: a 1x1 convolution (no padding) of
     // a second packed tensor A2 [N][H2][W2][cw2] sampled at (p*stride2, q*stride2) with filters
@@ -60,6 +64,13 @@ struct Geom {
     const uint32_t* B2;
     int H2, W2, cw2, stride2, bits2;
 };
+
+// Pixel (p, q) of row `rem` of an image in the order of Geom::pool2.
+__host__ __device__ inline void pool_row_pixel(const Geom& g, int rem, int& p, int& q) {
+    const int w = rem >> 2, pp = fast_div(w, g.div_qh);
+    p = 2 * pp + ((rem >> 1) & 1);
+    q = 2 * (w - pp * (g.Q >> 1)) + (rem & 1);
+}
 
 // What happens to each finished sum v[row][col] (all pointers may be null except as noted).
 struct Epi {
@@ -84,6 +95,7 @@ struct Epi {
     int out_f32;           // 1: `out` receives the sums converted to fp32 (exact: |v| < 2^24) instead of int32
     const int32_t* thr;    // thr[col]: bit = (v >= thr[col])
     uint32_t* bits;        // bits[row*ldbits_w + col/32]
+    uint32_t* pool_bits;   // Geom::pool2: OR of every 2x2 window's bits, [N][P/2][Q/2][ldbits_w]
     int ldbits_w;          // words between rows of bits; words beyond ceil(cols/32) are zeroed
 };
 
@@ -124,6 +136,8 @@ int persist_conv_variant(const Geom& g);
 int launch_persist_chain(const PersistNet& net, int max_tiles, int max_grid, unsigned* ctr, int sync, int spin_limit,
                          hipStream_t s);
 
+// Whether the matrix-core path serves this convolution with a kernel that can store 2x2-pooled bits beside the full ones.
+bool mfma_conv_pools(const Geom& g, const Epi& e);
 int launch_valu(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 // Skinny matrix products (at most 128 rows): workgroups of 32 columns x all rows whose waves split K.

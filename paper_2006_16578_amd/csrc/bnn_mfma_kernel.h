@@ -378,7 +378,8 @@ __device__ __forceinline__ void column_thresholds(int (&thi)[NT], bool (&cok)[NT
 // Bits only: compare the fp32 accumulators (exact integers) against the threshold shifted by the pad correction;
 // one v_cmp per accumulator register gives two packed words.
 // PANELS: the packed output is laid out in panels of 8 words (word wi of row `row` at ((wi / 8) * rows + row) * 8 + wi % 8).
-template <int MT, int NT, bool PANELS = false>
+// POOL: rows in the order of Geom::pool2, the windows' bits are stored too.
+template <int MT, int NT, bool PANELS = false, bool POOL = false>
 __device__ __forceinline__ void epilogue_bits(v16f (&acc)[MT][NT], const long long m0, const int n0, const int lane,
                                               const Geom& g, const Epi& e, const int corr_all, const int (&thi)[NT],
                                               const bool (&cok)[NT]) {
@@ -403,6 +404,26 @@ __device__ __forceinline__ void epilogue_bits(v16f (&acc)[MT][NT], const long lo
             }
         }
         const long long row = rbase + lane;
+        if constexpr (POOL) {                                // a window is four neighbouring lanes
+            if (lane < 32 && row < g.rows) {                 // (rows are a multiple of 4: whole windows)
+                const int n = fast_div((int)row, g.div_pq), rem = (int)row - n * (g.P * g.Q);
+                int p, q;
+                pool_row_pixel(g, rem, p, q);
+                const long long pix = (long long)n * (g.P * g.Q) + p * g.Q + q;
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    const int wi = (n0 >> 5) + j;
+                    uint32_t any = wout[j];
+                    any |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)any, 0xB1, 0xF, 0xF, true);    // quad_perm 1 0 3 2
+                    any |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)any, 0x4E, 0xF, 0xF, true);    // quad_perm 2 3 0 1
+                    if (wi < e.ldbits_w) {
+                        e.bits[pix * e.ldbits_w + wi] = wout[j];
+                        if ((lane & 3) == 0) e.pool_bits[(row >> 2) * e.ldbits_w + wi] = any;
+                    }
+                }
+            }
+            continue;
+        }
         if (lane < 32 && row < g.rows) {
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
@@ -591,7 +612,8 @@ __device__ __forceinline__ int extra_source(v16f (&acc)[MT][NT], const Geom& g, 
 // CPT3 > 0: a 3x3 window whose taps are exactly CPT3 chunks each (tw == CPT3 * 2 * V): the loop over the 9 * CPT3
 // chunks is unrolled in full, so that tap and chunk indices are compile-time constants and a request is a handful of
 // instructions (the layers of a network are short: their time is instruction issue, not the matrix cores).
-template <class TL, int V, bool CONV, bool EXCL, bool GUARD, int CPT3 = 0>
+// POOL: rows in the order of Geom::pool2 (a compile-time switch: the test alone cost the other layers 2 to 4 %).
+template <class TL, int V, bool CONV, bool EXCL, bool GUARD, int CPT3 = 0, bool POOL = false>
 __device__ __forceinline__ void mfma_tile(const uint32_t* __restrict__ A, const uint32_t* __restrict__ B, const Geom& g,
                                           const Epi& e, const int bx, const int by) {
     constexpr int MT = TL::MT, NT = TL::NT;
@@ -625,7 +647,8 @@ __device__ __forceinline__ void mfma_tile(const uint32_t* __restrict__ A, const 
         if (CONV) {
             const int n = fast_div((int)row, g.div_pq);
             const int rem = (int)row - n * (g.P * g.Q);
-            const int p = fast_div(rem, g.div_q), q = rem - p * g.Q;
+            int p = fast_div(rem, g.div_q), q = rem - p * g.Q;
+            if constexpr (POOL) pool_row_pixel(g, rem, p, q);
             y0[i] = p * g.stride - g.pad;
             x0[i] = q * g.stride - g.pad;
             aoff[i] = (uint32_t)(((((n - n_first) * g.H + y0[i]) * g.W + x0[i]) * g.lda_w + half * V) * 4);
@@ -808,21 +831,33 @@ __device__ __forceinline__ void mfma_tile(const uint32_t* __restrict__ A, const 
     const int pad_tap = cpt * 2 * V * 32 - g.bits_tap;
     int corr2 = 0;
     if (CONV && g.A2 != nullptr) corr2 = extra_source<MT, NT>(acc, g, m0, n0, lane, c2) - g.bits2;
+    if constexpr (POOL) {                               // bits only (mfma_conv_pools)
+        int thi[NT];
+        bool cok[NT];
+        column_thresholds<NT>(thi, cok, n0, l32, g, e);
+        epilogue_bits<MT, NT, false, true>(acc, m0, n0, lane, g, e, g.taps * pad_tap, thi, cok);
+        return;
+    }
     epilogue<MT, NT, CONV, EXCL>(acc, m0, n0, lane, g, e, g.taps * pad_tap + corr2, pad_tap, fetched);
 }
 
-template <class TL, int V, bool CONV, bool EXCL, bool GUARD, int CPT3 = 0>
+template <class TL, int V, bool CONV, bool EXCL, bool GUARD, int CPT3 = 0, bool POOL = false>
 __global__ __launch_bounds__(256, TL::MINB) void mfma_kernel(const uint32_t* __restrict__ A,
                                                              const uint32_t* __restrict__ B, Geom g, Epi e,
                                                              int gx, int gy) {
     int bx, by;
     if (!tile_coords(gx, gy, bx, by)) return;          // uniform for the workgroup
-    mfma_tile<TL, V, CONV, EXCL, GUARD, CPT3>(A, B, g, e, bx, by);
+    mfma_tile<TL, V, CONV, EXCL, GUARD, CPT3, POOL>(A, B, g, e, bx, by);
 }
 
 template <class TL, int V, bool EXCL, int CPT3>
 int launch_tile_3x3(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, int gx, int gy, unsigned nwg,
                     hipStream_t s) {
+    if constexpr (!EXCL)
+        if (g.pool2 != 0) {
+            hipLaunchKernelGGL((mfma_kernel<TL, V, true, false, false, CPT3, true>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
+            return check_launch();
+        }
     hipLaunchKernelGGL((mfma_kernel<TL, V, true, EXCL, false, CPT3>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
     return check_launch();
 }

@@ -313,6 +313,35 @@ def test_bwn_first_layer_11x11_wave_kernel(bnn, orc, shape):
     assert np.array_equal(host(yi), orc.bwn_conv_f32(xi, wb, C, st, pad))
 
 
+# 2x2 pooling behind a convolution, stored by the convolution itself on the direct kernels (even sizes) and by the pooling kernel
+# (odd sizes, other windows): every tile of the direct kernel, channel counts that fill no word, several pooled layers in a row, a
+# last 32-row block that is partly empty; check_cnn compares the full and the pooled bits of every layer
+@pytest.mark.parametrize("batch,hw,chans,win", [(3, 12, (64, 128, 40), 2), (5, 8, (128, 256, 256), 2), (1, 4, (96, 33, 70), 2),
+                                                (3, 9, (64, 65, 128), 2), (2, 12, (64, 64, 64), 3), (90, 32, (33, 256, 512), 2),
+                                                (40, 64, (512, 60, 128), 2)])
+def test_convolution_stores_pooled_bits(bnn, orc, batch, hw, chans, win):
+    rng = np.random.default_rng(batch * 100 + hw)
+    layers = [{"op": "bwn", "W": wl.random_bits(rng, (chans[0], 3, 3), 3), "thr": np.zeros(chans[0], np.float32), "C": 3, "stride": 1, "pad": 1}]
+    size = hw
+    for cin, cout in zip(chans, chans[1:]):
+        layers.append({"op": "bconv", "W": wl.random_bits(rng, (cout, 3, 3), cin), "thr": rng.integers(-20, 21, size=cout).astype(np.int32),
+                       "C": cin, "stride": 1, "pad": 1})
+        layers.append({"op": "pool", "win": win, "stride": 2})
+        size = (size - win) // 2 + 1
+    kernel = bnn.bconv_kernel_name(batch, hw, hw, chans[0], chans[1], 3, 1, 1)
+    print(batch, hw, chans, kernel, flush=True)
+    net = bnn.Net.from_layers(layers + [], hw)
+    x = rng.integers(-100, 101, size=(batch, hw, hw, 3)).astype(np.float32)     # exact in fp32: no bit depends on rounding
+    xd = to_dev(x)
+    net._out_kind, net._out_cols = torch.int32, 1
+    net.forward(xd)
+    outs = nets.cnn_forward(x, layers, tier=1, keep=True)
+    for i, ref in enumerate(outs):
+        got = words(net.layer_bits(i)).reshape(ref.shape)
+        assert np.array_equal(got, ref), "layer %d (%s)" % (i, layers[i]["op"])
+    assert outs[-1].shape[1] == size
+
+
 # 3x3 and 5x5 first layers of 3-channel images (one LDS record per pixel): every fragment shape (8, 16, 32 columns), one and two
 # 64-channel groups and ragged ones, stride 2, no and large padding, images smaller than a tile; integer inputs are exact in any
 # order, so the sums equal the oracle's bit for bit; thresholds of +-infinity; a NaN pixel changes no output that does not cover it
