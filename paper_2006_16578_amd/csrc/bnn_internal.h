@@ -161,7 +161,8 @@ int launch_mfma_conv_v4(const uint32_t* A, const uint32_t* B, const Geom& g, con
 int launch_mfma_conv_v2(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma_conv_v1(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 // Name of the kernel variant launch_mfma / launch_valu would pick for this geometry.
-const char* describe_mfma(const Geom& g, bool int32_out = false);
+// (pool2: a 2x2 pooling layer follows in a layer chain.)
+const char* describe_mfma(const Geom& g, bool int32_out = false, bool pool2 = false);
 const char* describe_valu(const Geom& g);
 
 int launch_threshold_pack(const int32_t* X, const int32_t* thr, uint32_t* bits, long long rows, int cols,

@@ -113,7 +113,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void conv_xlds_kernel(const uint32
     uint32_t boff[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
-        const int ch = SWAP ? n0 + 32 * ((l32 >> 2) & 1) + 16 * j + 4 * (l32 >> 3) + (l32 & 3) : n0 + 32 * j + l32;
+        const int ch = n0 + (SWAP ? mfma::dealt_column(j, l32) : 32 * j + l32);
         boff[j] = (uint32_t)(min(ch, g.cols - 1) * g.ldb_w + 4 * half) * 4u;            // < 2^31 (checked on the host)
     }
     const int nfull = x.kwords >> 3, tail = x.kwords & 7;
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void conv_xlds_kernel(const uint32
     }
 
     int corr = 0;                                       // pad bits of the fused second source only
-    if (g.A2 != nullptr) corr = mfma::extra_source<MT, NT, SWAP>(acc, g, m0, n0, lane, c2) - g.bits2;
+    if (g.A2 != nullptr) corr = mfma::extra_source<MT, NT, SWAP, SWAP>(acc, g, m0, n0, lane, c2) - g.bits2;
     if constexpr (!SWAP) {
         mfma::epilogue<MT, NT, true, false>(acc, m0, n0, lane, g, e, corr, 0);
     } else {

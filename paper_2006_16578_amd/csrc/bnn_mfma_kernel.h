@@ -565,10 +565,15 @@ __device__ __forceinline__ void epilogue(v16f (&acc)[MT][NT], const long long m0
         epilogue_generic<MT, NT, CONV, EXCL, false>(acc, m0, n0, lane, g, e, corr_all, pad_tap, thi, cok, row_corr, fetched);
 }
 
+// 64 columns dealt to the rows of two fragments so that a half-wave of the accumulators owns 32 consecutive ones: the column of
+// row l32 of fragment j (accumulator register r of fragment j then holds column 32 * half + 16 * j + r).
+__device__ __forceinline__ int dealt_column(int j, int l32) { return 32 * ((l32 >> 2) & 1) + 16 * j + 4 * (l32 >> 3) + (l32 & 3); }
+
 // The optional second source of a Geom (fused 1x1 downsample shortcut): a handful of K-steps read
 // straight from global memory.  Returns the number of bit positions it multiplied.  SWAP: the filters are the MFMA's
-// row operand (accumulators hold 16 channels of one pixel per lane instead of one channel of 16 pixels).
-template <int MT, int NT, bool SWAP = false>
+// row operand (accumulators hold 16 channels of one pixel per lane instead of one channel of 16 pixels).  DEALT: the columns lie
+// in the order of dealt_column() instead of their own; it has to be the order of the sums in acc.
+template <int MT, int NT, bool SWAP = false, bool DEALT = false>
 __device__ __forceinline__ int extra_source(v16f (&acc)[MT][NT], const Geom& g, const long long m0, const int n0,
                                             const int lane, const uint32_t c2) {
     const int l32 = lane & 31;
@@ -585,7 +590,7 @@ __device__ __forceinline__ int extra_source(v16f (&acc)[MT][NT], const Geom& g, 
         ar[i] = g.A2 + (((long long)n * g.H2 + p * g.stride2) * g.W2 + q * g.stride2) * g.cw2;
     }
 #pragma unroll
-    for (int j = 0; j < NT; ++j) br[j] = g.B2 + (long long)min(n0 + 32 * j + l32, g.cols - 1) * g.cw2;
+    for (int j = 0; j < NT; ++j) br[j] = g.B2 + (long long)min(n0 + (DEALT ? dealt_column(j, l32) : 32 * j + l32), g.cols - 1) * g.cw2;
     const int steps = (g.cw2 + 1) / 2;
     for (int ks = 0; ks < steps; ++ks) {
         const int wo = 2 * ks + half;

@@ -313,6 +313,46 @@ def test_bwn_first_layer_11x11_wave_kernel(bnn, orc, shape):
     assert np.array_equal(host(yi), orc.bwn_conv_f32(xi, wb, C, st, pad))
 
 
+# Residual chains large enough for the kernel whose pixels are expanded in LDS (at least 96 workgroup tiles), of widths that keep row-major
+# sums: a block with a 1x1 shortcut whose sum is not kept (a block with a shortcut or the head follows: bits only, its channels in the kernel's
+# own order), one whose sum is kept, identity blocks with a 16-bit residual in; both padding conventions; and a chain whose
+# sums pass 16 bits (48 -> 96 channels, then eight blocks of 512).  `served`: the blocks whose second convolution runs there.
+@pytest.mark.parametrize("batch,hw,cin,blocks,pad_mode,served", [
+    (64, 28, 64, ((64, 90, 1), (90, 86, 1), (86, 86, 1), (86, 64, 2)), 0, (0, 1, 2)),
+    (64, 8, 64, ((64, 300, 1), (300, 290, 1), (290, 290, 1)), 0, (0, 1, 2)),
+    (64, 28, 33, ((33, 100, 1), (100, 100, 2), (100, 64, 2)), 1, (0, 1)),
+    (32, 14, 64, ((64, 250, 1), (250, 230, 1), (230, 230, 1)), 1, (0, 1, 2)),
+    (64, 14, 48, ((48, 96, 1), (96, 512, 4)) + ((512, 512, 1),) * 7, 0, (0,))])
+def test_block_chains_expanded_in_lds(bnn, orc, batch, hw, cin, blocks, pad_mode, served):
+    rng = np.random.default_rng(batch + hw + cin)
+    W, tau = wl.random_bits(rng, (cin, 3, 3), 3), np.zeros(cin, np.float32)
+    net = bnn.Net()
+    net.input_bwn_f32(to_dev(W), to_dev(tau), hw, hw, 3, 1, 1)
+    params, size = [], hw
+    for b, (ci, co, st) in enumerate(blocks):
+        blk = {"cin": ci, "cout": co, "stride": st, "W1": wl.random_bits(rng, (co, 3, 3), ci), "W2": wl.random_bits(rng, (co, 3, 3), co),
+               "thr1": rng.integers(-20, 21, size=co).astype(np.int32), "thr2": rng.integers(-20, 21, size=co).astype(np.int32)}
+        if st != 1 or ci != co:
+            blk["Wd"] = wl.random_bits(rng, (co, 1, 1), ci)
+        params.append(blk)
+        net.add_block(to_dev(blk["W1"]), to_dev(blk["thr1"]), to_dev(blk["W2"]), to_dev(blk["thr2"]),
+                      to_dev(blk["Wd"]) if "Wd" in blk else None, ci, co, st, pad_mode)
+        size = (size - 1) // st + 1
+        kernel = bnn.bconv_kernel_name(batch, size, size, co, co, 3, 1, 1, pad_mode=pad_mode, shortcut="Wd" in blk)
+        assert kernel.startswith("mfma_fp4_conv_xlds") == (b in served), (b, kernel)
+    w = rng.normal(0.0, 0.02, size=(7, blocks[-1][1])).astype(np.float32)
+    net.add_head_f32(to_dev(w))
+    x = rng.integers(-100, 101, size=(batch, hw, hw, 3)).astype(np.float32)
+    net.forward(to_dev(x))
+    first = words(net.layer_bits(0)).reshape(batch, hw, hw, -1)
+    assert np.array_equal(first, orc.pack_f32(orc.bwn_conv_f32(x, W, 3, 1, 1), tau))
+    tr = nets.resnet18_forward(x, {"blocks": params, "fc_w": w, "stem_w": np.zeros((cin, 1, 1, 3), np.float32), "stem_thr": tau},
+                               stem_bits=first, tier=1, keep=True, pad_mode=pad_mode)
+    for b in range(len(blocks)):
+        got = words(net.layer_bits(b + 1)).reshape(tr["y%d" % b].shape)
+        assert np.array_equal(got, tr["y%d" % b]), "block %d" % b
+
+
 # 2x2 pooling behind a convolution, stored by the convolution itself on the direct kernels (even sizes) and by the pooling kernel
 # (odd sizes, other windows): every tile of the direct kernel, channel counts that fill no word, several pooled layers in a row, a
 # last 32-row block that is partly empty; check_cnn compares the full and the pooled bits of every layer
