@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void pack_kernel(PackJob j0, PackJob j1, unsig
         int col[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int rel = wi0 + min(u * WPL + lane / LW, left - 1);         // wi0 < ldb_w < 2^26
+            const int rel = wi0 + min(u * WPL + lane / LW, left - 1);         // wi0 < ldb_w <= 2^26: columns stay below 2^31
             const int dr = fast_div(rel, j.div_ldb);
             col[u] = (rel - dr * j.ldb_w) * 32 + e0;
             const int c = min(col[u], j.cols - E);
@@ -117,6 +117,8 @@ int launch_pack(PackJob j0, const PackJob* second, const TH* thr, TH thr0, hipSt
     // eight loads in flight per lane where that still gives the chip's SIMDs two waves each; else one
     const long long words = j0.words + j1.words;
     const bool deep = words >= 2048LL * WPL * UMAX;
+    // columns are counted in 32 bits (a matrix of 2^31 - 1 columns has 2^26 words in a row: more are pad words only)
+    if (j0.ldb_w > (1 << 26) || j1.ldb_w > (1 << 26)) return BNN_ERR_UNSUPPORTED;
     const int per_block = 4 * WPL * (deep ? UMAX : 1);
     const long long b0 = cdiv(j0.words, per_block), b1 = second != nullptr ? cdiv(j1.words, per_block) : 0;
     if (b0 + b1 >= (1LL << 31)) return BNN_ERR_UNSUPPORTED;

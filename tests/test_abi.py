@@ -107,6 +107,18 @@ def test_net_workspace_plan():
     assert big >= 2 * 64 * 8 * 8 * 64 * 2 + 2 * 64 * 8 * 8 * 8
 
 
+def test_packs_refuse_rows_beyond_32_bit_columns():
+    # a row stride of more than 2^26 words would pass 2^31 columns: refused before anything is launched (the pointers are never read)
+    import paper_2006_16578_amd as b
+    lib = b.load()
+    p, ld = ctypes.c_void_p(256), (1 << 26) + 1
+    rows = ctypes.c_int64(1)
+    assert lib.bnn_threshold_pack(p, p, p, rows, 64, 64, ld, None) == -3
+    assert lib.bnn_pack_f32(p, p, p, rows, 64, ld, None) == -3
+    assert lib.bnn_pack_u8(p, 127, p, rows, 64, ld, None) == -3
+    assert lib.bnn_sign_pack_f32(p, p, rows, 64, 64, ld, None) == -3
+
+
 def test_bench_refuses_more_than_one_gpu():
     import subprocess
     import sys
