@@ -24,6 +24,9 @@ struct PackJob {
 };
 
 template <typename T> struct PackVec { typedef T type __attribute__((ext_vector_type(16 / sizeof(T)), aligned(4))); };
+// 16 bytes as they are loaded: at any 4-byte boundary, of byte matrices (whose rows may start anywhere) at any byte
+template <typename T> struct PackRaw { typedef int32_t type __attribute__((ext_vector_type(4), aligned(4))); };
+template <> struct PackRaw<uint8_t> { typedef int32_t type __attribute__((ext_vector_type(4), aligned(1))); };
 
 template <int CTRL> __device__ __forceinline__ uint32_t or_dpp(uint32_t v) {
     return v | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
@@ -61,9 +64,9 @@ __global__ __launch_bounds__(256) void pack_kernel(PackJob j0, PackJob j1, unsig
         }
         if ((lane & (LW - 1)) == u) mine = m;
     };
-    if (j.cols >= E && (sizeof(T) == 4 || ((reinterpret_cast<uintptr_t>(j.x) & 3u) == 0 && (j.ldx & 3) == 0))) {       // uniform
+    if (j.cols >= E) {                               // uniform
         // no branch: a lane whose values pass the end of the row loads the row's last E values and shifts its bits
-        typedef typename PackVec<int32_t>::type V4;  // 16 bytes, 4-byte aligned
+        typedef typename PackRaw<T>::type V4;
         V4 raw[U];
         TH th[U][SCALAR_THR ? 1 : E];
         int col[U];
@@ -91,7 +94,7 @@ __global__ __launch_bounds__(256) void pack_kernel(PackJob j0, PackJob j1, unsig
             const int past = max(col[u] - (j.cols - E), 0);                   // values of this lane past the row's end
             meet(past < E ? m >> past : 0u, u);
         }
-    } else {                                         // rows of fewer than E values, byte rows that are not 4-byte aligned
+    } else {                                         // rows of fewer than E values
         for (int u = 0; u < U; ++u) {
             const int w = u * WPL + lane / LW, rel = wi0 + w;
             const int dr = fast_div(rel, j.div_ldb);

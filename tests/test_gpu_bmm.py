@@ -231,6 +231,17 @@ def test_packs_at_row_ends(bnn, orc, rows, cols, ld):
     assert np.array_equal(words(bnn.sign_pack_f32(to_dev(xf), ldb_w=ld)), ref)
 
 
+@pytest.mark.parametrize("offset", [1, 2, 3, 4])
+@pytest.mark.parametrize("rows,cols", [(37, 785), (5, 16), (3, 15), (1100, 4096), (5000, 1001)])
+def test_pack_bytes_at_any_address(bnn, orc, rows, cols, offset):
+    # byte rows need no alignment: every 16-byte load of the kernel may start anywhere (one load in flight and, from 131072 words, two)
+    rng = np.random.default_rng(rows + cols + offset)
+    x = rng.integers(0, 256, size=(rows, cols)).astype(np.uint8)
+    d = torch.zeros(offset + rows * cols, dtype=torch.uint8, device="cuda")
+    d[offset:] = to_dev(x).reshape(-1)
+    assert np.array_equal(words(bnn.pack_u8(d[offset:].reshape(rows, cols), 127)), orc.pack_u8(x, 127))
+
+
 def test_error_codes(bnn):
     A = torch.zeros((4, 4), dtype=torch.int32, device="cuda")
     with pytest.raises(bnn.BnnError) as e:
