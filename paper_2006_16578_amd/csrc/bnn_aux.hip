@@ -12,7 +12,8 @@ namespace {
 // in flight: a lane loads 16 bytes at a time (E values; 32 / E neighbouring lanes share an output word and meet through
 // lane exchanges), U such loads are issued before the first is used, and the unit of work is the output WORD -- not the row --
 // so that any row length and row stride keeps all lanes busy and a wave's U * 2 E words leave in coalesced stores.
-// Loads are non-temporal: x is read once.  Measured, inputs not in a cache: threshold of 205 MB of int32 + pooling of its
+// The loads of the deep form are non-temporal (x is read once); a smaller x may still be in a cache, where streaming costs (12 x 41x41x118
+// threshold + pooling 6.8 us streamed, 6.3 plain; 3 x 33x33x96 5.27 and 5.14).  Measured, inputs not in a cache: threshold of 205 MB of int32 + pooling of its
 // bits 85.4 us with one wave per row and one 4-byte load in flight, 36.2 us now; the general product of 4096^3 (two operands
 // of 67 MB binarized, then 35 us of product) 116 -> 54.5 us.  Two matrices in one launch: the operands of such a product.
 struct PackJob {
@@ -76,7 +77,8 @@ __global__ __launch_bounds__(256) void pack_kernel(PackJob j0, PackJob j1, unsig
             const int dr = fast_div(rel, j.div_ldb);
             col[u] = (rel - dr * j.ldb_w) * 32 + e0;
             const int c = min(col[u], j.cols - E);
-            raw[u] = __builtin_nontemporal_load(reinterpret_cast<const V4*>(xr0 + (long long)dr * j.ldx + c));
+            const V4* src = reinterpret_cast<const V4*>(xr0 + (long long)dr * j.ldx + c);
+            raw[u] = U > 1 ? __builtin_nontemporal_load(src) : *src;
             if constexpr (!SCALAR_THR) {
                 typedef TH THV __attribute__((ext_vector_type(4), aligned(4)));
                 const THV t = *reinterpret_cast<const THV*>(thr + c);
