@@ -306,7 +306,7 @@ const char* bnn_bconv_kernel_name_ex(int N, int H, int W, int C, int O, int k, i
                                      int out_kind, int flags) {
     int P, Q;
     if (out_kind != BNN_OUT_BITS && out_kind != BNN_OUT_INT32) return "invalid";
-    if (flags & ~(BNN_CONV_SHORTCUT | BNN_CONV_POOL2)) return "invalid";
+    if (flags & ~(BNN_CONV_SHORTCUT | BNN_CONV_POOL2 | BNN_CONV_RESIDUAL | BNN_CONV_KEEP_SUM)) return "invalid";
     if (conv_shape(N, H, W, C, O, k, stride, pad, pad_mode, &P, &Q) != BNN_OK) return "invalid";
     static const uint32_t some_words = 0u;        // the choice only asks whether there is a second source
     Geom g = {};
@@ -315,7 +315,7 @@ const char* bnn_bconv_kernel_name_ex(int N, int H, int W, int C, int O, int k, i
     g.rows = (long long)N * P * Q; g.cols = O; g.conv = 1; g.taps = k * k; g.tw = words(C); g.bits_tap = C;
     g.H = H; g.W = W; g.P = P; g.Q = Q; g.k = k; g.stride = stride; g.pad = pad; g.lda_w = g.tw; g.ldb_w = k * k * g.tw;
     return path == BNN_PATH_VALU ? describe_valu(g)
-                                 : describe_mfma(g, out_kind == BNN_OUT_INT32, (flags & BNN_CONV_POOL2) != 0);
+                                 : describe_mfma(g, out_kind == BNN_OUT_INT32, flags);
 }
 
 int bnn_bmm(const uint32_t* A, const uint32_t* B, int32_t* C, int M, int N, int K, int lda_w, int ldb_w, int ldc,

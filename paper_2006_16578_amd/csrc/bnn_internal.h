@@ -154,15 +154,15 @@ const char* describe_mfma_conv_patch(const Geom& g);
 int launch_mfma_conv_patch(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 // Other windows and channel counts whose input patch, expanded to E2M1, fits LDS.
 bool mfma_conv_xlds_takes(const Geom& g, const Epi& e);
-const char* describe_mfma_conv_xlds(const Geom& g);
+const char* describe_mfma_conv_xlds(const Geom& g, const Epi& e);
 int launch_mfma_conv_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma_conv_staged(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma_conv_v4(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma_conv_v2(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma_conv_v1(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 // Name of the kernel variant launch_mfma / launch_valu would pick for this geometry.
-// (pool2: a 2x2 pooling layer follows in a layer chain.)
-const char* describe_mfma(const Geom& g, bool int32_out = false, bool pool2 = false);
+// (flags: those of bnn_bconv_kernel_name_ex.)
+const char* describe_mfma(const Geom& g, bool int32_out = false, int flags = 0);
 const char* describe_valu(const Geom& g);
 
 int launch_threshold_pack(const int32_t* X, const int32_t* thr, uint32_t* bits, long long rows, int cols,

@@ -57,7 +57,7 @@ int launch_mfma(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
     return launch_mfma_conv_v1(A, B, g, e, s);
 }
 
-const char* describe_mfma(const Geom& g, bool int32_out, bool pool2) {
+const char* describe_mfma(const Geom& g, bool int32_out, int flags) {
     if (mfma_skinny_takes(g)) return describe_mfma_skinny(g);
     static int32_t some_output;
     static uint32_t some_bits;
@@ -65,16 +65,21 @@ const char* describe_mfma(const Geom& g, bool int32_out, bool pool2) {
     e.out = int32_out ? &some_output : nullptr;
     e.bits = int32_out ? nullptr : &some_bits;
     e.ldbits_w = (g.cols + 31) / 32;
+    e.ldc = g.cols;
+    static int16_t some_sums;
+    if (flags & BNN_CONV_RESIDUAL) e.resid16 = &some_sums;
+    if (flags & BNN_CONV_KEEP_SUM) e.out16 = &some_sums;
+    e.sums_tiled = (flags & (BNN_CONV_RESIDUAL | BNN_CONV_KEEP_SUM)) && g.cols % 32 == 0 ? 1 : 0;
     const int tile = mfma::pick_tile(g, &e);
     if (tile == 0 && mfma_wide_takes(g, e)) return "mfma_fp4_bmm_xlds_wg256x256";
     if (mfma_conv_patch_takes(g, e)) return describe_mfma_conv_patch(g);
-    if (mfma_conv_xlds_takes(g, e)) return describe_mfma_conv_xlds(g);
-    if (pool2 && mfma_conv_pools(g, e))
+    if (mfma_conv_xlds_takes(g, e)) return describe_mfma_conv_xlds(g, e);
+    if ((flags & BNN_CONV_POOL2) && mfma_conv_pools(g, e))
         return tile == 0   ? "mfma_fp4_conv_wg256x128_pool2"
                : tile == 1 ? "mfma_fp4_conv_wg512x64_pool2"
                : tile == 2 ? "mfma_fp4_conv_wg128x128_pool2"
                            : "mfma_fp4_conv_wg64x64_pool2";
-    const bool st = !g.b_tiled && staged_ok(g, tile);
+    const bool st = !g.b_tiled && !e.sums_tiled && staged_ok(g, tile);
     switch (tile) {
         case 0: return g.conv ? (st ? "mfma_fp4_conv_lds_wg256x128" : "mfma_fp4_conv_wg256x128")
                               : (st ? "mfma_fp4_bmm_lds_wg256x128" : "mfma_fp4_bmm_wg256x128");

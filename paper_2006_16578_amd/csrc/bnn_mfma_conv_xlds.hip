@@ -323,6 +323,22 @@ bool fill_args(const Geom& g, int tile_rows, int tile_cols, XArgs* x, size_t* ld
     return true;
 }
 
+// What a call asks of the epilogue.
+enum OutputForm {
+    OUT_BITS,               // packed bits alone: the filters are the row operand, the bits leave as whole words
+    OUT_SUMS,               // int32 sums alone
+    OUT_STREAMED_RESIDUAL,  // an int32 residual in, rows of whole 128-byte lines: epilogue_resid
+    OUT_RESIDUAL,           // any other residual in: the general epilogue
+    OUT_BITS_AND_SUMS       // bits and sums without a residual: the general epilogue
+};
+
+OutputForm output_form(const Epi& e) {
+    if (e.resid != nullptr || e.resid16 != nullptr || e.resid_bits != nullptr)
+        return e.resid != nullptr && e.out16 == nullptr && (e.ldc & 31) == 0 ? OUT_STREAMED_RESIDUAL : OUT_RESIDUAL;
+    if (e.out == nullptr && e.out16 == nullptr) return OUT_BITS;
+    return e.bits == nullptr ? OUT_SUMS : OUT_BITS_AND_SUMS;
+}
+
 template <int MT, int NT, int WM, int WN>
 int launch_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
     XArgs x;
@@ -330,8 +346,7 @@ int launch_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
     if (!fill_args(g, WM * MT * 32, WN * NT * 32, &x, &lds)) return BNN_ERR_UNSUPPORTED;
     const int gx = (int)cdiv(g.rows, WM * MT * 32), gy = (int)cdiv(g.cols, WN * NT * 32);
     const unsigned nwg = (unsigned)(cdiv((long long)gx * gy, 8) * 8);
-    const bool swap = e.bits != nullptr && e.out == nullptr && e.out16 == nullptr && e.resid == nullptr && e.resid16 == nullptr &&
-                      e.resid_bits == nullptr;
+    const bool swap = output_form(e) == OUT_BITS;
     static const hipError_t attr0 = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_xlds_kernel<MT, NT, WM, WN, true>),
                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)XLDS_MAX);
     static const hipError_t attr1 = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_xlds_kernel<MT, NT, WM, WN, false>),
@@ -345,10 +360,35 @@ int launch_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
 struct XTile { int rows, cols, mfmas; };                // mfmas: per wave and K-step
 constexpr XTile XTILES[] = {{0, 0, 0}, {256, 128, 8}, {128, 256, 8}, {512, 64, 8}, {128, 128, 4}, {256, 64, 4}};
 
+// Fewest workgroups from which this kernel is the faster one, 0: it is not.  With bits alone the 64 x 64 tiles of the direct kernel,
+// four times as many, win below about 96 (49 workgroups 0.87 of their speed, 98: 1.04, 171: 1.3).  Everything else leaves through the
+// accumulators' rows, load and store per element, and what a workgroup of four large wave tiles waits there (7 to 12 us through the general
+// epilogue) is hidden only by other workgroups: it takes more of them, or a longer K, whose saving outweighs it.  Measured, this kernel's
+// speed over the direct one's (3x3, channels = filters, -1 / excluded padding):
+//   sums alone         104 workgroups 0.83 to 0.99 / 1.2 to 1.3, 152: 1.03 to 1.07, 200: 1.2 to 1.4; the unrolled forms (4 and 8 words, excluded
+//                      padding) 0.95 to 1.03 at 104, 1.3 at 200; 90 channels against the 256x128 tile of the direct kernel 0.97
+//   streamed residual  104: 0.69 to 0.80 / 0.89 to 0.97, 152: 0.85 / 1.05, 200: 1.01 to 1.25 / 1.24 to 1.5, 392 and more: 1.08 to 1.4
+//   other residuals    104: 0.6 to 0.7 / 0.78 to 0.92, 152 with 90 words of K 0.77 / 0.9, 200: 0.90 with 27 words, 1.1 with 63, 1.46 with 126 / 1.1
+//                      to 1.5, the unrolled forms 0.83 to 0.95; 296 to 392: 1.1 to 1.6; 27 words against the 256x128 tile 0.97 to 1.05
+//   bits and sums      27 words 0.6 to 0.9 at any count, 63: 0.67 at 104, 1.0 at 200 and 392, 90: 1.13 to 1.37 from 296 /
+//                      18 words 0.93 at 392, 27: 0.99 at 200, 1.1 at 392, 63: 1.17 at 200, unrolled forms 0.8 at 200, 1.1 at 392
+int min_workgroups(const Geom& g, OutputForm form) {
+    const int kwords = g.taps * g.tw;
+    const bool unrolled = g.k == 3 && (g.tw == 2 || g.tw == 4 || g.tw == 8 || g.tw == 16);
+    const bool against_big_tile = !g.excl && kwords < 45 && mfma::pick_tile(g) == 0;
+    switch (form) {
+        case OUT_BITS: return 96;
+        case OUT_SUMS: return against_big_tile && (g.cols & 31) != 0 ? 0 : g.excl && !unrolled ? 96 : 128;
+        case OUT_STREAMED_RESIDUAL: return !g.excl ? 192 : unrolled ? 256 : 128;
+        case OUT_RESIDUAL: return against_big_tile ? 0 : (g.excl ? unrolled : kwords < 63) ? 256 : 192;
+        default: return kwords < (g.excl ? 27 : 63) ? 0 : (g.excl && kwords < 63) || unrolled ? 256 : 192;
+    }
+}
+
 // Tile for this geometry, 0: another kernel's.  Among the tiles whose patch fits LDS, the one with the least estimated time: rounds
 // of 512 workgroups times the cycles of one (K-steps, a little more than their MFMAs take where a step has only four; staging;
 // epilogue; the rest).
-int xlds_tile(const Geom& g) {
+int xlds_tile(const Geom& g, const Epi& e) {
     if (!g.conv || g.rows >= (1LL << 31) - 1024) return 0;
     // What the other kernels do as well or better (measured, this kernel's speed over theirs): 1x1 windows and
     // filters of less than two chunks, whose patch is used too little (0.7 to 0.9), the unrolled 3x3 forms of 2, 4, 8 and 16 words per pixel (0.85 to 1.06) -- except with excluded
@@ -359,16 +399,19 @@ int xlds_tile(const Geom& g) {
     const bool pad_bits = g.bits_tap != g.tw * 32;
     if (g.k == 3 && (g.tw == 2 || g.tw == 4 || g.tw == 8 || g.tw == 16) && !(g.excl && pad_bits)) return 0;
     if (!g.excl && (mfma::conv_stages_through_lds(g) || g.tw % 8 == 0)) return 0;
+    const OutputForm form = output_form(e);
+    const int least = min_workgroups(g, form);
+    if (least == 0) return 0;
+    const bool small_only = form == OUT_STREAMED_RESIDUAL || form == OUT_RESIDUAL;      // (the residual of four row fragments at a time: 0.92 of two)
     int best = 0;
     double best_cost = 0.;
     const double steps = (g.taps * g.tw + 1) / 2;
-    for (int t = 1; t <= 5; ++t) {
+    for (int t = small_only ? 4 : 1; t <= 5; ++t) {
         XArgs x;
         size_t lds;
         const long long gy = cdiv(g.cols, XTILES[t].cols), wgs = cdiv(g.rows, XTILES[t].rows) * gy;
-        // Few workgroups: the 64 x 64 tiles of the direct kernel have four times as many (49 workgroups 0.87 of its speed, 98: 1.04,
-        // 171: 1.3).  Many empty columns: 0.77 at 64 of 128.
-        if (wgs < 96 || (double)(gy * XTILES[t].cols) > 1.5 * g.cols) continue;
+        // Many empty columns: 0.77 at 64 of 128.
+        if (wgs < least || (double)(gy * XTILES[t].cols) > 1.5 * g.cols) continue;
         if (!fill_args(g, XTILES[t].rows, XTILES[t].cols, &x, &lds)) continue;
         const double m = XTILES[t].mfmas;
         const double wg = steps * m * (m < 8. ? 44. : 36.) + (double)x.px_max * g.tw / 4. + m * 160. + 1500.;
@@ -380,10 +423,10 @@ int xlds_tile(const Geom& g) {
 
 }  // namespace
 
-bool mfma_conv_xlds_takes(const Geom& g, const Epi& e) { return !e.sums_tiled && xlds_tile(g) != 0; }
+bool mfma_conv_xlds_takes(const Geom& g, const Epi& e) { return !e.sums_tiled && xlds_tile(g, e) != 0; }
 
-const char* describe_mfma_conv_xlds(const Geom& g) {
-    switch (xlds_tile(g)) {
+const char* describe_mfma_conv_xlds(const Geom& g, const Epi& e) {
+    switch (xlds_tile(g, e)) {
         case 1: return "mfma_fp4_conv_xlds_wg256x128";
         case 2: return "mfma_fp4_conv_xlds_wg128x256";
         case 3: return "mfma_fp4_conv_xlds_wg512x64";
@@ -393,7 +436,7 @@ const char* describe_mfma_conv_xlds(const Geom& g) {
 }
 
 int launch_mfma_conv_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
-    switch (xlds_tile(g)) {
+    switch (xlds_tile(g, e)) {
         case 1: return launch_xlds<4, 2, 2, 2>(A, B, g, e, s);
         case 2: return launch_xlds<4, 2, 1, 4>(A, B, g, e, s);
         case 3: return launch_xlds<4, 2, 4, 1>(A, B, g, e, s);

@@ -107,6 +107,30 @@ def test_net_workspace_plan():
     assert big >= 2 * 64 * 8 * 8 * 64 * 2 + 2 * 64 * 8 * 8 * 8
 
 
+def test_lds_expanded_convolutions_by_output():
+    # bits alone go to that kernel from 96 workgroups; sums and residuals leave through a slower epilogue and need more workgroups or a longer K
+    import paper_2006_16578_amd as b
+
+    def served(batch, hw, C, **kw):
+        return b.bconv_kernel_name(batch, hw, hw, C, C, 3, 1, 1, **kw).startswith("mfma_fp4_conv_xlds")
+
+    for pad_mode in (0, 1):
+        assert served(64, 14, 90, pad_mode=pad_mode) and served(64, 14, 90, pad_mode=pad_mode, shortcut=True)        # 98 workgroups
+        for kw in (dict(residual=True), dict(keep_sum=True, shortcut=True), dict(residual=True, keep_sum=True)):
+            assert not served(64, 14, 90, pad_mode=pad_mode, **kw)
+            assert served(256, 14, 300, pad_mode=pad_mode, **kw)
+    # 27 words of K, 392 workgroups: a residual pays in both conventions, bits and sums only where the direct kernel corrects by pixel
+    assert served(64, 28, 90, residual=True) and not served(64, 28, 90, shortcut=True, keep_sum=True)
+    assert served(64, 28, 90, pad_mode=1, residual=True) and served(64, 28, 90, pad_mode=1, shortcut=True, keep_sum=True)
+    # ... and not against the direct kernel's 256x128 tile
+    assert not served(128, 28, 90, residual=True) and served(128, 28, 90)
+    # sums alone: 128 workgroups, 96 with excluded padding and no unrolled form of the direct kernel
+    assert not served(64, 14, 90, int32_out=True) and served(128, 14, 90, int32_out=True) and served(64, 14, 90, pad_mode=1, int32_out=True)
+    assert not served(64, 14, 100, pad_mode=1, int32_out=True)
+    # blocked 16-bit sums stay on the direct kernels
+    assert not served(256, 14, 96, residual=True, keep_sum=True)
+
+
 def test_packs_refuse_rows_beyond_32_bit_columns():
     # a row stride of more than 2^26 words would pass 2^31 columns: refused before anything is launched (the pointers are never read)
     import paper_2006_16578_amd as b

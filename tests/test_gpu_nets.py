@@ -313,15 +313,18 @@ def test_bwn_first_layer_11x11_wave_kernel(bnn, orc, shape):
     assert np.array_equal(host(yi), orc.bwn_conv_f32(xi, wb, C, st, pad))
 
 
-# Residual chains large enough for the kernel whose pixels are expanded in LDS (at least 96 workgroup tiles), of widths that keep row-major
-# sums: a block with a 1x1 shortcut whose sum is not kept (a block with a shortcut or the head follows: bits only, its channels in the kernel's
-# own order), one whose sum is kept, identity blocks with a 16-bit residual in; both padding conventions; and a chain whose
-# sums pass 16 bits (48 -> 96 channels, then eight blocks of 512).  `served`: the blocks whose second convolution runs there.
+# Residual chains large enough for the kernel whose pixels are expanded in LDS, of widths that keep row-major sums: blocks with a 1x1 shortcut
+# whose sum is not kept (bits only, its channels in the kernel's own order) and whose sum is kept, identity blocks that add packed bits or
+# a 16-bit residual; both padding conventions; a chain whose sums pass 16 bits (eight blocks of 512).  `served`: the blocks whose
+# second convolution runs there (None: asked for by the chain with int32 sums, which bconv_kernel_name does not describe).
 @pytest.mark.parametrize("batch,hw,cin,blocks,pad_mode,served", [
-    (64, 28, 64, ((64, 90, 1), (90, 86, 1), (86, 86, 1), (86, 64, 2)), 0, (0, 1, 2)),
-    (64, 8, 64, ((64, 300, 1), (300, 290, 1), (290, 290, 1)), 0, (0, 1, 2)),
-    (64, 28, 33, ((33, 100, 1), (100, 100, 2), (100, 64, 2)), 1, (0, 1)),
-    (32, 14, 64, ((64, 250, 1), (250, 230, 1), (230, 230, 1)), 1, (0, 1, 2)),
+    (64, 28, 64, ((64, 90, 1), (90, 86, 1), (86, 64, 2)), 0, (0, 1)),
+    (64, 14, 64, ((64, 300, 1), (300, 300, 1), (300, 300, 1), (300, 290, 1), (290, 64, 2)), 0, (0, 1, 2, 3)),
+    (64, 8, 64, ((64, 300, 1), (300, 290, 1), (290, 50, 2)), 0, (0, 1)),
+    (64, 28, 90, ((90, 90, 1), (90, 90, 1), (90, 50, 1), (50, 100, 2), (100, 64, 2)), 1, (0, 1, 2, 3)),
+    (64, 28, 33, ((33, 90, 1), (90, 90, 1), (90, 64, 2)), 1, (0, 1)),
+    (32, 14, 64, ((64, 250, 1), (250, 230, 1), (230, 64, 2)), 1, (0, 1)),
+    (64, 28, 48, ((48, 96, 1), (96, 96, 1), (96, 96, 1), (96, 512, 7)) + ((512, 512, 1),) * 7, 1, None),
     (64, 14, 48, ((48, 96, 1), (96, 512, 4)) + ((512, 512, 1),) * 7, 0, (0,))])
 def test_block_chains_expanded_in_lds(bnn, orc, batch, hw, cin, blocks, pad_mode, served):
     rng = np.random.default_rng(batch + hw + cin)
@@ -338,8 +341,10 @@ def test_block_chains_expanded_in_lds(bnn, orc, batch, hw, cin, blocks, pad_mode
         net.add_block(to_dev(blk["W1"]), to_dev(blk["thr1"]), to_dev(blk["W2"]), to_dev(blk["thr2"]),
                       to_dev(blk["Wd"]) if "Wd" in blk else None, ci, co, st, pad_mode)
         size = (size - 1) // st + 1
-        kernel = bnn.bconv_kernel_name(batch, size, size, co, co, 3, 1, 1, pad_mode=pad_mode, shortcut="Wd" in blk)
-        assert kernel.startswith("mfma_fp4_conv_xlds") == (b in served), (b, kernel)
+        keep = b + 1 < len(blocks) and blocks[b + 1][0] == blocks[b + 1][1] and blocks[b + 1][2] == 1
+        kernel = bnn.bconv_kernel_name(batch, size, size, co, co, 3, 1, 1, pad_mode=pad_mode, shortcut="Wd" in blk,
+                                       residual="Wd" not in blk, keep_sum=keep)
+        assert served is None or kernel.startswith("mfma_fp4_conv_xlds") == (b in served), (b, kernel)
     w = rng.normal(0.0, 0.02, size=(7, blocks[-1][1])).astype(np.float32)
     net.add_head_f32(to_dev(w))
     x = rng.integers(-100, 101, size=(batch, hw, hw, 3)).astype(np.float32)
