@@ -158,8 +158,11 @@ const char* describe_mfma_conv_xlds(const Geom& g, const Epi& e);
 int launch_mfma_conv_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma_conv_staged(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma_conv_v4(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
+int launch_mfma_conv_v4_stream(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma_conv_v2(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
+int launch_mfma_conv_v2_stream(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma_conv_v1(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
+int launch_mfma_conv_v1_stream(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 // Name of the kernel variant launch_mfma / launch_valu would pick for this geometry.
 // (flags: those of bnn_bconv_kernel_name_ex.)
 const char* describe_mfma(const Geom& g, bool int32_out = false, int flags = 0);

@@ -52,9 +52,12 @@ int launch_mfma(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
     // (blocked 16-bit sums are implemented by the direct kernels only)
     if (!e.sums_tiled && staged_ok(g, tile)) return launch_mfma_conv_staged(A, B, g, e, s);
     if (!mfma::offsets_fit(g)) return BNN_ERR_UNSUPPORTED;
-    if (g.tw % 8 == 0) return launch_mfma_conv_v4(A, B, g, e, s);
-    if (g.tw % 4 == 0) return launch_mfma_conv_v2(A, B, g, e, s);
-    return launch_mfma_conv_v1(A, B, g, e, s);
+    const bool stream = mfma::streams_residual(g, e);
+    switch (mfma::conv_load_words(g)) {
+        case 4: return stream ? launch_mfma_conv_v4_stream(A, B, g, e, s) : launch_mfma_conv_v4(A, B, g, e, s);
+        case 2: return stream ? launch_mfma_conv_v2_stream(A, B, g, e, s) : launch_mfma_conv_v2(A, B, g, e, s);
+        default: return stream ? launch_mfma_conv_v1_stream(A, B, g, e, s) : launch_mfma_conv_v1(A, B, g, e, s);
+    }
 }
 
 const char* describe_mfma(const Geom& g, bool int32_out, int flags) {

@@ -73,11 +73,22 @@ __device__ __forceinline__ void push4(uint32_t& w, unsigned long long a, unsigne
 
 typedef uint32_t word4 __attribute__((ext_vector_type(4), aligned(4)));      // filters of odd word counts start at any word
 
+// What a call asks of the epilogue; a kernel is compiled for one form (with all of them in one kernel the compiler stopped specialising the
+// general epilogue: bits and sums of 256 x 14x14x200 43.8 us instead of 39.0).
+enum OutputForm {
+    OUT_BITS,               // packed bits alone: the filters are the row operand, the bits leave as whole words
+    OUT_SUMS,               // int32 sums alone
+    OUT_STREAMED_RESIDUAL,  // an int32 residual in, rows of whole 128-byte lines: epilogue_resid
+    OUT_RESIDUAL,           // any other residual in: the general epilogue
+    OUT_BITS_AND_SUMS       // bits and sums without a residual: the general epilogue
+};
+
 // MT x NT accumulators of 32 x 32 per wave, WM x WN waves.  SWAP: filters are the MFMA's row operand (bits only).
-template <int MT, int NT, int WM, int WN, bool SWAP>
+template <int MT, int NT, int WM, int WN, OutputForm FORM>
 __global__ __launch_bounds__(WM * WN * 64, 2) void conv_xlds_kernel(const uint32_t* __restrict__ A, const uint32_t* __restrict__ B, Geom g,
                                                                    Epi e, XArgs x, int gx, int gy) {
     static_assert(NT == 2, "a wave owns 64 channels, a half-wave 32 of them");
+    constexpr bool SWAP = FORM == OUT_BITS;
     constexpr int NTHR = WM * WN * 64, ROWS = WM * MT * 32, COLS = WN * NT * 32;
     extern __shared__ uint4 smem[];
     char* lds = reinterpret_cast<char*>(smem);          // offsets of the K words (int each), then the units
@@ -263,8 +274,24 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void conv_xlds_kernel(const uint32
 
     int corr = 0;                                       // pad bits of the fused second source only
     if (g.A2 != nullptr) corr = mfma::extra_source<MT, NT, SWAP, SWAP>(acc, g, m0, n0, lane, c2) - g.bits2;
-    if constexpr (!SWAP) {
-        mfma::epilogue<MT, NT, true, false>(acc, m0, n0, lane, g, e, corr, 0);
+    if constexpr (FORM == OUT_SUMS) {
+        mfma::epilogue_sums<MT, NT>(acc, m0, n0, lane, g, e, corr);
+    } else if constexpr (FORM == OUT_STREAMED_RESIDUAL) {
+        mfma::epilogue_streamed<MT, NT>(acc, m0, n0, lane, g, e, corr);
+    } else if constexpr (!SWAP) {
+        int thi[NT];
+        bool cok[NT];
+        mfma::column_thresholds<NT>(thi, cok, n0, l32, g, e);
+        const mfma::Fetched none = {make_uint4(0u, 0u, 0u, 0u), make_uint4(0u, 0u, 0u, 0u), false};
+        Epi es = e;
+        es.sums_tiled = 0;                              // (mfma_conv_xlds_takes)
+        if (e.out16 != nullptr) {                       // uniform: one kind of sums in each copy
+            es.out = nullptr;
+            mfma::epilogue_generic<MT, NT, true, false, FORM == OUT_RESIDUAL>(acc, m0, n0, lane, g, es, corr, 0, thi, cok, false, none);
+        } else {
+            es.out16 = nullptr;
+            mfma::epilogue_generic<MT, NT, true, false, FORM == OUT_RESIDUAL>(acc, m0, n0, lane, g, es, corr, 0, thi, cok, false, none);
+        }
     } else {
         // register r of tile j holds channel n0 + 32 * half + 16 * j + r of pixel m0 + 32 * i + l32
         float th[32];
@@ -323,15 +350,6 @@ bool fill_args(const Geom& g, int tile_rows, int tile_cols, XArgs* x, size_t* ld
     return true;
 }
 
-// What a call asks of the epilogue.
-enum OutputForm {
-    OUT_BITS,               // packed bits alone: the filters are the row operand, the bits leave as whole words
-    OUT_SUMS,               // int32 sums alone
-    OUT_STREAMED_RESIDUAL,  // an int32 residual in, rows of whole 128-byte lines: epilogue_resid
-    OUT_RESIDUAL,           // any other residual in: the general epilogue
-    OUT_BITS_AND_SUMS       // bits and sums without a residual: the general epilogue
-};
-
 OutputForm output_form(const Epi& e) {
     if (e.resid != nullptr || e.resid16 != nullptr || e.resid_bits != nullptr)
         return e.resid != nullptr && e.out16 == nullptr && (e.ldc & 31) == 0 ? OUT_STREAMED_RESIDUAL : OUT_RESIDUAL;
@@ -346,15 +364,26 @@ int launch_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
     if (!fill_args(g, WM * MT * 32, WN * NT * 32, &x, &lds)) return BNN_ERR_UNSUPPORTED;
     const int gx = (int)cdiv(g.rows, WM * MT * 32), gy = (int)cdiv(g.cols, WN * NT * 32);
     const unsigned nwg = (unsigned)(cdiv((long long)gx * gy, 8) * 8);
-    const bool swap = output_form(e) == OUT_BITS;
-    static const hipError_t attr0 = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_xlds_kernel<MT, NT, WM, WN, true>),
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)XLDS_MAX);
-    static const hipError_t attr1 = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_xlds_kernel<MT, NT, WM, WN, false>),
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)XLDS_MAX);
-    if (attr0 != hipSuccess || attr1 != hipSuccess) return BNN_ERR_DEVICE;
-    if (swap) hipLaunchKernelGGL((conv_xlds_kernel<MT, NT, WM, WN, true>), dim3(nwg), dim3(WM * WN * 64), lds, s, A, B, g, e, x, gx, gy);
-    else hipLaunchKernelGGL((conv_xlds_kernel<MT, NT, WM, WN, false>), dim3(nwg), dim3(WM * WN * 64), lds, s, A, B, g, e, x, gx, gy);
-    return check_launch();
+    auto launch = [&](auto form) {
+        constexpr OutputForm FORM = decltype(form)::value;
+        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_xlds_kernel<MT, NT, WM, WN, FORM>),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)XLDS_MAX);
+        if (attr != hipSuccess) return (int)BNN_ERR_DEVICE;
+        hipLaunchKernelGGL((conv_xlds_kernel<MT, NT, WM, WN, FORM>), dim3(nwg), dim3(WM * WN * 64), lds, s, A, B, g, e, x, gx, gy);
+        return check_launch();
+    };
+    switch (output_form(e)) {
+        case OUT_BITS: return launch(std::integral_constant<OutputForm, OUT_BITS>{});
+        case OUT_SUMS: return launch(std::integral_constant<OutputForm, OUT_SUMS>{});
+        case OUT_BITS_AND_SUMS: return launch(std::integral_constant<OutputForm, OUT_BITS_AND_SUMS>{});
+        case OUT_STREAMED_RESIDUAL:
+            if constexpr (MT == 2) return launch(std::integral_constant<OutputForm, OUT_STREAMED_RESIDUAL>{});
+            break;
+        case OUT_RESIDUAL:
+            if constexpr (MT == 2) return launch(std::integral_constant<OutputForm, OUT_RESIDUAL>{});
+            break;
+    }
+    return BNN_ERR_UNSUPPORTED;     // not dispatched: residuals take the tiles of two row fragments (xlds_tile)
 }
 
 struct XTile { int rows, cols, mfmas; };                // mfmas: per wave and K-step
@@ -370,18 +399,19 @@ constexpr XTile XTILES[] = {{0, 0, 0}, {256, 128, 8}, {128, 256, 8}, {512, 64, 8
 //   streamed residual  104: 0.69 to 0.80 / 0.89 to 0.97, 152: 0.85 / 1.05, 200: 1.01 to 1.25 / 1.24 to 1.5, 392 and more: 1.08 to 1.4
 //   other residuals    104: 0.6 to 0.7 / 0.78 to 0.92, 152 with 90 words of K 0.77 / 0.9, 200: 0.90 with 27 words, 1.1 with 63, 1.46 with 126 / 1.1
 //                      to 1.5, the unrolled forms 0.83 to 0.95; 296 to 392: 1.1 to 1.6; 27 words against the 256x128 tile 0.97 to 1.05
-//   bits and sums      27 words 0.6 to 0.9 at any count, 63: 0.67 at 104, 1.0 at 200 and 392, 90: 1.13 to 1.37 from 296 /
-//                      18 words 0.93 at 392, 27: 0.99 at 200, 1.1 at 392, 63: 1.17 at 200, unrolled forms 0.8 at 200, 1.1 at 392
+//   bits and sums      27 words 0.6 to 0.9 at any count, 63: 0.67 at 104, 1.0 at 200 and 392, against the 256x128 tile 0.94 to 0.97 (63 and 75
+//                      words), 90: 1.13 to 1.37 from 296 / 18 words 0.93 at 392, 27: 0.99 at 200, 1.1 at 392, 63: 1.17 at 200, unrolled
+//                      forms 0.8 at 200, 1.1 at 392
 int min_workgroups(const Geom& g, OutputForm form) {
     const int kwords = g.taps * g.tw;
     const bool unrolled = g.k == 3 && (g.tw == 2 || g.tw == 4 || g.tw == 8 || g.tw == 16);
-    const bool against_big_tile = !g.excl && kwords < 45 && mfma::pick_tile(g) == 0;
+    const bool against_big_tile = !g.excl && mfma::pick_tile(g) == 0;
     switch (form) {
         case OUT_BITS: return 96;
-        case OUT_SUMS: return against_big_tile && (g.cols & 31) != 0 ? 0 : g.excl && !unrolled ? 96 : 128;
+        case OUT_SUMS: return against_big_tile && kwords < 45 && (g.cols & 31) != 0 ? 0 : g.excl && !unrolled ? 96 : 128;
         case OUT_STREAMED_RESIDUAL: return !g.excl ? 192 : unrolled ? 256 : 128;
-        case OUT_RESIDUAL: return against_big_tile ? 0 : (g.excl ? unrolled : kwords < 63) ? 256 : 192;
-        default: return kwords < (g.excl ? 27 : 63) ? 0 : (g.excl && kwords < 63) || unrolled ? 256 : 192;
+        case OUT_RESIDUAL: return against_big_tile && kwords < 45 ? 0 : (g.excl ? unrolled : kwords < 63) ? 256 : 192;
+        default: return kwords < (g.excl ? 27 : against_big_tile ? 90 : 63) ? 0 : (g.excl && kwords < 63) || unrolled ? 256 : 192;
     }
 }
 

@@ -555,14 +555,26 @@ __device__ __forceinline__ void epilogue(v16f (&acc)[MT][NT], const long long m0
         case EPI_SUMS: epilogue_sums<MT, NT>(acc, m0, n0, lane, g, e, corr_all); return;
         default: break;
     }
-    if (CONV && MT * NT > 1 && e.resid != nullptr && e.out16 == nullptr && !row_corr && (e.ldc & 31) == 0 && m0 + 32 * MT <= g.rows && n0 + 32 * NT <= g.cols) {
-        epilogue_resid<MT, NT>(acc, m0, n0, lane, g, e, corr_all, thi);
-        return;
-    }
     if (e.resid != nullptr || e.resid16 != nullptr || e.resid_bits != nullptr)
         epilogue_generic<MT, NT, CONV, EXCL, true>(acc, m0, n0, lane, g, e, corr_all, pad_tap, thi, cok, row_corr, fetched);
     else
         epilogue_generic<MT, NT, CONV, EXCL, false>(acc, m0, n0, lane, g, e, corr_all, pad_tap, thi, cok, row_corr, fetched);
+}
+
+// Epilogue of the kernels built for a streamed residual (streams_residual): epilogue_resid, at the edges of the matrix the general body.
+template <int MT, int NT>
+__device__ __forceinline__ void epilogue_streamed(v16f (&acc)[MT][NT], const long long m0, const int n0, const int lane, const Geom& g,
+                                                  const Epi& e, const int corr_all) {
+    int thi[NT];
+    bool cok[NT];
+    column_thresholds<NT>(thi, cok, n0, lane & 31, g, e);
+    if (m0 + 32 * MT <= g.rows && n0 + 32 * NT <= g.cols) epilogue_resid<MT, NT>(acc, m0, n0, lane, g, e, corr_all, thi);
+    else {
+        Epi ei = e;                 // (the other residuals are not compiled in)
+        ei.resid16 = nullptr; ei.resid_bits = nullptr; ei.out16 = nullptr; ei.sums_tiled = 0;
+        epilogue_generic<MT, NT, true, false, true>(acc, m0, n0, lane, g, ei, corr_all, 0, thi, cok, false,
+                                                    Fetched{make_uint4(0u, 0u, 0u, 0u), make_uint4(0u, 0u, 0u, 0u), false});
+    }
 }
 
 // 64 columns dealt to the rows of two fragments so that a half-wave of the accumulators owns 32 consecutive ones: the column of
@@ -617,8 +629,11 @@ __device__ __forceinline__ int extra_source(v16f (&acc)[MT][NT], const Geom& g, 
 // CPT3 > 0: a 3x3 window whose taps are exactly CPT3 chunks each (tw == CPT3 * 2 * V): the loop over the 9 * CPT3
 // chunks is unrolled in full, so that tap and chunk indices are compile-time constants and a request is a handful of
 // instructions (the layers of a network are short: their time is instruction issue, not the matrix cores).
-// POOL: rows in the order of Geom::pool2 (a compile-time switch: the test alone cost the other layers 2 to 4 %).
-template <class TL, int V, bool CONV, bool EXCL, bool GUARD, int CPT3 = 0, bool POOL = false>
+// KIND: what the kernel is built for.  Rows in the order of Geom::pool2 and the streamed residual are kernels of their own: the test for the
+// pooled order alone cost the other layers 2 to 4 %, and with epilogue_resid beside it the general epilogue was compiled so much worse that
+// bits and sums of 256 x 14x14x90 took 23.9 us instead of 18.6.
+enum KernelKind { KIND_ANY, KIND_POOL, KIND_STREAM };
+template <class TL, int V, bool CONV, bool EXCL, bool GUARD, int CPT3 = 0, int KIND = KIND_ANY>
 __device__ __forceinline__ void mfma_tile(const uint32_t* __restrict__ A, const uint32_t* __restrict__ B, const Geom& g,
                                           const Epi& e, const int bx, const int by) {
     constexpr int MT = TL::MT, NT = TL::NT;
@@ -653,7 +668,7 @@ __device__ __forceinline__ void mfma_tile(const uint32_t* __restrict__ A, const 
             const int n = fast_div((int)row, g.div_pq);
             const int rem = (int)row - n * (g.P * g.Q);
             int p = fast_div(rem, g.div_q), q = rem - p * g.Q;
-            if constexpr (POOL) pool_row_pixel(g, rem, p, q);
+            if constexpr (KIND == KIND_POOL) pool_row_pixel(g, rem, p, q);
             y0[i] = p * g.stride - g.pad;
             x0[i] = q * g.stride - g.pad;
             aoff[i] = (uint32_t)(((((n - n_first) * g.H + y0[i]) * g.W + x0[i]) * g.lda_w + half * V) * 4);
@@ -836,7 +851,11 @@ __device__ __forceinline__ void mfma_tile(const uint32_t* __restrict__ A, const 
     const int pad_tap = cpt * 2 * V * 32 - g.bits_tap;
     int corr2 = 0;
     if (CONV && g.A2 != nullptr) corr2 = extra_source<MT, NT>(acc, g, m0, n0, lane, c2) - g.bits2;
-    if constexpr (POOL) {                               // bits only (mfma_conv_pools)
+    if constexpr (KIND == KIND_STREAM) {
+        epilogue_streamed<MT, NT>(acc, m0, n0, lane, g, e, g.taps * pad_tap + corr2);
+        return;
+    }
+    if constexpr (KIND == KIND_POOL) {                  // bits only (mfma_conv_pools)
         int thi[NT];
         bool cok[NT];
         column_thresholds<NT>(thi, cok, n0, l32, g, e);
@@ -846,28 +865,28 @@ __device__ __forceinline__ void mfma_tile(const uint32_t* __restrict__ A, const 
     epilogue<MT, NT, CONV, EXCL>(acc, m0, n0, lane, g, e, g.taps * pad_tap + corr2, pad_tap, fetched);
 }
 
-template <class TL, int V, bool CONV, bool EXCL, bool GUARD, int CPT3 = 0, bool POOL = false>
+template <class TL, int V, bool CONV, bool EXCL, bool GUARD, int CPT3 = 0, int KIND = KIND_ANY>
 __global__ __launch_bounds__(256, TL::MINB) void mfma_kernel(const uint32_t* __restrict__ A,
                                                              const uint32_t* __restrict__ B, Geom g, Epi e,
                                                              int gx, int gy) {
     int bx, by;
     if (!tile_coords(gx, gy, bx, by)) return;          // uniform for the workgroup
-    mfma_tile<TL, V, CONV, EXCL, GUARD, CPT3, POOL>(A, B, g, e, bx, by);
+    mfma_tile<TL, V, CONV, EXCL, GUARD, CPT3, KIND>(A, B, g, e, bx, by);
 }
 
-template <class TL, int V, bool EXCL, int CPT3>
+template <class TL, int V, bool EXCL, int CPT3, int KIND>
 int launch_tile_3x3(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, int gx, int gy, unsigned nwg,
                     hipStream_t s) {
-    if constexpr (!EXCL)
+    if constexpr (!EXCL && KIND == KIND_ANY)
         if (g.pool2 != 0) {
-            hipLaunchKernelGGL((mfma_kernel<TL, V, true, false, false, CPT3, true>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
+            hipLaunchKernelGGL((mfma_kernel<TL, V, true, false, false, CPT3, KIND_POOL>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
             return check_launch();
         }
-    hipLaunchKernelGGL((mfma_kernel<TL, V, true, EXCL, false, CPT3>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
+    hipLaunchKernelGGL((mfma_kernel<TL, V, true, EXCL, false, CPT3, KIND>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
     return check_launch();
 }
 
-template <class TL, int V, bool CONV, bool GUARD>
+template <class TL, int V, bool CONV, bool GUARD, int KIND>
 int launch_tile(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
     const int col_span = (e.bits != nullptr) ? max(g.cols, e.ldbits_w * 32) : g.cols;
     const int gx = (int)cdiv(g.rows, TL::ROWS), gy = (int)cdiv(col_span, TL::COLS);
@@ -875,17 +894,17 @@ int launch_tile(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
     if constexpr (CONV && !GUARD) {
         // 3x3 windows of one or two chunks per tap (C = 64 V, 128 V): the unrolled form
         if (g.k == 3 && g.taps == 9 && (g.tw == 2 * V || (V == 4 && g.tw == 4 * V))) {
-            if (g.tw == 2 * V) return g.excl ? launch_tile_3x3<TL, V, true, 1>(A, B, g, e, gx, gy, nwg, s)
-                                             : launch_tile_3x3<TL, V, false, 1>(A, B, g, e, gx, gy, nwg, s);
+            if (g.tw == 2 * V) return g.excl ? launch_tile_3x3<TL, V, true, 1, KIND>(A, B, g, e, gx, gy, nwg, s)
+                                             : launch_tile_3x3<TL, V, false, 1, KIND>(A, B, g, e, gx, gy, nwg, s);
             if constexpr (V == 4)        // (narrower loads are only chosen for tw not a multiple of 8)
-                return g.excl ? launch_tile_3x3<TL, V, true, 2>(A, B, g, e, gx, gy, nwg, s)
-                              : launch_tile_3x3<TL, V, false, 2>(A, B, g, e, gx, gy, nwg, s);
+                return g.excl ? launch_tile_3x3<TL, V, true, 2, KIND>(A, B, g, e, gx, gy, nwg, s)
+                              : launch_tile_3x3<TL, V, false, 2, KIND>(A, B, g, e, gx, gy, nwg, s);
         }
     }
     if (CONV && g.excl)
-        hipLaunchKernelGGL((mfma_kernel<TL, V, CONV, CONV, GUARD>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
+        hipLaunchKernelGGL((mfma_kernel<TL, V, CONV, CONV, GUARD, 0, KIND>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
     else
-        hipLaunchKernelGGL((mfma_kernel<TL, V, CONV, false, GUARD>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
+        hipLaunchKernelGGL((mfma_kernel<TL, V, CONV, false, GUARD, 0, KIND>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
     return check_launch();
 }
 
@@ -932,14 +951,26 @@ inline bool offsets_fit(const Geom& g) {
     return images * g.H * g.W * g.lda_w * 4 < (1LL << 31);
 }
 
-template <int V, bool CONV, bool GUARD>
+template <int V, bool CONV, bool GUARD, int KIND = KIND_ANY>
 int launch_shape(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
     switch (pick_tile(g, &e)) {
-        case 0: return launch_tile<TileBig, V, CONV, GUARD>(A, B, g, e, s);
-        case 1: return launch_tile<TileTall, V, CONV, GUARD>(A, B, g, e, s);
-        case 2: return launch_tile<TileMid, V, CONV, GUARD>(A, B, g, e, s);
-        default: return launch_tile<TileSmall, V, CONV, GUARD>(A, B, g, e, s);
+        case 0: return launch_tile<TileBig, V, CONV, GUARD, KIND>(A, B, g, e, s);
+        case 1: return launch_tile<TileTall, V, CONV, GUARD, KIND>(A, B, g, e, s);
+        case 2: return launch_tile<TileMid, V, CONV, GUARD, KIND>(A, B, g, e, s);
+        default:
+            if constexpr (KIND == KIND_STREAM) return BNN_ERR_UNSUPPORTED;      // not dispatched: see streams_residual
+            else return launch_tile<TileSmall, V, CONV, GUARD, KIND>(A, B, g, e, s);
     }
+}
+
+// Words per load of the direct kernel's convolutions.
+inline int conv_load_words(const Geom& g) { return g.tw % 8 == 0 ? 4 : g.tw % 4 == 0 ? 2 : 1; }
+
+// A row-major int32 residual that epilogue_resid takes: a convolution on one of the larger tiles, rows of whole 128-byte lines, and
+// one correction for all sums (with excluded padding and a partly filled K-step the general epilogue corrects each by its pixel).
+inline bool streams_residual(const Geom& g, const Epi& e) {
+    if (!g.conv || e.resid == nullptr || e.out16 != nullptr || (e.ldc & 31) != 0 || pick_tile(g) == 3) return false;
+    return !g.excl || g.bits_tap % (conv_load_words(g) * 64) == 0;
 }
 
 }  // namespace mfma

@@ -26,7 +26,8 @@ namespace bnn {
 namespace mfma {
 
 // U: bytes per global load instruction and lane: 16, or 8 when a pixel has only 8 bytes (C = 64).
-template <class TL, int U, bool CONV>
+// STREAM: built for a streamed residual (streams_residual).
+template <class TL, int U, bool CONV, bool STREAM>
 __global__ __launch_bounds__(256, TL::MINB) void mfma_staged_kernel(const uint32_t* __restrict__ A,
                                                                     const uint32_t* __restrict__ B, Geom g, Epi e,
                                                                     int gx, int gy) {
@@ -242,19 +243,21 @@ __global__ __launch_bounds__(256, TL::MINB) void mfma_staged_kernel(const uint32
     if (CONV && g.A2 != nullptr) corr2 = extra_source<MT, NT>(acc, g, m0, n0, lane, c2) - g.bits2;
     Epi es = e;
     es.sums_tiled = 0;          // blocked 16-bit sums go to the direct kernel (launch_mfma): that code is left out here
-    epilogue<MT, NT, CONV, false>(acc, m0, n0, lane, g, es, processed - g.taps * g.bits_tap + corr2, 0);
+    const int corr_all = processed - g.taps * g.bits_tap + corr2;
+    if constexpr (STREAM) epilogue_streamed<MT, NT>(acc, m0, n0, lane, g, es, corr_all);
+    else epilogue<MT, NT, CONV, false>(acc, m0, n0, lane, g, es, corr_all, 0);
 }
 
-template <class TL, int U, bool CONV>
+template <class TL, int U, bool CONV, bool STREAM = false>
 int launch_staged_tile(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
     const int col_span = (e.bits != nullptr) ? max(g.cols, e.ldbits_w * 32) : g.cols;
     const int gx = (int)cdiv(g.rows, TL::ROWS), gy = (int)cdiv(col_span, TL::COLS);
     const unsigned nwg = (unsigned)(cdiv((long long)gx * gy, 8) * 8);
     constexpr size_t lds_bytes = 2 * 4 * (TL::ROWS + 2 + TL::COLS + 2) * 16;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma_staged_kernel<TL, U, CONV>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma_staged_kernel<TL, U, CONV, STREAM>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (attr != hipSuccess) return BNN_ERR_DEVICE;
-    hipLaunchKernelGGL((mfma_staged_kernel<TL, U, CONV>), dim3(nwg), dim3(256), lds_bytes, s, A, B, g, e, gx, gy);
+    hipLaunchKernelGGL((mfma_staged_kernel<TL, U, CONV, STREAM>), dim3(nwg), dim3(256), lds_bytes, s, A, B, g, e, gx, gy);
     return check_launch();
 }
 
