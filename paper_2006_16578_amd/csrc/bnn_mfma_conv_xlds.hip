@@ -84,7 +84,8 @@ enum OutputForm {
 };
 
 // MT x NT accumulators of 32 x 32 per wave, WM x WN waves.  SWAP: filters are the MFMA's row operand (bits only).
-template <int MT, int NT, int WM, int WN, OutputForm FORM>
+// SHORTCUT: with the second source (its code beside the bits-only loop cost that 2 %: two more registers spilled).
+template <int MT, int NT, int WM, int WN, OutputForm FORM, bool SHORTCUT>
 __global__ __launch_bounds__(WM * WN * 64, 2) void conv_xlds_kernel(const uint32_t* __restrict__ A, const uint32_t* __restrict__ B, Geom g,
                                                                    Epi e, XArgs x, int gx, int gy) {
     static_assert(NT == 2, "a wave owns 64 channels, a half-wave 32 of them");
@@ -273,7 +274,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void conv_xlds_kernel(const uint32
     }
 
     int corr = 0;                                       // pad bits of the fused second source only
-    if (g.A2 != nullptr) corr = mfma::extra_source<MT, NT, SWAP, SWAP>(acc, g, m0, n0, lane, c2) - g.bits2;
+    if (SHORTCUT && g.A2 != nullptr) corr = mfma::extra_source<MT, NT, SWAP, SWAP>(acc, g, m0, n0, lane, c2) - g.bits2;
     if constexpr (FORM == OUT_SUMS) {
         mfma::epilogue_sums<MT, NT>(acc, m0, n0, lane, g, e, corr);
     } else if constexpr (FORM == OUT_STREAMED_RESIDUAL) {
@@ -364,23 +365,31 @@ int launch_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
     if (!fill_args(g, WM * MT * 32, WN * NT * 32, &x, &lds)) return BNN_ERR_UNSUPPORTED;
     const int gx = (int)cdiv(g.rows, WM * MT * 32), gy = (int)cdiv(g.cols, WN * NT * 32);
     const unsigned nwg = (unsigned)(cdiv((long long)gx * gy, 8) * 8);
-    auto launch = [&](auto form) {
+    auto launch = [&](auto form, auto shortcut) {
         constexpr OutputForm FORM = decltype(form)::value;
-        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_xlds_kernel<MT, NT, WM, WN, FORM>),
+        constexpr bool SHORTCUT = decltype(shortcut)::value;
+        static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_xlds_kernel<MT, NT, WM, WN, FORM, SHORTCUT>),
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)XLDS_MAX);
         if (attr != hipSuccess) return (int)BNN_ERR_DEVICE;
-        hipLaunchKernelGGL((conv_xlds_kernel<MT, NT, WM, WN, FORM>), dim3(nwg), dim3(WM * WN * 64), lds, s, A, B, g, e, x, gx, gy);
+        hipLaunchKernelGGL((conv_xlds_kernel<MT, NT, WM, WN, FORM, SHORTCUT>), dim3(nwg), dim3(WM * WN * 64), lds, s, A, B, g, e, x, gx, gy);
         return check_launch();
     };
+    // a second source comes with bits, with or without their sums; with another form it is not dispatched (xlds_tile)
+    const bool shortcut = g.A2 != nullptr;
+    constexpr std::true_type with{};
+    constexpr std::false_type none{};
     switch (output_form(e)) {
-        case OUT_BITS: return launch(std::integral_constant<OutputForm, OUT_BITS>{});
-        case OUT_SUMS: return launch(std::integral_constant<OutputForm, OUT_SUMS>{});
-        case OUT_BITS_AND_SUMS: return launch(std::integral_constant<OutputForm, OUT_BITS_AND_SUMS>{});
+        case OUT_BITS: {
+            constexpr std::integral_constant<OutputForm, OUT_BITS> f{};
+            return shortcut ? launch(f, with) : launch(f, none);
+        }
+        case OUT_BITS_AND_SUMS: return launch(std::integral_constant<OutputForm, OUT_BITS_AND_SUMS>{}, with);
+        case OUT_SUMS: return launch(std::integral_constant<OutputForm, OUT_SUMS>{}, none);
         case OUT_STREAMED_RESIDUAL:
-            if constexpr (MT == 2) return launch(std::integral_constant<OutputForm, OUT_STREAMED_RESIDUAL>{});
+            if constexpr (MT == 2) return launch(std::integral_constant<OutputForm, OUT_STREAMED_RESIDUAL>{}, none);
             break;
         case OUT_RESIDUAL:
-            if constexpr (MT == 2) return launch(std::integral_constant<OutputForm, OUT_RESIDUAL>{});
+            if constexpr (MT == 2) return launch(std::integral_constant<OutputForm, OUT_RESIDUAL>{}, none);
             break;
     }
     return BNN_ERR_UNSUPPORTED;     // not dispatched: residuals take the tiles of two row fragments (xlds_tile)
@@ -430,6 +439,7 @@ int xlds_tile(const Geom& g, const Epi& e) {
     if (g.k == 3 && (g.tw == 2 || g.tw == 4 || g.tw == 8 || g.tw == 16) && !(g.excl && pad_bits)) return 0;
     if (!g.excl && (mfma::conv_stages_through_lds(g) || g.tw % 8 == 0)) return 0;
     const OutputForm form = output_form(e);
+    if (g.A2 != nullptr && form != OUT_BITS && form != OUT_BITS_AND_SUMS) return 0;
     const int least = min_workgroups(g, form);
     if (least == 0) return 0;
     const bool small_only = form == OUT_STREAMED_RESIDUAL || form == OUT_RESIDUAL;      // (the residual of four row fragments at a time: 0.92 of two)
