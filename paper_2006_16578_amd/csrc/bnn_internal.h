@@ -153,9 +153,9 @@ bool mfma_conv_patch_takes(const Geom& g, const Epi& e);
 const char* describe_mfma_conv_patch(const Geom& g);
 int launch_mfma_conv_patch(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 // Other windows and channel counts whose input patch, expanded to E2M1, fits LDS.
-bool mfma_conv_xlds_takes(const Geom& g, const Epi& e);
-const char* describe_mfma_conv_xlds(const Geom& g, const Epi& e);
-int launch_mfma_conv_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
+int mfma_conv_xlds_tile(const Geom& g, const Epi& e);      // 0: not this kernel's
+const char* describe_mfma_conv_xlds(int tile);
+int launch_mfma_conv_xlds(int tile, const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma_conv_staged(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma_conv_v4(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma_conv_v4_stream(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);

@@ -23,7 +23,7 @@ bool staged_ok(const Geom& g, int tile) {
 // gain a launch and a kernel of 3 us; VGG for 32x32 images, batch 8: 49 -> 41 us with three pooling layers stored this way.
 bool mfma_conv_pools(const Geom& g, const Epi& e) {
     return g.conv && !g.excl && g.k == 3 && (g.tw == 2 || g.tw == 4 || g.tw == 8 || g.tw == 16) && (g.P & 1) == 0 && (g.Q & 1) == 0 && g.A2 == nullptr && mfma::epilogue_kind(e, true, false) == mfma::EPI_BITS &&
-           !mfma_conv_patch_takes(g, e) && !mfma_conv_xlds_takes(g, e) && !staged_ok(g, mfma::pick_tile(g, &e)) && mfma::offsets_fit(g);
+           !mfma_conv_patch_takes(g, e) && mfma_conv_xlds_tile(g, e) == 0 && !staged_ok(g, mfma::pick_tile(g, &e)) && mfma::offsets_fit(g);
 }
 
 int launch_mfma(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
@@ -48,7 +48,7 @@ int launch_mfma(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
         return mfma::launch_shape<4, false, true>(A, B, g, e, s);
     }
     if (mfma_conv_patch_takes(g, e)) return launch_mfma_conv_patch(A, B, g, e, s);
-    if (mfma_conv_xlds_takes(g, e)) return launch_mfma_conv_xlds(A, B, g, e, s);
+    if (const int xt = mfma_conv_xlds_tile(g, e)) return launch_mfma_conv_xlds(xt, A, B, g, e, s);
     // (blocked 16-bit sums are implemented by the direct kernels only)
     if (!e.sums_tiled && staged_ok(g, tile)) return launch_mfma_conv_staged(A, B, g, e, s);
     if (!mfma::offsets_fit(g)) return BNN_ERR_UNSUPPORTED;
@@ -76,7 +76,7 @@ const char* describe_mfma(const Geom& g, bool int32_out, int flags) {
     const int tile = mfma::pick_tile(g, &e);
     if (tile == 0 && mfma_wide_takes(g, e)) return "mfma_fp4_bmm_xlds_wg256x256";
     if (mfma_conv_patch_takes(g, e)) return describe_mfma_conv_patch(g);
-    if (mfma_conv_xlds_takes(g, e)) return describe_mfma_conv_xlds(g, e);
+    if (const int xt = mfma_conv_xlds_tile(g, e)) return describe_mfma_conv_xlds(xt);
     if ((flags & BNN_CONV_POOL2) && mfma_conv_pools(g, e))
         return tile == 0   ? "mfma_fp4_conv_wg256x128_pool2"
                : tile == 1 ? "mfma_fp4_conv_wg512x64_pool2"

@@ -285,7 +285,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void conv_xlds_kernel(const uint32
         mfma::column_thresholds<NT>(thi, cok, n0, l32, g, e);
         const mfma::Fetched none = {make_uint4(0u, 0u, 0u, 0u), make_uint4(0u, 0u, 0u, 0u), false};
         Epi es = e;
-        es.sums_tiled = 0;                              // (mfma_conv_xlds_takes)
+        es.sums_tiled = 0;                              // (mfma_conv_xlds_tile)
         if (e.out16 != nullptr) {                       // uniform: one kind of sums in each copy
             es.out = nullptr;
             mfma::epilogue_generic<MT, NT, true, false, FORM == OUT_RESIDUAL>(acc, m0, n0, lane, g, es, corr, 0, thi, cok, false, none);
@@ -329,7 +329,8 @@ long long patch_pixels(const Geom& g, int tile_rows) {
 
 constexpr size_t XLDS_MAX = 80 * 1024;                  // two workgroups per compute unit
 
-bool fill_args(const Geom& g, int tile_rows, int tile_cols, XArgs* x, size_t* lds_bytes) {
+// LDS layout of a tile; false: its patch does not fit, or 32-bit offsets do not reach.
+bool plan_lds(const Geom& g, int tile_rows, int tile_cols, XArgs* x, size_t* lds_bytes) {
     const long long px = patch_pixels(g, tile_rows);
     const long long kwords = (long long)g.taps * g.tw;
     const long long plane = px | 1, table = (kwords + 7) / 8 * 32;
@@ -345,8 +346,6 @@ bool fill_args(const Geom& g, int tile_rows, int tile_cols, XArgs* x, size_t* ld
     x->groups = g.tw / x->vw;
     x->table_bytes = (int)table; x->thr_at = (int)thr_at;
     x->last_mask = (g.bits_tap & 31) ? (1u << (g.bits_tap & 31)) - 1u : 0xFFFFFFFFu;
-    x->div_pcw = make_fastdiv((uint32_t)x->PCW); x->div_hp = make_fastdiv((uint32_t)x->HP);
-    x->div_groups = make_fastdiv((uint32_t)x->groups); x->div_tw = make_fastdiv((uint32_t)g.tw);
     *lds_bytes = (size_t)total;
     return true;
 }
@@ -362,7 +361,9 @@ template <int MT, int NT, int WM, int WN>
 int launch_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
     XArgs x;
     size_t lds;
-    if (!fill_args(g, WM * MT * 32, WN * NT * 32, &x, &lds)) return BNN_ERR_UNSUPPORTED;
+    if (!plan_lds(g, WM * MT * 32, WN * NT * 32, &x, &lds)) return BNN_ERR_UNSUPPORTED;
+    x.div_pcw = make_fastdiv((uint32_t)x.PCW); x.div_hp = make_fastdiv((uint32_t)x.HP);
+    x.div_groups = make_fastdiv((uint32_t)x.groups); x.div_tw = make_fastdiv((uint32_t)g.tw);
     const int gx = (int)cdiv(g.rows, WM * MT * 32), gy = (int)cdiv(g.cols, WN * NT * 32);
     const unsigned nwg = (unsigned)(cdiv((long long)gx * gy, 8) * 8);
     auto launch = [&](auto form, auto shortcut) {
@@ -452,7 +453,7 @@ int xlds_tile(const Geom& g, const Epi& e) {
         const long long gy = cdiv(g.cols, XTILES[t].cols), wgs = cdiv(g.rows, XTILES[t].rows) * gy;
         // Many empty columns: 0.77 at 64 of 128.
         if (wgs < least || (double)(gy * XTILES[t].cols) > 1.5 * g.cols) continue;
-        if (!fill_args(g, XTILES[t].rows, XTILES[t].cols, &x, &lds)) continue;
+        if (!plan_lds(g, XTILES[t].rows, XTILES[t].cols, &x, &lds)) continue;
         const double m = XTILES[t].mfmas;
         const double wg = steps * m * (m < 8. ? 44. : 36.) + (double)x.px_max * g.tw / 4. + m * 160. + 1500.;
         const double cost = (double)cdiv(wgs, 512) * wg;
@@ -463,10 +464,10 @@ int xlds_tile(const Geom& g, const Epi& e) {
 
 }  // namespace
 
-bool mfma_conv_xlds_takes(const Geom& g, const Epi& e) { return !e.sums_tiled && xlds_tile(g, e) != 0; }
+int mfma_conv_xlds_tile(const Geom& g, const Epi& e) { return e.sums_tiled ? 0 : xlds_tile(g, e); }
 
-const char* describe_mfma_conv_xlds(const Geom& g, const Epi& e) {
-    switch (xlds_tile(g, e)) {
+const char* describe_mfma_conv_xlds(int tile) {
+    switch (tile) {
         case 1: return "mfma_fp4_conv_xlds_wg256x128";
         case 2: return "mfma_fp4_conv_xlds_wg128x256";
         case 3: return "mfma_fp4_conv_xlds_wg512x64";
@@ -475,8 +476,8 @@ const char* describe_mfma_conv_xlds(const Geom& g, const Epi& e) {
     }
 }
 
-int launch_mfma_conv_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
-    switch (xlds_tile(g, e)) {
+int launch_mfma_conv_xlds(int tile, const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
+    switch (tile) {
         case 1: return launch_xlds<4, 2, 2, 2>(A, B, g, e, s);
         case 2: return launch_xlds<4, 2, 1, 4>(A, B, g, e, s);
         case 3: return launch_xlds<4, 2, 4, 1>(A, B, g, e, s);
