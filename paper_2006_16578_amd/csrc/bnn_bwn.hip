@@ -758,14 +758,6 @@ struct WaveGeom {
     static_assert(FP * FQ == 32 && PAIRS <= 64 && (STRIDE * CIN * 2) % 8 == 0, "one lane per pair; 8-byte aligned runs");
 };
 
-template <int N, class F, int I = 0>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<N, F, I + 1>(static_cast<F&&>(f));
-    }
-}
-
 struct WaveArgs {
     int N, H, W, O, pad, P, Q;
     int tiles_p, tiles_q;

@@ -50,31 +50,12 @@ struct PixGeom {
     static constexpr int MAX_PX = rows(NF) * PC;
 };
 
-template <int N, class F, int I = 0>
-__device__ __forceinline__ void static_for(F&& f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        static_for<N, F, I + 1>(static_cast<F&&>(f));
-    }
-}
-
 struct PixArgs {
     int H, W, O, pad, P, Q;
     int nf, PR, npx;        // fragments of a wave per tile; rows and pixels of a patch
     int tiles_p, tiles_q, ntiles;
     FastDiv div_tiles, div_tp;
 };
-
-// w = 2 w + bit for four compare results, the first becoming the highest bit.  The s_nop covers the two wait states between a
-// vector compare that writes an SGPR pair and a vector instruction that reads it: the compiler does not look into the block.
-__device__ __forceinline__ void push4(uint32_t& w, unsigned long long a, unsigned long long b, unsigned long long c, unsigned long long d) {
-    asm("s_nop 1\n\t"
-        "v_addc_co_u32_e64 %0, vcc, %0, %0, %1\n\t"
-        "v_addc_co_u32_e64 %0, vcc, %0, %0, %2\n\t"
-        "v_addc_co_u32_e64 %0, vcc, %0, %0, %3\n\t"
-        "v_addc_co_u32_e64 %0, vcc, %0, %0, %4"
-        : "+v"(w) : "s"(a), "s"(b), "s"(c), "s"(d) : "vcc");
-}
 
 __device__ __forceinline__ uint32_t bf16_sign(uint32_t word, int bit) {       // bit set: +1.0, clear: -1.0
     return 0x3F80u | ((~(word >> bit) & 1u) << 15);

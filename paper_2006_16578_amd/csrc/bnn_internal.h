@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "../../include/bnn.h"
 
 namespace bnn {
@@ -32,6 +34,26 @@ __host__ __device__ inline int fast_div(int n, const FastDiv& f) {
 #else
     return f.m == 0u ? (n >> f.sh) : (int)((((unsigned long long)(uint32_t)n * f.m) >> 32) >> f.sh);
 #endif
+}
+
+// f(integral_constant 0), ... f(integral_constant N - 1).
+template <int N, class F, int I = 0>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, F, I + 1>(static_cast<F&&>(f));
+    }
+}
+
+// w = 2 w + bit for four compare results, the first becoming the highest bit.  The s_nop covers the two wait states between a
+// vector compare that writes an SGPR pair and a vector instruction that reads it: the compiler does not look into the block.
+__device__ __forceinline__ void push4(uint32_t& w, unsigned long long a, unsigned long long b, unsigned long long c, unsigned long long d) {
+    asm("s_nop 1\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %1\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %2\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %3\n\t"
+        "v_addc_co_u32_e64 %0, vcc, %0, %0, %4"
+        : "+v"(w) : "s"(a), "s"(b), "s"(c), "s"(d) : "vcc");
 }
 
 // One +1/-1 contraction seen as an implicit GEMM: `rows` output rows (A rows of a BMM, output

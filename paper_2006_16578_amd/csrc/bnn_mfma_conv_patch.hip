@@ -29,6 +29,8 @@ namespace {
 
 using mfma::v16f;
 using mfma::v8i;
+using mfma::as_operand;
+using mfma::expand_unit;
 
 constexpr int MT = 2;            // a wave tile is 64 output pixels x all output channels
 // patch positions per lane whose words are requested one tile ahead (a stride-2 tile spans twice the cells)
@@ -43,18 +45,6 @@ struct PatchArgs {
     int ntiles;                  // wave tiles
     uint32_t pad_keep;           // -1 padding: all ones (a padding cell is the expansion of 0 bits); excluded padding: 0 (fp4 zeros)
 };
-
-__device__ __forceinline__ uint4 expand_unit(uint32_t w, uint32_t c2) {
-    return make_uint4(((w << 3) & 0x88888888u) | c2, ((w << 2) & 0x88888888u) | c2, ((w << 1) & 0x88888888u) | c2,
-                      (w & 0x88888888u) | c2);
-}
-
-__device__ __forceinline__ v8i as_operand(const uint4& u) {
-    v8i r;
-    r[0] = (int)u.x; r[1] = (int)u.y; r[2] = (int)u.z; r[3] = (int)u.w;
-    r[4] = 0; r[5] = 0; r[6] = 0; r[7] = 0;         // the upper half is not read for 4-bit formats
-    return r;
-}
 
 // 16 sign bits of a lane's registers (bit r = register r = channel 8a + 4 half + b, r = 4a + b) -> that lane pair's
 // packed word of 32 channels with a 1 where the value is NOT negative; both half-waves end up with the whole word.

@@ -30,6 +30,8 @@ namespace {
 
 using mfma::v16f;
 using mfma::v8i;
+using mfma::as_operand;
+using mfma::expand_unit;
 
 struct XArgs {
     int HP, PCW;            // rows of an image's padded frame that windows reach; pixels of a patch row
@@ -42,33 +44,10 @@ struct XArgs {
     FastDiv div_pcw, div_hp, div_groups, div_tw;
 };
 
-__device__ __forceinline__ uint4 expand_unit(uint32_t w, uint32_t c2) {
-    return make_uint4(((w << 3) & 0x88888888u) | c2, ((w << 2) & 0x88888888u) | c2, ((w << 1) & 0x88888888u) | c2,
-                      (w & 0x88888888u) | c2);
-}
-
-__device__ __forceinline__ v8i as_operand(const uint4& u) {
-    v8i r;
-    r[0] = (int)u.x; r[1] = (int)u.y; r[2] = (int)u.z; r[3] = (int)u.w;
-    r[4] = 0; r[5] = 0; r[6] = 0; r[7] = 0;         // the upper half is not read for 4-bit formats
-    return r;
-}
-
 // 1 nibble of ones for every set bit of w, in the layout of expand_unit.
 __device__ __forceinline__ uint4 nibble_mask(uint32_t w) {
     return make_uint4((w & 0x11111111u) * 15u, ((w >> 1) & 0x11111111u) * 15u, ((w >> 2) & 0x11111111u) * 15u,
                       ((w >> 3) & 0x11111111u) * 15u);
-}
-
-// w = 2 w + bit for four compare results, the first becoming the highest bit.  The s_nop covers the two wait states between a
-// vector compare that writes an SGPR pair and a vector instruction that reads it: the compiler does not look into the block.
-__device__ __forceinline__ void push4(uint32_t& w, unsigned long long a, unsigned long long b, unsigned long long c, unsigned long long d) {
-    asm("s_nop 1\n\t"
-        "v_addc_co_u32_e64 %0, vcc, %0, %0, %1\n\t"
-        "v_addc_co_u32_e64 %0, vcc, %0, %0, %2\n\t"
-        "v_addc_co_u32_e64 %0, vcc, %0, %0, %3\n\t"
-        "v_addc_co_u32_e64 %0, vcc, %0, %0, %4"
-        : "+v"(w) : "s"(a), "s"(b), "s"(c), "s"(d) : "vcc");
 }
 
 typedef uint32_t word4 __attribute__((ext_vector_type(4), aligned(4)));      // filters of odd word counts start at any word

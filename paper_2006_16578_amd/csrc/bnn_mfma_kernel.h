@@ -61,6 +61,19 @@ __device__ __forceinline__ v8i expand_fp4(uint32_t w, uint32_t c2) {
     return r;
 }
 
+// The same as one 16-byte unit, the form that lies in LDS; and such a unit as an operand.
+__device__ __forceinline__ uint4 expand_unit(uint32_t w, uint32_t c2) {
+    return make_uint4(((w << 3) & 0x88888888u) | c2, ((w << 2) & 0x88888888u) | c2, ((w << 1) & 0x88888888u) | c2,
+                      (w & 0x88888888u) | c2);
+}
+
+__device__ __forceinline__ v8i as_operand(const uint4& u) {
+    v8i r;
+    r[0] = (int)u.x; r[1] = (int)u.y; r[2] = (int)u.z; r[3] = (int)u.w;
+    r[4] = 0; r[5] = 0; r[6] = 0; r[7] = 0;         // the upper half is not read for 4-bit formats
+    return r;
+}
+
 // A lane's 32 bytes of a blocked 16-bit residual read ahead of the main loop (passed by value, so that it stays
 // in registers).
 struct Fetched {

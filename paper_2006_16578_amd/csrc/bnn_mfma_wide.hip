@@ -36,6 +36,8 @@ namespace {
 
 using mfma::v16f;
 using mfma::v8i;
+using mfma::as_operand;
+using mfma::expand_unit;
 
 constexpr int TILE = 256;                 // rows and columns of the workgroup tile
 constexpr int WS = TILE + 1;              // units between consecutive words of a slab: odd (see the layout note)
@@ -43,18 +45,6 @@ constexpr int WIDE_THREADS = 512;
 constexpr int MT = 4, NT = 2;             // accumulator tiles per wave: 128 x 64
 constexpr int WM = 2, WN = 4;             // waves per workgroup tile
 static_assert(WM * MT * 32 == TILE && WN * NT * 32 == TILE && WM * WN * 64 == WIDE_THREADS, "wave grid covers the tile");
-
-__device__ __forceinline__ uint4 expand_unit(uint32_t w, uint32_t c2) {
-    return make_uint4(((w << 3) & 0x88888888u) | c2, ((w << 2) & 0x88888888u) | c2, ((w << 1) & 0x88888888u) | c2,
-                      (w & 0x88888888u) | c2);
-}
-
-__device__ __forceinline__ v8i as_operand(const uint4& u) {
-    v8i r;
-    r[0] = (int)u.x; r[1] = (int)u.y; r[2] = (int)u.z; r[3] = (int)u.w;
-    r[4] = 0; r[5] = 0; r[6] = 0; r[7] = 0;         // the upper half is not read for 4-bit formats
-    return r;
-}
 
 constexpr int BP = TILE + 4;                        // units between the two planes of packed B
 constexpr int A_UNITS = 8 * WS;
