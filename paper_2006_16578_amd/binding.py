@@ -112,9 +112,15 @@ def _ptr(t):
 
 # What a call costs on the host counts: a small product runs 4 us on the GPU.  The two helpers below ask torch for the current
 # device and the raw stream only (0.3 us; a device context manager and a Stream object per call took 3.1 of 10 us).
+# (a private function of torch: without it the Stream object serves)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(t: torch.Tensor):
     """The current stream of t's device."""
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(t.get_device()))
+    if _raw_stream is None:
+        return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    return ctypes.c_void_p(_raw_stream(t.get_device()))
 
 
 _STAY = contextlib.nullcontext()

@@ -131,6 +131,17 @@ def test_lds_expanded_convolutions_by_output():
     assert not served(256, 14, 96, residual=True, keep_sum=True)
 
 
+def test_stream_without_the_private_torch_function(monkeypatch):
+    import types
+    from paper_2006_16578_amd import binding as b
+    t = types.SimpleNamespace(device="dev", get_device=lambda: 3)
+    monkeypatch.setattr(b, "_raw_stream", lambda index: 0x1000 + index)
+    assert b._stream(t).value == 0x1003
+    monkeypatch.setattr(b, "_raw_stream", None)
+    monkeypatch.setattr(b.torch.cuda, "current_stream", lambda device: types.SimpleNamespace(cuda_stream=0x2000 if device == "dev" else 0))
+    assert b._stream(t).value == 0x2000
+
+
 def test_packs_refuse_rows_beyond_32_bit_columns():
     # a row stride of more than 2^26 words would pass 2^31 columns: refused before anything is launched (the pointers are never read)
     import paper_2006_16578_amd as b
