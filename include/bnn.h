@@ -72,11 +72,13 @@ const char* bnn_bconv_kernel_name_out(int N, int H, int W, int C, int O, int k, 
 /* The same for a padding mode and for a convolution inside a layer chain.  flags: BNN_CONV_SHORTCUT, the convolution of a
  * residual block that also adds a 1x1 shortcut; BNN_CONV_RESIDUAL / BNN_CONV_KEEP_SUM, one that adds the chain's running sum / keeps
  * its own (16-bit sums, with BNN_OUT_BITS); BNN_CONV_POOL2, one with a 2x2 pooling layer of stride 2 behind it: the name then ends in
- * "_pool2" if the convolution's kernel stores the pooled bits itself. */
+ * "_pool2" if the convolution's kernel stores the pooled bits itself.  BNN_CONV_RESIDUAL32: bnn_bconv_thr with an int32 residual; the name
+ * ends in "_stream" if a kernel for streamed residuals serves it.  The string lives until the thread's next call. */
 #define BNN_CONV_SHORTCUT 1
 #define BNN_CONV_POOL2 2
 #define BNN_CONV_RESIDUAL 4
 #define BNN_CONV_KEEP_SUM 8
+#define BNN_CONV_RESIDUAL32 16
 const char* bnn_bconv_kernel_name_ex(int N, int H, int W, int C, int O, int k, int stride, int pad, int pad_mode, int path,
                                      int out_kind, int flags);
 

@@ -89,13 +89,14 @@ def bmm_kernel_name(M: int, N: int, K: int, path: int = PATH_AUTO, int32_out: bo
 
 def bconv_kernel_name(N, H, W, C, O, k, stride, pad, path: int = PATH_AUTO, int32_out: bool = False,
                       pad_mode: int = PAD_MINUS_ONE, shortcut: bool = False, pool2: bool = False, residual: bool = False,
-                      keep_sum: bool = False) -> str:
+                      keep_sum: bool = False, residual32: bool = False) -> str:
     """Of a convolution in a layer chain -- shortcut: a residual block's that also adds a 1x1 shortcut; residual / keep_sum: one that
     adds the running 16-bit sum / keeps its own; pool2: a 2x2 pooling layer follows (the name ends in "_pool2" if the
-    convolution's kernel stores the pooled bits)."""
+    convolution's kernel stores the pooled bits).  residual32: bconv_thr with an int32 residual ("_stream": a kernel for streamed
+    residuals)."""
     return load().bnn_bconv_kernel_name_ex(int(N), int(H), int(W), int(C), int(O), int(k), int(stride), int(pad), int(pad_mode),
                                            int(path), int(bool(int32_out)), int(bool(shortcut)) | 2 * int(bool(pool2)) | 4 * int(bool(residual))
-                                           | 8 * int(bool(keep_sum))).decode()
+                                           | 8 * int(bool(keep_sum)) | 16 * int(bool(residual32))).decode()
 
 
 def nwords(nbits: int) -> int:

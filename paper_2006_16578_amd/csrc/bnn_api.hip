@@ -306,7 +306,7 @@ const char* bnn_bconv_kernel_name_ex(int N, int H, int W, int C, int O, int k, i
                                      int out_kind, int flags) {
     int P, Q;
     if (out_kind != BNN_OUT_BITS && out_kind != BNN_OUT_INT32) return "invalid";
-    if (flags & ~(BNN_CONV_SHORTCUT | BNN_CONV_POOL2 | BNN_CONV_RESIDUAL | BNN_CONV_KEEP_SUM)) return "invalid";
+    if (flags & ~(BNN_CONV_SHORTCUT | BNN_CONV_POOL2 | BNN_CONV_RESIDUAL | BNN_CONV_KEEP_SUM | BNN_CONV_RESIDUAL32)) return "invalid";
     if (conv_shape(N, H, W, C, O, k, stride, pad, pad_mode, &P, &Q) != BNN_OK) return "invalid";
     static const uint32_t some_words = 0u;        // the choice only asks whether there is a second source
     Geom g = {};

@@ -1,5 +1,7 @@
 // Matrix-core path: dispatch and the BMM instantiations (kernels are in bnn_mfma_kernel.h and
 // bnn_mfma_staged.h).
+#include <stdio.h>
+
 #include "bnn_mfma_staged.h"
 
 namespace bnn {
@@ -72,25 +74,28 @@ const char* describe_mfma(const Geom& g, bool int32_out, int flags) {
     static int16_t some_sums;
     if (flags & BNN_CONV_RESIDUAL) e.resid16 = &some_sums;
     if (flags & BNN_CONV_KEEP_SUM) e.out16 = &some_sums;
+    if (flags & BNN_CONV_RESIDUAL32) e.resid = &some_output;
+    static thread_local char name[64];
+    auto with_suffix = [](const char* base, const char* suffix) {
+        snprintf(name, sizeof(name), "%s%s", base, suffix);
+        return (const char*)name;
+    };
     e.sums_tiled = (flags & (BNN_CONV_RESIDUAL | BNN_CONV_KEEP_SUM)) && g.cols % 32 == 0 ? 1 : 0;
     const int tile = mfma::pick_tile(g, &e);
     if (tile == 0 && mfma_wide_takes(g, e)) return "mfma_fp4_bmm_xlds_wg256x256";
     if (mfma_conv_patch_takes(g, e)) return describe_mfma_conv_patch(g);
-    if (const int xt = mfma_conv_xlds_tile(g, e)) return describe_mfma_conv_xlds(xt);
-    if ((flags & BNN_CONV_POOL2) && mfma_conv_pools(g, e))
-        return tile == 0   ? "mfma_fp4_conv_wg256x128_pool2"
-               : tile == 1 ? "mfma_fp4_conv_wg512x64_pool2"
-               : tile == 2 ? "mfma_fp4_conv_wg128x128_pool2"
-                           : "mfma_fp4_conv_wg64x64_pool2";
+    if (const int xt = mfma_conv_xlds_tile(g, e))         // (its streamed form needs whole lines only)
+        return with_suffix(describe_mfma_conv_xlds(xt), e.resid != nullptr && (e.ldc & 31) == 0 ? "_stream" : "");
+    const char* suffix = (flags & BNN_CONV_POOL2) && mfma_conv_pools(g, e) ? "_pool2" : mfma::streams_residual(g, e) ? "_stream" : "";
     const bool st = !g.b_tiled && !e.sums_tiled && staged_ok(g, tile);
     switch (tile) {
-        case 0: return g.conv ? (st ? "mfma_fp4_conv_lds_wg256x128" : "mfma_fp4_conv_wg256x128")
+        case 0: return g.conv ? with_suffix(st ? "mfma_fp4_conv_lds_wg256x128" : "mfma_fp4_conv_wg256x128", suffix)
                               : (st ? "mfma_fp4_bmm_lds_wg256x128" : "mfma_fp4_bmm_wg256x128");
-        case 1: return g.conv ? (st ? "mfma_fp4_conv_lds_wg512x64" : "mfma_fp4_conv_wg512x64")
+        case 1: return g.conv ? with_suffix(st ? "mfma_fp4_conv_lds_wg512x64" : "mfma_fp4_conv_wg512x64", suffix)
                               : (st ? "mfma_fp4_bmm_lds_wg512x64" : "mfma_fp4_bmm_wg512x64");
-        case 2: return g.conv ? (st ? "mfma_fp4_conv_lds_wg128x128" : "mfma_fp4_conv_wg128x128")
+        case 2: return g.conv ? with_suffix(st ? "mfma_fp4_conv_lds_wg128x128" : "mfma_fp4_conv_wg128x128", suffix)
                               : (st ? "mfma_fp4_bmm_lds_wg128x128" : "mfma_fp4_bmm_wg128x128");
-        default: return g.conv ? "mfma_fp4_conv_wg64x64" : "mfma_fp4_bmm_wg64x64";
+        default: return g.conv ? with_suffix("mfma_fp4_conv_wg64x64", suffix) : "mfma_fp4_bmm_wg64x64";
     }
 }
 

@@ -97,6 +97,31 @@ def test_shapes_expanded_in_lds(bnn, orc, shape):
         run_conv(bnn, orc, case, 0, pad_mode, ref=ref)
 
 
+# an int32 residual in rows of whole 128-byte lines: every kernel built for it (each load width and tile of the direct kernel, the staged
+# and the LDS-expanded one), the last 32-row blocks and column tiles partly empty; sums that overwrite the residual; and what keeps the general
+# epilogue: other row lengths, excluded padding with a partly filled K-step
+STREAMED = [(43, 28, 28, 96, 96, 1, 1, 0, 0, "mfma_fp4_conv_wg128x128_stream"), (43, 27, 29, 64, 96, 3, 1, 1, 0, "mfma_fp4_conv_wg128x128_stream"),
+            (43, 28, 28, 128, 160, 1, 1, 0, 0, "mfma_fp4_conv_wg128x128_stream"), (33, 28, 28, 256, 480, 1, 1, 0, 0, "mfma_fp4_conv_wg256x128_stream"),
+            (168, 28, 28, 64, 32, 1, 1, 0, 0, "mfma_fp4_conv_wg512x64_stream"), (43, 28, 28, 4224, 96, 1, 1, 0, 0, "mfma_fp4_conv_lds_wg128x128_stream"),
+            (43, 28, 28, 70, 96, 3, 1, 1, 0, "mfma_fp4_conv_xlds_wg128x128_stream"), (43, 28, 28, 256, 96, 3, 1, 1, 1, "mfma_fp4_conv_wg128x128_stream"),
+            (43, 28, 28, 128, 100, 1, 1, 0, 0, "mfma_fp4_conv_wg128x128"), (43, 28, 28, 96, 96, 1, 1, 0, 1, "mfma_fp4_conv_wg128x128"),
+            (2, 28, 28, 128, 96, 1, 1, 0, 0, "mfma_fp4_conv_wg64x64")]
+
+
+@pytest.mark.parametrize("shape", STREAMED)
+def test_streamed_residual(bnn, orc, shape):
+    N, H, W, C, O, k, st, pad, pad_mode, kernel = shape
+    assert bnn.bconv_kernel_name(N, H, W, C, O, k, st, pad, pad_mode=pad_mode, residual32=True) == kernel
+    case = wl.bconv_case(96, N, H, W, C, O, k, st, pad, index0=C % 83)
+    ref = orc.bconv(case["x"], case["filt"], C, st, pad, pad_mode, tier=1)
+    R = np.random.default_rng(C + O).integers(-300, 301, size=ref.shape).astype(np.int32)
+    x, f, tau, r = to_dev(case["x"]), to_dev(case["filt"]), to_dev(case["tau"]), to_dev(R)
+    want = orc.threshold_pack(ref + R, case["tau"])
+    assert np.array_equal(words(bnn.bconv_thr(x, f, tau, C, st, pad, pad_mode, residual=r)), want)
+    bits, S = bnn.bconv_thr(x, f, tau, C, st, pad, pad_mode, residual=r, sum_out=r)
+    assert np.array_equal(words(bits), want) and np.array_equal(host(S), ref + R)
+
+
 def test_paper_sweep_shape_c640(bnn, orc):
     # one shape of the paper's BConv sweep (batch 16, 64x64, 3x3, C = O = 640), as bench.py runs it
     case = wl.bconv_case(6, 16, 64, 64, 640, 640, 3, 1, 1, index0=640 % 97)

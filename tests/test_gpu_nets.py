@@ -360,22 +360,26 @@ def test_block_chains_expanded_in_lds(bnn, orc, batch, hw, cin, blocks, pad_mode
 
 # 2x2 pooling behind a convolution, stored by the convolution itself on the direct kernels (even sizes) and by the pooling kernel
 # (odd sizes, other windows): every tile of the direct kernel, channel counts that fill no word, several pooled layers in a row, a
-# last 32-row block that is partly empty; check_cnn compares the full and the pooled bits of every layer
-@pytest.mark.parametrize("batch,hw,chans,win", [(3, 12, (64, 128, 40), 2), (5, 8, (128, 256, 256), 2), (1, 4, (96, 33, 70), 2),
-                                                (3, 9, (64, 65, 128), 2), (2, 12, (64, 64, 64), 3), (90, 32, (33, 256, 512), 2),
-                                                (40, 64, (512, 60, 128), 2)])
-def test_convolution_stores_pooled_bits(bnn, orc, batch, hw, chans, win):
+# last 32-row block that is partly empty; the full and the pooled bits of every layer against the oracle.  `kernels`: what serves each
+# convolution, "_pool2" where it stores the pooled bits
+@pytest.mark.parametrize("batch,hw,chans,win,kernels", [
+    (3, 12, (64, 128, 40), 2, ("wg64x64_pool2", "wg64x64_pool2")), (5, 8, (128, 256, 256), 2, ("wg64x64_pool2", "wg64x64_pool2")),
+    (1, 4, (96, 33, 70), 2, ("wg64x64", "wg64x64_pool2")), (3, 9, (64, 65, 128), 2, ("wg64x64", "wg64x64")),
+    (2, 12, (64, 64, 64), 3, ("wg64x64", "wg64x64")), (90, 32, (33, 256, 512), 2, ("wg256x128_pool2", "wg128x128_pool2")),
+    (40, 64, (512, 60, 128), 2, ("wg512x64_pool2", "wg128x128_pool2"))])
+def test_convolution_stores_pooled_bits(bnn, orc, batch, hw, chans, win, kernels):
     rng = np.random.default_rng(batch * 100 + hw)
     layers = [{"op": "bwn", "W": wl.random_bits(rng, (chans[0], 3, 3), 3), "thr": np.zeros(chans[0], np.float32), "C": 3, "stride": 1, "pad": 1}]
     size = hw
-    for cin, cout in zip(chans, chans[1:]):
+    for cin, cout, kernel in zip(chans, chans[1:], kernels):
+        # (the choice is the one the chain makes; a window of 3 or another stride is never asked for)
+        assert bnn.bconv_kernel_name(batch, size, size, cin, cout, 3, 1, 1, pool2=win == 2) == "mfma_fp4_conv_" + kernel
         layers.append({"op": "bconv", "W": wl.random_bits(rng, (cout, 3, 3), cin), "thr": rng.integers(-20, 21, size=cout).astype(np.int32),
                        "C": cin, "stride": 1, "pad": 1})
         layers.append({"op": "pool", "win": win, "stride": 2})
         size = (size - win) // 2 + 1
-    kernel = bnn.bconv_kernel_name(batch, hw, hw, chans[0], chans[1], 3, 1, 1)
-    print(batch, hw, chans, kernel, flush=True)
-    net = bnn.Net.from_layers(layers + [], hw)
+    print(batch, hw, chans, kernels, flush=True)
+    net = bnn.Net.from_layers(layers, hw)
     x = rng.integers(-100, 101, size=(batch, hw, hw, 3)).astype(np.float32)     # exact in fp32: no bit depends on rounding
     xd = to_dev(x)
     net._out_kind, net._out_cols = torch.int32, 1
