@@ -9,7 +9,7 @@
 // 8-byte operand reads with bank conflicts, three 2-byte LDS stores for every input value, three vector instructions per
 // accumulator register to pack its bits, and a patch that was loaded, multiplied and dropped with nothing overlapped.  Here:
 //  * A pixel's nine terms are one 16-byte record (h0 h1 | h2 m0 | m1 m2 | l0 l1) plus l2 apart.  A K run (the 8 slots of a
-//    half-wave) is ONE aligned, conflict-free 16-byte read: a tap's record; the l2 terms of a filter row, kept as 8-byte units
+//    half-wave) is ONE aligned 16-byte read, consecutive lanes consecutive records: a tap's record; the l2 terms of a filter row, kept as 8-byte units
 //    (l2 of four consecutive pixels) beside the records, fill one more run per filter row.  K^2 + K runs in all -- 12 for
 //    3x3, 12 MFMAs per 32 pixels x 64 channels, what the 81 products per output need at 16 slots an instruction.
 //  * The weights are the MFMA's row operand and stay in registers for the whole launch (the workgroups are persistent), expanded
@@ -20,11 +20,11 @@
 //  * Two patch buffers: the next tile's pixels are requested before this tile is multiplied and split into the other buffer
 //    after it; one barrier per tile.  The packed words leave only after that staging: memory operations retire in order, and
 //    stores issued earlier put their latency in front of the wait for the pixels (103 -> 90 us back to back).
-// Measured (input not in a cache), old -> this kernel: 128 x 224x224x3, 3x3, 64 channels 151 -> 81 us (with the expansion launch;
-// 1.6 TB/s of input and output, the matrix pipe busy about 45 % at 12 MFMAs per fragment); stride 2 65 -> 36 us; 64 x 224x224x3, 5x5
+// Measured (input not in a cache), old -> this kernel: 128 x 224x224x3, 3x3, 64 channels 151 -> 78 us (with the expansion launch;
+// 1.7 TB/s of input and output, the matrix pipe busy 47 %, 9.2 vector instructions per MFMA); stride 2 65 -> 36 us; 64 x 224x224x3, 5x5
 // stride 1 139 -> 86 us, 128 channels stride 2 93 -> 53 us; small calls lose the expansion launch (2 to 3 us).
-// Left: MFMAs alone run this stream in about 55 us, packing alone in 31, staging alone in 34; two waves per SIMD overlap
-// them in part.  Three waves per SIMD (one accumulator set, less read ahead) spill and are slower (101 us back to back against 94).
+// Left: the MFMAs by themselves take 37 us at the clock held (12 in 187 ns per SIMD); the multiply phase alone, MFMAs and operand reads, about 55,
+// packing alone 31, staging alone 34; two waves per SIMD overlap them in part.  Three waves per SIMD (one accumulator set, less read ahead) spill and are slower (101 us back to back against 94).
 #include <type_traits>
 
 #include "bnn_internal.h"

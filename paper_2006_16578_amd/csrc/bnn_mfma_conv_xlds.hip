@@ -6,19 +6,20 @@
 // its words with 4-byte loads, masks them per tap, and expands both operands -- 25 vector instructions per MFMA at 96 channels and
 // a 5x5 window, a third of the K slots spent on rounding each tap up to whole K-steps, the matrix pipe busy 18 % of the time.  Here:
 //  * LDS holds one 16-byte unit per pixel and 32-channel word (the four operand registers of a lane), in planes [word][pixel]:
-//    the 32 pixels of a fragment read 32 consecutive units (two-way conflicts at stride 2).  A tap's pixel is a constant offset
+//    the 32 pixels of a fragment read 32 consecutive units, interrupted where it crosses an image row (two units to a bank at stride 2).  A tap's pixel is a constant offset
 //    away, so K runs over the flattened words of a filter, whatever the channel count: words 8c .. 8c + 3 of chunk c go to the
 //    lower half-wave, 8c + 4 .. 8c + 7 to the upper one; only the last chunk of a filter can be partly empty (its missing words are units of zeros).
 //  * Padding is data: an out-of-frame pixel is the unit of -1 bits, or with excluded padding a unit of zeros, and the bits past the
 //    last channel are zeros too, so that no K slot needs a mask and no sum needs a correction in either convention.
-//  * A K-step of a wave (128 pixels x 64 channels) is eight MFMAs, four 16-byte LDS reads and about twenty vector instructions
-//    (expansion of two filter words, four addresses): below what the issue slots beside the MFMAs hold.
+//  * A K-step of a wave (128 pixels x 64 channels) is eight MFMAs, four 16-byte LDS reads and, by the source, about twenty vector instructions
+//    (expansion of two filter words, four addresses); over the whole kernel, staging and epilogue included, 6.9 per MFMA are counted.
 //  * Bits only: the filters are the MFMA's row operand, with channels dealt to its rows so that a half-wave owns 32 consecutive
 //    ones; packing is a compare and an add-with-carry per accumulator register, and a lane stores whole words of its pixel.
 //    Everything else keeps pixels as rows and the shared epilogue (32 consecutive channels per store instruction).
-// Measured (graph replay, old kernels -> this one): 64 x 27x27x96 -> 200, 5x5, excluded padding 47.5 -> 19.8 us; 128 x 56x56x48 -> 48,
-// 3x3, excluded padding 48.4 -> 18.1; 128 x 28x28x96 -> 192, 3x3 26.5 -> 19.7; 100 x 9x9x300 -> 300 18.6 -> 11.8.  Of the 19.8 us, the
-// K loop is 12.8 (20 % above what its MFMAs take where a SIMD has two waves), staging 1.5, launch and epilogue the rest.
+// Measured (graph replay of single launches, direct kernel -> this one): 64 x 27x27x96 -> 200, 5x5, excluded padding 46.8 -> 19.4 us (43.7 -> 17.6 as
+// passes queued one after another); 128 x 56x56x48 -> 48, 3x3, excluded padding 48.8 -> 18.3; 128 x 28x28x96 -> 192, 3x3 27.3 -> 20.0;
+// 100 x 9x9x300 -> 300 18.6 -> 11.8.  Parts switched off in the first shape: K loop 12.8 us (20 % above what its MFMAs take where a
+// SIMD has two waves), staging 1.5, launch and epilogue the rest.
 // The patch covers whole padded rows of the images a tile of consecutive output pixels touches, so small images pack several to a
 // tile.  Two workgroups per compute unit: one stages while the other multiplies.
 #include <type_traits>

@@ -496,7 +496,9 @@ __device__ __forceinline__ void epilogue_sums(v16f (&acc)[MT][NT], const long lo
 // byte of which is touched once, bypass the caches.  Only for rows of whole 128-byte lines: where rows share lines (100, 250, 511
 // channels) streaming costs 20 to 50 %, and without it this body is 6 to 9 % behind the generic one.
 // 256 x 28x28x128 -> 128, 3x3, residual in, sum and bits out (209 MB): 68.4 us
-// with the generic body (28 vector instructions per MFMA, 3.1 TB/s), 51.5 us with this one (4.1 TB/s).
+// with the generic body (28 vector instructions per MFMA, 3.1 TB/s), 51 us with this one (18 per MFMA, 4.1 TB/s).  At small sizes, where the sum is the
+// next block's residual and could have stayed in a cache, streaming measured no loss: blocks of 1 to 256 images at 56x56x64, 28x28x128,
+// 14x14x256 and 7x7x512, each sum the next one's residual: equal below about 20 MB of sums, 1.07 to 1.15 of the speed above.
 template <int MT, int NT>
 __device__ __forceinline__ void epilogue_resid(v16f (&acc)[MT][NT], const long long m0, const int n0, const int lane, const Geom& g,
                                                const Epi& e, const int corr_all, const int (&thi)[NT]) {
