@@ -421,7 +421,8 @@ int xlds_tile(const Geom& g, const Epi& e) {
     if (!g.excl && (mfma::conv_stages_through_lds(g) || g.tw % 8 == 0)) return 0;
     const OutputForm form = output_form(e);
     if (g.A2 != nullptr && form != OUT_BITS && form != OUT_BITS_AND_SUMS) return 0;
-    const int least = min_workgroups(g, form);
+    // (images beyond the direct kernel's 32-bit offsets would be left to the vector ALU)
+    const int least = mfma::offsets_fit(g) ? min_workgroups(g, form) : 96;
     if (least == 0) return 0;
     const bool small_only = form == OUT_STREAMED_RESIDUAL || form == OUT_RESIDUAL;      // (the residual of four row fragments at a time: 0.92 of two)
     int best = 0;

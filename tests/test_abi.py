@@ -127,6 +127,10 @@ def test_lds_expanded_convolutions_by_output():
     # sums alone: 128 workgroups, 96 with excluded padding and no unrolled form of the direct kernel
     assert not served(64, 14, 90, int32_out=True) and served(128, 14, 90, int32_out=True) and served(64, 14, 90, pad_mode=1, int32_out=True)
     assert not served(64, 14, 100, pad_mode=1, int32_out=True)
+    # ... except images of 1 GiB, which the direct kernel cannot address
+    for kw in (dict(residual=True), dict(keep_sum=True, shortcut=True)):
+        assert b.bconv_kernel_name(2, 1 << 20, 256, 32, 90, 4, 1, 1, **kw).startswith("mfma_fp4_conv_xlds")
+        assert not b.bconv_kernel_name(2, 1 << 10, 256, 32, 90, 4, 1, 1, **kw).startswith("mfma_fp4_conv_xlds")
     # blocked 16-bit sums stay on the direct kernels
     assert not served(256, 14, 96, residual=True, keep_sum=True)
 
