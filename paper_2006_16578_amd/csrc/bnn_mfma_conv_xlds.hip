@@ -380,15 +380,16 @@ struct XTile { int rows, cols, mfmas; };                // mfmas: per wave and K
 constexpr XTile XTILES[] = {{0, 0, 0}, {256, 128, 8}, {128, 256, 8}, {512, 64, 8}, {128, 128, 4}, {256, 64, 4}};
 
 // Fewest workgroups from which this kernel is the faster one, 0: it is not.  With bits alone the 64 x 64 tiles of the direct kernel,
-// four times as many, win below about 96 (49 workgroups 0.87 of their speed, 98: 1.04, 171: 1.3).  Everything else leaves through the
+// four times as many, win below about 96 (49 workgroups 0.87 of their speed, 98: 1.04, 171: 1.3; more in most_staged).  Everything else leaves through the
 // accumulators' rows, load and store per element, and what a workgroup of four large wave tiles waits there (7 to 12 us through the general
 // epilogue) is hidden only by other workgroups: it takes more of them, or a longer K, whose saving outweighs it.  Measured, this kernel's
 // speed over the direct one's (3x3, channels = filters, -1 / excluded padding):
-//   sums alone         104 workgroups 0.83 to 0.99 / 1.2 to 1.3, 152: 1.03 to 1.07, 200: 1.2 to 1.4; the unrolled forms (4 and 8 words, excluded
+//   sums alone         104 workgroups 0.83 to 0.99 / 1.2 to 1.3, 129: 0.96 to 1.05, 152: 1.03 to 1.07, 200: 1.2 to 1.4; the unrolled forms (4 and 8 words, excluded
 //                      padding) 0.95 to 1.03 at 104, 1.3 at 200; 90 channels against the 256x128 tile of the direct kernel 0.97
 //   streamed residual  104: 0.69 to 0.80 / 0.89 to 0.97, 152: 0.85 / 1.05, 200: 1.01 to 1.25 / 1.24 to 1.5, 392 and more: 1.08 to 1.4
 //   other residuals    104: 0.6 to 0.7 / 0.78 to 0.92, 152 with 90 words of K 0.77 / 0.9, 200: 0.90 with 27 words, 1.1 with 63, 1.46 with 126 / 1.1
-//                      to 1.5, the unrolled forms 0.83 to 0.95; 296 to 392: 1.1 to 1.6; 27 words against the 256x128 tile 0.97 to 1.05
+//                      to 1.5, the unrolled forms 0.83 to 0.95; 296 to 392: 1.1 to 1.6; 27 words against the 256x128 tile 0.97 to 1.05; the unrolled
+//                      form of two words, more than 64 channels out, 0.93 to 0.97 at 516 to 744
 //   bits and sums      27 words 0.6 to 0.9 at any count, 63: 0.67 at 104, 1.0 at 200 and 392, against the 256x128 tile 0.94 to 0.97 (63 and 75
 //                      words), 90: 1.13 to 1.37 from 296 / 18 words 0.93 at 392, 27: 0.99 at 200, 1.1 at 392, 63: 1.17 at 200, unrolled
 //                      forms 0.8 at 200, 1.1 at 392
@@ -398,11 +399,26 @@ int min_workgroups(const Geom& g, OutputForm form) {
     const bool against_big_tile = !g.excl && mfma::pick_tile(g) == 0;
     switch (form) {
         case OUT_BITS: return 96;
-        case OUT_SUMS: return against_big_tile && kwords < 45 && (g.cols & 31) != 0 ? 0 : g.excl && !unrolled ? 96 : 128;
+        case OUT_SUMS: return against_big_tile && kwords < 45 && (g.cols & 31) != 0 ? 0 : g.excl && !unrolled ? 96 : 132;
         case OUT_STREAMED_RESIDUAL: return !g.excl ? 192 : unrolled ? 256 : 128;
-        case OUT_RESIDUAL: return against_big_tile && kwords < 45 ? 0 : (g.excl ? unrolled : kwords < 63) ? 256 : 192;
+        case OUT_RESIDUAL: return (against_big_tile && kwords < 45) || (g.excl && unrolled && g.tw == 2 && g.cols > 64) ? 0 : (g.excl ? unrolled : kwords < 63 || g.tw % 4 == 0) ? 256 : 192;
         default: return kwords < (g.excl ? 27 : against_big_tile ? 90 : 63) ? 0 : (g.excl && kwords < 63) || unrolled ? 256 : 192;
     }
+}
+
+// Most LDS units a workgroup may stage per K-step with -1 padding and few workgroups.  Up to half of the compute units hold one workgroup then, and what
+// it stages and waits is not hidden, while the direct kernel has no sum to correct and, at whole groups of four words, loads 8 bytes at a
+// time.  Measured over 500 geometries of 96 to 160 workgroups, strides 1 to 3 (this kernel's speed over the direct one's): four words 0.83 to 0.95 up to
+// 144 workgroups; one word 1.09 and more up to 200 units, 0.79 at 344; two and odd counts 1.03 and more up to 80 units, 0.83 to 0.98 from 85; six words
+// 1.4 at 32 units, 0.94 to 0.98 from 92; all of them 1.03 and more from 132 workgroups (one of 60: 0.96).  With excluded padding 1.05 and more everywhere.
+// Residuals in rows that are not whole lines keep workgroups waiting at any count: groups of four words 0.86 to 0.96 from 104 units (590 to 760
+// workgroups, both conventions), 1.01 to 1.14 up to 51.
+double most_staged(const Geom& g, OutputForm form, long long wgs) {
+    if (form == OUT_RESIDUAL) return g.tw % 4 == 0 ? 100. : 1e30;
+    if (g.excl || wgs >= 192) return 1e30;
+    if (g.tw % 4 == 0) return 0.;
+    if (wgs >= 132) return 1e30;
+    return g.tw == 1 ? 200. : g.tw % 2 == 1 || g.tw == 2 ? 80. : 60.;
 }
 
 // Tile for this geometry, 0: another kernel's.  Among the tiles whose patch fits LDS, the one with the least estimated time: rounds
@@ -422,7 +438,8 @@ int xlds_tile(const Geom& g, const Epi& e) {
     const OutputForm form = output_form(e);
     if (g.A2 != nullptr && form != OUT_BITS && form != OUT_BITS_AND_SUMS) return 0;
     // (images beyond the direct kernel's 32-bit offsets would be left to the vector ALU)
-    const int least = mfma::offsets_fit(g) ? min_workgroups(g, form) : 96;
+    const bool direct_reaches = mfma::offsets_fit(g);
+    const int least = direct_reaches ? min_workgroups(g, form) : 96;
     if (least == 0) return 0;
     const bool small_only = form == OUT_STREAMED_RESIDUAL || form == OUT_RESIDUAL;      // (the residual of four row fragments at a time: 0.92 of two)
     int best = 0;
@@ -435,6 +452,7 @@ int xlds_tile(const Geom& g, const Epi& e) {
         // Many empty columns: 0.77 at 64 of 128.
         if (wgs < least || (double)(gy * XTILES[t].cols) > 1.5 * g.cols) continue;
         if (!plan_lds(g, XTILES[t].rows, XTILES[t].cols, &x, &lds)) continue;
+        if (direct_reaches && (double)x.px_max * g.tw > most_staged(g, form, wgs) * steps) continue;
         const double m = XTILES[t].mfmas;
         const double wg = steps * m * (m < 8. ? 44. : 36.) + (double)x.px_max * g.tw / 4. + m * 160. + 1500.;
         const double cost = (double)cdiv(wgs, 512) * wg;

@@ -124,13 +124,19 @@ def test_lds_expanded_convolutions_by_output():
     assert served(64, 28, 90, pad_mode=1, residual=True) and served(64, 28, 90, pad_mode=1, shortcut=True, keep_sum=True)
     # ... and not against the direct kernel's 256x128 tile
     assert not served(128, 28, 90, residual=True) and served(128, 28, 90)
-    # sums alone: 128 workgroups, 96 with excluded padding and no unrolled form of the direct kernel
+    # sums alone: 132 workgroups, 96 with excluded padding and no unrolled form of the direct kernel
     assert not served(64, 14, 90, int32_out=True) and served(128, 14, 90, int32_out=True) and served(64, 14, 90, pad_mode=1, int32_out=True)
     assert not served(64, 14, 100, pad_mode=1, int32_out=True)
     # ... except images of 1 GiB, which the direct kernel cannot address
     for kw in (dict(residual=True), dict(keep_sum=True, shortcut=True)):
         assert b.bconv_kernel_name(2, 1 << 20, 256, 32, 90, 4, 1, 1, **kw).startswith("mfma_fp4_conv_xlds")
         assert not b.bconv_kernel_name(2, 1 << 10, 256, 32, 90, 4, 1, 1, **kw).startswith("mfma_fp4_conv_xlds")
+    # bits alone below 192 workgroups, -1 padding: what a workgroup stages per K-step is bounded, by the words of a pixel
+    def conv(batch, hw, C, O, k, stride, pad_mode=0):
+        return b.bconv_kernel_name(batch, hw, hw, C, O, k, stride, k // 2, pad_mode=pad_mode).startswith("mfma_fp4_conv_xlds")
+
+    assert not conv(123, 32, 64, 55, 5, 2) and conv(123, 32, 64, 55, 5, 2, 1) and conv(300, 32, 64, 55, 5, 2)
+    assert not conv(64, 14, 128, 120, 5, 1) and conv(64, 14, 96, 120, 5, 1)
     # blocked 16-bit sums stay on the direct kernels
     assert not served(256, 14, 96, residual=True, keep_sum=True)
 
