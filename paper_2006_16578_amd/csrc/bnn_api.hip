@@ -6,6 +6,7 @@
 #include <new>
 #include <vector>
 
+#include "bnn_fc_chain.h"
 #include "bnn_internal.h"
 
 using namespace bnn;
@@ -688,6 +689,30 @@ struct PersistCtx {
     }
 };
 
+// The fully-connected layers at the head of a network, an 8-bit input layer in front of them included, as one launch (bnn_fc_chain.hip).
+// Returns how many layers `ch` takes: 0 where one launch per layer is better.
+int fc_chain_plan(const bnn_net* net, const void* input, void* output, int batch, char* ws, FcChain* ch) {
+    const bnn_net::Layer& L0 = net->layers[0];
+    const bool u8 = L0.kind == bnn_net::IN_U8;
+    if (!u8 && L0.kind != bnn_net::IN_BITS) return 0;
+    ch->rows = batch; ch->out = static_cast<int32_t*>(output); ch->in_ldw = L0.words_per_row;
+    if (u8) {
+        ch->in_u8 = static_cast<const uint8_t*>(input); ch->in_cols = L0.a; ch->in_thr = L0.thr_u8;
+        ch->in_bits_out = reinterpret_cast<uint32_t*>(ws + L0.bits_off);
+    } else {
+        ch->in_bits = static_cast<const uint32_t*>(input);
+    }
+    for (size_t i = 1; i < net->layers.size() && ch->nlayers < FC_CHAIN_MAX; ++i) {
+        const bnn_net::Layer& L = net->layers[i];
+        if (L.kind != bnn_net::FC || (L.t0 == nullptr && L.b > 64)) break;
+        FcChainLayer& C = ch->layer[ch->nlayers++];
+        C.W = static_cast<const uint32_t*>(L.w0); C.thr = static_cast<const int32_t*>(L.t0);
+        C.bits = L.t0 ? reinterpret_cast<uint32_t*>(ws + L.bits_off) : nullptr;
+        C.K = L.a; C.N = L.b; C.tw = round4(words(L.a)); C.ldo = L.words_per_row;
+    }
+    return fc_chain_takes(*ch) ? 1 + ch->nlayers : 0;
+}
+
 int forward_impl(bnn_net* net, const void* input, void* output, int batch, char* ws, const Plan& pl, int path, void* stream,
                  PersistCtx* pc) {
     const uint32_t* cur = nullptr;      // bits of the current activation
@@ -699,6 +724,20 @@ int forward_impl(bnn_net* net, const void* input, void* output, int batch, char*
         const bnn_net::Layer& L = net->layers[i];
         uint32_t* obits = reinterpret_cast<uint32_t*>(ws + L.bits_off);
         int rc = BNN_OK;
+        if (i == 0 && pc == nullptr && path != BNN_PATH_VALU) {
+            FcChain ch = {};
+            const int run = fc_chain_plan(net, input, output, batch, ws, &ch);
+            if (run > 0) {
+                const bnn_net::Layer& last = net->layers[run - 1];
+                if (last.t0 == nullptr && !output) return BNN_ERR_INVALID_ARG;
+                if ((last.t0 == nullptr && !aligned16(output)) || (L.kind == bnn_net::IN_BITS && !aligned16(input))) return BNN_ERR_ALIGNMENT;
+                rc = launch_fc_chain(ch, static_cast<hipStream_t>(stream));
+                if (rc != BNN_OK) return rc;
+                cur = reinterpret_cast<uint32_t*>(ws + last.bits_off); curC = last.C; cur_ld = last.words_per_row;
+                i = run - 1;
+                continue;
+            }
+        }
         // persistent forward: contractions are collected (dispatch() records them while capture_sink is set) and run
         // as one kernel per unbroken run of FC / CONV / BLOCK layers; every other layer first lets that kernel go
         const bool contraction = L.kind == bnn_net::FC || L.kind == bnn_net::CONV || L.kind == bnn_net::BLOCK;

@@ -40,6 +40,44 @@ def test_mlp(bnn, orc, batch, path):
     assert np.array_equal(scores, ref)
 
 
+@pytest.mark.parametrize("dims,u8,batch", [
+    ((784, 1024, 1024, 1024, 10), True, 4097), ((784, 1024, 1024, 1024, 10), True, 4081),    # 32-row workgroups; the last of 16 rows ragged
+    ((16, 33, 1), True, 1), ((17, 64, 64, 64, 64), True, 15), ((1000, 65, 129, 31, 64), True, 17), ((4001, 70, 10), True, 129),
+    ((1, 1, 1), False, 16), ((31, 1100, 3), False, 33), ((2049, 127, 900, 12), False, 200), ((128, 64, 64, 64, 64, 64, 64, 5), False, 5000),
+    ((15, 100, 10), True, 40), ((300, 100, 65), True, 40)])                # not the chain's: rows of 15 bytes, 65 sums (its first layers are)
+@pytest.mark.parametrize("last_thr", [False, True])
+def test_fc_chain(bnn, orc, dims, u8, batch, last_thr):
+    # fully-connected layers at the head of a network in one launch: widths on and off words, 64-column groups and 1024-bit parts, and
+    # thresholds no sum can reach, or every sum does
+    rng = np.random.default_rng(sum(dims) + batch)
+    p = wl.mlp_params(dims, config=97)
+    thr = [rng.integers(-40, 41, size=n).astype(np.int32) for n in dims[1:]]
+    for t in thr:
+        t[::7] = rng.choice([-2 ** 31, 2 ** 31 - 1, 0], size=t[::7].shape)
+    in_thr = int(rng.choice([127, 0, 255]))
+    net = bnn.Net()
+    if u8:
+        net.input_u8(dims[0], in_thr)
+        x = rng.integers(0, 256, size=(batch, dims[0])).astype(np.uint8)
+        bits = orc.pack_u8(x, in_thr, ldb_w=p["W"][0].shape[1])
+    else:
+        net.input_bits(dims[0])
+        x = bits = wl.random_bits(rng, batch, dims[0], p["W"][0].shape[1])
+    nl = len(dims) - 1
+    for l in range(nl):
+        net.add_fc(to_dev(p["W"][l]), to_dev(thr[l]) if l + 1 < nl or last_thr else None, p["K"][l])
+    out = net.forward(to_dev(x))
+    if u8:
+        assert np.array_equal(words(net.layer_bits(0)), bits)
+    for l in range(nl):
+        v = orc.bmm(bits, p["W"][l], p["K"][l])
+        if l + 1 == nl and not last_thr:
+            assert np.array_equal(host(out), v)
+            break
+        bits = orc.threshold_pack(v, thr[l], ldb_w=wl.round_up(wl.nwords(dims[l + 1]), 4))
+        assert np.array_equal(words(net.layer_bits(l + 1)), bits), "layer %d" % (l + 1)
+
+
 def build_resnet(bnn, p, hw, pad_mode=0):
     net = bnn.Net()
     net.input_conv_f32(to_dev(p["stem_w"]), to_dev(p["stem_thr"]), hw, hw, 4, 3)
