@@ -49,6 +49,7 @@ int launch_mfma(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
         if (g.tw % 8 == 0) return mfma::launch_shape<4, false, false>(A, B, g, e, s);
         return mfma::launch_shape<4, false, true>(A, B, g, e, s);
     }
+    if (mfma_conv_band_takes(g, e)) return launch_mfma_conv_band(A, B, g, e, s);
     if (mfma_conv_patch_takes(g, e)) return launch_mfma_conv_patch(A, B, g, e, s);
     if (const int xt = mfma_conv_xlds_tile(g, e)) return launch_mfma_conv_xlds(xt, A, B, g, e, s);
     // (blocked 16-bit sums are implemented by the direct kernels only)
@@ -83,10 +84,12 @@ const char* describe_mfma(const Geom& g, bool int32_out, int flags) {
     e.sums_tiled = (flags & (BNN_CONV_RESIDUAL | BNN_CONV_KEEP_SUM)) && g.cols % 32 == 0 ? 1 : 0;
     const int tile = mfma::pick_tile(g, &e);
     if (tile == 0 && mfma_wide_takes(g, e)) return "mfma_fp4_bmm_xlds_wg256x256";
+    const bool pools = (flags & BNN_CONV_POOL2) && mfma_conv_pools(g, e);
+    if (!pools && mfma_conv_band_takes(g, e)) return "mfma_fp4_conv3x3_band_wg64";
     if (mfma_conv_patch_takes(g, e)) return describe_mfma_conv_patch(g);
     if (const int xt = mfma_conv_xlds_tile(g, e))         // (its streamed form needs whole lines only)
         return with_suffix(describe_mfma_conv_xlds(xt), e.resid != nullptr && (e.ldc & 31) == 0 ? "_stream" : "");
-    const char* suffix = (flags & BNN_CONV_POOL2) && mfma_conv_pools(g, e) ? "_pool2" : mfma::streams_residual(g, e) ? "_stream" : "";
+    const char* suffix = pools ? "_pool2" : mfma::streams_residual(g, e) ? "_stream" : "";
     const bool st = !g.b_tiled && !e.sums_tiled && staged_ok(g, tile);
     switch (tile) {
         case 0: return g.conv ? with_suffix(st ? "mfma_fp4_conv_lds_wg256x128" : "mfma_fp4_conv_wg256x128", suffix)

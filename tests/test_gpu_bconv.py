@@ -297,3 +297,22 @@ def test_patch_kernel_3x3(bnn, orc, shape):
         for n0 in (0, N - 1):
             assert np.array_equal(orc.bconv_images(case["x"], case["filt"], C, 1, 1, pad_mode, n0, 1), ref1[n0:n0 + 1])
         run_conv(bnn, orc, case, 0, pad_mode, ref=ref1)
+
+
+# 3x3 layers of 128, 256 and 512 channels whose pixels fill bands on all compute units: bands of every number of row tiles per wave, with none, one or
+# several tiles left over, with missing tiles (a wave past the band's end), K split over two groups of waves, several rounds; images smaller than
+# a row tile, images of many bands, odd sizes, ragged last rows.  (N, H, W, C, O)
+@pytest.mark.parametrize("pad_mode", [0, 1])
+@pytest.mark.parametrize("shape", [
+    (66, 13, 11, 256, 512), (53, 15, 16, 256, 512), (37, 18, 20, 256, 512), (7, 50, 51, 256, 512), (1, 160, 162, 256, 512), (900, 5, 7, 256, 256),
+    (80, 13, 15, 256, 576), (31, 13, 13, 512, 512), (24, 15, 17, 512, 512), (390, 5, 5, 512, 512), (12, 33, 34, 512, 512), (171, 14, 14, 512, 64),
+    (33, 24, 25, 128, 512), (16, 41, 41, 128, 512), (52, 31, 29, 128, 320), (1025, 6, 6, 128, 512)])
+def test_bands(bnn, orc, shape, pad_mode):
+    N, H, W, C, O = shape
+    assert bnn.bconv_kernel_name(N, H, W, C, O, 3, 1, 1, pad_mode=pad_mode) == "mfma_fp4_conv3x3_band_wg64"
+    case = wl.bconv_case(93, N, H, W, C, O, 3, 1, 1)
+    ref = orc.bconv(case["x"], case["filt"], C, 1, 1, pad_mode)
+    tau = case["tau"].copy()
+    tau[::7], tau[3::11] = -2 ** 31, 2 ** 31 - 1         # thresholds beyond every sum
+    bits = words(bnn.bconv_thr(to_dev(case["x"]), to_dev(case["filt"]), to_dev(tau), C, 1, 1, pad_mode))
+    assert np.array_equal(bits, orc.threshold_pack(ref, tau))

@@ -641,3 +641,24 @@ def test_conv_f32_split_exact_products(bnn, orc):
     _, y = bnn.conv_f32_split_thr(to_dev(x), to_dev(w), to_dev(np.zeros(3, np.float32)), 1, 1, want_f32=True)
     assert host(y)[0, 4, 4, 2] == np.float32(np.float64(x[0, 4, 4, 1]) * np.float64(w[2, 1, 1, 1]))
     assert np.array_equal(host(y), orc.conv_f32(x, w, 1, 1))
+
+
+# Residual chains whose second convolutions run in bands (3x3, 128 / 256 / 512 channels): a first residual taken from bits, blocked 16-bit sums in
+# and out, a 1x1 shortcut with and without its sum kept and with a source that fills no word pair (96 channels: what it multiplies beyond its width
+# is taken back), K split over two groups of waves; `banded`: the blocks whose second convolution is one.
+@pytest.mark.parametrize("pad_mode", [0, 1])
+@pytest.mark.parametrize("batch,hw,cin,blocks,banded", [
+    (85, 14, 256, ((256, 256, 1), (256, 256, 1), (256, 256, 1)), (0, 1, 2)),
+    (117, 14, 96, ((96, 256, 1), (256, 256, 1), (256, 512, 2)), (0, 1, 2)),
+    (100, 14, 256, ((256, 512, 2), (512, 512, 1), (512, 512, 1)), (0, 1, 2)),
+    (126, 7, 96, ((96, 512, 1), (512, 512, 1)), (0, 1)), (126, 7, 512, ((512, 512, 1), (512, 128, 1)), (0,)),
+    (191, 15, 96, ((96, 128, 1), (128, 128, 1), (128, 128, 1)), (0, 1, 2)), (150, 15, 128, ((128, 128, 1), (128, 128, 1)), (0, 1))])
+def test_block_chains_in_bands(bnn, orc, batch, hw, cin, blocks, banded, pad_mode):
+    size = hw
+    for b, (ci, co, st) in enumerate(blocks):
+        size = (size - 1) // st + 1
+        keep = b + 1 < len(blocks) and blocks[b + 1][0] == blocks[b + 1][1] and blocks[b + 1][2] == 1
+        shortcut = st != 1 or ci != co
+        kernel = bnn.bconv_kernel_name(batch, size, size, co, co, 3, 1, 1, pad_mode=pad_mode, shortcut=shortcut, residual=not shortcut, keep_sum=keep)
+        assert (kernel == "mfma_fp4_conv3x3_band_wg64") == (b in banded), (b, kernel)
+    test_block_chains_expanded_in_lds(bnn, orc, batch, hw, cin, blocks, pad_mode, None)
