@@ -177,6 +177,10 @@ int launch_mfma_conv_patch(const uint32_t* A, const uint32_t* B, const Geom& g, 
 // 3x3 stride-1 pad-1 convolutions of 128, 256 or 512 channels in: a workgroup per band of pixels and 64 channels, pixels expanded in LDS.
 bool mfma_conv_band_takes(const Geom& g, const Epi& e);
 int launch_mfma_conv_band(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
+// Small 3x3 convolutions of 128, 256 or 512 channels in: a workgroup per 32 x 32 outputs, a wave per tap.  pooled: asked for with 2x2-pooled bits beside
+// the full ones.
+bool mfma_conv_taps_takes(const Geom& g, const Epi& e, bool pooled);
+int launch_mfma_conv_taps(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 // Other windows and channel counts whose input patch, expanded to E2M1, fits LDS.
 int mfma_conv_xlds_tile(const Geom& g, const Epi& e);      // 0: not this kernel's
 const char* describe_mfma_conv_xlds(int tile);

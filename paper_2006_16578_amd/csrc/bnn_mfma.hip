@@ -54,6 +54,7 @@ int launch_mfma(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
     if (const int xt = mfma_conv_xlds_tile(g, e)) return launch_mfma_conv_xlds(xt, A, B, g, e, s);
     // (blocked 16-bit sums are implemented by the direct kernels only)
     if (!e.sums_tiled && staged_ok(g, tile)) return launch_mfma_conv_staged(A, B, g, e, s);
+    if (tile == 3 && mfma_conv_taps_takes(g, e, g.pool2 != 0)) return launch_mfma_conv_taps(A, B, g, e, s);
     if (!mfma::offsets_fit(g)) return BNN_ERR_UNSUPPORTED;
     const bool stream = mfma::streams_residual(g, e);
     switch (mfma::conv_load_words(g)) {
@@ -90,6 +91,7 @@ const char* describe_mfma(const Geom& g, bool int32_out, int flags) {
     if (const int xt = mfma_conv_xlds_tile(g, e))         // (its streamed form needs whole lines only)
         return with_suffix(describe_mfma_conv_xlds(xt), e.resid != nullptr && (e.ldc & 31) == 0 ? "_stream" : "");
     const char* suffix = pools ? "_pool2" : mfma::streams_residual(g, e) ? "_stream" : "";
+    if (tile == 3 && mfma_conv_taps_takes(g, e, pools)) return with_suffix("mfma_fp4_conv_taps_wg32x32", suffix);
     const bool st = !g.b_tiled && !e.sums_tiled && staged_ok(g, tile);
     switch (tile) {
         case 0: return g.conv ? with_suffix(st ? "mfma_fp4_conv_lds_wg256x128" : "mfma_fp4_conv_wg256x128", suffix)

@@ -316,3 +316,16 @@ def test_bands(bnn, orc, shape, pad_mode):
     tau[::7], tau[3::11] = -2 ** 31, 2 ** 31 - 1         # thresholds beyond every sum
     bits = words(bnn.bconv_thr(to_dev(case["x"]), to_dev(case["filt"]), to_dev(tau), C, 1, 1, pad_mode))
     assert np.array_equal(bits, orc.threshold_pack(ref, tau))
+
+
+# Small 3x3 layers of 128, 256 and 512 channels: a wave per tap.  Images smaller than the window, strides, paddings, ragged last rows and columns.
+@pytest.mark.parametrize("pad_mode", [0, 1])
+@pytest.mark.parametrize("shape", [(1, 1, 1, 128, 1, 1, 1), (3, 7, 5, 128, 70, 1, 1), (5, 9, 8, 128, 130, 2, 1), (2, 11, 13, 256, 64, 3, 2), (4, 14, 14, 256, 300, 1, 1),
+                                   (8, 8, 8, 512, 512, 1, 1), (1, 2, 2, 512, 33, 1, 1), (6, 16, 15, 512, 96, 2, 0)])
+def test_wave_per_tap(bnn, orc, shape, pad_mode):
+    N, H, W, C, O, st, pad = shape
+    assert bnn.bconv_kernel_name(N, H, W, C, O, 3, st, pad, pad_mode=pad_mode) == "mfma_fp4_conv_taps_wg32x32"
+    case = wl.bconv_case(94, N, H, W, C, O, 3, st, pad)
+    ref = orc.bconv(case["x"], case["filt"], C, st, pad, pad_mode)
+    bits = words(bnn.bconv_thr(to_dev(case["x"]), to_dev(case["filt"]), to_dev(case["tau"]), C, st, pad, pad_mode))
+    assert np.array_equal(bits, orc.threshold_pack(ref, case["tau"]))

@@ -662,3 +662,28 @@ def test_block_chains_in_bands(bnn, orc, batch, hw, cin, blocks, banded, pad_mod
         kernel = bnn.bconv_kernel_name(batch, size, size, co, co, 3, 1, 1, pad_mode=pad_mode, shortcut=shortcut, residual=not shortcut, keep_sum=keep)
         assert (kernel == "mfma_fp4_conv3x3_band_wg64") == (b in banded), (b, kernel)
     test_block_chains_expanded_in_lds(bnn, orc, batch, hw, cin, blocks, pad_mode, None)
+
+
+# Small 3x3 layers with a wave per tap: 2x2-pooled bits stored beside the full ones, and residual chains (first residual from bits, blocked 16-bit
+# sums in and out, a 1x1 shortcut on a tenth wave whose source fills no word pair).
+@pytest.mark.parametrize("batch,hw,chans", [(8, 16, (128, 256, 512)), (2, 20, (256, 500, 60)), (11, 8, (512, 512, 70))])
+def test_wave_per_tap_stores_pooled_bits(bnn, orc, batch, hw, chans):
+    kernels = []
+    for i, (cin, cout) in enumerate(zip(chans, chans[1:])):
+        size = hw >> i
+        kernels.append(bnn.bconv_kernel_name(batch, size, size, cin, cout, 3, 1, 1, pool2=True)[len("mfma_fp4_conv_"):])
+    assert "taps_wg32x32_pool2" in kernels
+    test_convolution_stores_pooled_bits(bnn, orc, batch, hw, chans, 2, kernels)
+
+
+@pytest.mark.parametrize("pad_mode", [0, 1])
+@pytest.mark.parametrize("batch,hw,cin,blocks", [
+    (3, 14, 96, ((96, 128, 1), (128, 128, 1), (128, 256, 2), (256, 256, 1))), (2, 9, 256, ((256, 256, 1), (256, 256, 1), (256, 512, 2), (512, 512, 1)))])
+def test_block_chains_wave_per_tap(bnn, orc, batch, hw, cin, blocks, pad_mode):
+    size = hw
+    for ci, co, st in blocks:
+        size = (size - 1) // st + 1
+        shortcut = st != 1 or ci != co
+        assert bnn.bconv_kernel_name(batch, size, size, co, co, 3, 1, 1, pad_mode=pad_mode, shortcut=shortcut, residual=not shortcut,
+                                     keep_sum=shortcut) == "mfma_fp4_conv_taps_wg32x32"
+    test_block_chains_expanded_in_lds(bnn, orc, batch, hw, cin, blocks, pad_mode, None)
