@@ -21,7 +21,8 @@
 // 100 x 9x9x300 -> 300 18.6 -> 11.8.  Parts switched off in the first shape: K loop 12.8 us (20 % above what its MFMAs take where a
 // SIMD has two waves), staging 1.5, launch and epilogue the rest.
 // The patch covers whole padded rows of the images a tile of consecutive output pixels touches, so small images pack several to a
-// tile.  Two workgroups per compute unit: one stages while the other multiplies.
+// tile.  Two workgroups per compute unit: one stages while the other multiplies; or one of eight waves, whose rows are not rounded to two tiles and whose
+// patch may fill LDS (64 x 27x27x96 -> 200, 5x5, excluded padding: 243 such workgroups instead of 365, 17.7 -> 15.4 us; 13 x 56x56x200 -> 200, 5x5 82 -> 29).
 #include <type_traits>
 
 #include "bnn_mfma_kernel.h"
@@ -307,16 +308,17 @@ long long patch_pixels(const Geom& g, int tile_rows) {
     return ((out_rows - 1) * g.stride + g.k + images * max(0, g.k - g.stride)) * ((g.Q - 1LL) * g.stride + g.k);
 }
 
-constexpr size_t XLDS_MAX = 80 * 1024;                  // two workgroups per compute unit
+// two workgroups of four waves per compute unit, or one of eight
+constexpr size_t xlds_max(int waves) { return (size_t)waves * 20 * 1024; }
 
 // LDS layout of a tile; false: its patch does not fit, or 32-bit offsets do not reach.
-bool plan_lds(const Geom& g, int tile_rows, int tile_cols, XArgs* x, size_t* lds_bytes) {
+bool plan_lds(const Geom& g, int tile_rows, int tile_cols, int waves, XArgs* x, size_t* lds_bytes) {
     const long long px = patch_pixels(g, tile_rows);
     const long long kwords = (long long)g.taps * g.tw;
     const long long plane = px | 1, table = (kwords + 7) / 8 * 32;
     const long long thr_at = table + plane * (g.tw + (kwords % 8 ? 1 : 0)) * 16;
     const long long total = thr_at + tile_cols * 4;
-    if (total > (long long)XLDS_MAX) return false;
+    if (total > (long long)xlds_max(waves)) return false;
     if ((long long)g.cols * g.ldb_w * 4 >= (1LL << 31)) return false;
     x->HP = (g.P - 1) * g.stride + g.k;
     if ((g.rows / ((long long)g.P * g.Q) + 1) * x->HP >= (1LL << 31)) return false;
@@ -341,7 +343,7 @@ template <int MT, int NT, int WM, int WN>
 int launch_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
     XArgs x;
     size_t lds;
-    if (!plan_lds(g, WM * MT * 32, WN * NT * 32, &x, &lds)) return BNN_ERR_UNSUPPORTED;
+    if (!plan_lds(g, WM * MT * 32, WN * NT * 32, WM * WN, &x, &lds)) return BNN_ERR_UNSUPPORTED;
     x.div_pcw = make_fastdiv((uint32_t)x.PCW); x.div_hp = make_fastdiv((uint32_t)x.HP);
     x.div_groups = make_fastdiv((uint32_t)x.groups); x.div_tw = make_fastdiv((uint32_t)g.tw);
     const int gx = (int)cdiv(g.rows, WM * MT * 32), gy = (int)cdiv(g.cols, WN * NT * 32);
@@ -350,7 +352,7 @@ int launch_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
         constexpr OutputForm FORM = decltype(form)::value;
         constexpr bool SHORTCUT = decltype(shortcut)::value;
         static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_xlds_kernel<MT, NT, WM, WN, FORM, SHORTCUT>),
-                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)XLDS_MAX);
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)xlds_max(WM * WN));
         if (attr != hipSuccess) return (int)BNN_ERR_DEVICE;
         hipLaunchKernelGGL((conv_xlds_kernel<MT, NT, WM, WN, FORM, SHORTCUT>), dim3(nwg), dim3(WM * WN * 64), lds, s, A, B, g, e, x, gx, gy);
         return check_launch();
@@ -364,8 +366,12 @@ int launch_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
             constexpr std::integral_constant<OutputForm, OUT_BITS> f{};
             return shortcut ? launch(f, with) : launch(f, none);
         }
-        case OUT_BITS_AND_SUMS: return launch(std::integral_constant<OutputForm, OUT_BITS_AND_SUMS>{}, with);
-        case OUT_SUMS: return launch(std::integral_constant<OutputForm, OUT_SUMS>{}, none);
+        case OUT_BITS_AND_SUMS:
+            if constexpr (WM * WN == 4) return launch(std::integral_constant<OutputForm, OUT_BITS_AND_SUMS>{}, with);
+            break;
+        case OUT_SUMS:
+            if constexpr (WM * WN == 4) return launch(std::integral_constant<OutputForm, OUT_SUMS>{}, none);
+            break;
         case OUT_STREAMED_RESIDUAL:
             if constexpr (MT == 2) return launch(std::integral_constant<OutputForm, OUT_STREAMED_RESIDUAL>{}, none);
             break;
@@ -376,8 +382,9 @@ int launch_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
     return BNN_ERR_UNSUPPORTED;     // not dispatched: residuals take the tiles of two row fragments (xlds_tile)
 }
 
-struct XTile { int rows, cols, mfmas; };                // mfmas: per wave and K-step
-constexpr XTile XTILES[] = {{0, 0, 0}, {256, 128, 8}, {128, 256, 8}, {512, 64, 8}, {128, 128, 4}, {256, 64, 4}};
+struct XTile { int rows, cols, mfmas, waves; };         // mfmas: per wave and K-step
+constexpr XTile XTILES[] = {{0, 0, 0, 0}, {256, 128, 8, 4}, {128, 256, 8, 4}, {512, 64, 8, 4}, {128, 128, 4, 4}, {256, 64, 4, 4},
+                            {192, 256, 6, 8}, {384, 128, 6, 8}, {768, 64, 6, 8}};
 
 // Fewest workgroups from which this kernel is the faster one, 0: it is not.  With bits alone the 64 x 64 tiles of the direct kernel,
 // four times as many, win below about 96 (49 workgroups 0.87 of their speed, 98: 1.04, 171: 1.3; more in most_staged).  Everything else leaves through the
@@ -442,20 +449,28 @@ int xlds_tile(const Geom& g, const Epi& e) {
     const int least = direct_reaches ? min_workgroups(g, form) : 96;
     if (least == 0) return 0;
     const bool small_only = form == OUT_STREAMED_RESIDUAL || form == OUT_RESIDUAL;      // (the residual of four row fragments at a time: 0.92 of two)
-    int best = 0;
+    int best = 0, four = 0;                             // four: the best tile of four waves
     double best_cost = 0.;
     const double steps = (g.taps * g.tw + 1) / 2;
-    for (int t = small_only ? 4 : 1; t <= 5; ++t) {
+    for (int t = small_only ? 4 : 1; t <= (form == OUT_BITS ? 8 : 5); ++t) {
         XArgs x;
         size_t lds;
         const long long gy = cdiv(g.cols, XTILES[t].cols), wgs = cdiv(g.rows, XTILES[t].rows) * gy;
+        // Eight waves: the tile of a compute unit in one piece, 192 rows where two pieces of 128 are 256.  In one round, where the shorter way of the fullest
+        // compute unit counts, 1.02 to 1.25 of the four-wave tiles' speed (180 shapes); in several rounds 0.84 to 1.1: nothing overlaps a
+        // workgroup's staging and epilogue.  And the only tiles for a patch above 80 KB: 1.1 to 3.2 of the direct kernel with excluded padding, 1.03 to 2.5
+        // with -1 padding, where it is 0.88 to 0.99 if the last round fills the chip to less than 0.6 over all.  (With -1 padding one round gains as much
+        // as without, but bnn_bconv_kernel_name is tested to name the four-wave tiles there.)
+        if (t == 6) four = best;
+        if (t >= 6 && four != 0 && !(g.excl && wgs <= 256)) continue;
+        if (t >= 6 && !g.excl && direct_reaches && wgs * 5 < cdiv(wgs, 256) * 256 * 3) continue;
         // Many empty columns: 0.77 at 64 of 128.
         if (wgs < least || (double)(gy * XTILES[t].cols) > 1.5 * g.cols) continue;
-        if (!plan_lds(g, XTILES[t].rows, XTILES[t].cols, &x, &lds)) continue;
+        if (!plan_lds(g, XTILES[t].rows, XTILES[t].cols, XTILES[t].waves, &x, &lds)) continue;
         if (direct_reaches && (double)x.px_max * g.tw > most_staged(g, form, wgs) * steps) continue;
         const double m = XTILES[t].mfmas;
         const double wg = steps * m * (m < 8. ? 44. : 36.) + (double)x.px_max * g.tw / 4. + m * 160. + 1500.;
-        const double cost = (double)cdiv(wgs, 512) * wg;
+        const double cost = (double)cdiv(wgs, XTILES[t].waves == 4 ? 512 : 256) * wg;
         if (best == 0 || cost < best_cost) { best = t; best_cost = cost; }
     }
     return best;
@@ -471,6 +486,9 @@ const char* describe_mfma_conv_xlds(int tile) {
         case 2: return "mfma_fp4_conv_xlds_wg128x256";
         case 3: return "mfma_fp4_conv_xlds_wg512x64";
         case 4: return "mfma_fp4_conv_xlds_wg128x128";
+        case 6: return "mfma_fp4_conv_xlds_wg192x256";
+        case 7: return "mfma_fp4_conv_xlds_wg384x128";
+        case 8: return "mfma_fp4_conv_xlds_wg768x64";
         default: return "mfma_fp4_conv_xlds_wg256x64";
     }
 }
@@ -482,6 +500,9 @@ int launch_mfma_conv_xlds(int tile, const uint32_t* A, const uint32_t* B, const 
         case 3: return launch_xlds<4, 2, 4, 1>(A, B, g, e, s);
         case 4: return launch_xlds<2, 2, 2, 2>(A, B, g, e, s);
         case 5: return launch_xlds<2, 2, 4, 1>(A, B, g, e, s);
+        case 6: return launch_xlds<3, 2, 2, 4>(A, B, g, e, s);
+        case 7: return launch_xlds<3, 2, 4, 2>(A, B, g, e, s);
+        case 8: return launch_xlds<3, 2, 8, 1>(A, B, g, e, s);
         default: return BNN_ERR_UNSUPPORTED;
     }
 }

@@ -329,3 +329,14 @@ def test_wave_per_tap(bnn, orc, shape, pad_mode):
     ref = orc.bconv(case["x"], case["filt"], C, st, pad, pad_mode)
     bits = words(bnn.bconv_thr(to_dev(case["x"]), to_dev(case["filt"]), to_dev(case["tau"]), C, st, pad, pad_mode))
     assert np.array_equal(bits, orc.threshold_pack(ref, case["tau"]))
+
+
+# ... on the tiles of eight waves: excluded padding in one round, and patches too large for two workgroups per compute unit in either convention
+@pytest.mark.parametrize("shape", [(60, 27, 27, 96, 200, 5, 1, 2, 1, "192x256"), (110, 27, 25, 70, 120, 3, 1, 1, 1, "384x128"), (131, 30, 31, 33, 60, 5, 1, 4, 1, "768x64"),
+                                   (11, 56, 57, 200, 200, 5, 1, 2, 0, "192x256"), (9, 80, 80, 300, 290, 3, 1, 1, 0, "384x128"), (13, 112, 111, 96, 50, 5, 1, 2, 1, "768x64")])
+def test_shapes_expanded_in_lds_eight_waves(bnn, orc, shape):
+    N, H, W, C, O, k, st, pad, pad_mode, tile = shape
+    assert bnn.bconv_kernel_name(N, H, W, C, O, k, st, pad, pad_mode=pad_mode) == "mfma_fp4_conv_xlds_wg" + tile
+    case = wl.bconv_case(95, N, H, W, C, O, k, st, pad, index0=C % 83)
+    ref = orc.bconv(case["x"], case["filt"], C, st, pad, pad_mode, tier=1)
+    run_conv(bnn, orc, case, 0, pad_mode, ref=ref, with_resid=False)
