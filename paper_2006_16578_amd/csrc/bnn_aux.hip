@@ -541,36 +541,36 @@ __global__ __launch_bounds__(256) void head_kernel(const uint32_t* __restrict__ 
 
 // The same head as two kernels, for callers that give it a place for the pooled sums: the pooling runs once per
 // image instead of once per (image group, output group) workgroup, and the FC runs on the matrix cores.
-// Pooling: four adjacent lanes share one packed word (32 channels) of one image, each counting every fourth
-// position (set bits per channel, 4 channels at a time in the bytes of one register: HW <= 255); the four partial
-// counts meet through lane exchanges, and lane t of the four writes channels q + 8 t.
+// Pooling: sixteen lanes share one packed word (32 channels) of one image, each counting every sixteenth position (set bits per
+// channel, 4 channels at a time in the bytes of one register: HW <= 255); four neighbouring lanes hold four neighbouring words. The partial counts
+// meet through lane exchanges, and the first lane of four t writes channels q + 8 t.  (Sixteen and not four: 256 images of 7x7x512 are 256 workgroups
+// instead of 64 and one memory round trip; 5.8 -> 4.9 us under the profiler.)
 __global__ __launch_bounds__(256) void head_pool_kernel(const uint32_t* __restrict__ bits, int32_t* __restrict__ pooled_out,
                                                         int N, int HW, int C) {
     const int cw = (C + 31) / 32;
-    const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long item = idx >> 2;
-    const int part = (int)(idx & 3);
-    const bool live = item < (long long)N * cw;            // whole groups of four lanes are live or not
+    const long long wave = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const int lane = threadIdx.x & 63, part = lane >> 2;
+    const long long item = wave * 4 + (lane & 3);
+    const bool live = item < (long long)N * cw;            // the sixteen lanes of a word are live or not
     const int n = live ? (int)(item / cw) : 0, wi = live ? (int)(item - (long long)n * cw) : 0;
     uint32_t cnt[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) cnt[q] = 0u;
     const uint32_t* b = bits + (long long)n * HW * cw + wi;
-    for (int i0 = part; i0 < HW; i0 += 64) {               // 16 independent loads in flight
-        uint32_t v[16];
+    for (int i0 = part; i0 < HW; i0 += 64) {               // four independent loads in flight
+        uint32_t v[4];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) v[u] = (live && i0 + 4 * u < HW) ? b[(long long)(i0 + 4 * u) * cw] : 0u;
+        for (int u = 0; u < 4; ++u) v[u] = (live && i0 + 16 * u < HW) ? b[(long long)(i0 + 16 * u) * cw] : 0u;
 #pragma unroll
-        for (int u = 0; u < 16; ++u)
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
             for (int q = 0; q < 8; ++q) cnt[q] += (v[u] >> q) & 0x01010101u;
     }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        cnt[q] += (uint32_t)__shfl_xor((int)cnt[q], 1);
-        cnt[q] += (uint32_t)__shfl_xor((int)cnt[q], 2);
-    }
-    if (!live) return;
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+        for (int m = 4; m < 64; m *= 2) cnt[q] += (uint32_t)__shfl_xor((int)cnt[q], m);
+    if (!live || part >= 4) return;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         const int c = wi * 32 + q + 8 * part;
@@ -581,51 +581,90 @@ __global__ __launch_bounds__(256) void head_pool_kernel(const uint32_t* __restri
 // FC on the pooled sums with the fp32 matrix instruction (exact fp32 products, fp32 accumulation): a workgroup
 // computes 32 images x 32 outputs, its eight waves taking every eighth step of 8 channels; lane l holds image /
 // output l % 32 and channels 4 * (l / 32) .. + 3 of the step, one MFMA per channel pair.  The eight partial tiles meet
-// in LDS; the division by HW is applied once, to the finished sum.  VEC: C is a multiple of 4 (16-byte loads).
-// (Eight waves: at 512 channels every wave has all of its loads in flight at once -- one memory round trip; a lane's
-// loads go to 32 different rows, so what a wave can have in flight is what bounds this kernel.)
+// in LDS; the division by HW is applied once, to the finished sum.
+// VEC: C is a multiple of 4.  Both operands then pass through LDS, 512 channels at a time: read as operands, every lane in another row than its
+// neighbours, the address side took about a cycle for each lane (16 loads of 1 KB per wave, eight waves: 4 us); read by rows they are whole lines.
+// 256 x 512 -> 1000: 9.9 -> 8.4 us under the profiler, both kernels of the head 12.1 -> 10.0 (graph replays), of one image 10.1 -> 8.4.  The same sums
+// in the same order.  Left: 2 us of fp32 MFMAs, 128 KB of operands per workgroup, the launches.
 typedef float fc_v16f __attribute__((ext_vector_type(16)));
-constexpr int FC_STEPS = 8;                     // steps (of 8 channels) a wave requests before it multiplies them
+constexpr int FC_STEPS = 8;                     // steps (of 8 channels) of a wave per pass
 constexpr int FC_WAVES = 8;
+constexpr int FC_CHANNELS = 8 * FC_STEPS * FC_WAVES;
+// floats from row to row in LDS: an odd number of 16-byte units (the rows of a fragment read lie on different banks)
+__host__ __device__ constexpr int fc_pitch(int C) { return (C < FC_CHANNELS ? (C + 7) / 8 * 8 : FC_CHANNELS) + 4; }
 
 template <bool VEC>
 __global__ __launch_bounds__(64 * FC_WAVES) void head_fc_kernel(const int32_t* __restrict__ pooled, const float* __restrict__ w,
                                                                 float* __restrict__ y, int N, int HW, int C, int J) {
-    __shared__ float red[FC_WAVES][16 * 64];
+    extern __shared__ float4 fc_lds[];          // VEC: 32 rows of pooled sums, 32 of weights; then the partial tiles
+    float* const lds = reinterpret_cast<float*>(fc_lds);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, half = lane >> 5;
     const int n0 = blockIdx.x * 32, j0 = blockIdx.y * 32;
-    const bool nok = n0 + l32 < N, jok = j0 + l32 < J;
-    const int32_t* prow = pooled + (long long)min(n0 + l32, N - 1) * C;
-    const float* wrow = w + (long long)min(j0 + l32, J - 1) * C;
     fc_v16f acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    const int steps = (C + 7) / 8;
-    for (int s0 = wave; s0 < steps; s0 += FC_WAVES * FC_STEPS) {
-        float a[FC_STEPS][4], b[FC_STEPS][4];
+    if constexpr (VEC) {
+        const int pitch = fc_pitch(C), units = (pitch - 4) / 4;
+        float* const pl = lds, * const wl = lds + 32 * pitch;
+        constexpr int PER = 32 / FC_WAVES, COLS = FC_CHANNELS / 4 / 64;
+        for (int c0 = 0; c0 < C; c0 += FC_CHANNELS) {
+            int4 pv[PER][COLS];
+            float4 wv[PER][COLS];
 #pragma unroll
-        for (int u = 0; u < FC_STEPS; ++u) {
-            const int c = 8 * (s0 + FC_WAVES * u) + 4 * half;
-            if (VEC) {
-                const bool ok = c < C;                      // C % 4 == 0: the four channels are in range together
-                const int4 pa = (ok && nok) ? *reinterpret_cast<const int4*>(prow + c) : make_int4(0, 0, 0, 0);
-                const float4 wb = (ok && jok) ? *reinterpret_cast<const float4*>(wrow + c) : make_float4(0.f, 0.f, 0.f, 0.f);
-                a[u][0] = (float)pa.x; a[u][1] = (float)pa.y; a[u][2] = (float)pa.z; a[u][3] = (float)pa.w;
-                b[u][0] = wb.x; b[u][1] = wb.y; b[u][2] = wb.z; b[u][3] = wb.w;
-            } else {
+            for (int i = 0; i < PER; ++i)
+#pragma unroll
+                for (int k = 0; k < COLS; ++k) {            // (past the end of a row, a matrix: zeros)
+                    const int row = PER * wave + i, c = c0 + 4 * (lane + 64 * k);
+                    pv[i][k] = (c < C && n0 + row < N) ? *reinterpret_cast<const int4*>(pooled + (long long)(n0 + row) * C + c) : make_int4(0, 0, 0, 0);
+                    wv[i][k] = (c < C && j0 + row < J) ? *reinterpret_cast<const float4*>(w + (long long)(j0 + row) * C + c) : make_float4(0.f, 0.f, 0.f, 0.f);
+                }
+            if (c0 > 0) __syncthreads();
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+#pragma unroll
+                for (int k = 0; k < COLS; ++k)
+                    if (lane + 64 * k < units) {
+                        const int at = (PER * wave + i) * pitch + 4 * (lane + 64 * k);
+                        *reinterpret_cast<float4*>(pl + at) = make_float4((float)pv[i][k].x, (float)pv[i][k].y, (float)pv[i][k].z, (float)pv[i][k].w);
+                        *reinterpret_cast<float4*>(wl + at) = wv[i][k];
+                    }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < FC_STEPS; ++u) {
+                const int c = 8 * (wave + FC_WAVES * u);
+                if (c >= 4 * units) break;                  // uniform per wave
+                const float4 a = *reinterpret_cast<const float4*>(pl + l32 * pitch + c + 4 * half), b = *reinterpret_cast<const float4*>(wl + l32 * pitch + c + 4 * half);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
+            }
+        }
+        __syncthreads();
+    } else {
+        const int steps = (C + 7) / 8;
+        const bool nok = n0 + l32 < N, jok = j0 + l32 < J;
+        const int32_t* prow = pooled + (long long)min(n0 + l32, N - 1) * C;
+        const float* wrow = w + (long long)min(j0 + l32, J - 1) * C;
+        for (int s0 = wave; s0 < steps; s0 += FC_WAVES * FC_STEPS) {
+            float a[FC_STEPS][4], b[FC_STEPS][4];
+#pragma unroll
+            for (int u = 0; u < FC_STEPS; ++u) {
+                const int c = 8 * (s0 + FC_WAVES * u) + 4 * half;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     a[u][q] = (c + q < C && nok) ? (float)prow[c + q] : 0.f;
                     b[u][q] = (c + q < C && jok) ? wrow[c + q] : 0.f;
                 }
             }
+#pragma unroll
+            for (int u = 0; u < FC_STEPS; ++u)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][q], b[u][q], acc, 0, 0, 0);
         }
-#pragma unroll
-        for (int u = 0; u < FC_STEPS; ++u)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][q], b[u][q], acc, 0, 0, 0);
     }
+    float (*const red)[16 * 64] = reinterpret_cast<float (*)[16 * 64]>(lds);
 #pragma unroll
     for (int r = 0; r < 16; ++r) red[wave][r * 64 + lane] = acc[r];
     __syncthreads();
@@ -734,12 +773,19 @@ int launch_head_f32(const uint32_t* bits, const float* w, float* y, int32_t* poo
                     hipStream_t s) {
     if (C > HEAD_MAXC || HW > 255) return BNN_ERR_UNSUPPORTED;
     if (pooled != nullptr) {
-        const long long lanes = 4LL * N * ((C + 31) / 32);
+        const long long lanes = cdiv((long long)N * ((C + 31) / 32), 4) * 64;     // a wave for four words
         hipLaunchKernelGGL(head_pool_kernel, dim3((unsigned)cdiv(lanes, 256)), dim3(256), 0, s, bits, pooled, N, HW, C);
         const dim3 grid((unsigned)cdiv(N, 32), (unsigned)cdiv(J, 32));
         const bool vec = C % 4 == 0 && ((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(pooled)) & 15u) == 0;
-        if (vec) hipLaunchKernelGGL(head_fc_kernel<true>, grid, dim3(64 * FC_WAVES), 0, s, pooled, w, y, N, HW, C, J);
-        else hipLaunchKernelGGL(head_fc_kernel<false>, grid, dim3(64 * FC_WAVES), 0, s, pooled, w, y, N, HW, C, J);
+        constexpr size_t tiles = (size_t)FC_WAVES * 16 * 64 * sizeof(float);
+        if (vec) {
+            static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&head_fc_kernel<true>),
+                                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (attr != hipSuccess) return BNN_ERR_DEVICE;
+            const size_t operands = (size_t)64 * fc_pitch(C) * sizeof(float);
+            hipLaunchKernelGGL(head_fc_kernel<true>, grid, dim3(64 * FC_WAVES), operands > tiles ? operands : tiles, s, pooled, w, y, N, HW, C, J);
+        } else
+            hipLaunchKernelGGL(head_fc_kernel<false>, grid, dim3(64 * FC_WAVES), tiles, s, pooled, w, y, N, HW, C, J);
         return check_launch();
     }
     const size_t lds_bytes = (size_t)2 * C * HEAD_LD * sizeof(float);
