@@ -102,16 +102,107 @@ __global__ __launch_bounds__(64 * WAVES) void mfma_skinny_kernel(const uint32_t*
     }
 }
 
+// At most 16 rows and few columns: 16 columns to a workgroup (v_mfma_f32_16x16x128_f8f6f4, the weights as row operand), twice as many workgroups, and
+// a load takes 64 neighbouring bytes of 16 rows instead of 32 of 32 (the address side works line by line: of the 4.8 us of 8 x 1024 x 8192 two were its).
+// A lane ends up with four channels of one row of A.
+// Measured (graph replays of bits, 32 columns -> this one): 8 x 1024 x 8192 4.84 -> 3.85 us, 8 x 1024 x 1024 3.34 -> 2.93, 8 x 10 x 1024 3.20 -> 2.92, 16 x 4000 x 4096
+// 4.09 -> 3.47, 4 x 4000 x 25088 8.06 -> 5.55, 8 x 64 x 16384 6.42 -> 4.58 (int32: 6.57 -> 4.32).
+typedef float v4f __attribute__((ext_vector_type(4)));
+constexpr int WAVES16 = 8;
+
+__global__ __launch_bounds__(64 * WAVES16) void mfma_skinny16_kernel(const uint32_t* __restrict__ A, const uint32_t* __restrict__ B, Geom g, Epi e) {
+    __shared__ float4 part[WAVES16][64];
+    const int lane = threadIdx.x & 63, l16 = lane & 15, grp = lane >> 4;
+    const int wave = threadIdx.x >> 6;
+    const int n0 = (int)blockIdx.x * 16, rows = (int)g.rows;
+
+    uint32_t c2;
+    asm volatile("v_mov_b32 %0, 0x22222222" : "=v"(c2));
+    const uint32_t* ap = A + (long long)min(l16, rows - 1) * g.lda_w;
+    const uint32_t* bp = B + (long long)min(n0 + l16, g.cols - 1) * g.ldb_w;
+
+    // chunk c: words 16 c + 4 grp .. + 3 of a row; tw is a multiple of 4, groups past the row's end are zero bits
+    const int T = (g.tw + 15) / 16;
+    const int mine = (T - wave + WAVES16 - 1) / WAVES16;
+    uint4 ra[DEPTH], rb[DEPTH];
+    uint32_t keep[DEPTH];
+    auto request = [&](int buf, int t) {
+        if (t < mine) {
+            const int wo = (wave + WAVES16 * t) * 16 + 4 * grp;
+            const bool ok = wo < g.tw;
+            rb[buf] = *reinterpret_cast<const uint4*>(bp + (ok ? wo : 0));
+            ra[buf] = *reinterpret_cast<const uint4*>(ap + (ok ? wo : 0));
+            keep[buf] = ok ? 0xFFFFFFFFu : 0u;
+        }
+    };
+    v4f acc = {0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](int buf) {
+        const uint32_t km = keep[buf];
+        const uint32_t aw[4] = {ra[buf].x & km, ra[buf].y & km, ra[buf].z & km, ra[buf].w & km};
+        const uint32_t bw[4] = {rb[buf].x & km, rb[buf].y & km, rb[buf].z & km, rb[buf].w & km};
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(mfma::expand_fp4(bw[v], c2), mfma::expand_fp4(aw[v], c2), acc, 4, 4, 0, 0, 0, 0);
+    };
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) request(d, d);
+    int thr[4] = {0, 0, 0, 0};                          // behind the operands, ahead of the barrier
+    if (e.bits != nullptr)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) thr[r] = e.thr[min(n0 + 4 * grp + r, g.cols - 1)];
+    for (int t = 0; t < mine; t += DEPTH) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            if (t + d < mine) multiply(d);
+            request(d, t + d + DEPTH);
+        }
+    }
+    part[wave][lane] = make_float4(acc[0], acc[1], acc[2], acc[3]);
+    __syncthreads();
+    if (wave != 0) return;
+    float4 sum = part[0][lane];                         // exact: whole numbers below 2^24
+#pragma unroll
+    for (int w = 1; w < WAVES16; ++w) {
+        const float4 v = part[w][lane];
+        sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
+    }
+    const int corr = T * 512 - g.bits_tap;              // positions past K: 0 bits in both operands (+1 each)
+    const int v[4] = {(int)sum.x - corr, (int)sum.y - corr, (int)sum.z - corr, (int)sum.w - corr};
+    const int ch = n0 + 4 * grp;
+    if (e.out != nullptr && l16 < rows)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (ch + r < g.cols) e.out[(long long)l16 * e.ldc + ch + r] = e.out_f32 ? __float_as_int((float)v[r]) : v[r];
+    if (e.bits != nullptr) {                            // uniform: the four groups of a row meet in a half-word
+        uint32_t b = 0u;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) b |= (ch + r < g.cols && v[r] >= thr[r]) ? 1u << (4 * grp + r) : 0u;
+        b |= (uint32_t)__shfl_xor((int)b, 16);
+        b |= (uint32_t)__shfl_xor((int)b, 32);
+        if (grp == 0 && l16 < rows && (int)blockIdx.x < 2 * e.ldbits_w)
+            reinterpret_cast<uint16_t*>(e.bits)[2LL * l16 * e.ldbits_w + blockIdx.x] = (uint16_t)b;
+    }
+}
+
+// Below 256 such workgroups, one per compute unit.  (From 4096 columns on the kernel above has 128 or more of its own; that 8 x 4096 x 4096 is its is
+// tested behaviour of bnn_bmm_kernel_name.)
+bool takes16(const Geom& g) { return g.rows <= 16 && g.cols < 4096; }
+
 }  // namespace
 
 bool mfma_skinny_takes(const Geom& g) { return !g.conv && !g.b_tiled && g.rows <= 128; }
 
 const char* describe_mfma_skinny(const Geom& g) {
+    if (takes16(g)) return "mfma_fp4_bmm_skinny_m16";
     return g.rows <= 32 ? "mfma_fp4_bmm_skinny_m32" : g.rows <= 64 ? "mfma_fp4_bmm_skinny_m64" : "mfma_fp4_bmm_skinny_m128";
 }
 
 int launch_mfma_skinny(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
     const int col_span = (e.bits != nullptr) ? max(g.cols, e.ldbits_w * 32) : g.cols;
+    if (takes16(g) && e.resid == nullptr && e.out16 == nullptr) {
+        hipLaunchKernelGGL(mfma_skinny16_kernel, dim3((unsigned)cdiv(col_span, 16)), dim3(64 * WAVES16), 0, s, A, B, g, e);
+        return check_launch();
+    }
     const dim3 grid((unsigned)cdiv(col_span, 32));
     if (g.rows <= 32) hipLaunchKernelGGL((mfma_skinny_kernel<1, 8>), grid, dim3(64 * 8), 0, s, A, B, g, e);
     else if (g.rows <= 64) hipLaunchKernelGGL((mfma_skinny_kernel<2, 4>), grid, dim3(64 * 4), 0, s, A, B, g, e);

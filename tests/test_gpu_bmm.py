@@ -367,3 +367,25 @@ def test_random_shapes_all_paths(bnn, orc, seed):
             assert np.array_equal(host(bnn.bmm(to_dev(A), to_dev(B), K, path=path)), ref)
             bits = words(bnn.bmm_thr(to_dev(A), to_dev(B), to_dev(tau), K, path=path))
             assert np.array_equal(bits, orc.threshold_pack(ref, tau, ldb_w=bits.shape[1]))
+
+
+# At most 16 rows, fewer than 4096 columns: 16 columns to a workgroup.  Ragged columns (half-words of the last output word, words of zeros behind it), K off
+# every group and chunk, one and several rounds per wave, thresholds beyond every sum.
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (1, 16, 128), (3, 17, 129), (8, 100, 511), (15, 33, 513), (16, 48, 4096), (16, 1000, 4100), (8, 10, 16384), (7, 4095, 700),
+                                   (2, 30, 66000)])
+def test_skinny_16_rows(bnn, orc, M, N, K):
+    assert bnn.bmm_kernel_name(M, N, K) == "mfma_fp4_bmm_skinny_m16"
+    rng = np.random.default_rng(M + N + K)
+    ld = bnn.round_up(bnn.nwords(K), 4)
+    A, B = (np.zeros((r, ld), np.uint32) for r in (M, N))
+    A[:, :bnn.nwords(K)], B[:, :bnn.nwords(K)] = wl.random_bits(rng, (M,), K), wl.random_bits(rng, (N,), K)
+    tau = rng.integers(-60, 61, size=N).astype(np.int32)
+    tau[::7], tau[3::5] = -2 ** 31, 2 ** 31 - 1
+    pm = lambda X: np.unpackbits(X.view(np.uint8), axis=1, bitorder="little")[:, :K].astype(np.float64) * 2 - 1
+    ref = (pm(A) @ pm(B).T).astype(np.int32)            # exact: whole numbers below 2^53
+    assert np.array_equal(host(bnn.bmm(to_dev(A), to_dev(B), K)), ref)
+    bits = words(bnn.bmm_thr(to_dev(A), to_dev(B), to_dev(tau), K))
+    want = np.zeros_like(bits)
+    packed = orc.threshold_pack(ref.reshape(1, 1, M, N), tau).reshape(M, -1)
+    want[:, :packed.shape[1]] = packed
+    assert np.array_equal(bits, want)
