@@ -724,13 +724,14 @@ int forward_impl(bnn_net* net, const void* input, void* output, int batch, char*
         const bnn_net::Layer& L = net->layers[i];
         uint32_t* obits = reinterpret_cast<uint32_t*>(ws + L.bits_off);
         int rc = BNN_OK;
-        if (i == 0 && pc == nullptr && path != BNN_PATH_VALU) {
+        if (i == 0 && pc == nullptr && (path == BNN_PATH_AUTO || path == BNN_PATH_MFMA)) {      // (dispatch() refuses other paths)
             FcChain ch = {};
             const int run = fc_chain_plan(net, input, output, batch, ws, &ch);
-            if (run > 0) {
+            if (run > 0) {      // refuses what the layers one by one would, in their order
                 const bnn_net::Layer& last = net->layers[run - 1];
+                if (L.kind == bnn_net::IN_BITS && !aligned16(input)) return BNN_ERR_ALIGNMENT;
                 if (last.t0 == nullptr && !output) return BNN_ERR_INVALID_ARG;
-                if ((last.t0 == nullptr && !aligned16(output)) || (L.kind == bnn_net::IN_BITS && !aligned16(input))) return BNN_ERR_ALIGNMENT;
+                if (last.t0 == nullptr && !aligned16(output)) return BNN_ERR_ALIGNMENT;
                 rc = launch_fc_chain(ch, static_cast<hipStream_t>(stream));
                 if (rc != BNN_OK) return rc;
                 cur = reinterpret_cast<uint32_t*>(ws + last.bits_off); curC = last.C; cur_ld = last.words_per_row;

@@ -107,6 +107,30 @@ def test_net_workspace_plan():
     assert big >= 2 * 64 * 8 * 8 * 64 * 2 + 2 * 64 * 8 * 8 * 8
 
 
+def test_fc_run_refuses_what_its_layers_refuse():
+    # an unknown path and a misaligned input (a missing output beside it) of a network whose fully-connected layers go as one launch: the layers' own answers,
+    # before anything is launched
+    import paper_2006_16578_amd as b
+    lib = b.load()
+    dummy = ctypes.c_void_p(256)
+
+    def forward(dims, inp, out, path):
+        net, ws = ctypes.c_void_p(), ctypes.c_size_t()
+        assert lib.bnn_net_create(ctypes.byref(net)) == 0 and lib.bnn_net_input_bits(net, dims[0]) == 0
+        for i, (k, n) in enumerate(zip(dims, dims[1:])):
+            assert lib.bnn_net_add_fc(net, dummy, dummy if i + 2 < len(dims) else None, k, n) == 0
+        assert lib.bnn_net_workspace_bytes(net, 8, ctypes.byref(ws)) == 0
+        rc = lib.bnn_net_forward(net, ctypes.c_void_p(inp), ctypes.c_void_p(out), 8, ctypes.c_void_p(4096), ws, path, None)
+        assert lib.bnn_net_destroy(net) == 0
+        return rc
+
+    for dims in ((256, 128, 10), (256, 128, 64, 10)):
+        for path in (-1, 3, 7):
+            assert forward(dims, 256, 256, path) == -1
+        for path in (b.PATH_AUTO, b.PATH_MFMA):
+            assert forward(dims, 264, 256, path) == -2 and forward(dims, 264, 0, path) == -2
+
+
 def test_lds_expanded_convolutions_by_output():
     # bits alone go to that kernel from 96 workgroups; sums and residuals leave through a slower epilogue and need more workgroups or a longer K
     import paper_2006_16578_amd as b
