@@ -582,20 +582,23 @@ __global__ __launch_bounds__(256) void head_pool_kernel(const uint32_t* __restri
 // computes 32 images x 32 outputs, its eight waves taking every eighth step of 8 channels; lane l holds image /
 // output l % 32 and channels 4 * (l / 32) .. + 3 of the step, one MFMA per channel pair.  The eight partial tiles meet
 // in LDS; the division by HW is applied once, to the finished sum.
-// VEC: C is a multiple of 4.  Both operands then pass through LDS, 512 channels at a time: read as operands, every lane in another row than its
+// VEC: C is a multiple of 4.  Both operands then pass through LDS, 64 * FC_STEPS channels at a time: read as operands, every lane in another row than its
 // neighbours, the address side took about a cycle for each lane (16 loads of 1 KB per wave, eight waves: 4 us); read by rows they are whole lines.
 // 256 x 512 -> 1000: 9.9 -> 8.4 us under the profiler, both kernels of the head 12.1 -> 10.0 (graph replays), of one image 10.1 -> 8.4.  The same sums
 // in the same order.  Left: 2 us of fp32 MFMAs, 128 KB of operands per workgroup, the launches.
+// FC_STEPS: steps (of 8 channels) of a wave per pass.  8 while there is a workgroup per compute unit at most (one memory round trip up to 512 channels); beyond that
+// 4, 66 KB instead of 132: two workgroups of a compute unit, one loads while the other multiplies.  The order of the sums is the same.  Under the
+// profiler, 32 operands at a time without LDS / 8 steps / 4 steps: 257 x 512 -> 1000 13.3 / 11.8 / 10.1 us, 4096 x 512 -> 1000 91 / 86 / 69, 32768 x 512 -> 10
+// 20.6 / 25.2 / 19.7, 1024 x 1024 -> 1000 46 / 38 / 31; 256 x 512 -> 1000 8.3 / 7.3 / 7.6, 256 x 1024 -> 1000 13.4 / 11.7 / 12.2.
 typedef float fc_v16f __attribute__((ext_vector_type(16)));
-constexpr int FC_STEPS = 8;                     // steps (of 8 channels) of a wave per pass
 constexpr int FC_WAVES = 8;
-constexpr int FC_CHANNELS = 8 * FC_STEPS * FC_WAVES;
 // floats from row to row in LDS: an odd number of 16-byte units (the rows of a fragment read lie on different banks)
-__host__ __device__ constexpr int fc_pitch(int C) { return (C < FC_CHANNELS ? (C + 7) / 8 * 8 : FC_CHANNELS) + 4; }
+__host__ __device__ constexpr int fc_pitch(int C, int channels) { return (C < channels ? (C + 7) / 8 * 8 : channels) + 4; }
 
-template <bool VEC>
+template <bool VEC, int FC_STEPS>
 __global__ __launch_bounds__(64 * FC_WAVES) void head_fc_kernel(const int32_t* __restrict__ pooled, const float* __restrict__ w,
                                                                 float* __restrict__ y, int N, int HW, int C, int J) {
+    constexpr int FC_CHANNELS = 8 * FC_STEPS * FC_WAVES;
     extern __shared__ float4 fc_lds[];          // VEC: 32 rows of pooled sums, 32 of weights; then the partial tiles
     float* const lds = reinterpret_cast<float*>(fc_lds);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -605,7 +608,7 @@ __global__ __launch_bounds__(64 * FC_WAVES) void head_fc_kernel(const int32_t* _
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
     if constexpr (VEC) {
-        const int pitch = fc_pitch(C), units = (pitch - 4) / 4;
+        const int pitch = fc_pitch(C, FC_CHANNELS), units = (pitch - 4) / 4;
         float* const pl = lds, * const wl = lds + 32 * pitch;
         constexpr int PER = 32 / FC_WAVES, COLS = FC_CHANNELS / 4 / 64;
         for (int c0 = 0; c0 < C; c0 += FC_CHANNELS) {
@@ -778,14 +781,17 @@ int launch_head_f32(const uint32_t* bits, const float* w, float* y, int32_t* poo
         const dim3 grid((unsigned)cdiv(N, 32), (unsigned)cdiv(J, 32));
         const bool vec = C % 4 == 0 && ((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(pooled)) & 15u) == 0;
         constexpr size_t tiles = (size_t)FC_WAVES * 16 * 64 * sizeof(float);
-        if (vec) {
-            static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&head_fc_kernel<true>),
+        auto launch = [&](auto steps) {
+            constexpr int STEPS = decltype(steps)::value;
+            static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&head_fc_kernel<true, STEPS>),
                                                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-            if (attr != hipSuccess) return BNN_ERR_DEVICE;
-            const size_t operands = (size_t)64 * fc_pitch(C) * sizeof(float);
-            hipLaunchKernelGGL(head_fc_kernel<true>, grid, dim3(64 * FC_WAVES), operands > tiles ? operands : tiles, s, pooled, w, y, N, HW, C, J);
-        } else
-            hipLaunchKernelGGL(head_fc_kernel<false>, grid, dim3(64 * FC_WAVES), tiles, s, pooled, w, y, N, HW, C, J);
+            if (attr != hipSuccess) return (int)BNN_ERR_DEVICE;
+            const size_t operands = (size_t)64 * fc_pitch(C, 64 * STEPS) * sizeof(float);
+            hipLaunchKernelGGL((head_fc_kernel<true, STEPS>), grid, dim3(64 * FC_WAVES), operands > tiles ? operands : tiles, s, pooled, w, y, N, HW, C, J);
+            return check_launch();
+        };
+        if (vec) return (long long)grid.x * grid.y > 256 ? launch(std::integral_constant<int, 4>{}) : launch(std::integral_constant<int, 8>{});
+        hipLaunchKernelGGL((head_fc_kernel<false, 8>), grid, dim3(64 * FC_WAVES), tiles, s, pooled, w, y, N, HW, C, J);
         return check_launch();
     }
     const size_t lds_bytes = (size_t)2 * C * HEAD_LD * sizeof(float);

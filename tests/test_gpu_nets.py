@@ -225,6 +225,12 @@ def test_head_pooled(bnn, orc, shape):
     assert (np.abs(host(y1) - ref) <= tol).all()
 
 
+# The FC of a head beyond one workgroup per compute unit: passes of 256 channels instead of 512, ragged last ones and one alone; images, outputs off 32
+@pytest.mark.parametrize("shape", [(8200, 2, 2, 512, 10), (300, 1, 1, 1020, 900), (290, 3, 1, 260, 1000), (4130, 1, 2, 64, 70)])
+def test_head_many_workgroups(bnn, orc, shape):
+    test_head_pooled(bnn, orc, shape)
+
+
 @pytest.mark.parametrize("shape", [(2, 21, 19, 3, 5, 7, 4, 3), (1, 9, 9, 1, 1, 3, 1, 1), (3, 16, 12, 4, 70, 5, 2, 2),
                                    (2, 32, 32, 3, 64, 7, 4, 3), (1, 8, 8, 2, 33, 1, 1, 0)])
 def test_conv_f32_shapes(bnn, orc, shape):
