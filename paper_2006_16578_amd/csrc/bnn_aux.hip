@@ -541,35 +541,39 @@ __global__ __launch_bounds__(256) void head_kernel(const uint32_t* __restrict__ 
 
 // The same head as two kernels, for callers that give it a place for the pooled sums: the pooling runs once per
 // image instead of once per (image group, output group) workgroup, and the FC runs on the matrix cores.
-// Pooling: sixteen lanes share one packed word (32 channels) of one image, each counting every sixteenth position (set bits per
-// channel, 4 channels at a time in the bytes of one register: HW <= 255); four neighbouring lanes hold four neighbouring words. The partial counts
-// meet through lane exchanges, and the first lane of four t writes channels q + 8 t.  (Sixteen and not four: 256 images of 7x7x512 are 256 workgroups
-// instead of 64 and one memory round trip; 5.8 -> 4.9 us under the profiler.)
+// Pooling: PARTS lanes share one packed word (32 channels) of one image, each counting every PARTS-th position (set bits per
+// channel, 4 channels at a time in the bytes of one register: HW <= 255); neighbouring lanes hold neighbouring words. The partial counts
+// meet through lane exchanges, and the first four of a word's lanes, t, write channels q + 8 t.  Sixteen lanes: 256 images of 7x7x512 are 256 workgroups
+// instead of 64 and one memory round trip; 4.6 -> 3.6 us under the profiler.  Four from 2^18 words on, which fill the chip
+// twice with four lanes and need fewer lane exchanges: 16384 x 7x7x512 30.1 -> 27.9, 32768 55 -> 47, 32768 x 4x4x256 30.5 -> 27.9 (8192 x 7x7x512 17.2 / 16.6, 8192 x 7x7x800
+// 24.5 / 25.2) -- unless a wave's sixteen words are those of many images: 65536 x 8x8x64 16.9 / 24.2.
+template <int PARTS>
 __global__ __launch_bounds__(256) void head_pool_kernel(const uint32_t* __restrict__ bits, int32_t* __restrict__ pooled_out,
                                                         int N, int HW, int C) {
+    constexpr int WORDS = 64 / PARTS;                      // words of a wave; loads in flight
     const int cw = (C + 31) / 32;
     const long long wave = ((long long)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int lane = threadIdx.x & 63, part = lane >> 2;
-    const long long item = wave * 4 + (lane & 3);
-    const bool live = item < (long long)N * cw;            // the sixteen lanes of a word are live or not
+    const int lane = threadIdx.x & 63, part = lane / WORDS;
+    const long long item = wave * WORDS + lane % WORDS;
+    const bool live = item < (long long)N * cw;            // the lanes of a word are live or not
     const int n = live ? (int)(item / cw) : 0, wi = live ? (int)(item - (long long)n * cw) : 0;
     uint32_t cnt[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) cnt[q] = 0u;
     const uint32_t* b = bits + (long long)n * HW * cw + wi;
-    for (int i0 = part; i0 < HW; i0 += 64) {               // four independent loads in flight
-        uint32_t v[4];
+    for (int i0 = part; i0 < HW; i0 += 64) {
+        uint32_t v[WORDS];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = (live && i0 + 16 * u < HW) ? b[(long long)(i0 + 16 * u) * cw] : 0u;
+        for (int u = 0; u < WORDS; ++u) v[u] = (live && i0 + PARTS * u < HW) ? b[(long long)(i0 + PARTS * u) * cw] : 0u;
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < WORDS; ++u)
 #pragma unroll
             for (int q = 0; q < 8; ++q) cnt[q] += (v[u] >> q) & 0x01010101u;
     }
 #pragma unroll
     for (int q = 0; q < 8; ++q)
 #pragma unroll
-        for (int m = 4; m < 64; m *= 2) cnt[q] += (uint32_t)__shfl_xor((int)cnt[q], m);
+        for (int m = WORDS; m < 64; m *= 2) cnt[q] += (uint32_t)__shfl_xor((int)cnt[q], m);
     if (!live || part >= 4) return;
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
@@ -776,8 +780,10 @@ int launch_head_f32(const uint32_t* bits, const float* w, float* y, int32_t* poo
                     hipStream_t s) {
     if (C > HEAD_MAXC || HW > 255) return BNN_ERR_UNSUPPORTED;
     if (pooled != nullptr) {
-        const long long lanes = cdiv((long long)N * ((C + 31) / 32), 4) * 64;     // a wave for four words
-        hipLaunchKernelGGL(head_pool_kernel, dim3((unsigned)cdiv(lanes, 256)), dim3(256), 0, s, bits, pooled, N, HW, C);
+        const int cw = (C + 31) / 32;
+        const long long items = (long long)N * cw;
+        if (items < (1 << 18) || cw < 8) hipLaunchKernelGGL(head_pool_kernel<16>, dim3((unsigned)cdiv(items, 16)), dim3(256), 0, s, bits, pooled, N, HW, C);
+        else hipLaunchKernelGGL(head_pool_kernel<4>, dim3((unsigned)cdiv(items, 64)), dim3(256), 0, s, bits, pooled, N, HW, C);
         const dim3 grid((unsigned)cdiv(N, 32), (unsigned)cdiv(J, 32));
         const bool vec = C % 4 == 0 && ((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(pooled)) & 15u) == 0;
         constexpr size_t tiles = (size_t)FC_WAVES * 16 * 64 * sizeof(float);

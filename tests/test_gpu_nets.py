@@ -231,6 +231,12 @@ def test_head_many_workgroups(bnn, orc, shape):
     test_head_pooled(bnn, orc, shape)
 
 
+# Its pooling from 2^18 packed words on: four lanes to a word instead of sixteen; a last wave with some of its sixteen words, positions off four, a partly filled word
+@pytest.mark.parametrize("shape", [(32770, 1, 3, 250, 3), (16391, 2, 1, 512, 2), (8740, 1, 1, 964, 1)])
+def test_head_pooling_of_many_words(bnn, orc, shape):
+    test_head_pooled(bnn, orc, shape)
+
+
 @pytest.mark.parametrize("shape", [(2, 21, 19, 3, 5, 7, 4, 3), (1, 9, 9, 1, 1, 3, 1, 1), (3, 16, 12, 4, 70, 5, 2, 2),
                                    (2, 32, 32, 3, 64, 7, 4, 3), (1, 8, 8, 2, 33, 1, 1, 0)])
 def test_conv_f32_shapes(bnn, orc, shape):
