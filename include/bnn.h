@@ -371,6 +371,10 @@ int bnn_net_forward_persistent(bnn_net* net, const void* input, void* output, in
  * This is the one call of the library that waits for the device (it synchronises `stream`).
  * BNN_ERR_WORKSPACE when the net has not run a persistent forward. */
 int bnn_net_persistent_status(bnn_net* net, int* aborted, void* stream);
+/* How many layers at the head of the net (the input layer included) bnn_net_forward runs as one launch for `batch` inputs on the matrix cores, 0: each layer
+ * is launched by itself.  Fully-connected layers only; recorded != 0: on a stream that is being recorded into a graph, whose replay costs the
+ * host nothing.  The results are the same.  Decided on the host: no device is needed to ask. */
+int bnn_net_fc_run(const bnn_net* net, int batch, int recorded, int* layers);
 /* After a forward: device pointer (inside the workspace) and shape of the packed bits produced by
  * layer `layer` (0 = input layer), for layer-by-layer checking.  words_per_row receives the row
  * length in words, rows the number of rows (batch, or batch*P*Q). */

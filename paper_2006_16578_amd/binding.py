@@ -29,7 +29,7 @@ EXPORTS = ["bnn_status_string", "bnn_version", "bnn_bmm_kernel_name", "bnn_bconv
            "bnn_bconv_general_workspace_bytes", "bnn_bconv_general_f32", "bnn_unpack_i32", "bnn_maxpool_or", "bnn_conv_f32_thr", "bnn_conv_f32_split_workspace_bytes", "bnn_conv_f32_split_thr", "bnn_conv_f32_split_thr_ex", "bnn_bwn_workspace_bytes", "bnn_bwn_conv_thr", "bnn_head_f32", "bnn_net_create",
            "bnn_net_destroy", "bnn_net_input_u8", "bnn_net_input_bits", "bnn_net_input_conv_f32", "bnn_net_input_bwn_f32", "bnn_net_add_fc",
            "bnn_net_add_conv", "bnn_net_add_pool", "bnn_net_add_block", "bnn_net_add_head_f32", "bnn_net_workspace_bytes",
-           "bnn_net_forward", "bnn_net_forward_static", "bnn_static_workspace_init", "bnn_net_forward_persistent", "bnn_net_persistent_status", "bnn_net_layer_bits"]
+           "bnn_net_forward", "bnn_net_forward_static", "bnn_static_workspace_init", "bnn_net_forward_persistent", "bnn_net_persistent_status", "bnn_net_fc_run", "bnn_net_layer_bits"]
 
 
 class BnnError(RuntimeError):
@@ -633,6 +633,12 @@ class Net:
     def workspace_bytes(self, batch: int) -> int:
         n = ctypes.c_size_t()
         _check(load().bnn_net_workspace_bytes(self._h, int(batch), ctypes.byref(n)), "bnn_net_workspace_bytes")
+        return n.value
+
+    def fc_run(self, batch: int, recorded: bool = False) -> int:
+        """How many layers at the head of the net forward() runs as one launch (0: each by itself); recorded: under graph capture."""
+        n = ctypes.c_int()
+        _check(load().bnn_net_fc_run(self._h, int(batch), int(recorded), ctypes.byref(n)), "bnn_net_fc_run")
         return n.value
 
     def forward(self, x, out=None, path: int = PATH_AUTO):

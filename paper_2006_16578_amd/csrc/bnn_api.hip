@@ -689,8 +689,19 @@ struct PersistCtx {
     }
 };
 
+// Whether launches on this stream are being recorded into a graph.  (A stream that cannot be asked, the default one while another is recorded, cannot be
+// launched on either: the launch reports it.)
+bool being_recorded(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status == hipStreamCaptureStatusActive;
+}
+
 // The fully-connected layers at the head of a network, an 8-bit input layer in front of them included, as one launch (bnn_fc_chain.hip).
-// Returns how many layers `ch` takes: 0 where one launch per layer is better.
+// Returns how many layers `ch` holds (0: none); whether one launch per layer is better is asked of fc_chain_takes().
 int fc_chain_plan(const bnn_net* net, const void* input, void* output, int batch, char* ws, FcChain* ch) {
     const bnn_net::Layer& L0 = net->layers[0];
     const bool u8 = L0.kind == bnn_net::IN_U8;
@@ -710,7 +721,7 @@ int fc_chain_plan(const bnn_net* net, const void* input, void* output, int batch
         C.bits = L.t0 ? reinterpret_cast<uint32_t*>(ws + L.bits_off) : nullptr;
         C.K = L.a; C.N = L.b; C.tw = round4(words(L.a)); C.ldo = L.words_per_row;
     }
-    return fc_chain_takes(*ch) ? 1 + ch->nlayers : 0;
+    return 1 + ch->nlayers;
 }
 
 int forward_impl(bnn_net* net, const void* input, void* output, int batch, char* ws, const Plan& pl, int path, void* stream,
@@ -727,12 +738,13 @@ int forward_impl(bnn_net* net, const void* input, void* output, int batch, char*
         if (i == 0 && pc == nullptr && (path == BNN_PATH_AUTO || path == BNN_PATH_MFMA)) {      // (dispatch() refuses other paths)
             FcChain ch = {};
             const int run = fc_chain_plan(net, input, output, batch, ws, &ch);
-            if (run > 0) {      // refuses what the layers one by one would, in their order
+            const hipStream_t s = static_cast<hipStream_t>(stream);
+            if (run > 0 && fc_chain_takes(ch, false) && (!being_recorded(s) || fc_chain_takes(ch, true))) {     // refuses what the layers one by one would, in their order
                 const bnn_net::Layer& last = net->layers[run - 1];
                 if (L.kind == bnn_net::IN_BITS && !aligned16(input)) return BNN_ERR_ALIGNMENT;
                 if (last.t0 == nullptr && !output) return BNN_ERR_INVALID_ARG;
                 if (last.t0 == nullptr && !aligned16(output)) return BNN_ERR_ALIGNMENT;
-                rc = launch_fc_chain(ch, static_cast<hipStream_t>(stream));
+                rc = launch_fc_chain(ch, s);
                 if (rc != BNN_OK) return rc;
                 cur = reinterpret_cast<uint32_t*>(ws + last.bits_off); curC = last.C; cur_ld = last.words_per_row;
                 i = run - 1;
@@ -959,6 +971,18 @@ int bnn_net_forward_static(bnn_net* net, const void* input, void* output, int ba
     const int rc = static_workspace(&ws);
     if (rc != BNN_OK) return rc;
     return bnn_net_forward(net, input, output, batch, ws, (size_t)BNN_STATIC_WORKSPACE_BYTES, path, stream);
+}
+
+int bnn_net_fc_run(const bnn_net* net, int batch, int recorded, int* layers) {
+    if (!net || !layers || batch < 1 || net->layers.empty()) return BNN_ERR_INVALID_ARG;
+    bnn_net asked = *net;                         // plan() writes into the layers
+    const Plan pl = plan(&asked, batch);
+    if (pl.rc != BNN_OK) return pl.rc;
+    static char some_memory[16];                  // the choice only asks which operands there are, never touches them
+    FcChain ch = {};
+    const int run = fc_chain_plan(&asked, some_memory, some_memory, batch, some_memory, &ch);
+    *layers = run > 0 && fc_chain_takes(ch, false) && (recorded == 0 || fc_chain_takes(ch, true)) ? run : 0;
+    return BNN_OK;
 }
 
 int bnn_net_layer_bits(const bnn_net* net, int layer, const uint32_t** bits, int64_t* rows, int* words_per_row) {

@@ -26,8 +26,9 @@ struct FcChain {
     FcChainLayer layer[FC_CHAIN_MAX];
 };
 
-// Whether one launch is the better one for these layers (the fields that launch_fc_chain fills are not read).
-bool fc_chain_takes(const FcChain& a);
+// Whether one launch is the better one for these layers (the fields that launch_fc_chain fills are not read).  replayed: for launches that are recorded into a
+// graph, whose replay costs the host nothing.
+bool fc_chain_takes(const FcChain& a, bool replayed);
 int launch_fc_chain(FcChain a, hipStream_t s);
 
 }  // namespace bnn

@@ -333,19 +333,39 @@ int launch_chain(FcChain a, hipStream_t s) {
 
 }  // namespace
 
-// One launch is worth what it saves, 2.2 us (host) to 4 us (kernels of 129 rows and more) for each layer, and costs about 2.7 us for each 2^20 weight
-// bits that every workgroup expands.  Measured, a pass of a network through Net.forward, one launch per layer -> one launch, us:
-//   784-1024-1024-1024-10 on 8-bit values: 8 rows 15.2 -> 14.5, 1024 19.7 -> 15.3, 4096 24.5 -> 16.0, 8192 28.2 -> 23.0; 16384 38.8 -> 43.5
-//   the same on packed rows, 8 rows: 13.3 -> 14.0 (2.8 * 2^20 bits, four launches); 784-1024-1024-10 11.5 -> 11.0
-//   784-512-512-10 on 8-bit values: 8 rows 13.8 -> 9.3, 4096 14.7 -> 10.3; 256-10: 9.5 -> 7.3
+// One launch is worth what it saves and costs about 2.7 us for each 2^20 weight bits that every workgroup expands.
+// Queued from the host it saves 2.2 us (host) to 4 us (kernels of 129 rows and more) for each layer.  Measured, a pass of a network through
+// Net.forward, one launch per layer -> one launch, us:
+//   784-1024-1024-1024-10 on 8-bit values: 8 rows 17.6 -> 14.8, 128 19.6 -> 15.2, 1024 19.6 -> 15.4, 4096 24.5 -> 16.0, 8192 28.2 -> 23.0; 16384 38.8 -> 43.5
+//   the same on packed rows: 256 16.7 -> 14.8; 8 rows 13.3 -> 14.0 (2.8 * 2^20 bits, four launches); 784-1024-1024-10, 8 rows 12.6 -> 11.2
+//   784-512-512-10 on 8-bit values: 8 rows 15.1 -> 9.6, 1024 15.2 -> 10.2; 1024-1024-10 on packed rows: 8 rows 10.1 -> 8.3, 1024 10.1 -> 8.7
 // Sums of more than 64 columns leave element by element (784-256, 4096 rows: 8.8 -> 10.4; 1024-1024-1024-1000 19.9 -> 33.2), and behind other layers, where the
 // queue is full and a launch costs less, two layers are no gain (1024-1024-10 at the end of a VGG for 32x32 images: 41.5 -> 43.4).
-bool fc_chain_takes(const FcChain& in) {
+// Replayed from a graph a layer costs its kernel alone, and the kernels for few rows (bnn_mfma_skinny.hip) end after 2.3 us: the run's gain over them, graph replays,
+// at 1 to 16 / 17 to 64 / 65 to 128 / 129 to 1024 / 1025 to 4096 rows (launches, 2^20 bits):
+//   784-1024-1024-1024-10 on 8-bit values (5, 2.9)  0.82 to 0.85 / 0.99 to 1.10 / 1.27 / 1.18 / 1.34 to 1.49;  packed (4, 2.9)  - / - / - / 1.05 / 1.22 to 1.42
+//   784-640-640-640-10 on 8-bit values (5, 1.3)     0.91 to 0.96 / 1.11 to 1.22 / 1.40 / 1.22 / 1.24 to 1.44;  512 wide (5, 0.7)  1.04 / 1.23 / 1.5 / 1.3 / 1.3
+//   784-1024-1024-10 on 8-bit values (4, 1.9)       0.79 to 0.85 / 1.01 to 1.11 / 1.27 / 1.16 / 1.29 to 1.46;  packed (3, 1.9)  0.70 / 0.87 to 0.98 / 1.15 / 1.04 / 1.16
+//   784-512-512-10 on 8-bit values (4, 0.7)         0.97 to 1.02 / 1.20 to 1.31 / 1.5 / 1.28 / 1.29 to 1.41;   packed (3, 0.7)  0.87 / 1.06 to 1.19 / 1.37 / 1.13 / 1.14
+//   256-256-256-256-10 (5 and 4, 0.2)               1.07 to 1.19 / 1.3 to 1.5 / 1.65 to 1.75 / 1.2 to 1.4 / 1.2 to 1.4
+//   784-128-10, 784-256-10 on 8-bit values (3; 0.1, 0.2)  0.96 to 1.06 / 1.19 to 1.32 / 1.47 / 1.25 / 1.27
+//   1500-1024-512-10 (3, 2.0)  - / - / - / 0.92 to 0.94 / 0.98 to 1.13;  1024-1024-10 packed (2, 1.01)  0.65 / 0.82 to 0.92 / 1.08 / 0.99 to 1.01 / 1.10 to 1.24
+//   2048-512-64 packed (2, 1.03)  0.65 / 0.76 to 0.84 / 1.02 / 0.95 to 0.97 / 0.94 to 1.12;  784-512-10 packed (2, 0.4)  0.75 / 0.94 to 1.05 / 1.22 / 1.03 / 1.06
+//   784-64 on 8-bit values (2, 0.05)  0.83 to 0.89 / 0.97 to 1.08 / 1.13 / 1.03 / 0.96 to 1.02, beyond 4096 rows 0.85 to 0.88; everything else there 0.97 to 1.4
+// (2048-512-64 at 8192 rows, where a launch of its own takes the 128x128 tiles for the first layer, is the one loss found there: 0.85, queued 0.91 to 0.96).
+bool fc_chain_takes(const FcChain& in, bool replayed) {
     const int launches = in.nlayers + (in.in_u8 != nullptr ? 1 : 0);
     if (in.nlayers < 1 || launches < 2 || in.rows > (long long)ROWS2 * CUS || (in.in_u8 != nullptr && in.in_cols < 16)) return false;
     long long bits = 0;
     for (int l = 0; l < in.nlayers; ++l) bits += (long long)in.layer[l].N * in.layer[l].tw * 32;
     if (bits > (in.rows > 128 ? launches << 20 : launches * 680000LL)) return false;
+    if (replayed) {
+        constexpr long long M = 1 << 20;
+        if (in.nlayers == 1 && in.rows > (long long)ROWS1 * CUS) return false;
+        if (in.rows <= 16 && bits > (launches - 3) * M / 2 + M / 5) return false;
+        if (in.rows > 16 && in.rows <= 64 && bits > (15 * launches - 28) * M / 16) return false;
+        if (in.rows > 128 && in.rows <= 1024 && bits > (launches - 1) * M) return false;
+    }
     FcChain a = in;
     fill(a);
     return a.rows <= (long long)ROWS1 * CUS ? lds_bytes(a, ROWS1, 12) <= 160 * 1024 : lds_bytes(a, ROWS2, 8) <= 160 * 1024;

@@ -131,6 +131,37 @@ def test_fc_run_refuses_what_its_layers_refuse():
             assert forward(dims, 264, 256, path) == -2 and forward(dims, 264, 0, path) == -2
 
 
+def test_fc_run_by_size():
+    # how many layers at the head of a network go as one launch, queued and recorded into a graph: host logic
+    import paper_2006_16578_amd as b
+    lib = b.load()
+    dummy = ctypes.c_void_p(256)
+
+    def run(dims, u8, batch, recorded=0):
+        net, n = ctypes.c_void_p(), ctypes.c_int(-1)
+        assert lib.bnn_net_create(ctypes.byref(net)) == 0
+        assert (lib.bnn_net_input_u8(net, dims[0], 127) if u8 else lib.bnn_net_input_bits(net, dims[0])) == 0
+        for i, (k, m) in enumerate(zip(dims, dims[1:])):
+            assert lib.bnn_net_add_fc(net, dummy, dummy if i + 2 < len(dims) else None, k, m) == 0
+        assert lib.bnn_net_fc_run(net, batch, recorded, ctypes.byref(n)) == 0 and lib.bnn_net_destroy(net) == 0
+        return n.value
+
+    mlp = (784, 1024, 1024, 1024, 10)
+    assert [run(mlp, True, m) for m in (1, 16, 128, 4096, 8192, 8193)] == [5, 5, 5, 5, 5, 0]
+    assert [run(mlp, False, m) for m in (8, 128, 129)] == [0, 0, 5]
+    # replayed, the kernels for few rows are the faster ones: none of these layers up to 16 rows unless they are many and small
+    assert [run(mlp, True, m, 1) for m in (1, 16, 17, 64, 128, 129, 8192)] == [0, 0, 5, 5, 5, 5, 5]
+    assert [run((1024, 1024, 10), False, m, 1) for m in (8, 16, 64, 65, 128, 129, 1024, 1025)] == [0, 0, 0, 3, 3, 0, 0, 3]
+    assert [run((1024, 1024, 10), False, m) for m in (8, 128, 129, 4096)] == [3, 3, 3, 3]
+    assert run((256, 256, 256, 256, 10), True, 8, 1) == 5 and run((784, 256, 10), True, 8, 1) == 0 and run((784, 256, 10), True, 17, 1) == 3
+    assert [run((784, 64), True, m, 1) for m in (16, 17, 4096, 4097)] == [0, 2, 2, 0] and run((784, 64), True, 4097) == 2
+    # four layers behind the input at most; sums of at most 64 columns; 8-bit rows of 16 or more; what fits LDS
+    assert run((128, 64, 64, 64, 64, 64, 5), False, 40) == 5 and run((300, 100, 65), True, 40) == 2 and run((15, 100, 10), True, 40) == 0
+    assert run((4001, 70, 10), True, 129) == 0 and run((3001, 70, 10), True, 129) == 3
+    n = ctypes.c_int()
+    assert lib.bnn_net_fc_run(None, 8, 0, ctypes.byref(n)) == -1
+
+
 def test_lds_expanded_convolutions_by_output():
     # bits alone go to that kernel from 96 workgroups; sums and residuals leave through a slower epilogue and need more workgroups or a longer K
     import paper_2006_16578_amd as b

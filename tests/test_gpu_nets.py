@@ -78,6 +78,43 @@ def test_fc_chain(bnn, orc, dims, u8, batch, last_thr):
         assert np.array_equal(words(net.layer_bits(l + 1)), bits), "layer %d" % (l + 1)
 
 
+# The same layers recorded into a graph, where fewer of them are worth one launch: replays with eager passes and other inputs between them
+@pytest.mark.parametrize("dims,u8,batch,queued,recorded", [
+    ((784, 1024, 1024, 1024, 10), True, 8, 5, 0), ((784, 1024, 1024, 1024, 10), True, 100, 5, 5), ((1024, 1024, 10), False, 150, 3, 0), ((256, 256, 256, 256, 10), False, 16, 5, 5)])
+def test_fc_run_recorded(bnn, orc, dims, u8, batch, queued, recorded):
+    rng = np.random.default_rng(sum(dims) + batch)
+    p = wl.mlp_params(dims, config=98)
+    net = bnn.Net()
+    net.input_u8(dims[0], 127) if u8 else net.input_bits(dims[0])
+    for l, thr in enumerate(p["thr"] + [None]):
+        net.add_fc(to_dev(p["W"][l]), to_dev(thr) if thr is not None else None, p["K"][l])
+    assert net.fc_run(batch) == queued and net.fc_run(batch, recorded=True) == recorded
+
+    def inputs():
+        x = rng.integers(0, 256, size=(batch, dims[0])).astype(np.uint8) if u8 else wl.random_bits(rng, batch, dims[0], p["W"][0].shape[1])
+        bits = orc.pack_u8(x, 127, ldb_w=p["W"][0].shape[1]) if u8 else x
+        for l, thr in enumerate(p["thr"]):
+            bits = orc.threshold_pack(orc.bmm(bits, p["W"][l], p["K"][l]), thr, ldb_w=p["W"][l + 1].shape[1])
+        return to_dev(x), orc.bmm(bits, p["W"][-1], p["K"][-1])
+
+    x, ref = inputs()
+    static, out = x.clone(), torch.empty((batch, dims[-1]), dtype=torch.int32, device="cuda")
+    assert np.array_equal(host(net.forward(static)), ref)
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            net.forward(static, out=out)
+    torch.cuda.current_stream().wait_stream(side)
+    for _ in range(4):
+        x, ref = inputs()
+        static.copy_(x)
+        out.zero_()
+        graph.replay()
+        assert np.array_equal(host(out), ref)
+        assert np.array_equal(host(net.forward(x)), ref)
+
+
 def build_resnet(bnn, p, hw, pad_mode=0):
     net = bnn.Net()
     net.input_conv_f32(to_dev(p["stem_w"]), to_dev(p["stem_thr"]), hw, hw, 4, 3)
