@@ -40,13 +40,16 @@ def test_mlp(bnn, orc, batch, path):
     assert np.array_equal(scores, ref)
 
 
-@pytest.mark.parametrize("dims,u8,batch", [
-    ((784, 1024, 1024, 1024, 10), True, 4097), ((784, 1024, 1024, 1024, 10), True, 4081),    # 32-row workgroups; the last of 16 rows ragged
-    ((16, 33, 1), True, 1), ((17, 64, 64, 64, 64), True, 15), ((1000, 65, 129, 31, 64), True, 17), ((4001, 70, 10), True, 129),
-    ((1, 1, 1), False, 16), ((31, 1100, 3), False, 33), ((2049, 127, 900, 12), False, 200), ((128, 64, 64, 64, 64, 64, 64, 5), False, 5000),
-    ((15, 100, 10), True, 40), ((300, 100, 65), True, 40)])                # not the chain's: rows of 15 bytes, 65 sums (its first layers are)
+# run: the layers of the one launch, with sums and with thresholds in the last layer
+@pytest.mark.parametrize("dims,u8,batch,run", [
+    ((784, 1024, 1024, 1024, 10), True, 4097, (5, 5)), ((784, 1024, 1024, 1024, 10), True, 4081, (5, 5)),    # 32-row workgroups; the last of 16 rows ragged
+    ((16, 33, 1), True, 1, (3, 3)), ((17, 64, 64, 64, 64), True, 15, (5, 5)), ((1000, 65, 129, 31, 64), True, 17, (5, 5)), ((3001, 70, 10), True, 129, (3, 3)),
+    ((1, 1, 1), False, 16, (3, 3)), ((31, 1100, 3), False, 33, (3, 3)), ((2049, 127, 900, 12), False, 200, (4, 4)),
+    ((128, 64, 64, 64, 64, 64, 64, 5), False, 5000, (5, 5)),               # (four layers behind the input at most)
+    ((15, 100, 10), True, 40, (0, 0)), ((300, 100, 65), True, 40, (2, 3)),  # rows of 15 bytes, 65 sums (its first layers are the run's)
+    ((4001, 70, 10), True, 129, (0, 0))])                                  # beyond LDS
 @pytest.mark.parametrize("last_thr", [False, True])
-def test_fc_chain(bnn, orc, dims, u8, batch, last_thr):
+def test_fc_chain(bnn, orc, dims, u8, batch, run, last_thr):
     # fully-connected layers at the head of a network in one launch: widths on and off words, 64-column groups and 1024-bit parts, and
     # thresholds no sum can reach, or every sum does
     rng = np.random.default_rng(sum(dims) + batch)
@@ -66,6 +69,7 @@ def test_fc_chain(bnn, orc, dims, u8, batch, last_thr):
     nl = len(dims) - 1
     for l in range(nl):
         net.add_fc(to_dev(p["W"][l]), to_dev(thr[l]) if l + 1 < nl or last_thr else None, p["K"][l])
+    assert net.fc_run(batch) == run[last_thr]
     out = net.forward(to_dev(x))
     if u8:
         assert np.array_equal(words(net.layer_bits(0)), bits)
