@@ -108,10 +108,10 @@ struct Epi {
     // each block in the order the matrix cores hand out a 32x32 accumulator (sums16_index): a lane's 16 values
     // are 32 contiguous bytes, so the residual moves as two 16-byte accesses per lane instead of sixteen
     // 2-byte ones.  The tensor is private to the layer chain, which produces and consumes it with these kernels;
-    // which element a lane's register holds is private to the kernel that writes a block (the 3x3 patch kernel keeps
-    // 16 channels of one pixel per lane, the others one channel of 16 pixels).  That is safe because a block's sums
-    // are only ever read by the second convolution of the next identity block: the same geometry and epilogue kind,
-    // hence the same kernel choice.
+    // which element a lane's register holds is private to the kernel that writes a block (the band and patch kernels keep
+    // 16 channels of one pixel per lane, the direct and wave-per-tap kernels one channel of 16 pixels).  That is safe because a
+    // block's sums are only ever read by the second convolution of the next identity block, of the same geometry and epilogue kind,
+    // and because the kernel of EPI_CHAIN is chosen by those alone: not by what is added (A2, resid16, resid_bits), by out16 or by excl.
     int sums_tiled;
     int ldc;               // elements between rows of out / resid
     int out_f32;           // 1: `out` receives the sums converted to fp32 (exact: |v| < 2^24) instead of int32

@@ -52,7 +52,7 @@ int launch_mfma(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
     if (mfma_conv_band_takes(g, e)) return launch_mfma_conv_band(A, B, g, e, s);
     if (mfma_conv_patch_takes(g, e)) return launch_mfma_conv_patch(A, B, g, e, s);
     if (const int xt = mfma_conv_xlds_tile(g, e)) return launch_mfma_conv_xlds(xt, A, B, g, e, s);
-    // (blocked 16-bit sums are implemented by the direct kernels only)
+    // (blocked 16-bit sums are implemented by the band, patch, wave-per-tap and direct kernels)
     if (!e.sums_tiled && staged_ok(g, tile)) return launch_mfma_conv_staged(A, B, g, e, s);
     if (tile == 3 && mfma_conv_taps_takes(g, e, g.pool2 != 0)) return launch_mfma_conv_taps(A, B, g, e, s);
     if (!mfma::offsets_fit(g)) return BNN_ERR_UNSUPPORTED;

@@ -459,6 +459,8 @@ BandPlan plan_band(const Geom& g, const Epi& e) {
     }
     if (nx == 0) return pl;
     // Where this kernel is the faster one (its speed over the patch and direct kernels'; 7x7 to 28x28, bands of every length up to three rounds):
+    // (A chain's decision may depend on the geometry alone, the same for every block of it: Epi::sums_tiled.  pick_tile() depends on excl only where
+    // conv_stages_through_lds() does, from 320 words of K on; here there are 144 at most.)
     if (g.tw == 4) {
         // 128 channels in.  Up to 128 out, bits alone: 0.88 to 1.09 of the patch kernel, which stays.  With sums (chains of three blocks, whole): one round
         // 1.07 to 1.18, two 0.99 to 1.10, three 0.96 to 0.98.  More channels out, against the direct kernel: 0.92 to 1.01 up to 8 tiles, then 1.05 to 1.37.

@@ -196,6 +196,26 @@ def test_lds_expanded_convolutions_by_output():
     assert not served(256, 14, 96, residual=True, keep_sum=True)
 
 
+def test_blocked_sums_are_read_by_the_kernel_that_writes_them():
+    # the 16-bit sums between two blocks lie in the order of the writing kernel: over shapes, whichever way a block pads, with a shortcut, a residual and a
+    # last sum that is not kept, the same kernel (the direct one's tiles and the wave-per-tap kernel share an order)
+    import paper_2006_16578_amd as b
+
+    def order(name):
+        assert "xlds" not in name and "lds_wg" not in name
+        return "band" if "_band_" in name else "patch" if "_patch_" in name else "accumulator"
+
+    seen = set()
+    for hw in (5, 7, 13, 14, 28, 33, 56):
+        for C in (32, 64, 96, 128, 192, 256, 320, 512, 1024):
+            for batch in (1, 2, 4, 8, 16, 26, 40, 57, 73, 85, 104, 128, 146, 200, 256, 292, 400, 512, 585, 1024):
+                kinds = {order(b.bconv_kernel_name(batch, hw, hw, C, C, 3, 1, 1, pad_mode=pad_mode, **kw)) for pad_mode in (0, 1)
+                         for kw in (dict(shortcut=True, keep_sum=True), dict(residual=True, keep_sum=True), dict(residual=True))}
+                assert len(kinds) == 1, (batch, hw, C, kinds)
+                seen |= kinds
+    assert seen == {"band", "patch", "accumulator"}
+
+
 def test_stream_without_the_private_torch_function(monkeypatch):
     import types
     from paper_2006_16578_amd import binding as b

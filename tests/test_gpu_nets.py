@@ -740,3 +740,28 @@ def test_block_chains_wave_per_tap(bnn, orc, batch, hw, cin, blocks, pad_mode):
         assert bnn.bconv_kernel_name(batch, size, size, co, co, 3, 1, 1, pad_mode=pad_mode, shortcut=shortcut, residual=not shortcut,
                                      keep_sum=shortcut) == "mfma_fp4_conv_taps_wg32x32"
     test_block_chains_expanded_in_lds(bnn, orc, batch, hw, cin, blocks, pad_mode, None)
+
+
+# Blocks of a chain may pad in different ways; the 16-bit sums between them are blocked in the order of the kernel that writes them, so that kernel
+# must not depend on the padding: in bands (K split and not), patches and a wave per tap
+@pytest.mark.parametrize("batch,hw,C,kernel", [(126, 7, 512, "3x3_band_wg64"), (85, 14, 256, "3x3_band_wg64"), (191, 15, 128, "3x3_band_wg64"),
+                                               (200, 15, 64, "3x3_patch_wave64x64"), (3, 9, 256, "_taps_wg32x32")])
+def test_block_chains_of_mixed_padding(bnn, orc, batch, hw, C, kernel):
+    rng = np.random.default_rng(batch + hw + C)
+    net, modes, blocks = bnn.Net(), (0, 1, 0, 1), []
+    net.input_bwn_f32(to_dev(wl.random_bits(rng, (C, 3, 3), 3)), to_dev(np.zeros(C, np.float32)), hw, hw, 3, 1, 1)
+    for pad_mode in modes:
+        assert bnn.bconv_kernel_name(batch, hw, hw, C, C, 3, 1, 1, pad_mode=pad_mode, residual=True, keep_sum=True) == "mfma_fp4_conv" + kernel
+        blk = [wl.random_bits(rng, (C, 3, 3), C), rng.integers(-20, 21, size=C).astype(np.int32), wl.random_bits(rng, (C, 3, 3), C),
+               rng.integers(-20, 21, size=C).astype(np.int32)]
+        net.add_block(*map(to_dev, blk), None, C, C, 1, pad_mode)
+        blocks.append(blk)
+    net.add_head_f32(to_dev(rng.normal(0.0, 0.02, size=(7, C)).astype(np.float32)))
+    net.forward(to_dev(rng.integers(-100, 101, size=(batch, hw, hw, 3)).astype(np.float32)))
+    x = words(net.layer_bits(0)).reshape(batch, hw, hw, -1)
+    total = orc.unpack_pm1(x.reshape(-1, x.shape[-1]), C).astype(np.int32).reshape(batch, hw, hw, C)
+    for b, (pad_mode, (w1, t1, w2, t2)) in enumerate(zip(modes, blocks)):
+        h = orc.threshold_pack(orc.bconv(x, w1, C, 1, 1, pad_mode, tier=1), t1)
+        total = total + orc.bconv(h, w2, C, 1, 1, pad_mode, tier=1)
+        x = orc.threshold_pack(total, t2)
+        assert np.array_equal(words(net.layer_bits(b + 1)).reshape(x.shape), x), "block %d" % b
