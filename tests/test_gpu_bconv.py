@@ -340,3 +340,17 @@ def test_shapes_expanded_in_lds_eight_waves(bnn, orc, shape):
     case = wl.bconv_case(95, N, H, W, C, O, k, st, pad, index0=C % 83)
     ref = orc.bconv(case["x"], case["filt"], C, st, pad, pad_mode, tier=1)
     run_conv(bnn, orc, case, 0, pad_mode, ref=ref, with_resid=False)
+
+
+# Inputs beyond 2 GiB: bands (unsigned byte offsets), and a wave per tap in one image beyond the direct kernel's offsets; against the vector-ALU kernel, which
+# addresses with 64 bits
+@pytest.mark.parametrize("shape,kernel", [((172000, 14, 14, 512, 64, 1), "3x3_band_wg64"), ((1, 6001, 5990, 512, 40, 99), "_taps_wg32x32")])
+def test_inputs_beyond_2_gib(bnn, shape, kernel):
+    N, H, W, C, O, st = shape
+    assert N * H * W * C // 8 > 2 ** 31
+    assert bnn.bconv_kernel_name(N, H, W, C, O, 3, st, 1) == "mfma_fp4_conv" + kernel
+    g = torch.Generator(device="cuda").manual_seed(96)
+    draw = lambda *s: torch.randint(-2 ** 31, 2 ** 31, s, dtype=torch.int32, device="cuda", generator=g)
+    x, filt, tau = draw(N, H, W, C // 32), draw(O, 3, 3, C // 32), torch.randint(-64, 65, (O,), dtype=torch.int32, device="cuda", generator=g)
+    y = bnn.bconv_thr(x, filt, tau, C, st, 1)
+    assert torch.equal(y, bnn.bconv_thr(x, filt, tau, C, st, 1, path=bnn.PATH_VALU))
