@@ -468,8 +468,9 @@ BandPlan plan_band(const Geom& g, const Epi& e) {
     } else if (g.tw == 8) {
         // 256 in: bits 0.96 to 1.02 at 8 tiles, from 9 on 1.04 to 1.4 (64 out: 1.05 to 1.7); chains 1.06 to 1.32.
         if (pl.kind == mfma::EPI_BITS && rounds == 1 && most <= 8) return pl;
-        // (1.3 here too, but that 128 x 28x28x256 -> 256 is the direct kernel's is tested behaviour of bnn_bconv_kernel_name)
-        if (pl.kind == mfma::EPI_BITS && !g.excl && g.cols == 256 && rounds == 2 && most >= 25) return pl;
+        // 256 out with -1 padding, two rounds of 25 tiles: 1.25 to 1.32 here too (26 tiles 1.25, 27 and 28 1.17), but that 128 x 28x28x256 -> 256, which
+        // is one of these, is the direct kernel's is tested behaviour of bnn_bconv_kernel_name.
+        if (pl.kind == mfma::EPI_BITS && !g.excl && g.cols == 256 && rounds == 2 && most == 25) return pl;
     } else if (g.cols > 64) {
         // 512 in: both kernels' times are staircases of different steps, so they are estimated (us at 512 in, measured within 4 %): a round here
         // 1.2 + 0.9 per tile of the busiest SIMD, the direct kernel 14.4 per 256x128 tile of the fullest compute unit, or 4.5 + 6.2 per 128x128 tile.

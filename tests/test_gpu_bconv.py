@@ -304,7 +304,7 @@ def test_patch_kernel_3x3(bnn, orc, shape):
 # a row tile, images of many bands, odd sizes, ragged last rows.  (N, H, W, C, O)
 @pytest.mark.parametrize("pad_mode", [0, 1])
 @pytest.mark.parametrize("shape", [
-    (66, 13, 11, 256, 512), (53, 15, 16, 256, 512), (37, 18, 20, 256, 512), (7, 50, 51, 256, 512), (1, 160, 162, 256, 512), (900, 5, 7, 256, 256),
+    (66, 13, 11, 256, 512), (53, 15, 16, 256, 512), (37, 18, 20, 256, 512), (7, 50, 51, 256, 512), (1, 160, 162, 256, 512), (900, 5, 7, 256, 256), (544, 14, 14, 256, 256),
     (80, 13, 15, 256, 576), (31, 13, 13, 512, 512), (24, 15, 17, 512, 512), (390, 5, 5, 512, 512), (12, 33, 34, 512, 512), (171, 14, 14, 512, 64),
     (33, 24, 25, 128, 512), (16, 41, 41, 128, 512), (52, 31, 29, 128, 320), (1025, 6, 6, 128, 512)])
 def test_bands(bnn, orc, shape, pad_mode):
