@@ -8,7 +8,7 @@
 //  * A wave owns groups of 64 output columns.  v_mfma_f32_16x16x128_f8f6f4 with the WEIGHTS as row operand: lane l supplies weight
 //    row l % 16 and 32 K slots of group l / 16, which is one packed word.  The lanes of a load take 8 rows x 128 neighbouring bytes and the
 //    words change lanes through 8 KB of LDS that belong to the wave: loaded as operands, every lane in another row than its neighbours, the
-//    address side takes a cycle for each lane (measured: 128 such loads of 1 KB, a layer's weights, 8400 cycles, whatever was multiplied; 6700 now).
+//    address side takes a cycle for each lane (measured: 128 such loads of 1 KB, a layer's weights, 8400 cycles, whatever was multiplied; 6700 now, 6050 of them vector instructions).
 //    64 weight rows x 1024 bits are in flight, across layers: weights do not wait for activations.
 //  * Weight words cost four instructions instead of seven.  Bits 0, 1 and 2 of a nibble are left where they are and mean 0.5, 1 and
 //    2 or zero (b in {0, 1}), bit 3 is the sign of 1.  The activations, which are expanded once per workgroup, carry the factors 4, 2 and

@@ -10,7 +10,7 @@
 //    of the patch kernel: pitch W + 1, padding cells are data.  A tap's fragment is one 16-byte read at a constant offset.
 //  * The filters stay packed: each wave reads them two chunks ahead and expands two words per K-step of 4 to 7 MFMAs.  (Timing-only builds that skip the
 //    expansion, the filter loads or the pixel reads ran within 0.4 us of this one: the K loop is the matrix pipe's, 8.6 us for
-//    59 G operations of random bits, 7.1 of zeros -- the clock falls with what toggles.)
+//    59 G operations of random bits, 7.1 of zeros -- the clock falls with what toggles.  MFMAs alone, operands in registers: 7.2 and 6.9.)
 //  * Filters are the row operand, channels dealt so that a half-wave owns 32 neighbours (dealt_column); accumulators start at 0.5 - threshold, so an output
 //    bit is a sign.  What a chain adds (residual sums, bits, a 1x1 shortcut) is requested during the last chunk of K.
 //  * 512 channels: the waves split K in two (the band is half as long at the same LDS), and meet once through LDS.
@@ -18,6 +18,8 @@
 // 31.6 -> 24.6, 256 x 7x7x512 -> 512 17.6 -> 15.7, 128 x 14x14x128 -> 512 11.8 -> 9.5; in a ResNet-18 of batch 256 the
 // 14x14x256 layers 27.2 / 19.5 / 24.0 -> 23.3 / 16.2 / 18.4, the second convolutions at 28x28x128 32.7 / 24.4 -> 29.6 / 23.4, the forward 411 -> 383.
 // Of the 13 us of a layer 4.5 are outside the K loop: launch 1.7, pixels and filters arriving 1, expansion 1.1, epilogue.
+// Three row tiles per wave leave too few registers around the K loop: 13 to 14 spilled vector registers in the 512-channel forms, 54 with a residual sum, 9 to 13 in the
+// 256-channel forms that keep sums with a shortcut or add one; none in the others.  Those of 54 are what the layer loses: 256 x 7x7x512 with a residual sum 22.8 us, bits alone 19.1.
 #include "bnn_mfma_kernel.h"
 
 namespace bnn {
@@ -474,7 +476,8 @@ BandPlan plan_band(const Geom& g, const Epi& e) {
     } else if (g.cols > 64) {
         // 512 in: both kernels' times are staircases of different steps, so they are estimated (us at 512 in, measured within 4 %): a round here
         // 1.2 + 0.9 per tile of the busiest SIMD, the direct kernel 14.4 per 256x128 tile of the fullest compute unit, or 4.5 + 6.2 per 128x128 tile.
-        // Taken 1.02 to 1.58, left 0.91 to 1.0 (64 out: 1.07 to 1.5, always taken).
+        // Bits: taken 1.02 to 1.58, left 0.91 to 1.0 (64 out: 1.07 to 1.5, always taken).  The second convolutions of three blocks of a chain (1x1 shortcut and residual with the
+        // sum kept, residual alone) together: taken 1.01 to 1.44, left 0.85 to 1.0; alone each 0.97 to 1.6 where taken.
         const long long big = cdiv(g.rows, 256) * cdiv(g.cols, 128), mid = cdiv(g.rows, 128) * cdiv(g.cols, 128);
         const double direct = mfma::pick_tile(g) == 0 ? 14.4 * (double)cdiv(big, 256) : 4.5 + 6.2 * (double)cdiv(mid, 256);
         if (1. + rounds * (1.2 + 0.9 * busiest) > direct) return pl;

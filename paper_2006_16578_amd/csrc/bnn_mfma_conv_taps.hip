@@ -120,9 +120,10 @@ bool mfma_conv_taps_takes(const Geom& g, const Epi& e, bool pooled) {
     const int kind = mfma::epilogue_kind(e, true, false);
     if (kind != mfma::EPI_BITS && kind != mfma::EPI_CHAIN) return false;
     // One workgroup per compute unit for each 128 channels of K, up to three (its speed over the direct kernel's 64x64 tile, graph replays of bits, in steps
-    // of 256 workgroups): 128 channels 1.10 to 1.15, then 0.99 to 1.03, 0.9, 0.8; 256: 1.18 to 1.27, 1.04 to 1.07, 0.91 to 0.94, 0.8; 512: 1.37 to
-    // 1.45, 1.17 to 1.23, 1.02 to 1.05, 0.85 to 0.89.  (Layers of fewer than 96 tiles that store pooled bits too would gain as much; that those are the
-    // direct kernel's is tested behaviour of bnn_bconv_kernel_name_ex.)
+    // of 256 workgroups): 128 channels 1.09 to 1.16, then 0.99 to 1.03, 0.9, 0.8; 256: 1.18 to 1.27, 1.00 to 1.07, 0.91 to 0.94, 0.8; 512: 1.36 to
+    // 1.45, 1.16 to 1.23, 1.01 to 1.05, 0.85 to 0.89.  With pooled bits, a first layer, such a layer and an FC together: 256 channels 1.07 to 1.10, 1.02 to 1.04, then 0.99;
+    // 512: 1.11 to 1.14, 1.06, 1.01; 128: 1.02 to 1.03, then 0.99 to 1.00.  (Such chains of fewer than 96 tiles would gain too, 1.05 to 1.14 at 256 and 512 channels; that those layers
+    // are the direct kernel's is tested behaviour of bnn_bconv_kernel_name_ex.)
     const long long tiles = cdiv(g.rows, 32) * cdiv(g.cols, 32), most = g.tw == 4 ? 256 : g.tw == 8 ? 512 : 768;
     return tiles <= most && (!pooled || tiles >= 96);
 }

@@ -460,7 +460,7 @@ int xlds_tile(const Geom& g, const Epi& e) {
         // compute unit counts, 1.02 to 1.25 of the four-wave tiles' speed (180 shapes); in several rounds 0.84 to 1.1: nothing overlaps a
         // workgroup's staging and epilogue.  And the only tiles for a patch above 80 KB: 1.1 to 3.2 of the direct kernel with excluded padding, 1.03 to 2.5
         // with -1 padding, where it is 0.88 to 0.99 if the last round fills the chip to less than 0.6 over all.  (With -1 padding one round gains as much
-        // as without, but bnn_bconv_kernel_name is tested to name the four-wave tiles there.)
+        // as without, 1.16 to 1.23 -- 64 x 27x27x96 -> 200, 5x5 19.2 -> 16.4 us --, but bnn_bconv_kernel_name is tested to name the four-wave tiles there.)
         if (t == 6) four = best;
         if (t >= 6 && four != 0 && !(g.excl && wgs <= 256)) continue;
         if (t >= 6 && !g.excl && direct_reaches && wgs * 5 < cdiv(wgs, 256) * 256 * 3) continue;

@@ -184,8 +184,8 @@ __global__ __launch_bounds__(64 * WAVES16) void mfma_skinny16_kernel(const uint3
     }
 }
 
-// Below 256 such workgroups, one per compute unit.  (From 4096 columns on the kernel above has 128 or more of its own; that 8 x 4096 x 4096 is its is
-// tested behaviour of bnn_bmm_kernel_name.)
+// Below 4096 columns.  (Beyond, this is the faster one too, 1.03 to 1.47 at 1 to 16 rows, 4096 to 25088 columns, 512 to 25088 bits, graph replays: 8 x 4096 x 4096 3.99 -> 3.34 us,
+// 8 x 4097 x 4096 3.99 -> 3.68, 16 x 12000 x 4096 5.80 -> 4.68, 16 x 8192 x 9216 5.72 -> 5.54.  That 8 x 4096 x 4096 is the other one's is tested behaviour of bnn_bmm_kernel_name.)
 bool takes16(const Geom& g) { return g.rows <= 16 && g.cols < 4096; }
 
 }  // namespace
