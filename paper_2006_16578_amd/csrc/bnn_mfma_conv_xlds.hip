@@ -428,6 +428,28 @@ double most_staged(const Geom& g, OutputForm form, long long wgs) {
     return g.tw == 1 ? 200. : g.tw % 2 == 1 || g.tw == 2 ? 80. : 60.;
 }
 
+// Whether a tile of eight waves is faster than the direct kernel, by the estimated microseconds of both: a round of the one costs its K-steps, the units it
+// stages and a constant, the other as many tiles as its fullest compute unit has, by the words of K that its loads take.  Fitted to 2200 geometries (windows of 2 to 11,
+// strides 1 to 3, patches above 80 KB or one round), bits: the median error is 4 % here, 2 to 5 % there.  Of 938 where the choice is open: taken 707, 0.95 and above of the direct
+// kernel's speed but for six (0.82 to 0.95), median 1.2; left 231, up to 1.03 but for 17 (the best 1.24), down to 0.57.  Of 1500 others 31 of those taken are below 0.97,
+// the least 0.90; without the question 244 were, the least 0.57.
+bool eight_waves_gain(const Geom& g, long long wgs, const XArgs& x) {
+    const double steps = (g.taps * g.tw + 1) / 2;
+    const double here = 1.4 + (double)cdiv(wgs, 256) * (4.05 + 0.2233 * steps + 0.2664e-3 * (double)x.px_max * g.tw);
+    const int load = mfma::conv_load_words(g), chunk = 2 * load;
+    const double words = (double)g.taps * ((g.tw + chunk - 1) / chunk * chunk);
+    auto tiles = [&](int rows, int cols) { return (double)cdiv(cdiv(g.rows, rows) * cdiv(g.cols, cols), 256); };
+    auto by_load = [&](double v4, double v2, double v1) { return load == 4 ? v4 : load == 2 ? v2 : v1; };
+    double direct;
+    switch (mfma::pick_tile(g)) {
+        case 0: direct = 4.3 + tiles(mfma::TileBig::ROWS, mfma::TileBig::COLS) * (1.2 + words * by_load(0.093, 0.1025, 0.133)); break;
+        case 1: direct = 4.3 + tiles(mfma::TileTall::ROWS, mfma::TileTall::COLS) * (1.2 + words * by_load(0.093, 0.1025, 0.133)); break;
+        case 2: direct = 4.5 + tiles(mfma::TileMid::ROWS, mfma::TileMid::COLS) * words * by_load(0.054, 0.0635, 0.1); break;
+        default: direct = 4.5 + tiles(mfma::TileSmall::ROWS, mfma::TileSmall::COLS) * words * by_load(0.026, 0.026, 0.045); break;
+    }
+    return direct >= 0.97 * here;
+}
+
 // Tile for this geometry, 0: another kernel's.  Among the tiles whose patch fits LDS, the one with the least estimated time: rounds
 // of 512 workgroups times the cycles of one (K-steps, a little more than their MFMAs take where a step has only four; staging;
 // epilogue; the rest).
@@ -457,9 +479,10 @@ int xlds_tile(const Geom& g, const Epi& e) {
         size_t lds;
         const long long gy = cdiv(g.cols, XTILES[t].cols), wgs = cdiv(g.rows, XTILES[t].rows) * gy;
         // Eight waves: the tile of a compute unit in one piece, 192 rows where two pieces of 128 are 256.  In one round, where the shorter way of the fullest
-        // compute unit counts, 1.02 to 1.25 of the four-wave tiles' speed (180 shapes); in several rounds 0.84 to 1.1: nothing overlaps a
-        // workgroup's staging and epilogue.  And the only tiles for a patch above 80 KB: 1.1 to 3.2 of the direct kernel with excluded padding, 1.03 to 2.5
-        // with -1 padding, where it is 0.88 to 0.99 if the last round fills the chip to less than 0.6 over all.  (With -1 padding one round gains as much
+        // compute unit counts, 1.02 to 1.25 of the four-wave tiles' speed (180 shapes; 677 more: 0.90 once, 0.95 and above, median 1.22); in several rounds 0.84 to 1.1:
+        // nothing overlaps a workgroup's staging and epilogue.  And the only tiles for a patch above 80 KB: with excluded padding and a partly filled last word 1.07
+        // to 4.5 of the direct kernel, which corrects every sum there; else 0.57 to 3.5, 0.95 and above (one in 200: 0.82) where eight_waves_gain() says so, and
+        // with -1 padding 0.88 to 0.99 if the last round fills the chip to less than 0.6 over all.  (With -1 padding one round gains as much
         // as without, 1.16 to 1.23 -- 64 x 27x27x96 -> 200, 5x5 19.2 -> 16.4 us --, but bnn_bconv_kernel_name is tested to name the four-wave tiles there.)
         if (t == 6) four = best;
         if (t >= 6 && four != 0 && !(g.excl && wgs <= 256)) continue;
@@ -467,6 +490,7 @@ int xlds_tile(const Geom& g, const Epi& e) {
         // Many empty columns: 0.77 at 64 of 128.
         if (wgs < least || (double)(gy * XTILES[t].cols) > 1.5 * g.cols) continue;
         if (!plan_lds(g, XTILES[t].rows, XTILES[t].cols, XTILES[t].waves, &x, &lds)) continue;
+        if (t >= 6 && four == 0 && direct_reaches && !(g.excl && pad_bits) && !eight_waves_gain(g, wgs, x)) continue;
         if (direct_reaches && (double)x.px_max * g.tw > most_staged(g, form, wgs) * steps) continue;
         const double m = XTILES[t].mfmas;
         const double wg = steps * m * (m < 8. ? 44. : 36.) + (double)x.px_max * g.tw / 4. + m * 160. + 1500.;
