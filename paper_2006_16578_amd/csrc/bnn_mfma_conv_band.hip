@@ -444,6 +444,7 @@ BandPlan plan_band(const Geom& g, const Epi& e) {
     const int first = (int)cdiv((long long)ntiles * gy, (long long)slots * (rw * 3 + spare));
     double best = 0.;
     int nx = 0, rounds = 0, most = 0, busiest = 0;
+    long long span = 0;                              // cells of a band
     for (int r = first; r <= first + 2; ++r) {
         const int n = (int)min((long long)ntiles, (long long)slots * r / gy);
         if (n == 0) continue;
@@ -456,11 +457,16 @@ BandPlan plan_band(const Geom& g, const Epi& e) {
         const size_t exchange = pl.wk == 2 ? (size_t)(rw * 2 * mt + 4) * 256 : 0, start_at = cells > exchange ? cells : exchange;
         const size_t bytes = start_at * 16 + 8 * pl.wk * START_PITCH * 4;
         if (bytes > BAND_LDS * pl.waves / 8 || (nx != 0 && cost >= best)) continue;
-        best = cost; nx = n; rounds = r; most = t; busiest = per_simd;
+        best = cost; nx = n; rounds = r; most = t; busiest = per_simd; span = band_cells(g, 32LL * t);
         pl.mt = mt; pl.lds_bytes = bytes; pl.ba.start_at = (int)start_at;
     }
     if (nx == 0) return pl;
-    // Where this kernel is the faster one (its speed over the patch and direct kernels'; 7x7 to 28x28, bands of every length up to three rounds):
+    // Where this kernel is the faster one (its speed over the patch and direct kernels'; 7x7 to 28x28, bands of every length up to three rounds, and bits of 1124
+    // random layers of 5x5 to 200x200).  Beyond a round or two both kernels' times are staircases of different steps, so they are estimated in us: the direct kernel by the
+    // tiles of its fullest compute unit, a round here by the tiles of the busiest SIMD and the cells of a band (median errors 1 to 2 %; 4 % at 512 channels).
+    const int tile = mfma::pick_tile(g);
+    const long long tile_rows = tile == 0 ? 256 : tile == 1 ? 512 : tile == 2 ? 128 : 64, tile_cols = tile == 0 || tile == 2 ? 128 : 64;
+    const double fullest = (double)cdiv(cdiv(g.rows, tile_rows) * cdiv(g.cols, tile_cols), 256);
     // (A chain's decision may depend on the geometry alone, the same for every block of it: Epi::sums_tiled.  pick_tile() depends on excl only where
     // conv_stages_through_lds() does, from 320 words of K on; here there are 144 at most.)
     if (g.tw == 4) {
@@ -473,14 +479,20 @@ BandPlan plan_band(const Geom& g, const Epi& e) {
         // 256 out with -1 padding, two rounds of 25 tiles: 1.25 to 1.32 here too (26 tiles 1.25, 27 and 28 1.17), but that 128 x 28x28x256 -> 256, which
         // is one of these, is the direct kernel's is tested behaviour of bnn_bconv_kernel_name.
         if (pl.kind == mfma::EPI_BITS && !g.excl && g.cols == 256 && rounds == 2 && most == 25) return pl;
+        // The 25 random layers of 495 that this leaves or nearly leaves: 0.95 to 1.03, five rounds and wide images above all (19 x 146x139x256 -> 128 44.7 -> 47.0 us); chains of 61
+        // to 64 tiles, three rounds, 0.955 to 0.985 (488 x 16x16x256), 60 tiles 1.07, 66 1.12.
+        const double direct = tile == 0 ? 3.1 + 6.8 * fullest : tile == 1 ? 2.5 + 6.9 * fullest : tile == 2 ? 3.9 + 3.1 * fullest : 2.6 + 1.48 * fullest;
+        const double corrects = pl.kind == mfma::EPI_BITS && g.excl ? 1.06 : 1.;        // (a chain's blocks choose alike)
+        if (1.4 + rounds * (2.4 + 0.643 * busiest + 0.154e-3 * (double)span) > 1.02 * corrects * direct) return pl;
     } else if (g.cols > 64) {
-        // 512 in: both kernels' times are staircases of different steps, so they are estimated (us at 512 in, measured within 4 %): a round here
-        // 1.2 + 0.9 per tile of the busiest SIMD, the direct kernel 14.4 per 256x128 tile of the fullest compute unit, or 4.5 + 6.2 per 128x128 tile.
-        // Bits: taken 1.02 to 1.58, left 0.91 to 1.0 (64 out: 1.07 to 1.5, always taken).  The second convolutions of three blocks of a chain (1x1 shortcut and residual with the
+        // 512 in: a round here 1.2 + 0.9 per tile of the busiest SIMD, the direct kernel 14.4 per 256x128 tile of the fullest compute unit, or 4.5 + 6.2 per 128x128 tile.
+        // Bits: taken 1.02 to 1.58, left 0.91 to 1.0.  The second convolutions of three blocks of a chain (1x1 shortcut and residual with the
         // sum kept, residual alone) together: taken 1.01 to 1.44, left 0.85 to 1.0; alone each 0.97 to 1.6 where taken.
-        const long long big = cdiv(g.rows, 256) * cdiv(g.cols, 128), mid = cdiv(g.rows, 128) * cdiv(g.cols, 128);
-        const double direct = mfma::pick_tile(g) == 0 ? 14.4 * (double)cdiv(big, 256) : 4.5 + 6.2 * (double)cdiv(mid, 256);
+        const double direct = tile == 0 ? 14.4 * fullest : 4.5 + 6.2 * (double)cdiv(cdiv(g.rows, 128) * cdiv(g.cols, 128), 256);
         if (1. + rounds * (1.2 + 0.9 * busiest) > direct) return pl;
+    } else if (tile == 1) {
+        // 64 out: 1.0 to 1.74, but 0.92 and 0.97 for two of 86 (28 x 94x94x512 -> 64 30.3 -> 33.1 us).
+        if (1.7 + rounds * (1.9 + 0.72 * busiest + 1e-3 * (double)span) > 1.06 * (1.5 + 13.7 * fullest)) return pl;
     }
     pl.ba.wp1 = g.W + 1; pl.ba.hp1 = g.H + 1;
     pl.ba.div_wp1 = make_fastdiv((uint32_t)(g.W + 1)); pl.ba.div_hp1 = make_fastdiv((uint32_t)(g.H + 1));

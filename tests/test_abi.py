@@ -107,6 +107,21 @@ def test_net_workspace_plan():
     assert big >= 2 * 64 * 8 * 8 * 64 * 2 + 2 * 64 * 8 * 8 * 8
 
 
+def test_bands_where_they_gain():
+    # steps of the band kernel and of the direct kernel's tiles: where a round more costs more than the direct kernel's next tile, the direct kernel
+    import paper_2006_16578_amd as b
+
+    def band(B, h, w, C, O, **kw):
+        return "_band_" in b.bconv_kernel_name(B, h, w, C, O, 3, 1, 1, **kw)
+
+    for pad_mode in (0, 1):
+        chain = dict(residual=True, keep_sum=True, pad_mode=pad_mode)
+        assert [band(B, 16, 16, 256, 256, **chain) for B in (480, 488, 512, 528)] == [True, False, False, True]
+        assert band(24, 14, 14, 256, 256) == band(24, 14, 14, 256, 256, **chain) == False
+    assert not band(19, 146, 139, 256, 128) and not band(21, 192, 192, 256, 64) and band(256, 14, 14, 256, 256) and band(64, 56, 56, 256, 128)
+    assert not band(28, 94, 94, 512, 64) and band(171, 14, 14, 512, 64) and band(195, 54, 54, 512, 64)
+
+
 def test_eight_wave_tiles_where_they_gain():
     # patches above 80 KB: the direct kernel where it was measured the faster one (0.66 to 0.8 of its time), the eight-wave tiles where those are (1.1 to 2.5),
     # always for a partly filled last word with excluded padding
