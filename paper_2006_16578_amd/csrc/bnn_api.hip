@@ -416,7 +416,7 @@ static int bmm_panels_common(const uint32_t* Ap, const uint32_t* Bp, int32_t* C,
     g.tw = kw8;
     Epi e = {};
     e.out = C; e.ldc = ldc; e.thr = thr; e.bits = Cbits_p; e.ldbits_w = (words(N) + 7) / 8 * 8;
-    return launch_mfma_wide_panels(Ap, Bp, g, e, static_cast<hipStream_t>(stream));
+    return launch_mfma_bits_panels(Ap, Bp, g, e, static_cast<hipStream_t>(stream));
 }
 int bnn_bmm_panels(const uint32_t* Ap, const uint32_t* Bp, int32_t* C, int M, int N, int K, int ldc, void* stream) {
     if (!C) return BNN_ERR_INVALID_ARG;

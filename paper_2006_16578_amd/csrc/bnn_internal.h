@@ -167,9 +167,11 @@ bool mfma_skinny_takes(const Geom& g);
 const char* describe_mfma_skinny(const Geom& g);
 int launch_mfma_skinny(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 // Large matrix products: 256 x 256 workgroup tiles whose operands are expanded once, on their way into LDS.
-bool mfma_wide_takes(const Geom& g, const Epi& e);
-int launch_mfma_wide(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
-int launch_mfma_wide_panels(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
+enum BitsChoice { BITS_NONE = 0, BITS_256x256, BITS_256x128, BITS_192x128, BITS_128x128, BITS_128x128W8, BITS_128x64, BITS_K64x64, BITS_K32x32 };
+BitsChoice mfma_bits_choice(const Geom& g, const Epi& e, int tile);       // tile: pick_tile's
+int launch_mfma_bits(BitsChoice tile, const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
+const char* describe_mfma_bits(BitsChoice tile);
+int launch_mfma_bits_panels(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 // 3x3 stride-1 pad-1 convolutions with at most 128 channels in and out: filters resident in LDS, wave-private input patches.
 bool mfma_conv_patch_takes(const Geom& g, const Epi& e);
 const char* describe_mfma_conv_patch(const Geom& g);

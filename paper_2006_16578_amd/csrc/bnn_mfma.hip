@@ -32,7 +32,7 @@ bool mfma_conv_pools(const Geom& g, const Epi& e) {
 int launch_mfma(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
     if (mfma_skinny_takes(g)) return launch_mfma_skinny(A, B, g, e, s);
     const int tile = mfma::pick_tile(g, &e);
-    if (tile == 0 && mfma_wide_takes(g, e)) return launch_mfma_wide(A, B, g, e, s);
+    if (const BitsChoice bt = mfma_bits_choice(g, e, tile)) return launch_mfma_bits(bt, A, B, g, e, s);
     if (!g.conv) {
         if (!g.b_tiled && staged_ok(g, tile)) {
             switch (tile) {
@@ -85,7 +85,7 @@ const char* describe_mfma(const Geom& g, bool int32_out, int flags) {
     };
     e.sums_tiled = (flags & (BNN_CONV_RESIDUAL | BNN_CONV_KEEP_SUM)) && g.cols % 32 == 0 ? 1 : 0;
     const int tile = mfma::pick_tile(g, &e);
-    if (tile == 0 && mfma_wide_takes(g, e)) return "mfma_fp4_bmm_xlds_wg256x256";
+    if (const BitsChoice bt = mfma_bits_choice(g, e, tile)) return describe_mfma_bits(bt);
     const bool pools = (flags & BNN_CONV_POOL2) && mfma_conv_pools(g, e);
     if (!pools && mfma_conv_band_takes(g, e)) return "mfma_fp4_conv3x3_band_wg64";
     if (mfma_conv_patch_takes(g, e)) return describe_mfma_conv_patch(g);

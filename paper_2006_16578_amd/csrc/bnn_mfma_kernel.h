@@ -67,6 +67,17 @@ __device__ __forceinline__ uint4 expand_unit(uint32_t w, uint32_t c2) {
                       (w & 0x88888888u) | c2);
 }
 
+// Four packed words as four operands of bits in {0, 1}: operand V of four holds bit V of every nibble, left where it stands, so that a register costs
+// one instruction.  There it means 0.5, 1 or 2 (bits 0, 1, 2; bit 3 is moved to bit 2's place) or zero; where both operands hold bit V, the
+// product of two set bits is 0.25, 1, 4, 4, and scale_of_bit(V), the exponent byte of a factor 16, 4, 1, 1, makes it 4.
+template <int V>
+__device__ __forceinline__ uint4 bit_unit(const uint4& w) {
+    if constexpr (V == 3) return make_uint4((w.x >> 1) & 0x44444444u, (w.y >> 1) & 0x44444444u, (w.z >> 1) & 0x44444444u, (w.w >> 1) & 0x44444444u);
+    constexpr uint32_t m = 0x11111111u << V;
+    return make_uint4(w.x & m, w.y & m, w.z & m, w.w & m);
+}
+__device__ __forceinline__ constexpr int scale_of_bit(int v) { return v == 0 ? 131 : v == 1 ? 129 : 127; }
+
 __device__ __forceinline__ v8i as_operand(const uint4& u) {
     v8i r;
     r[0] = (int)u.x; r[1] = (int)u.y; r[2] = (int)u.z; r[3] = (int)u.w;
@@ -392,10 +403,12 @@ __device__ __forceinline__ void column_thresholds(int (&thi)[NT], bool (&cok)[NT
 // one v_cmp per accumulator register gives two packed words.
 // PANELS: the packed output is laid out in panels of 8 words (word wi of row `row` at ((wi / 8) * rows + row) * 8 + wi % 8).
 // POOL: rows in the order of Geom::pool2, the windows' bits are stored too.
-template <int MT, int NT, bool PANELS = false, bool POOL = false>
+// before(i): called ahead of row tile i (a kernel whose sums are not finished until then).
+struct Nothing { __device__ __forceinline__ void operator()(int) const {} };
+template <int MT, int NT, bool PANELS = false, bool POOL = false, class Before = Nothing>
 __device__ __forceinline__ void epilogue_bits(v16f (&acc)[MT][NT], const long long m0, const int n0, const int lane,
                                               const Geom& g, const Epi& e, const int corr_all, const int (&thi)[NT],
-                                              const bool (&cok)[NT]) {
+                                              const bool (&cok)[NT], const Before& before = Before()) {
     float thf[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) thf[j] = cok[j] ? (float)thi[j] + (float)corr_all : __builtin_inff();
@@ -403,6 +416,7 @@ __device__ __forceinline__ void epilogue_bits(v16f (&acc)[MT][NT], const long lo
     for (int i = 0; i < MT; ++i) {
         const long long rbase = m0 + 32 * i;
         if (rbase >= g.rows) break;                          // uniform per wave
+        before(i);
         uint32_t wout[NT];
 #pragma unroll
         for (int j = 0; j < NT; ++j) wout[j] = 0u;
@@ -450,9 +464,9 @@ __device__ __forceinline__ void epilogue_bits(v16f (&acc)[MT][NT], const long lo
 // Sums only (int32, or the same values as fp32): blocks of 32 x 32 that lie inside the matrix are stored without
 // per-element tests, from a scalar base per accumulator register (its row) plus one 32-bit offset per lane (its
 // column and half) -- no vector address arithmetic; the edge blocks test every element.
-template <int MT, int NT>
+template <int MT, int NT, class Before = Nothing>
 __device__ __forceinline__ void epilogue_sums(v16f (&acc)[MT][NT], const long long m0, const int n0, const int lane,
-                                              const Geom& g, const Epi& e, const int corr_all) {
+                                              const Geom& g, const Epi& e, const int corr_all, const Before& before = Before()) {
     const int l32 = lane & 31;
     const int half = lane >> 5;
     const long long m0u = ((long long)__builtin_amdgcn_readfirstlane((int)(m0 >> 32)) << 32) |
@@ -463,6 +477,7 @@ __device__ __forceinline__ void epilogue_sums(v16f (&acc)[MT][NT], const long lo
     for (int i = 0; i < MT; ++i) {
         const long long rbase = m0u + 32 * i;
         if (rbase >= g.rows) break;
+        before(i);
         const bool rows_in = rbase + 32 <= g.rows;
 #pragma unroll
         for (int j = 0; j < NT; ++j) {

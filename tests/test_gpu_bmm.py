@@ -389,3 +389,39 @@ def test_skinny_16_rows(bnn, orc, M, N, K):
     packed = orc.threshold_pack(ref.reshape(1, 1, M, N), tau).reshape(M, -1)
     want[:, :packed.shape[1]] = packed
     assert np.array_equal(bits, want)
+
+
+# The kernels that multiply bits as {0, 1}, on each of their tiles: last row and column tiles of one row or column and one short of whole, K off every word, granule,
+# chunk and slab (an odd and an even number of 256-bit chunks, one slab, the last one partly filled), wider leading dimensions, and output words beyond the last
+# column -- whole tiles of them.
+BITS = [(129, 1, 2426, 0, "wg32x32"), (160, 505, 8310, 1, "wg32x32"), (191, 65, 1281, 1, "wg32x32"), (161, 31, 2049, 0, "wg64x64"), (142, 7, 1262, 0, "wg64x64"),
+        (4673, 40, 6064, 0, "wg64x64"), (197, 4133, 1285, 1, "lds_wg128x64"), (912, 4258, 523, 0, "lds_wg128x64"), (16001, 513, 3333, 0, "lds_wg128x64"),
+        (2738, 1117, 520, 0, "lds_wg128x128"), (1921, 2047, 2304, 1, "lds_wg128x128"), (3204, 1848, 1793, 0, "lds_wg192x128"), (3001, 2047, 3500, 1, "lds_wg192x128"),
+        (4097, 3001, 3620, 0, "lds_wg256x128"), (2700, 2218, 3876, 1, "lds_wg256x128"), (3841, 4000, 1300, 0, "xlds_wg256x256"),
+        (4353, 3001, 2070, 0, "xlds_wg256x256"), (4122, 3046, 517, 1, "xlds_wg256x256")]
+
+
+@pytest.mark.parametrize("M,N,K,int32_out,kernel", BITS)
+def test_bits_as_zero_and_one(bnn, orc, M, N, K, int32_out, kernel):
+    assert bnn.bmm_kernel_name(M, N, K, int32_out=bool(int32_out)) == "mfma_fp4_bmm_" + kernel
+    rng = np.random.default_rng(M + N + K)
+    kw = bnn.nwords(K)
+    A, B = (np.zeros((r, bnn.round_up(kw, 4) + x), np.uint32) for r, x in ((M, 0), (N, 8)))
+    A[:, :kw], B[:, :kw] = wl.random_bits(rng, (M,), K), wl.random_bits(rng, (N,), K)
+    A[0, :kw], B[0, :kw] = A[M - 1, :kw], 0             # a row of A twice, a column of -1
+    pm = lambda X: torch.from_numpy(np.unpackbits(X[:, :kw].copy().view(np.uint8), axis=1, bitorder="little")[:, :K].astype(np.float32) * 2 - 1).cuda()
+    ref = host(pm(A) @ pm(B).t().contiguous()).astype(np.int32)           # exact: whole numbers below 2^24
+    A, B = to_dev(A), to_dev(B)
+    if int32_out:
+        out = torch.full((M, N + 12), -77, dtype=torch.int32, device="cuda")
+        got = host(bnn.bmm(A, B, K, out=out))
+        assert np.array_equal(got[:, :N], ref) and (got[:, N:] == -77).all()
+        return
+    tau = rng.integers(-60, 61, size=N).astype(np.int32)
+    tau[::7], tau[3::5] = -2 ** 31, 2 ** 31 - 1
+    for extra in (0, 4, 12):
+        bits = words(bnn.bmm_thr(A, B, to_dev(tau), K, ldcb_w=bnn.round_up(bnn.nwords(N), 4) + extra))
+        want = np.zeros_like(bits)
+        packed = np.packbits(ref >= tau, axis=1, bitorder="little")
+        want.view(np.uint8)[:, :packed.shape[1]] = packed
+        assert np.array_equal(bits, want)
