@@ -1,4 +1,4 @@
-"""Builds libbnn.so (HIP, gfx950 only) in-tree next to this file.
+"""Builds libbnn.so (HIP, gfx950 only) and _native.so (the binding's native module, host code) in-tree next to this file.
 
     python -m paper_2006_16578_amd.build [--force]
 
@@ -16,6 +16,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libbnn.so")
+NATIVE = os.path.join(HERE, "_native.so")
+CXX = os.environ.get("CXX", "g++")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 SOURCES = ["bnn_api.hip", "bnn_valu.hip", "bnn_mfma.hip", "bnn_mfma_conv_v4.hip", "bnn_mfma_conv_v2.hip",
            "bnn_mfma_conv_v1.hip", "bnn_mfma_conv_v4_stream.hip", "bnn_mfma_conv_v2_stream.hip",
@@ -56,10 +58,29 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def _compile_native(force: bool) -> None:
+    """The binding's native module: compiled against torch's headers, resolved against the torch that the process has loaded."""
+    src = os.path.join(CSRC, "bnn_python.cpp")
+    newest = max(os.path.getmtime(p) for p in [src] + _headers())
+    if not force and os.path.exists(NATIVE) and os.path.getmtime(NATIVE) >= newest:
+        return
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = NATIVE + ".tmp.%d" % os.getpid()
+    subprocess.check_call([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(root, "include"),
+                           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), src, "-o", tmp, "-L" + os.path.join(root, "lib"),
+                           "-lc10", "-ltorch_cpu", "-ltorch_python"])
+    os.replace(tmp, NATIVE)
+
+
 def build(force: bool = False, jobs: int = 8) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        native = ex.submit(_compile_native, force)
         objs = list(ex.map(lambda s: _compile(s, force), SOURCES))
+        native.result()
     if force or not os.path.exists(LIB) or any(os.path.getmtime(o) > os.path.getmtime(LIB) for o in objs):
         tmp = LIB + ".tmp.%d" % os.getpid()
         subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp] + objs)
