@@ -425,3 +425,14 @@ def test_bits_as_zero_and_one(bnn, orc, M, N, K, int32_out, kernel):
         packed = np.packbits(ref >= tau, axis=1, bitorder="little")
         want.view(np.uint8)[:, :packed.shape[1]] = packed
         assert np.array_equal(bits, want)
+
+
+# Few rows: 16 columns to a workgroup while that is at most a workgroup per compute unit (4096 columns), 32 beyond; up to 16 rows always 16.  Row counts around the row
+# tiles, columns around 4096, K off every group and chunk, less than one chunk per wave and several; thresholds beyond every sum, sums of wider leading dimensions.
+@pytest.mark.parametrize("M,N,K", [(16, 4096, 700), (1, 4097, 4100), (13, 9001, 129), (17, 4095, 513), (31, 4096, 8200), (32, 4097, 4096), (17, 5003, 31), (33, 4096, 1000),
+                                   (48, 4001, 5000), (64, 4099, 600), (65, 4090, 2049), (113, 4096, 96), (128, 4097, 1025), (100, 10, 20000)])
+def test_skinny_columns(bnn, orc, M, N, K):
+    name = "m16" if M <= 16 and N < 4096 else "m32" if M <= 32 else "m64" if M <= 64 else "m128"
+    assert bnn.bmm_kernel_name(M, N, K) == "mfma_fp4_bmm_skinny_" + name
+    test_bits_as_zero_and_one(bnn, orc, M, N, K, 0, "skinny_" + name)
+    test_bits_as_zero_and_one(bnn, orc, M, N, K, 1, "skinny_" + name)
