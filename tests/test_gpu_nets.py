@@ -514,6 +514,21 @@ def test_bwn_first_layer_pixel_records(bnn, orc, shape):
     assert np.array_equal(got[~covers], only[~covers]) and not got[covers].any()
 
 
+# weights and thresholds of 64 channels at a time go through LDS: groups one channel short, whole and one over, for workgroups of one
+# and of two groups
+@pytest.mark.parametrize("k,st", [(3, 1), (3, 2), (5, 1), (5, 2)])
+@pytest.mark.parametrize("O", [2, 63, 64, 127, 129, 191])
+def test_bwn_first_layer_channel_groups(bnn, orc, O, k, st):
+    rng = np.random.default_rng(O * 10 + k + st)
+    wb = wl.random_bits(rng, (O, k, k), 3)
+    thr = rng.integers(-900, 901, size=O).astype(np.float32)
+    x = rng.integers(-300, 301, size=(2, 20, 11, 3)).astype(np.float32)
+    ref = orc.bwn_conv_f32(x, wb, 3, st, 1)
+    assert np.array_equal(words(bnn.bwn_conv_thr(to_dev(x), to_dev(wb), to_dev(thr), 3, st, 1)), orc.pack_f32(ref, thr))
+    bits, y = bnn.bwn_conv_thr(to_dev(x), to_dev(wb), to_dev(thr), 3, st, 1, want_f32=True)
+    assert np.array_equal(host(y), ref) and np.array_equal(words(bits), orc.pack_f32(ref, thr))
+
+
 def test_bwn_exact_cases(bnn, orc):
     # (a) integer inputs: the three-way bf16 split is exact and sums below 2^24 never round, so the fp32
     # result equals the oracle's bit for bit; (b) isolated values with all 24 significand bits set (at most
