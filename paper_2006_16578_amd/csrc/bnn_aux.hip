@@ -128,8 +128,8 @@ int launch_pack(PackJob j0, const PackJob* second, const TH* thr, TH thr0, hipSt
     const long long b0 = cdiv(j0.words, per_block), b1 = second != nullptr ? cdiv(j1.words, per_block) : 0;
     if (b0 + b1 >= (1LL << 31)) return BNN_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)(b0 + b1));
-    if (deep) hipLaunchKernelGGL((pack_kernel<T, TH, SCALAR_THR, UMAX>), grid, dim3(256), 0, s, j0, j1, (unsigned)b0, thr, thr0);
-    else hipLaunchKernelGGL((pack_kernel<T, TH, SCALAR_THR, 1>), grid, dim3(256), 0, s, j0, j1, (unsigned)b0, thr, thr0);
+    if (deep) launch((pack_kernel<T, TH, SCALAR_THR, UMAX>), grid, dim3(256), 0, s, j0, j1, (unsigned)b0, thr, thr0);
+    else launch((pack_kernel<T, TH, SCALAR_THR, 1>), grid, dim3(256), 0, s, j0, j1, (unsigned)b0, thr, thr0);
     return check_launch();
 }
 
@@ -719,14 +719,14 @@ int launch_sign_pack2_f32(const float* x0, uint32_t* bits0, long long rows0, int
 int launch_tile_b(const uint32_t* B, uint32_t* Bt, int N, int ldb_w, hipStream_t s) {
     const int upr = ldb_w / 4;
     const long long nunits = cdiv(N, 32) * 32 * (long long)upr;
-    hipLaunchKernelGGL(tile_b_kernel, dim3((unsigned)cdiv(nunits, 256)), dim3(256), 0, s, reinterpret_cast<const uint4*>(B),
+    launch(tile_b_kernel, dim3((unsigned)cdiv(nunits, 256)), dim3(256), 0, s, reinterpret_cast<const uint4*>(B),
                        reinterpret_cast<uint4*>(Bt), N, upr, nunits);
     return check_launch();
 }
 
 int launch_panels_from_rows(const uint32_t* X, uint32_t* Xp, long long rows, int K, int ldx_w, hipStream_t s) {
     const long long nunits = cdiv(K, 256) * rows * 2;
-    hipLaunchKernelGGL(panels_from_rows_kernel, dim3((unsigned)cdiv(nunits, 256)), dim3(256), 0, s, X, reinterpret_cast<uint4*>(Xp),
+    launch(panels_from_rows_kernel, dim3((unsigned)cdiv(nunits, 256)), dim3(256), 0, s, X, reinterpret_cast<uint4*>(Xp),
                        rows, K, ldx_w, nunits);
     return check_launch();
 }
@@ -734,27 +734,27 @@ int launch_panels_from_rows(const uint32_t* X, uint32_t* Xp, long long rows, int
 int launch_rows_from_panels(const uint32_t* Xp, uint32_t* X, long long rows, int K, int ldx_w, hipStream_t s) {
     const int upr = ldx_w / 4;
     const long long nunits = rows * upr;
-    hipLaunchKernelGGL(rows_from_panels_kernel, dim3((unsigned)cdiv(nunits, 256)), dim3(256), 0, s,
+    launch(rows_from_panels_kernel, dim3((unsigned)cdiv(nunits, 256)), dim3(256), 0, s,
                        reinterpret_cast<const uint4*>(Xp), reinterpret_cast<uint4*>(X), rows, (int)cdiv(K, 256), upr, nunits);
     return check_launch();
 }
 
 int launch_probe_stride(const uint32_t* buf, long long* cycles, int stride_bytes, int rows, int iters, int dependent,
                         hipStream_t s) {
-    hipLaunchKernelGGL(probe_stride_kernel, dim3(1), dim3(64), 0, s, buf, cycles, stride_bytes, rows, iters, dependent);
+    launch(probe_stride_kernel, dim3(1), dim3(64), 0, s, buf, cycles, stride_bytes, rows, iters, dependent);
     return check_launch();
 }
 
 int launch_unpack_i32(const uint32_t* bits, int32_t* out, long long rows, int cols, int ldb_w, int ldo, hipStream_t s) {
     dim3 grid((unsigned)min((long long)cdiv(cols, 256), 64LL), (unsigned)min(rows, 65535LL));
-    hipLaunchKernelGGL(unpack_kernel, grid, dim3(256), 0, s, bits, out, rows, cols, ldb_w, ldo);
+    launch(unpack_kernel, grid, dim3(256), 0, s, bits, out, rows, cols, ldb_w, ldo);
     return check_launch();
 }
 
 int launch_maxpool_or(const uint32_t* in, uint32_t* out, int N, int H, int W, int C, int win, int stride, hipStream_t s) {
     const int P = (H - win) / stride + 1, Q = (W - win) / stride + 1, cw = (C + 31) / 32;
     const long long n = (long long)N * P * Q * cw;
-    hipLaunchKernelGGL(maxpool_or_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, in, out, n, H, W, cw, P, Q, win, stride);
+    launch(maxpool_or_kernel, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, in, out, n, H, W, cw, P, Q, win, stride);
     return check_launch();
 }
 
@@ -771,7 +771,7 @@ int launch_conv_f32_thr(const float* x, const float* w, const float* thr, float*
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (attr != hipSuccess) return BNN_ERR_DEVICE;
     }
-    hipLaunchKernelGGL(conv_f32_kernel, grid, dim3(256), lds_bytes, s, x, w, thr, y, bits, N, H, W, C, O, k, stride, pad, P,
+    launch(conv_f32_kernel, grid, dim3(256), lds_bytes, s, x, w, thr, y, bits, N, H, W, C, O, k, stride, pad, P,
                        Q);
     return check_launch();
 }
@@ -782,22 +782,22 @@ int launch_head_f32(const uint32_t* bits, const float* w, float* y, int32_t* poo
     if (pooled != nullptr) {
         const int cw = (C + 31) / 32;
         const long long items = (long long)N * cw;
-        if (items < (1 << 18) || cw < 8) hipLaunchKernelGGL(head_pool_kernel<16>, dim3((unsigned)cdiv(items, 16)), dim3(256), 0, s, bits, pooled, N, HW, C);
-        else hipLaunchKernelGGL(head_pool_kernel<4>, dim3((unsigned)cdiv(items, 64)), dim3(256), 0, s, bits, pooled, N, HW, C);
+        if (items < (1 << 18) || cw < 8) launch(head_pool_kernel<16>, dim3((unsigned)cdiv(items, 16)), dim3(256), 0, s, bits, pooled, N, HW, C);
+        else launch(head_pool_kernel<4>, dim3((unsigned)cdiv(items, 64)), dim3(256), 0, s, bits, pooled, N, HW, C);
         const dim3 grid((unsigned)cdiv(N, 32), (unsigned)cdiv(J, 32));
         const bool vec = C % 4 == 0 && ((reinterpret_cast<uintptr_t>(w) | reinterpret_cast<uintptr_t>(pooled)) & 15u) == 0;
         constexpr size_t tiles = (size_t)FC_WAVES * 16 * 64 * sizeof(float);
-        auto launch = [&](auto steps) {
+        auto project = [&](auto steps) {
             constexpr int STEPS = decltype(steps)::value;
             static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&head_fc_kernel<true, STEPS>),
                                                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
             if (attr != hipSuccess) return (int)BNN_ERR_DEVICE;
             const size_t operands = (size_t)64 * fc_pitch(C, 64 * STEPS) * sizeof(float);
-            hipLaunchKernelGGL((head_fc_kernel<true, STEPS>), grid, dim3(64 * FC_WAVES), operands > tiles ? operands : tiles, s, pooled, w, y, N, HW, C, J);
+            launch((head_fc_kernel<true, STEPS>), grid, dim3(64 * FC_WAVES), operands > tiles ? operands : tiles, s, pooled, w, y, N, HW, C, J);
             return check_launch();
         };
-        if (vec) return (long long)grid.x * grid.y > 256 ? launch(std::integral_constant<int, 4>{}) : launch(std::integral_constant<int, 8>{});
-        hipLaunchKernelGGL((head_fc_kernel<false, 8>), grid, dim3(64 * FC_WAVES), tiles, s, pooled, w, y, N, HW, C, J);
+        if (vec) return (long long)grid.x * grid.y > 256 ? project(std::integral_constant<int, 4>{}) : project(std::integral_constant<int, 8>{});
+        launch((head_fc_kernel<false, 8>), grid, dim3(64 * FC_WAVES), tiles, s, pooled, w, y, N, HW, C, J);
         return check_launch();
     }
     const size_t lds_bytes = (size_t)2 * C * HEAD_LD * sizeof(float);
@@ -806,7 +806,7 @@ int launch_head_f32(const uint32_t* bits, const float* w, float* y, int32_t* poo
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (attr != hipSuccess) return BNN_ERR_DEVICE;
     }
-    hipLaunchKernelGGL(head_kernel, dim3((unsigned)cdiv(N, HEAD_IMGS), (unsigned)cdiv(J, HEAD_OUTS)), dim3(256), lds_bytes, s, bits,
+    launch(head_kernel, dim3((unsigned)cdiv(N, HEAD_IMGS), (unsigned)cdiv(J, HEAD_OUTS)), dim3(256), lds_bytes, s, bits,
                        w, y, pooled, N, HW, C, J);
     return check_launch();
 }

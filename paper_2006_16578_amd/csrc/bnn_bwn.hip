@@ -605,10 +605,10 @@ int launch_bwn_direct(const float* x, const void* weights, const float* thr, flo
     uint4* wexp = static_cast<uint4*>(workspace);
     const int nunits = col_tiles * NPL * 2 * nsteps * COLS;
     if (NPL == 1)
-        hipLaunchKernelGGL(bwn_expand_kernel, dim3((unsigned)cdiv(nunits, 256)), dim3(256), 0, s, static_cast<const uint32_t*>(weights),
+        launch(bwn_expand_kernel, dim3((unsigned)cdiv(nunits, 256)), dim3(256), 0, s, static_cast<const uint32_t*>(weights),
                            wexp, C, C, O, k, COLS, 1, nsteps, nunits);
     else
-        hipLaunchKernelGGL(conv_f32_expand_kernel, dim3((unsigned)cdiv(nunits, 256)), dim3(256), 0, s,
+        launch(conv_f32_expand_kernel, dim3((unsigned)cdiv(nunits, 256)), dim3(256), 0, s,
                            static_cast<const float*>(weights), wexp, C, O, k, COLS, nsteps, nunits, 1);
     // one workgroup per CU (registers allow no more), resident for the whole call
     const long long groups = cdiv(npix, MT * 32);
@@ -621,7 +621,7 @@ int launch_bwn_direct(const float* x, const void* weights, const float* thr, flo
     }
     const long long wgs = min(cdiv(groups, WAVES), (long long)max(1, cus / col_tiles));
     dim3 grid((unsigned)wgs, (unsigned)col_tiles);
-    hipLaunchKernelGGL((bwn_conv_kernel<MT, NT, WAVES, NPL, TERMS>), grid, dim3(WAVES * 64), lds_bytes, s, x, wexp, thr, y, bits, N, H, W, C, O, k, stride,
+    launch((bwn_conv_kernel<MT, NT, WAVES, NPL, TERMS>), grid, dim3(WAVES * 64), lds_bytes, s, x, wexp, thr, y, bits, N, H, W, C, O, k, stride,
                        pad, P, Q, make_fastdiv(P * Q), make_fastdiv(Q));
     return check_launch();
 }
@@ -673,10 +673,10 @@ int launch_bwn_staged_v(const float* x, const uint32_t* wbits, const float* thr,
     }
     uint4* wexp = static_cast<uint4*>(workspace);
     const int nunits = col_tiles * 2 * g.nsteps * COLS;
-    hipLaunchKernelGGL(bwn_expand_kernel, dim3((unsigned)cdiv(nunits, 256)), dim3(256), 0, s, wbits, wexp, C, g.Cp, O, k, COLS, 0,
+    launch(bwn_expand_kernel, dim3((unsigned)cdiv(nunits, 256)), dim3(256), 0, s, wbits, wexp, C, g.Cp, O, k, COLS, 0,
                        g.nsteps, nunits);
     dim3 grid((unsigned)(N * g.tiles_p * g.tiles_q), (unsigned)col_tiles);
-    hipLaunchKernelGGL((bwn_staged_kernel<MT, NT, WAVES, CIN, WANT_Y>), grid, dim3(WAVES * 64), lds_bytes, s, x, wexp, thr, y, bits, g);
+    launch((bwn_staged_kernel<MT, NT, WAVES, CIN, WANT_Y>), grid, dim3(WAVES * 64), lds_bytes, s, x, wexp, thr, y, bits, g);
     return check_launch();
 }
 
@@ -1069,7 +1069,7 @@ int launch_conv_f32_wave_v(const float* x, const void* w, const float* thr, floa
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         return BNN_ERR_DEVICE;
     const long long wgs = min(cdiv(g.ntiles, G::WAVES), (long long)max(1, cus / col_tiles));
-    hipLaunchKernelGGL((conv_f32_wave_kernel<G, TERMS, WANT_Y>), dim3((unsigned)wgs, (unsigned)col_tiles), dim3(G::WAVES * 64), G::LDS, s, x,
+    launch((conv_f32_wave_kernel<G, TERMS, WANT_Y>), dim3((unsigned)wgs, (unsigned)col_tiles), dim3(G::WAVES * 64), G::LDS, s, x,
                        w, thr, y, bits, g);
     return check_launch();
 }

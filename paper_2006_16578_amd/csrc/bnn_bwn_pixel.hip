@@ -404,7 +404,7 @@ int launch_pixel_v(const PixCall& c, PixArgs g) {
     // workgroups resident at a time: what registers (launch bounds) and LDS allow
     const long long per_cu = min((long long)(2 / CT), (long long)(160 * 1024 / lds));
     const long long wgs = min((long long)g.ntiles, max(1LL, c.cus * per_cu / ct));
-    hipLaunchKernelGGL((bwn_pixel_kernel<G, CT, WANT_Y>), dim3((unsigned)wgs, (unsigned)ct), dim3(256 * CT), lds, c.s, c.x, c.wbits, c.thr, c.y, c.bits, g);
+    launch((bwn_pixel_kernel<G, CT, WANT_Y>), dim3((unsigned)wgs, (unsigned)ct), dim3(256 * CT), lds, c.s, c.x, c.wbits, c.thr, c.y, c.bits, g);
     return check_launch();
 }
 

@@ -326,7 +326,7 @@ int launch_chain(FcChain a, hipStream_t s) {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&fc_chain_kernel<RT, WAVES, U8>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return BNN_ERR_DEVICE;
-    hipLaunchKernelGGL((fc_chain_kernel<RT, WAVES, U8>), dim3((unsigned)cdiv(a.rows, 16 * RT)), dim3(64 * WAVES),
+    launch((fc_chain_kernel<RT, WAVES, U8>), dim3((unsigned)cdiv(a.rows, 16 * RT)), dim3(64 * WAVES),
                        (size_t)lds_bytes(a, 16 * RT, WAVES), s, a);
     return check_launch();
 }

@@ -411,7 +411,7 @@ int launch_ksplit(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma_ksplit_kernel<TL>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (attr != hipSuccess) return BNN_ERR_DEVICE;
-    hipLaunchKernelGGL((mfma_ksplit_kernel<TL>), dim3(nwg), dim3(TL::THREADS), lds_bytes, s, A, B, g, e, gx, gy);
+    launch((mfma_ksplit_kernel<TL>), dim3(nwg), dim3(TL::THREADS), lds_bytes, s, A, B, g, e, gx, gy);
     return check_launch();
 }
 
@@ -424,7 +424,7 @@ int launch_bits(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma_bits_kernel<TL, PANELS>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (attr != hipSuccess) return BNN_ERR_DEVICE;
-    hipLaunchKernelGGL((mfma_bits_kernel<TL, PANELS>), dim3(nwg), dim3(TL::THREADS), lds_bytes, s, A, B, g, e, gx, gy);
+    launch((mfma_bits_kernel<TL, PANELS>), dim3(nwg), dim3(TL::THREADS), lds_bytes, s, A, B, g, e, gx, gy);
     return check_launch();
 }
 

@@ -49,7 +49,7 @@ int launch_bits_form(const uint32_t* A, const uint32_t* B, const Geom& g, const 
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma::mfma_bits_kernel<TL, FULL, PANELS>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)TL::LDS_BYTES);
     if (attr != hipSuccess) return BNN_ERR_DEVICE;
-    hipLaunchKernelGGL((mfma::mfma_bits_kernel<TL, FULL, PANELS>), dim3(nwg), dim3(TL::THREADS), TL::LDS_BYTES, s, A, B, g, e, gx, gy);
+    launch((mfma::mfma_bits_kernel<TL, FULL, PANELS>), dim3(nwg), dim3(TL::THREADS), TL::LDS_BYTES, s, A, B, g, e, gx, gy);
     return check_launch();
 }
 
@@ -66,7 +66,7 @@ int launch_ksplit(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma::mfma_ksplit_kernel<TL>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)TL::LDS_BYTES);
     if (attr != hipSuccess) return BNN_ERR_DEVICE;
-    hipLaunchKernelGGL((mfma::mfma_ksplit_kernel<TL>), dim3(nwg), dim3(TL::THREADS), TL::LDS_BYTES, s, A, B, g, e, gx, gy);
+    launch((mfma::mfma_ksplit_kernel<TL>), dim3(nwg), dim3(TL::THREADS), TL::LDS_BYTES, s, A, B, g, e, gx, gy);
     return check_launch();
 }
 

@@ -509,7 +509,7 @@ int launch_band_form(const uint32_t* A, const uint32_t* B, const Geom& g, const 
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)BAND_LDS);
     if (attr != hipSuccess) return BNN_ERR_DEVICE;
     const unsigned nwg = (unsigned)(cdiv((long long)pl.ba.nx * pl.ba.gy, 8) * 8);
-    hipLaunchKernelGGL((conv_band_kernel<CW, MT, WAVES, WK, SUMS, RES>), dim3(nwg), dim3(64 * WAVES), pl.lds_bytes, s, A, B, g, e, pl.ba);
+    launch((conv_band_kernel<CW, MT, WAVES, WK, SUMS, RES>), dim3(nwg), dim3(64 * WAVES), pl.lds_bytes, s, A, B, g, e, pl.ba);
     return check_launch();
 }
 

@@ -505,7 +505,7 @@ int launch_patch_kind(const uint32_t* A, const uint32_t* B, const Geom& g, const
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return BNN_ERR_DEVICE;
     const unsigned nwg = (unsigned)min(256, pl.pa.ntiles);   // one workgroup per compute unit; few tiles: spread over all of them
-    hipLaunchKernelGGL((conv_patch_kernel<NT, CW, WAVES, KIND, S>), dim3(nwg), dim3(64 * WAVES), pl.lds_bytes, s, A, B, g, e, pl.pa);
+    launch((conv_patch_kernel<NT, CW, WAVES, KIND, S>), dim3(nwg), dim3(64 * WAVES), pl.lds_bytes, s, A, B, g, e, pl.pa);
     return check_launch();
 }
 

@@ -105,11 +105,11 @@ int launch_taps(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
     const size_t lds = (size_t)waves * 4096;
     if (g.pool2) {
         if constexpr (EXCL) return BNN_ERR_UNSUPPORTED;          // not dispatched: mfma_conv_pools
-        else hipLaunchKernelGGL((conv_taps_kernel<V, CH, EXCL, TAPS_POOL>), grid, dim3(64 * waves), lds, s, A, B, g, e, gx, gy);
+        else launch((conv_taps_kernel<V, CH, EXCL, TAPS_POOL>), grid, dim3(64 * waves), lds, s, A, B, g, e, gx, gy);
     } else if (mfma::epilogue_kind(e, true, false) == mfma::EPI_CHAIN)
-        hipLaunchKernelGGL((conv_taps_kernel<V, CH, EXCL, TAPS_CHAIN>), grid, dim3(64 * waves), lds, s, A, B, g, e, gx, gy);
+        launch((conv_taps_kernel<V, CH, EXCL, TAPS_CHAIN>), grid, dim3(64 * waves), lds, s, A, B, g, e, gx, gy);
     else
-        hipLaunchKernelGGL((conv_taps_kernel<V, CH, EXCL, TAPS_BITS>), grid, dim3(64 * waves), lds, s, A, B, g, e, gx, gy);
+        launch((conv_taps_kernel<V, CH, EXCL, TAPS_BITS>), grid, dim3(64 * waves), lds, s, A, B, g, e, gx, gy);
     return check_launch();
 }
 

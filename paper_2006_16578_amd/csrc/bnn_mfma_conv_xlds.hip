@@ -354,7 +354,7 @@ int launch_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
         static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_xlds_kernel<MT, NT, WM, WN, FORM, SHORTCUT>),
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)xlds_max(WM * WN));
         if (attr != hipSuccess) return (int)BNN_ERR_DEVICE;
-        hipLaunchKernelGGL((conv_xlds_kernel<MT, NT, WM, WN, FORM, SHORTCUT>), dim3(nwg), dim3(WM * WN * 64), lds, s, A, B, g, e, x, gx, gy);
+        launch((conv_xlds_kernel<MT, NT, WM, WN, FORM, SHORTCUT>), dim3(nwg), dim3(WM * WN * 64), lds, s, A, B, g, e, x, gx, gy);
         return check_launch();
     };
     // a second source comes with bits, with or without their sums; with another form it is not dispatched (xlds_tile)

@@ -909,10 +909,10 @@ int launch_tile_3x3(const uint32_t* A, const uint32_t* B, const Geom& g, const E
                     hipStream_t s) {
     if constexpr (!EXCL && KIND == KIND_ANY)
         if (g.pool2 != 0) {
-            hipLaunchKernelGGL((mfma_kernel<TL, V, true, false, false, CPT3, KIND_POOL>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
+            launch((mfma_kernel<TL, V, true, false, false, CPT3, KIND_POOL>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
             return check_launch();
         }
-    hipLaunchKernelGGL((mfma_kernel<TL, V, true, EXCL, false, CPT3, KIND>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
+    launch((mfma_kernel<TL, V, true, EXCL, false, CPT3, KIND>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
     return check_launch();
 }
 
@@ -932,9 +932,9 @@ int launch_tile(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
         }
     }
     if (CONV && g.excl)
-        hipLaunchKernelGGL((mfma_kernel<TL, V, CONV, CONV, GUARD, 0, KIND>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
+        launch((mfma_kernel<TL, V, CONV, CONV, GUARD, 0, KIND>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
     else
-        hipLaunchKernelGGL((mfma_kernel<TL, V, CONV, false, GUARD, 0, KIND>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
+        launch((mfma_kernel<TL, V, CONV, false, GUARD, 0, KIND>), dim3(nwg), dim3(256), 0, s, A, B, g, e, gx, gy);
     return check_launch();
 }
 

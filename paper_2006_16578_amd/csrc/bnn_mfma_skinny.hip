@@ -218,7 +218,7 @@ __global__ __launch_bounds__(64 * WAVES16) void mfma_skinny16_kernel(const uint3
 template <int RT>
 int launch_skinny16(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, int col_span, hipStream_t s) {
     const Skinny a = {e.thr, e.bits, e.out, (int)g.rows, g.cols, g.tw, g.lda_w, g.ldb_w, e.ldc, e.ldbits_w, g.bits_tap, e.out_f32};
-    hipLaunchKernelGGL(mfma_skinny16_kernel<RT>, dim3((unsigned)cdiv(col_span, 16)), dim3(64 * WAVES16), 0, s, A, B, a);
+    launch(mfma_skinny16_kernel<RT>, dim3((unsigned)cdiv(col_span, 16)), dim3(64 * WAVES16), 0, s, A, B, a);
     return check_launch();
 }
 
@@ -247,9 +247,9 @@ int launch_mfma_skinny(const uint32_t* A, const uint32_t* B, const Geom& g, cons
         return g.rows <= 64 ? launch_skinny16<4>(A, B, g, e, col_span, s) : launch_skinny16<8>(A, B, g, e, col_span, s);
     }
     const dim3 grid((unsigned)cdiv(col_span, 32));
-    if (g.rows <= 32) hipLaunchKernelGGL((mfma_skinny_kernel<1, 8>), grid, dim3(64 * 8), 0, s, A, B, g, e);
-    else if (g.rows <= 64) hipLaunchKernelGGL((mfma_skinny_kernel<2, 4>), grid, dim3(64 * 4), 0, s, A, B, g, e);
-    else hipLaunchKernelGGL((mfma_skinny_kernel<4, 4>), grid, dim3(64 * 4), 0, s, A, B, g, e);
+    if (g.rows <= 32) launch((mfma_skinny_kernel<1, 8>), grid, dim3(64 * 8), 0, s, A, B, g, e);
+    else if (g.rows <= 64) launch((mfma_skinny_kernel<2, 4>), grid, dim3(64 * 4), 0, s, A, B, g, e);
+    else launch((mfma_skinny_kernel<4, 4>), grid, dim3(64 * 4), 0, s, A, B, g, e);
     return check_launch();
 }
 

@@ -257,7 +257,7 @@ int launch_staged_tile(const uint32_t* A, const uint32_t* B, const Geom& g, cons
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma_staged_kernel<TL, U, CONV, STREAM>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
     if (attr != hipSuccess) return BNN_ERR_DEVICE;
-    hipLaunchKernelGGL((mfma_staged_kernel<TL, U, CONV, STREAM>), dim3(nwg), dim3(256), lds_bytes, s, A, B, g, e, gx, gy);
+    launch((mfma_staged_kernel<TL, U, CONV, STREAM>), dim3(nwg), dim3(256), lds_bytes, s, A, B, g, e, gx, gy);
     return check_launch();
 }
 

@@ -133,8 +133,8 @@ int launch_persist_chain(const PersistNet& net, int max_tiles, int max_grid, uns
         want = max(want, row_groups < (1 << 20) ? (int)row_groups : (1 << 20));
     }
     const int grid = min(min(want, max_wg), max(1, max_grid));
-    hipLaunchKernelGGL(persist_clear_kernel, dim3(1), dim3(64), 0, s, ctr);
-    hipLaunchKernelGGL(persist_chain_kernel, dim3((unsigned)grid), dim3(256), 0, s, net, net.layers, ctr, spin_limit, sync);
+    launch(persist_clear_kernel, dim3(1), dim3(64), 0, s, ctr);
+    launch(persist_chain_kernel, dim3((unsigned)grid), dim3(256), 0, s, net, net.layers, ctr, spin_limit, sync);
     return check_launch();
 }
 

@@ -141,8 +141,8 @@ template <int VW, bool CONV>
 int launch_vw(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
     const int col_span = (e.bits != nullptr) ? max(g.cols, e.ldbits_w * 32) : g.cols;
     dim3 grid((unsigned)cdiv(g.rows, 64), (unsigned)cdiv(col_span, 128));
-    if (g.excl) hipLaunchKernelGGL((valu_kernel<VW, CONV, true>), grid, dim3(256), 0, s, A, B, g, e);
-    else        hipLaunchKernelGGL((valu_kernel<VW, CONV, false>), grid, dim3(256), 0, s, A, B, g, e);
+    if (g.excl) launch((valu_kernel<VW, CONV, true>), grid, dim3(256), 0, s, A, B, g, e);
+    else        launch((valu_kernel<VW, CONV, false>), grid, dim3(256), 0, s, A, B, g, e);
     return check_launch();
 }
 
