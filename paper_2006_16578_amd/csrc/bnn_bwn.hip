@@ -597,6 +597,10 @@ int launch_bwn_direct(const float* x, const void* weights, const float* thr, flo
     const size_t lds_bytes = (size_t)NPL * 2 * nsteps * COLS * 16;
     if (lds_bytes > 160 * 1024) return BNN_ERR_UNSUPPORTED;
     if (workspace_bytes < lds_bytes * col_tiles) return BNN_ERR_WORKSPACE;
+    if constexpr (NPL == 1) {
+        int rc = BNN_OK;
+        if (try_bwn_rect(x, static_cast<const uint32_t*>(weights), thr, y, bits, N, H, W, C, O, k, stride, pad, P, Q, s, &rc)) return rc;
+    }
     if (lds_bytes > 64 * 1024) {
         static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bwn_conv_kernel<MT, NT, WAVES, NPL, TERMS>),
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
@@ -686,6 +690,7 @@ int launch_bwn_staged(const float* x, const uint32_t* wbits, const float* thr, f
     if (workspace_bytes < (size_t)g.wbytes * cdiv(O, NT * 32)) return BNN_ERR_WORKSPACE;
     int rc = BNN_OK;
     if (try_bwn_pixel(x, wbits, thr, y, bits, N, g.H, g.W, C, O, k, g.stride, g.pad, g.P, g.Q, s, &rc)) return rc;
+    if (try_bwn_rect(x, wbits, thr, y, bits, N, g.H, g.W, C, O, k, g.stride, g.pad, g.P, g.Q, s, &rc)) return rc;
     // the fp32 sums are a test / debugging output: only the generic-channel variant carries them
     if (y != nullptr)
         return launch_bwn_staged_v<MT, NT, WAVES, 0, true>(x, wbits, thr, y, bits, N, C, O, k, g, lds_bytes, workspace, s);
@@ -702,15 +707,16 @@ size_t bwn_workspace_bytes(int C, int O, int k) {
     return (size_t)(cdiv(O, 128) * 128 * 2 * nsteps * 16);
 }
 
-bool try_bwn_wave(const float* x, const uint32_t* wbits, const float* thr, float* y, uint32_t* bits, int N, int H, int W, int C, int O,
-                  int k, int stride, int pad, int P, int Q, void* workspace, size_t workspace_bytes, hipStream_t s, int* rc);
-
 int launch_bwn_conv_thr(const float* x, const uint32_t* wbits, const float* thr, float* y, uint32_t* bits, int N, int H, int W,
                         int C, int O, int k, int stride, int pad, void* workspace, size_t workspace_bytes, hipStream_t s) {
     const int P = (H + 2 * pad - k) / stride + 1, Q = (W + 2 * pad - k) / stride + 1;
-    int wave_rc = BNN_OK;
-    if (try_bwn_wave(x, wbits, thr, y, bits, N, H, W, C, O, k, stride, pad, P, Q, workspace, workspace_bytes, s, &wave_rc))
-        return wave_rc;                        // wave-private patches in LDS for the filter geometries that kernel is built for
+    // 11x11 windows of at least 4096 rectangles of 4x8 pixels ask for the expanded weights of 64 channels at a time, everything else for what
+    // its kernel below keeps in the workspace, whichever kernel serves the call (the strided-window and pixel kernels need none).
+    int rc = BNN_OK;
+    if (k == 11 && stride == 4 && C == 3 && (long long)N * cdiv(P, 4) * cdiv(Q, 8) >= 4096) {
+        if (workspace == nullptr || workspace_bytes < (size_t)2 * 28 * 64 * 16 * cdiv(O, 64)) return BNN_ERR_WORKSPACE;
+        if (try_bwn_rect(x, wbits, thr, y, bits, N, H, W, C, O, k, stride, pad, P, Q, s, &rc)) return rc;
+    }
     BwnTile g;
     size_t lds = 0;
     // LDS-staged kernel with small workgroups while several of them fit a CU side by side (one loads its
@@ -737,11 +743,10 @@ int launch_bwn_conv_thr(const float* x, const uint32_t* wbits, const float* thr,
 // epilogue, so the only memory wait a wave sees is one it has had a whole rectangle of MFMA work to cover; the eight
 // waves of a workgroup share nothing but the weights (copied to LDS once: the workgroups are persistent) and drift
 // apart, so that on every SIMD one wave stages while the other multiplies.  No barrier after the weights are in.
-// WAVES_: waves per workgroup (what fits LDS beside the weights); WPL_: weight planes -- 3 for real-valued weights (split
-// like the inputs), 1 for binarized weights (+1.0 / -1.0 are exact in bf16).
-template <int KS_, int STRIDE_, int CIN_, int FP_, int FQ_, int WAVES_ = 8, int WPL_ = 3>
+// WPL: weight planes (real-valued weights are split like the inputs).
+template <int KS_, int STRIDE_, int CIN_, int FP_, int FQ_>
 struct WaveGeom {
-    static constexpr int KS = KS_, STRIDE = STRIDE_, CIN = CIN_, FP = FP_, FQ = FQ_, WPL = WPL_;
+    static constexpr int KS = KS_, STRIDE = STRIDE_, CIN = CIN_, FP = FP_, FQ = FQ_, WPL = 3;
     static constexpr int PR = (FP - 1) * STRIDE + KS;                        // patch rows
     static constexpr int ROW_ELEMS = ((FQ - 1) * STRIDE + KS) * CIN;         // input values of a patch row
     static constexpr int SEG = KS * CIN;                                     // values of one filter row
@@ -753,7 +758,7 @@ struct WaveGeom {
     static constexpr int PAIRS = PITCH / 4;                                  // 2-element units written per patch row (data + zeroed slack)
     static constexpr int PLANE = PR * PITCH;                                 // bytes of one bf16 plane of a patch
     static constexpr int WUNITS = NRUNS * 64;                                // 16-byte units of one weight plane in LDS
-    static constexpr int WAVES = WAVES_;
+    static constexpr int WAVES = 8;                                // what fits LDS beside the weights
     static constexpr size_t LDS = (size_t)WPL * WUNITS * 16 + (size_t)WAVES * 3 * PLANE;
     static_assert(FP * FQ == 32 && PAIRS <= 64 && (STRIDE * CIN * 2) % 8 == 0, "one lane per pair; 8-byte aligned runs");
 };
@@ -766,12 +771,10 @@ struct WaveArgs {
 };
 
 template <class G, int TERMS, bool WANT_Y>
-__global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const float* __restrict__ x, const void* __restrict__ wv,
+__global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const float* __restrict__ x, const float* __restrict__ wv,
                                                                         const float* __restrict__ thr, float* __restrict__ y,
                                                                         uint32_t* __restrict__ bits, WaveArgs g) {
     constexpr int NT = 2, COLS = 64;
-    constexpr bool BWN = G::WPL == 1;                                  // wv: weight bits [O][k][k][1 word] instead of floats [O][k][k][C]
-    static_assert(G::WPL == 3 || (G::WPL == 1 && G::CIN <= 32 && TERMS == 3), "three planes of real weights or one of +-1");
     extern __shared__ uint4 smem[];
     uint4* wlds = smem;                                                // [weight planes][NRUNS][64 columns] units of 8 bf16
     const int tid = (int)threadIdx.x;
@@ -863,7 +866,7 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
     };
     int t = tile_of(0);
     if (t < g.ntiles) request(t);              // the first patch is on its way while the weights are staged
-    if constexpr (!BWN) {   // weights of this channel tile -> LDS, split on the way (w [O][k][k][C]; a run is 8 consecutive values of one filter
+    {   // weights of this channel tile -> LDS, split on the way (w [O][k][k][C]; a run is 8 consecutive values of one filter
         // row, zero past the row's end; column = output channel): unit (plane, run, column) of wlds.  Every load is issued
         // before the first split; pairs past the end repeat the last one and store nothing.
         constexpr int PER = (G::WUNITS + G::WAVES * 64 - 1) / (G::WAVES * 64);
@@ -873,7 +876,7 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
             const int p = min(tid + i * G::WAVES * 64, G::WUNITS - 1);
             const int rho = p >> 6, o = min(n0 + (p & 63), g.O - 1);
             const int r = rho / G::RPR, j = rho - r * G::RPR;
-            const float* wrow = static_cast<const float*>(wv) + ((long long)o * G::KS + r) * G::SEG;
+            const float* wrow = wv + ((long long)o * G::KS + r) * G::SEG;
 #pragma unroll
             for (int e = 0; e < 8; ++e) xs[i][e] = wrow[min(8 * j + e, G::SEG - 1)];
         }
@@ -900,41 +903,6 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
                 wlds[G::WUNITS + p] = make_uint4(mid[0], mid[1], mid[2], mid[3]);
                 wlds[2 * G::WUNITS + p] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
             }
-        }
-    }
-    if constexpr (BWN) {    // weight bits of this channel tile -> LDS as bf16 +1.0 / -1.0 (0 past a filter row's end and past
-        // the last channel): a run of 8 values lies in at most 8 / C + 2 tap words, all of them requested before the first is used
-        const uint32_t* wbits = static_cast<const uint32_t*>(wv);
-        constexpr int PER = (G::WUNITS + G::WAVES * 64 - 1) / (G::WAVES * 64), TW = 8 / G::CIN + 2;
-        uint32_t tw[PER][TW];
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int p = min(tid + i * G::WAVES * 64, G::WUNITS - 1);
-            const int rho = p >> 6, o = min(n0 + (p & 63), g.O - 1);
-            const int r = rho / G::RPR, j = rho - r * G::RPR;
-            const uint32_t* wrow = wbits + ((long long)o * G::KS + r) * G::KS;          // one word per tap
-            const int t0 = (8 * j) / G::CIN;
-#pragma unroll
-            for (int q = 0; q < TW; ++q) tw[i][q] = wrow[min(t0 + q, G::KS - 1)];
-        }
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int p = tid + i * G::WAVES * 64;
-            const int rho = min(p, G::WUNITS - 1) >> 6;
-            const int j = rho % G::RPR;
-            const bool col_ok = n0 + (p & 63) < g.O;
-            const int t0 = (8 * j) / G::CIN;
-            uint32_t pk[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int el = 8 * j + e, t = el / G::CIN, c = el - t * G::CIN;
-                uint32_t word = 0u;
-#pragma unroll
-                for (int q = 0; q < TW; ++q) word = (t - t0 == q) ? tw[i][q] : word;
-                const uint32_t val = !(col_ok && el < G::SEG) ? 0u : ((word >> c) & 1u) ? 0x3F80u : 0xBF80u;
-                pk[e >> 1] |= val << (16 * (e & 1));
-            }
-            if (p < G::WUNITS) wlds[p] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
         }
     }
     if (t < g.ntiles) stage(t);
@@ -1049,7 +1017,7 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
 }
 
 template <class G, int TERMS, bool WANT_Y>
-int launch_conv_f32_wave_v(const float* x, const void* w, const float* thr, float* y, uint32_t* bits, int N, int H, int W, int O,
+int launch_conv_f32_wave_v(const float* x, const float* w, const float* thr, float* y, uint32_t* bits, int N, int H, int W, int O,
                            int pad, int P, int Q, void* workspace, size_t workspace_bytes, hipStream_t s) {
     const int col_tiles = (int)cdiv(O, 64);
     WaveArgs g;
@@ -1090,23 +1058,6 @@ bool try_conv_f32_wave(const float* x, const float* w, const float* thr, float* 
     else
         *rc = products == 6 ? launch_conv_f32_wave_v<G, 6, false>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, workspace, workspace_bytes, s)
                             : launch_conv_f32_wave_v<G, 9, false>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, workspace, workspace_bytes, s);
-    return true;
-}
-
-// Binarized weights on the wave-private kernel: the 11x11 stride-4 first layer of 3-channel images (one weight plane,
-// three term products; six waves: a patch is 23 rows).  true: launched (rc receives the status).
-bool try_bwn_wave(const float* x, const uint32_t* wbits, const float* thr, float* y, uint32_t* bits, int N, int H, int W, int C, int O,
-                  int k, int stride, int pad, int P, int Q, void* workspace, size_t workspace_bytes, hipStream_t s, int* rc) {
-    if (!(k == 11 && stride == 4 && C == 3)) return false;
-    if ((long long)W * C < 2 || (long long)H * W * C >= (1LL << 31)) return false;
-    constexpr int FP = 4, FQ = 8;
-    typedef WaveGeom<11, 4, 3, FP, FQ, 6, 1> G;
-    static_assert(G::LDS <= LDS_MAX, "weights and six patches fit LDS");
-    const long long tiles = (long long)N * cdiv(P, FP) * cdiv(Q, FQ);
-    if (tiles >= (1LL << 31) - 65536) return false;
-    if (tiles < 4096) return false;            // small batches: the LDS-staged and direct kernels (more workgroups, shorter prologue)
-    *rc = y != nullptr ? launch_conv_f32_wave_v<G, 3, true>(x, wbits, thr, y, bits, N, H, W, O, pad, P, Q, workspace, workspace_bytes, s)
-                       : launch_conv_f32_wave_v<G, 3, false>(x, wbits, thr, y, bits, N, H, W, O, pad, P, Q, workspace, workspace_bytes, s);
     return true;
 }
 

@@ -1,0 +1,382 @@
+// First layer with binarized weights for large strided windows (11x11 and 7x7, stride 4) of 3-channel images: a rectangle of
+// output pixels and up to 128 channels per wave, input patch in the wave's own LDS, weights as sign bits in registers.
+//
+// Same arithmetic as the kernels of bnn_bwn.hip: an fp32 value is the exact sum of three bf16 terms, a +1/-1 weight is exact in bf16,
+// the products are accumulated in fp32 by v_mfma_f32_32x32x16_bf16 (smallest terms first) and compared with the fp32 threshold.
+//
+// What bounded these layers before was everything beside the matrix pipe.  Expanded weights of 64 channels (56 KB for 11x11) left LDS for six
+// patches, so two of the four SIMDs had one wave; the weights were read from LDS beside the pixels for every rectangle; a
+// layer of 128 channels staged and split every patch twice; and each of 40 loads of a lane fetched one tap of one channel, 64
+// lines at a time.  Small calls took a kernel that loads, masks and splits its runs in the K loop.  Here:
+//  * a lane keeps the signs of its columns (one of every 32 channels) for the whole launch, 32 bits for four K-steps of a column
+//    (28 registers for 128 channels and 28 steps), and makes a bf16 operand register of them by a shift and a bit select, 2.7
+//    vector instructions beside each 32-cycle MFMA;
+//  * LDS holds nothing but eight patches, two waves for every SIMD; a K-step reads 3 KB for 3 NT MFMAs;
+//  * the weights reach the lanes by way of LDS (the patches' space, idle until the first is staged): whole lines once per
+//    workgroup, rows of bits, then the words.
+// The patch of the wave's next rectangle is requested before the K loop and split after the epilogue; no barrier after the prologue.
+// Measured, before -> now (weights included): 11x11, n x 224x224x3 -> 128: n = 1 31.7 -> 8.4 us, 16 33.5 -> 18.2, 64 61 -> 52, 128 107 -> 91;
+// 7x7 -> 64: n = 1 20.1 -> 5.6, 16 21.1 -> 7.5, 128 64 -> 31.5.  The MFMAs of the 128-image 11x11 layer take 60 us (K slots 82 % full); the two
+// waves of a SIMD overlap the rest of each other in part (another wave priority for one of them changes nothing).
+#include <type_traits>
+
+#include "bnn_internal.h"
+
+namespace bnn {
+namespace {
+
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef float float2_ub __attribute__((ext_vector_type(2), aligned(4)));       // 8-byte load, 4-byte aligned
+extern "C" __device__ int bnn_rect_writelane_i32(int val, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
+
+template <int KS_, int STRIDE_>
+struct RectGeom {
+    static constexpr int KS = KS_, STRIDE = STRIDE_, CIN = 3, FP = 4, FQ = 8, WAVES = 8;
+    static constexpr int TAPS = KS * KS;
+    static constexpr int PR = (FP - 1) * STRIDE + KS;                        // patch rows
+    static constexpr int ROW_ELEMS = ((FQ - 1) * STRIDE + KS) * CIN;         // input values of a patch row
+    static constexpr int SEG = KS * CIN;                                     // values of one filter row
+    static constexpr int RPR = (SEG + 7) / 8;                                // runs of 8 per filter row
+    static constexpr int LAST = SEG - 8 * (RPR - 1);                         // values of a row's last run
+    static constexpr int NRUNS = KS * RPR;
+    static constexpr int NSTEPS = (NRUNS + 1) / 2;                           // MFMA K-steps (two runs each, one per half-wave)
+    static constexpr int WQ = (NSTEPS + 3) / 4;                              // sign words of a column
+    static constexpr int REACH = (FQ - 1) * STRIDE * CIN + 8 * RPR;          // farthest element a run reads from a patch row, + 1
+    static constexpr int PITCH = (2 * (REACH > ROW_ELEMS ? REACH : ROW_ELEMS) + 7) / 8 * 8;    // bytes between patch rows
+    static constexpr int PAIRS = PITCH / 4;                                  // 2-element units written per patch row (data + zeroed slack)
+    static constexpr int PLANE = PR * PITCH;                                 // bytes of one bf16 plane of a patch
+    static constexpr size_t LDS = (size_t)WAVES * 3 * PLANE;
+    static_assert(FP * FQ == 32 && PAIRS <= 64 && (STRIDE * CIN * 2) % 8 == 0, "one lane per pair; 8-byte aligned runs");
+    static_assert(SEG <= 64 && LDS <= 160 * 1024, "a filter row of signs in two words; eight patches in LDS");
+};
+
+struct RectArgs {
+    int H, W, O, pad, P, Q;
+    int tiles_p, tiles_q;
+    int ntiles;              // images * tiles_p * tiles_q
+    FastDiv div_tiles, div_tq;
+};
+
+// bits 0, 2, 4, ... of a word, packed
+__device__ __forceinline__ uint32_t even_bits(uint32_t v) {
+    v &= 0x55555555u;
+    v = (v | (v >> 1)) & 0x33333333u;
+    v = (v | (v >> 2)) & 0x0F0F0F0Fu;
+    v = (v | (v >> 4)) & 0x00FF00FFu;
+    return (v | (v >> 8)) & 0x0000FFFFu;
+}
+
+template <class G, int NT, bool WANT_Y>
+__global__ __launch_bounds__(G::WAVES * 64, 1) void bwn_rect_kernel(const float* __restrict__ x, const uint32_t* __restrict__ wbits,
+                                                                   const float* __restrict__ thr, float* __restrict__ y,
+                                                                   uint32_t* __restrict__ bits, RectArgs g) {
+    constexpr int COLS = 32 * NT, NTHR = G::WAVES * 64;
+    extern __shared__ uint4 smem[];
+    const int tid = (int)threadIdx.x;
+    const int lane = tid & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);        // scalar: everything derived from the rectangle index stays scalar
+    char* patch = reinterpret_cast<char*>(smem) + wave * (3 * G::PLANE);      // this wave's three planes
+    const int n0 = (int)blockIdx.y * COLS;
+    const int ow = (g.O + 31) / 32;
+
+    // this lane's output pixel inside a rectangle (rows vary fastest over the lanes: fewer bank conflicts of the 8-byte reads)
+    const int dp = l32 % G::FP, dq = l32 / G::FP;
+    const char* abase = patch + dp * (G::STRIDE * G::PITCH) + dq * (G::STRIDE * G::CIN * 2);
+    const char* a_same = abase + half * 16;                                   // upper half-wave's run follows in the same filter row
+    const char* a_next = abase + half * (G::PITCH - (G::RPR - 1) * 16);       // ... begins the next row
+    const int rowlen = g.W * G::CIN;                                          // values per image row (H * W * C < 2^31: checked on the host)
+
+    // ---- patch prefetch: lane l holds elements 2l, 2l + 1 of every patch row.  A pair may hang over the left or right
+    // edge of the image row by one element: it is then loaded one element further in, and stage() picks the element that is data.
+    float2_ub pre[G::PR];
+    auto tile_origin = [&](int t, int& n, int& p0, int& q0) {
+        n = fast_div(t, g.div_tiles);
+        const int rem = t - n * (g.tiles_p * g.tiles_q);
+        const int tp = fast_div(rem, g.div_tq);
+        p0 = tp * G::FP;
+        q0 = (rem - tp * g.tiles_q) * G::FQ;
+    };
+    auto request = [&](int t) {
+        int n, p0, q0;
+        tile_origin(t, n, p0, q0);
+        const int y0 = p0 * G::STRIDE - g.pad;
+        const int e0 = (q0 * G::STRIDE - g.pad) * G::CIN + 2 * lane;
+        const uint32_t lane_bytes = (uint32_t)min(max(e0, 0), rowlen - 2) * 4u;          // rowlen >= 2 (checked on the host)
+        const float* img = x + (long long)n * g.H * rowlen;                             // uniform
+#pragma unroll
+        for (int r = 0; r < G::PR; ++r) {
+            const int yy = min(max(y0 + r, 0), g.H - 1);                                // uniform: rows outside the image are zeroed in stage()
+            const char* rowp = reinterpret_cast<const char*>(img + yy * rowlen);
+            pre[r] = *reinterpret_cast<const float2_ub*>(rowp + lane_bytes);
+        }
+    };
+    auto stage = [&](int t) {                  // splits the prefetched patch of rectangle t into the wave's three planes
+        int n, p0, q0;
+        tile_origin(t, n, p0, q0);
+        const int y0 = p0 * G::STRIDE - g.pad;
+        const int e0 = (q0 * G::STRIDE - g.pad) * G::CIN + 2 * lane;
+        const bool shifted = min(max(e0, 0), rowlen - 2) != e0;
+        const uint32_t m0 = (e0 >= 0 && e0 < rowlen && 2 * lane < G::ROW_ELEMS) ? 0xFFFFFFFFu : 0u;
+        const uint32_t m1 = (e0 + 1 >= 0 && e0 + 1 < rowlen && 2 * lane + 1 < G::ROW_ELEMS) ? 0xFFFFFFFFu : 0u;
+        static_assert(2 * (G::PAIRS - 1) >= G::ROW_ELEMS, "the last pair is slack: the lanes past it repeat its stores of zeros");
+        char* dst = patch + 4 * min(lane, G::PAIRS - 1);
+#pragma unroll
+        for (int r = 0; r < G::PR; ++r) {
+            const uint32_t ym = (unsigned)(y0 + r) < (unsigned)g.H ? 0xFFFFFFFFu : 0u;     // uniform
+            const uint32_t ua = __float_as_uint(shifted ? pre[r][1] : pre[r][0]) & m0 & ym;
+            const uint32_t ub = __float_as_uint(shifted ? pre[r][0] : pre[r][1]) & m1 & ym;
+            const float a = __uint_as_float(ua), b = __uint_as_float(ub);
+            const float ra = a - __uint_as_float(ua & 0xffff0000u), rb = b - __uint_as_float(ub & 0xffff0000u);
+            const uint32_t va = __float_as_uint(ra), vb = __float_as_uint(rb);
+            const float la = ra - __uint_as_float(va & 0xffff0000u), lb = rb - __uint_as_float(vb & 0xffff0000u);
+            *reinterpret_cast<uint32_t*>(dst + r * G::PITCH) = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
+            *reinterpret_cast<uint32_t*>(dst + r * G::PITCH + G::PLANE) = __builtin_amdgcn_perm(vb, va, 0x07060302u);
+            *reinterpret_cast<uint32_t*>(dst + r * G::PITCH + 2 * G::PLANE) =
+                __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);
+        }
+    };
+
+    // Rectangle of this wave in round r: whole rounds give a workgroup's waves consecutive rectangles; the last, partial
+    // round is dealt across the workgroups (wave 0 of each first).
+    const int step = (int)gridDim.x * G::WAVES;
+    const int whole = g.ntiles / step;
+    auto tile_of = [&](int r) {
+        if (r < whole) return r * step + (int)blockIdx.x * G::WAVES + wave;
+        return r == whole ? whole * step + wave * (int)gridDim.x + (int)blockIdx.x : g.ntiles;   // past the last round: no rectangle
+    };
+    int t = tile_of(0);
+    if (t < g.ntiles) request(t);              // the first patch is on its way while the weights are prepared
+
+    // ---- thresholds (channels past the last: never reached) and sign words of this lane's NT columns
+    float th[NT];
+    bool cok[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const int col = n0 + 32 * j + l32;
+        cok[j] = col < g.O;
+        th[j] = __builtin_nanf("");
+        if (!WANT_Y || bits != nullptr) {
+            const float v = thr[min(col, g.O - 1)];
+            th[j] = cok[j] ? v : th[j];
+        }
+    }
+    uint32_t sw[G::WQ][NT];                    // step 4q + s, register i: element 2i at bit 4s + i, element 2i + 1 at bit 16 + 4s + i; set: -1
+    {
+        constexpr int RAW = COLS * G::TAPS, PER = (RAW + NTHR - 1) / NTHR;
+        constexpr int ROWS = COLS * G::KS, WORDS = COLS * 2 * G::WQ;
+        static_assert((size_t)(RAW + 2 * ROWS + WORDS) * 4 <= G::LDS, "the patches' space holds the weights first");
+        uint32_t* raw = reinterpret_cast<uint32_t*>(smem);             // [column][tap]
+        uint32_t* rows = raw + RAW;                                    // [column][filter row][2]: the row's values as bits, set: -1
+        uint32_t* words = rows + 2 * ROWS;                             // [q][half][column]
+        const uint32_t* src = wbits + (long long)n0 * G::TAPS;
+        const int last = min(COLS, g.O - n0) * G::TAPS - 1;
+        uint32_t v[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) v[i] = src[min(tid + i * NTHR, last)];
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
+            if (tid + i * NTHR < RAW) raw[tid + i * NTHR] = v[i];
+        __syncthreads();
+        for (int e = tid; e < ROWS; e += NTHR) {
+            unsigned long long row = 0u;
+#pragma unroll
+            for (int tap = 0; tap < G::KS; ++tap) row |= (unsigned long long)(~raw[e * G::KS + tap] & 7u) << (3 * tap);
+            rows[2 * e] = (uint32_t)row;
+            rows[2 * e + 1] = (uint32_t)(row >> 32);
+        }
+        __syncthreads();
+        for (int e = tid; e < WORDS; e += NTHR) {
+            const int col = e % COLS, h = (e / COLS) & 1, q = e / (2 * COLS);
+            uint32_t four = 0u;                                        // the runs of steps 4q .. 4q + 3, a byte each
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int rho = 2 * (4 * q + s) + h;
+                if (rho < G::NRUNS) {
+                    const int r = rho / G::RPR, j = rho - r * G::RPR;
+                    four |= ((rows[2 * (col * G::KS + r) + (j >> 2)] >> (8 * (j & 3))) & 0xFFu) << (8 * s);
+                }
+            }
+            words[e] = even_bits(four) | (even_bits(four >> 1) << 16);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < G::WQ; ++q)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) sw[q][j] = words[(2 * q + half) * COLS + 32 * j + l32];
+        __syncthreads();                       // the last barrier: the patches' space is free
+    }
+
+    if (t < g.ntiles) stage(t);
+    for (int r = 0; t < g.ntiles; ++r) {
+        const int t_next = tile_of(r + 1);
+        const bool more = t_next < g.ntiles;
+        if (more) request(t_next);
+
+        v16f acc[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[j][i] = 0.f;
+        // the words are read anew for every rectangle: otherwise the compiler keeps expanded operands of all steps (and spills)
+#pragma unroll
+        for (int q = 0; q < G::WQ; ++q)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) asm volatile("" : "+v"(sw[q][j]));
+        // two operand sets: the reads and the expansion of step st + 1 run between the MFMAs of step st
+        uint4 oa[2][3], ob[2][NT];
+        auto fetch = [&](auto st_tag) {
+            constexpr int st = decltype(st_tag)::value;
+            constexpr int rho0 = 2 * st, rho1 = 2 * st + 1;
+            constexpr bool upper = rho1 < G::NRUNS;                    // false: the upper half-wave's weights are zero, its values the lower's
+            constexpr bool wraps = rho0 % G::RPR == G::RPR - 1;
+            constexpr int off = (rho0 / G::RPR) * G::PITCH + (rho0 % G::RPR) * 16;
+            const char* asrc = !upper ? abase : wraps ? a_next : a_same;
+#pragma unroll
+            for (int pl = 0; pl < 3; ++pl) {
+                const uint2 lo = *reinterpret_cast<const uint2*>(asrc + off + pl * G::PLANE);
+                const uint2 hi = *reinterpret_cast<const uint2*>(asrc + off + pl * G::PLANE + 8);
+                oa[st & 1][pl] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            }
+            // values of the run each half-wave multiplies
+            constexpr int v0 = wraps ? G::LAST : 8, v1 = !upper ? 0 : rho1 % G::RPR == G::RPR - 1 ? G::LAST : 8;
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                uint32_t reg[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t m0 = (2 * i < v0 ? 0xFFFFu : 0u) | (2 * i + 1 < v0 ? 0xFFFF0000u : 0u);
+                    const uint32_t m1 = (2 * i < v1 ? 0xFFFFu : 0u) | (2 * i + 1 < v1 ? 0xFFFF0000u : 0u);
+                    reg[i] = ((sw[st / 4][j] << (15 - 4 * (st % 4) - i)) & 0x80008000u) | 0x3F803F80u;
+                    if (m0 != 0xFFFFFFFFu || m1 != 0xFFFFFFFFu) reg[i] &= half ? m1 : m0;
+                }
+                ob[st & 1][j] = make_uint4(reg[0], reg[1], reg[2], reg[3]);
+            }
+        };
+        auto multiply = [&](auto st_tag) {
+            constexpr int st = decltype(st_tag)::value;
+#pragma unroll
+            for (int pl = 2; pl >= 0; --pl)                            // smallest terms first
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, oa[st & 1][pl]),
+                                                                     __builtin_bit_cast(v8bf, ob[st & 1][j]), acc[j], 0, 0, 0);
+        };
+        fetch(std::integral_constant<int, 0>{});
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<G::NSTEPS>([&](auto st_tag) {
+            constexpr int st = decltype(st_tag)::value;
+            if constexpr (st + 1 < G::NSTEPS) fetch(std::integral_constant<int, st + 1>{});
+            multiply(st_tag);
+            // keeps the reads and the expansion of the next step between this step's MFMAs
+#pragma unroll
+            for (int q = 0; q < 3 * NT; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);     // an MFMA
+                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);     // vector instructions
+                if (q % 2 == 0 || NT < 4) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);     // an LDS read
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+
+        // ---- epilogue: threshold -> packed bits (and / or the fp32 sums)
+        int n, p0, q0;
+        tile_origin(t, n, p0, q0);
+        const long long img_pix = (long long)n * g.P * g.Q;
+        uint32_t wout[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) wout[j] = 0u;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int lo_row = 8 * (i >> 2) + (i & 3);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const float v = acc[j][i];
+                if (WANT_Y) {
+                    const int m = lo_row + 4 * half;                   // rectangle pixel of this register in this lane
+                    const int mp = m % G::FP, mq = m / G::FP;
+                    if (p0 + mp < g.P && q0 + mq < g.Q && cok[j])
+                        y[(img_pix + (long long)(p0 + mp) * g.Q + q0 + mq) * g.O + n0 + 32 * j + l32] = v;
+                }
+                if (!WANT_Y || bits != nullptr) {
+                    const unsigned long long ball = __builtin_amdgcn_ballot_w64(v >= th[j]);
+                    wout[j] = (uint32_t)bnn_rect_writelane_i32((int)(uint32_t)ball, lo_row, (int)wout[j]);
+                    wout[j] = (uint32_t)bnn_rect_writelane_i32((int)(uint32_t)(ball >> 32), lo_row + 4, (int)wout[j]);
+                }
+            }
+        }
+        if ((!WANT_Y || bits != nullptr) && lane < 32 && p0 + dp < g.P && q0 + dq < g.Q) {
+            const long long pix = img_pix + (long long)(p0 + dp) * g.Q + q0 + dq;
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const int wi = (n0 >> 5) + j;
+                if (wi < ow) bits[pix * ow + wi] = wout[j];
+            }
+        }
+        if (more) stage(t_next);               // every read of this rectangle's patch has been consumed by its MFMAs
+        t = t_next;
+    }
+}
+
+struct RectCall {
+    const float* x; const uint32_t* wbits; const float* thr; float* y; uint32_t* bits;
+    int cus;
+    hipStream_t s;
+};
+
+template <class G, int NT, bool WANT_Y>
+int launch_rect_v(const RectCall& c, const RectArgs& g) {
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bwn_rect_kernel<G, NT, WANT_Y>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS);
+    if (attr != hipSuccess) return BNN_ERR_DEVICE;
+    const int col_tiles = (int)cdiv(g.O, 32 * NT);
+    const int wgs = min(g.ntiles, max(1, c.cus / col_tiles));          // one workgroup per compute unit (LDS), resident for the whole call
+    launch(bwn_rect_kernel<G, NT, WANT_Y>, dim3((unsigned)wgs, (unsigned)col_tiles), dim3(G::WAVES * 64), G::LDS, c.s, c.x, c.wbits, c.thr, c.y,
+           c.bits, g);
+    return check_launch();
+}
+
+template <class G, int NT>
+int launch_rect_nt(const RectCall& c, const RectArgs& g) {
+    return c.y != nullptr ? launch_rect_v<G, NT, true>(c, g) : launch_rect_v<G, NT, false>(c, g);
+}
+
+template <class G>
+int launch_rect(const RectCall& c, RectArgs g, int N) {
+    g.tiles_p = (int)cdiv(g.P, G::FP); g.tiles_q = (int)cdiv(g.Q, G::FQ);
+    g.ntiles = N * g.tiles_p * g.tiles_q;
+    g.div_tiles = make_fastdiv((uint32_t)(g.tiles_p * g.tiles_q));
+    g.div_tq = make_fastdiv((uint32_t)g.tiles_q);
+    // Channels of a wave (32 NT): the least work for the SIMD with the most waves, the patch of a rectangle costing about as much as the
+    // products of 16 channels and a wave that has its SIMD to itself, with nothing to overlap, a little more.  Measured, NT = 2 / 3 / 4, us:
+    // n x 224x224x3 -> 128, 11x11: n = 4 8.6 / 10.5 / 12.1, 8 11.8 / 15.0 / 12.8, 12 15.2 / 19.7 / 18.2, 16 19.9 / 25.7 / 18.4, 64 53.7 / 69.5 / 51.5,
+    // 128 99 / 130 / 91; -> 96: n = 4 8.6 / 10.1 / 12.0, 8 11.7 / 10.8 / 12.8, 64 53.2 / 41.9 / 50.7; 7x7 windows alike.
+    int nt = 2;
+    double best = 0.;
+    for (int n = 2; n <= 4; ++n) {
+        const long long per_simd = cdiv((long long)g.ntiles * cdiv(g.O, 32 * n), 4LL * c.cus);
+        const double cost = (double)per_simd * (n + 0.5) + (per_simd == 1 ? 0.7 : 0.);
+        if (n == 2 || cost < best) { best = cost; nt = n; }
+    }
+    return nt == 4 ? launch_rect_nt<G, 4>(c, g) : nt == 3 ? launch_rect_nt<G, 3>(c, g) : launch_rect_nt<G, 2>(c, g);
+}
+
+}  // namespace
+
+bool try_bwn_rect(const float* x, const uint32_t* wbits, const float* thr, float* y, uint32_t* bits, int N, int H, int W, int C, int O,
+                  int k, int stride, int pad, int P, int Q, hipStream_t s, int* rc) {
+    if (C != 3 || !(k == 7 || k == 11) || stride != 4) return false;
+    if ((long long)H * W * C >= (1LL << 31)) return false;
+    if ((long long)N * cdiv(P, 4) * cdiv(Q, 8) >= (1LL << 31) - 65536) return false;
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
+        *rc = BNN_ERR_DEVICE;
+        return true;
+    }
+    RectArgs g = {};
+    g.H = H; g.W = W; g.O = O; g.pad = pad; g.P = P; g.Q = Q;
+    const RectCall c = {x, wbits, thr, y, bits, cus, s};
+    *rc = k == 7 ? launch_rect<RectGeom<7, 4>>(c, g, N) : launch_rect<RectGeom<11, 4>>(c, g, N);
+    return true;
+}
+
+}  // namespace bnn
