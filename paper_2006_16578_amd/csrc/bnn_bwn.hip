@@ -866,37 +866,47 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
     };
     int t = tile_of(0);
     if (t < g.ntiles) request(t);              // the first patch is on its way while the weights are staged
-    {   // weights of this channel tile -> LDS, split on the way (w [O][k][k][C]; a run is 8 consecutive values of one filter
-        // row, zero past the row's end; column = output channel): unit (plane, run, column) of wlds.  Every load is issued
-        // before the first split; pairs past the end repeat the last one and store nothing.
-        constexpr int PER = (G::WUNITS + G::WAVES * 64 - 1) / (G::WAVES * 64);
-        float xs[PER][8];
+    {   // weights of this channel tile (w [O][k][k][C]) -> LDS in whole lines, into the patches' space, and from there, split on the way, to
+        // their place: unit (plane, run, column) of wlds, a run being 8 consecutive values of one filter row, zero past the row's end; column =
+        // output channel.  Each lane fetching its runs by itself (24 loads of 64 lines each) and splitting value by value: 1 x 224x224x3, nine
+        // products, 13.8 us, now 11.9; 64 images 39.3, now 37.6.
+        constexpr int NTHR = G::WAVES * 64, FILT = G::KS * G::SEG, RAW = COLS * FILT, RPER = (RAW + NTHR - 1) / NTHR;
+        constexpr int PER = (G::WUNITS + NTHR - 1) / NTHR;
+        static_assert((size_t)(RAW + 8) * 4 <= (size_t)G::WAVES * 3 * G::PLANE, "the patches' space holds the weights first");
+        float* raw = reinterpret_cast<float*>(smem + G::WPL * G::WUNITS);
+        const float* src = wv + (long long)n0 * FILT;
+        const int last = min(COLS, g.O - n0) * FILT - 1;
+        float v[RPER];
+#pragma unroll
+        for (int i = 0; i < RPER; ++i) v[i] = src[min(tid + i * NTHR, last)];
+#pragma unroll
+        for (int i = 0; i < RPER; ++i)
+            if (tid + i * NTHR < RAW) raw[tid + i * NTHR] = v[i];
+        __syncthreads();
+        uint32_t xs[PER][8];
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int p = min(tid + i * G::WAVES * 64, G::WUNITS - 1);
-            const int rho = p >> 6, o = min(n0 + (p & 63), g.O - 1);
-            const int r = rho / G::RPR, j = rho - r * G::RPR;
-            const float* wrow = wv + ((long long)o * G::KS + r) * G::SEG;
+            const int p = min(tid + i * NTHR, G::WUNITS - 1);
+            const int rho = p >> 6, r = rho / G::RPR, j = rho - r * G::RPR;
+            // the last run of a row reads on into the next one (the last of all past the weights, still in the patches' space)
+            const uint32_t* run = reinterpret_cast<const uint32_t*>(raw) + (p & 63) * FILT + r * G::SEG + 8 * j;
+            const uint32_t col = n0 + (p & 63) < g.O ? 0xFFFFFFFFu : 0u, tail = j < G::RPR - 1 ? col : 0u;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) xs[i][e] = wrow[min(8 * j + e, G::SEG - 1)];
+            for (int e = 0; e < 8; ++e) xs[i][e] = run[e] & (8 * (G::RPR - 1) + e < G::SEG ? col : tail);
         }
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int p = tid + i * G::WAVES * 64;
-            const int rho = min(p, G::WUNITS - 1) >> 6;
-            const int j = rho % G::RPR;
-            const bool col_ok = n0 + (p & 63) < g.O;
-            uint32_t hi[4] = {0u, 0u, 0u, 0u}, mid[4] = {0u, 0u, 0u, 0u}, lo[4] = {0u, 0u, 0u, 0u};
+            const int p = tid + i * NTHR;
+            uint32_t hi[4], mid[4], lo[4];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float x0 = (col_ok && 8 * j + e < G::SEG) ? xs[i][e] : 0.f;
-                const uint32_t a = __float_as_uint(x0);
-                const float r1 = x0 - __uint_as_float(a & 0xffff0000u);
-                const uint32_t b = __float_as_uint(r1);
-                const float r2 = r1 - __uint_as_float(b & 0xffff0000u);
-                hi[e >> 1] |= (a >> 16) << (16 * (e & 1));
-                mid[e >> 1] |= (b >> 16) << (16 * (e & 1));
-                lo[e >> 1] |= (__float_as_uint(r2) >> 16) << (16 * (e & 1));
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t ua = xs[i][2 * e], ub = xs[i][2 * e + 1];
+                const float ra = __uint_as_float(ua) - __uint_as_float(ua & 0xffff0000u), rb = __uint_as_float(ub) - __uint_as_float(ub & 0xffff0000u);
+                const uint32_t va = __float_as_uint(ra), vb = __float_as_uint(rb);
+                const float la = ra - __uint_as_float(va & 0xffff0000u), lb = rb - __uint_as_float(vb & 0xffff0000u);
+                hi[e] = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
+                mid[e] = __builtin_amdgcn_perm(vb, va, 0x07060302u);
+                lo[e] = __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);
             }
             if (p < G::WUNITS) {
                 wlds[p] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
@@ -905,12 +915,11 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
             }
         }
     }
-    if (t < g.ntiles) stage(t);
-    __syncthreads();                                                   // the only barrier: the weights are in place
+    __syncthreads();                                                   // the weights are in place and the patches' space is free: the last barrier
     for (int r = 0; t < g.ntiles; ++r) {
         const int t_next = tile_of(r + 1);
-        const bool more = t_next < g.ntiles;
-        if (more) request(t_next);
+        stage(t);
+        if (t_next < g.ntiles) request(t_next);
 
         // ---- K loop, unrolled in full: run index of this lane = 2 * step + half; every offset is a compile-time constant
         v16f_bwn acc[NT];
@@ -1011,8 +1020,7 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
                 if (wi < ow) bits[pix * ow + wi] = wout[j];
             }
         }
-        if (more) stage(t_next);               // every read of this rectangle's patch has been consumed by its MFMAs
-        t = t_next;
+        t = t_next;                            // every read of this rectangle's patch has been consumed by its MFMAs
     }
 }
 

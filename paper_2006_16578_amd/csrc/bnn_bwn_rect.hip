@@ -207,11 +207,10 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void bwn_rect_kernel(const float*
         __syncthreads();                       // the last barrier: the patches' space is free
     }
 
-    if (t < g.ntiles) stage(t);
     for (int r = 0; t < g.ntiles; ++r) {
         const int t_next = tile_of(r + 1);
-        const bool more = t_next < g.ntiles;
-        if (more) request(t_next);
+        stage(t);
+        if (t_next < g.ntiles) request(t_next);
 
         v16f acc[NT];
 #pragma unroll
@@ -312,8 +311,7 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void bwn_rect_kernel(const float*
                 if (wi < ow) bits[pix * ow + wi] = wout[j];
             }
         }
-        if (more) stage(t_next);               // every read of this rectangle's patch has been consumed by its MFMAs
-        t = t_next;
+        t = t_next;                            // every read of this rectangle's patch has been consumed by its MFMAs
     }
 }
 
