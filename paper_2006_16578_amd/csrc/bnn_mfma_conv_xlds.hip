@@ -348,7 +348,7 @@ int launch_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
     x.div_groups = make_fastdiv((uint32_t)x.groups); x.div_tw = make_fastdiv((uint32_t)g.tw);
     const int gx = (int)cdiv(g.rows, WM * MT * 32), gy = (int)cdiv(g.cols, WN * NT * 32);
     const unsigned nwg = (unsigned)(cdiv((long long)gx * gy, 8) * 8);
-    auto launch = [&](auto form, auto shortcut) {
+    auto run = [&](auto form, auto shortcut) {
         constexpr OutputForm FORM = decltype(form)::value;
         constexpr bool SHORTCUT = decltype(shortcut)::value;
         static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_xlds_kernel<MT, NT, WM, WN, FORM, SHORTCUT>),
@@ -364,19 +364,19 @@ int launch_xlds(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
     switch (output_form(e)) {
         case OUT_BITS: {
             constexpr std::integral_constant<OutputForm, OUT_BITS> f{};
-            return shortcut ? launch(f, with) : launch(f, none);
+            return shortcut ? run(f, with) : run(f, none);
         }
         case OUT_BITS_AND_SUMS:
-            if constexpr (WM * WN == 4) return launch(std::integral_constant<OutputForm, OUT_BITS_AND_SUMS>{}, with);
+            if constexpr (WM * WN == 4) return run(std::integral_constant<OutputForm, OUT_BITS_AND_SUMS>{}, with);
             break;
         case OUT_SUMS:
-            if constexpr (WM * WN == 4) return launch(std::integral_constant<OutputForm, OUT_SUMS>{}, none);
+            if constexpr (WM * WN == 4) return run(std::integral_constant<OutputForm, OUT_SUMS>{}, none);
             break;
         case OUT_STREAMED_RESIDUAL:
-            if constexpr (MT == 2) return launch(std::integral_constant<OutputForm, OUT_STREAMED_RESIDUAL>{}, none);
+            if constexpr (MT == 2) return run(std::integral_constant<OutputForm, OUT_STREAMED_RESIDUAL>{}, none);
             break;
         case OUT_RESIDUAL:
-            if constexpr (MT == 2) return launch(std::integral_constant<OutputForm, OUT_RESIDUAL>{}, none);
+            if constexpr (MT == 2) return run(std::integral_constant<OutputForm, OUT_RESIDUAL>{}, none);
             break;
     }
     return BNN_ERR_UNSUPPORTED;     // not dispatched: residuals take the tiles of two row fragments (xlds_tile)
