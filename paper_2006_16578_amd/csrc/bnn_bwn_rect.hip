@@ -1,4 +1,4 @@
-// First layer with binarized weights for large strided windows (11x11 and 7x7, stride 4) of 3-channel images: a rectangle of
+// First layer with binarized weights for large strided windows (11x11 stride 4, 7x7 stride 2 and 4) of 3-channel images: a rectangle of
 // output pixels and up to 128 channels per wave, input patch in the wave's own LDS, weights as sign bits in registers.
 //
 // Same arithmetic as the kernels of bnn_bwn.hip: an fp32 value is the exact sum of three bf16 terms, a +1/-1 weight is exact in bf16,
@@ -16,7 +16,8 @@
 //    workgroup, rows of bits, then the words.
 // The patch of the wave's next rectangle is requested before the K loop and split after the epilogue; no barrier after the prologue.
 // Measured, before -> now (weights included): 11x11, n x 224x224x3 -> 128: n = 1 31.7 -> 8.4 us, 16 33.5 -> 18.2, 64 61 -> 52, 128 107 -> 91;
-// 7x7 -> 64: n = 1 20.1 -> 5.6, 16 21.1 -> 7.5, 128 64 -> 31.5.  The MFMAs of the 128-image 11x11 layer take 60 us (K slots 82 % full); the two
+// 7x7 stride 4 -> 64: n = 1 20.1 -> 5.6, 16 21.1 -> 7.5, 128 64 -> 31.5; stride 2 -> 64: n = 1 13.5 -> 5.6, 32 47 -> 28.5, 128 157 -> 91
+// (two workgroups a compute unit there, which its patches and 114 registers allow: 88, but 8 x 112x112x3 5.7 -> 6.9).  The MFMAs of the 128-image 11x11 layer take 60 us (K slots 82 % full); the two
 // waves of a SIMD overlap the rest of each other in part (another wave priority for one of them changes nothing).
 #include <type_traits>
 
@@ -30,9 +31,9 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float float2_ub __attribute__((ext_vector_type(2), aligned(4)));       // 8-byte load, 4-byte aligned
 extern "C" __device__ int bnn_rect_writelane_i32(int val, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
 
-template <int KS_, int STRIDE_>
+template <int KS_, int STRIDE_, int FQ_>
 struct RectGeom {
-    static constexpr int KS = KS_, STRIDE = STRIDE_, CIN = 3, FP = 4, FQ = 8, WAVES = 8;
+    static constexpr int KS = KS_, STRIDE = STRIDE_, CIN = 3, FQ = FQ_, FP = 32 / FQ_, WAVES = 8;
     static constexpr int TAPS = KS * KS;
     static constexpr int PR = (FP - 1) * STRIDE + KS;                        // patch rows
     static constexpr int ROW_ELEMS = ((FQ - 1) * STRIDE + KS) * CIN;         // input values of a patch row
@@ -47,7 +48,8 @@ struct RectGeom {
     static constexpr int PAIRS = PITCH / 4;                                  // 2-element units written per patch row (data + zeroed slack)
     static constexpr int PLANE = PR * PITCH;                                 // bytes of one bf16 plane of a patch
     static constexpr size_t LDS = (size_t)WAVES * 3 * PLANE;
-    static_assert(FP * FQ == 32 && PAIRS <= 64 && (STRIDE * CIN * 2) % 8 == 0, "one lane per pair; 8-byte aligned runs");
+    static constexpr bool ALIGNED8 = (STRIDE * CIN * 2) % 8 == 0;            // of every run, else 4 bytes
+    static_assert(FP * FQ == 32 && PAIRS <= 64 && (STRIDE * CIN * 2) % 4 == 0, "one lane per pair; aligned runs");
     static_assert(SEG <= 64 && LDS <= 160 * 1024, "a filter row of signs in two words; eight patches in LDS");
 };
 
@@ -233,9 +235,14 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void bwn_rect_kernel(const float*
             const char* asrc = !upper ? abase : wraps ? a_next : a_same;
 #pragma unroll
             for (int pl = 0; pl < 3; ++pl) {
-                const uint2 lo = *reinterpret_cast<const uint2*>(asrc + off + pl * G::PLANE);
-                const uint2 hi = *reinterpret_cast<const uint2*>(asrc + off + pl * G::PLANE + 8);
-                oa[st & 1][pl] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+                const char* run = asrc + off + pl * G::PLANE;
+                if constexpr (G::ALIGNED8) {
+                    const uint2 lo = *reinterpret_cast<const uint2*>(run), hi = *reinterpret_cast<const uint2*>(run + 8);
+                    oa[st & 1][pl] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+                } else {
+                    const uint32_t* w = reinterpret_cast<const uint32_t*>(run);
+                    oa[st & 1][pl] = make_uint4(w[0], w[1], w[2], w[3]);
+                }
             }
             // values of the run each half-wave multiplies
             constexpr int v0 = wraps ? G::LAST : 8, v1 = !upper ? 0 : rho1 % G::RPR == G::RPR - 1 ? G::LAST : 8;
@@ -362,9 +369,9 @@ int launch_rect(const RectCall& c, RectArgs g, int N) {
 
 bool try_bwn_rect(const float* x, const uint32_t* wbits, const float* thr, float* y, uint32_t* bits, int N, int H, int W, int C, int O,
                   int k, int stride, int pad, int P, int Q, hipStream_t s, int* rc) {
-    if (C != 3 || !(k == 7 || k == 11) || stride != 4) return false;
+    if (C != 3 || !(k == 7 ? stride == 2 || stride == 4 : k == 11 && stride == 4)) return false;
     if ((long long)H * W * C >= (1LL << 31)) return false;
-    if ((long long)N * cdiv(P, 4) * cdiv(Q, 8) >= (1LL << 31) - 65536) return false;
+    if ((long long)N * cdiv(P, 2) * cdiv(Q, 8) >= (1LL << 31) - 65536) return false;
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) {
         *rc = BNN_ERR_DEVICE;
@@ -373,7 +380,8 @@ bool try_bwn_rect(const float* x, const uint32_t* wbits, const float* thr, float
     RectArgs g = {};
     g.H = H; g.W = W; g.O = O; g.pad = pad; g.P = P; g.Q = Q;
     const RectCall c = {x, wbits, thr, y, bits, cus, s};
-    *rc = k == 7 ? launch_rect<RectGeom<7, 4>>(c, g, N) : launch_rect<RectGeom<11, 4>>(c, g, N);
+    *rc = k == 11 ? launch_rect<RectGeom<11, 4, 8>>(c, g, N)
+        : stride == 4 ? launch_rect<RectGeom<7, 4, 8>>(c, g, N) : launch_rect<RectGeom<7, 2, 16>>(c, g, N);
     return true;
 }
 

@@ -514,29 +514,31 @@ def test_bwn_first_layer_pixel_records(bnn, orc, shape):
     assert np.array_equal(got[~covers], only[~covers]) and not got[covers].any()
 
 
-# 11x11 and 7x7 stride-4 first layers of 3-channel images (signs in registers, a rectangle of 4 x 8 outputs per wave): 64, 96 and 128 channels
+# 11x11 stride-4 and 7x7 first layers of 3-channel images (signs in registers, a rectangle of 4 x 8 or 2 x 16 outputs per wave): 64, 96 and 128 channels
 # per wave by the number of rectangles, ragged and several channel tiles, one image row or column of rectangles, one output, large and no
 # padding, several rectangles per wave; integers are exact in any order; infinite thresholds and a pixel of +infinity
 @pytest.mark.parametrize("shape", [(1, 11, 11, 1, 11, 0), (2, 50, 37, 33, 11, 2), (3, 227, 227, 128, 11, 2), (9, 223, 224, 96, 11, 2),
                                    (20, 224, 221, 128, 11, 2), (12, 224, 230, 129, 11, 5), (30, 225, 120, 300, 11, 0),
                                    (2, 9, 60, 64, 7, 3), (3, 224, 224, 65, 7, 3), (9, 224, 224, 96, 7, 3), (40, 224, 224, 128, 7, 3),
-                                   (25, 201, 190, 190, 7, 6), (60, 33, 34, 40, 7, 0)])
+                                   (25, 201, 190, 190, 7, 6), (60, 33, 34, 40, 7, 0),
+                                   (1, 7, 7, 1, 7, 0, 2), (3, 31, 36, 65, 7, 3, 2), (5, 112, 109, 96, 7, 3, 2), (9, 130, 127, 128, 7, 3, 2),
+                                   (14, 60, 221, 200, 7, 5, 2)])
 def test_bwn_first_layer_strided_windows(bnn, orc, shape):
-    N, H, W, O, k, pad = shape
+    N, H, W, O, k, pad, st = shape if len(shape) == 7 else shape + (4,)
     rng = np.random.default_rng(sum(shape))
     wb = wl.random_bits(rng, (O, k, k), 3)
     thr = rng.integers(-4000, 4001, size=O).astype(np.float32)
     thr[0], thr[O // 2] = np.inf, -np.inf
     x = rng.integers(-500, 501, size=(N, H, W, 3)).astype(np.float32)
     print(shape, flush=True)
-    ref = orc.bwn_conv_f32(x, wb, 3, 4, pad)
-    bits, y = bnn.bwn_conv_thr(to_dev(x), to_dev(wb), to_dev(thr), 3, 4, pad, want_f32=True)
+    ref = orc.bwn_conv_f32(x, wb, 3, st, pad)
+    bits, y = bnn.bwn_conv_thr(to_dev(x), to_dev(wb), to_dev(thr), 3, st, pad, want_f32=True)
     assert np.array_equal(host(y), ref) and np.array_equal(words(bits), orc.pack_f32(ref, thr))
-    only = words(bnn.bwn_conv_thr(to_dev(x), to_dev(wb), to_dev(thr), 3, 4, pad))
+    only = words(bnn.bwn_conv_thr(to_dev(x), to_dev(wb), to_dev(thr), 3, st, pad))
     assert np.array_equal(only, words(bits))
     # a pixel of +infinity (its lower terms are NaN): no bit of a channel that does not exist, other images unchanged
     x[0, H // 2, W // 2, 1] = np.inf
-    got = words(bnn.bwn_conv_thr(to_dev(x), to_dev(wb), to_dev(thr), 3, 4, pad))
+    got = words(bnn.bwn_conv_thr(to_dev(x), to_dev(wb), to_dev(thr), 3, st, pad))
     assert np.array_equal(got[1:], only[1:])
     if O % 32:
         assert not (got[..., -1].view(np.uint32) >> np.uint32(O % 32)).any()
