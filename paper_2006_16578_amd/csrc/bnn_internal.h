@@ -162,11 +162,11 @@ int launch_persist_chain(const PersistNet& net, int max_tiles, int max_grid, uns
 bool mfma_conv_pools(const Geom& g, const Epi& e);
 int launch_valu(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
-// Skinny matrix products (at most 128 rows): workgroups of 32 columns x all rows whose waves split K.
+// Skinny matrix products (at most 128 rows): workgroups of 16 or 32 columns x all rows whose waves split K.
 bool mfma_skinny_takes(const Geom& g);
 const char* describe_mfma_skinny(const Geom& g);
 int launch_mfma_skinny(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
-// Large matrix products: 256 x 256 workgroup tiles whose operands are expanded once, on their way into LDS.
+// Matrix products on bits as {0, 1}: the tile for a product (BITS_NONE: another kernel serves it).
 enum BitsChoice { BITS_NONE = 0, BITS_256x256, BITS_256x128, BITS_192x128, BITS_128x128, BITS_128x128W8, BITS_128x64, BITS_K64x64, BITS_K32x32 };
 BitsChoice mfma_bits_choice(const Geom& g, const Epi& e, int tile);       // tile: pick_tile's
 int launch_mfma_bits(BitsChoice tile, const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
