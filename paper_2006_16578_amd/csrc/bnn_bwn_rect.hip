@@ -15,8 +15,8 @@
 //  * the weights reach the lanes by way of LDS (the patches' space, idle until the first is staged): whole lines once per
 //    workgroup, rows of bits, then the words.
 // The patch of the wave's next rectangle is requested before the K loop and split after the epilogue; no barrier after the prologue.
-// Measured, before -> now (weights included): 11x11, n x 224x224x3 -> 128: n = 1 31.7 -> 8.4 us, 16 33.5 -> 18.2, 64 61 -> 52, 128 107 -> 91;
-// 7x7 stride 4 -> 64: n = 1 20.1 -> 5.6, 16 21.1 -> 7.5, 128 64 -> 31.5; stride 2 -> 64: n = 1 13.5 -> 5.6, 32 47 -> 28.5, 128 157 -> 91
+// Measured, before -> now (weights included): 11x11, n x 224x224x3 -> 128: n = 1 31.7 -> 9.0 us, 16 33.5 -> 18.8, 64 61 -> 53.8, 128 107 -> 92;
+// 7x7 stride 4 -> 64: n = 1 20.1 -> 5.8, 16 21.1 -> 7.7, 128 64 -> 33.5; stride 2 -> 64: n = 1 13.5 -> 5.7, 32 47 -> 29, 128 157 -> 94
 // (two workgroups a compute unit there, which its patches and 114 registers allow: 88, but 8 x 112x112x3 5.7 -> 6.9).  The MFMAs of the 128-image 11x11 layer take 60 us (K slots 82 % full); the two
 // waves of a SIMD overlap the rest of each other in part (another wave priority for one of them changes nothing).
 #include <type_traits>
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void bwn_rect_kernel(const float*
         auto fetch = [&](auto st_tag) {
             constexpr int st = decltype(st_tag)::value;
             constexpr int rho0 = 2 * st, rho1 = 2 * st + 1;
-            constexpr bool upper = rho1 < G::NRUNS;                    // false: the upper half-wave's weights are zero, its values the lower's
+            constexpr bool upper = rho1 < G::NRUNS;                    // false: there is no run for the upper half-wave
             constexpr bool wraps = rho0 % G::RPR == G::RPR - 1;
             constexpr int off = (rho0 / G::RPR) * G::PITCH + (rho0 % G::RPR) * 16;
             const char* asrc = !upper ? abase : wraps ? a_next : a_same;
@@ -244,23 +244,31 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void bwn_rect_kernel(const float*
                     oa[st & 1][pl] = make_uint4(w[0], w[1], w[2], w[3]);
                 }
             }
-            // values of the run each half-wave multiplies
-            constexpr int v0 = wraps ? G::LAST : 8, v1 = !upper ? 0 : rho1 % G::RPR == G::RPR - 1 ? G::LAST : 8;
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 uint32_t reg[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint32_t m0 = (2 * i < v0 ? 0xFFFFu : 0u) | (2 * i + 1 < v0 ? 0xFFFF0000u : 0u);
-                    const uint32_t m1 = (2 * i < v1 ? 0xFFFFu : 0u) | (2 * i + 1 < v1 ? 0xFFFF0000u : 0u);
-                    reg[i] = ((sw[st / 4][j] << (15 - 4 * (st % 4) - i)) & 0x80008000u) | 0x3F803F80u;
-                    if (m0 != 0xFFFFFFFFu || m1 != 0xFFFFFFFFu) reg[i] &= half ? m1 : m0;
-                }
+                for (int i = 0; i < 4; ++i) reg[i] = ((sw[st / 4][j] << (15 - 4 * (st % 4) - i)) & 0x80008000u) | 0x3F803F80u;
                 ob[st & 1][j] = make_uint4(reg[0], reg[1], reg[2], reg[3]);
             }
         };
         auto multiply = [&](auto st_tag) {
             constexpr int st = decltype(st_tag)::value;
+            // What a row's last run reads past the filter becomes zero here, not in the weights: a pixel that is not finite then touches no
+            // output whose window does not cover it.  (As the values arrive, the masks wait for LDS a step early: 3 to 9 % slower.)
+            constexpr int v0 = (2 * st) % G::RPR == G::RPR - 1 ? G::LAST : 8;                  // values of the run each half-wave multiplies
+            constexpr int v1 = 2 * st + 1 >= G::NRUNS ? 0 : (2 * st + 1) % G::RPR == G::RPR - 1 ? G::LAST : 8;
+            auto keep = [&](uint32_t v, int i) {
+                const uint32_t m0 = (2 * i < v0 ? 0xFFFFu : 0u) | (2 * i + 1 < v0 ? 0xFFFF0000u : 0u);
+                const uint32_t m1 = (2 * i < v1 ? 0xFFFFu : 0u) | (2 * i + 1 < v1 ? 0xFFFF0000u : 0u);
+                return m0 == 0xFFFFFFFFu && m1 == 0xFFFFFFFFu ? v : v & (half ? m1 : m0);
+            };
+            if constexpr (v0 < 8 || v1 < 8)
+#pragma unroll
+                for (int pl = 0; pl < 3; ++pl) {
+                    uint4& a = oa[st & 1][pl];
+                    a = make_uint4(keep(a.x, 0), keep(a.y, 1), keep(a.z, 2), keep(a.w, 3));
+                }
 #pragma unroll
             for (int pl = 2; pl >= 0; --pl)                            // smallest terms first
 #pragma unroll
