@@ -760,7 +760,9 @@ struct WaveGeom {
     static constexpr int WUNITS = NRUNS * 64;                                // 16-byte units of one weight plane in LDS
     static constexpr int WAVES = 8;                                // what fits LDS beside the weights
     static constexpr size_t LDS = (size_t)WPL * WUNITS * 16 + (size_t)WAVES * 3 * PLANE;
-    static_assert(FP * FQ == 32 && PAIRS <= 64 && (STRIDE * CIN * 2) % 8 == 0, "one lane per pair; 8-byte aligned runs");
+    static constexpr int LAST = SEG - 8 * (RPR - 1);                         // values of a row's last run
+    static constexpr bool ALIGNED8 = (STRIDE * CIN * 2) % 8 == 0;            // of every run, else 4 bytes
+    static_assert(FP * FQ == 32 && PAIRS <= 64 && (STRIDE * CIN * 2) % 4 == 0, "one lane per pair; aligned runs");
 };
 
 struct WaveArgs {
@@ -941,9 +943,14 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
             const char* bsrc = upper_real ? bbase + rho0 * (COLS * 16) : bbase - half * (COLS * 16) + rho0 * (COLS * 16);
 #pragma unroll
             for (int pl = 0; pl < 3; ++pl) {
-                const uint2 lo = *reinterpret_cast<const uint2*>(asrc + pl * G::PLANE);
-                const uint2 hi = *reinterpret_cast<const uint2*>(asrc + pl * G::PLANE + 8);
-                oa[st & 1][pl] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+                const char* run = asrc + pl * G::PLANE;
+                if constexpr (G::ALIGNED8) {
+                    const uint2 lo = *reinterpret_cast<const uint2*>(run), hi = *reinterpret_cast<const uint2*>(run + 8);
+                    oa[st & 1][pl] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+                } else {
+                    const uint32_t* w = reinterpret_cast<const uint32_t*>(run);
+                    oa[st & 1][pl] = make_uint4(w[0], w[1], w[2], w[3]);
+                }
                 if (pl < G::WPL)
 #pragma unroll
                     for (int j = 0; j < NT; ++j)
@@ -952,9 +959,27 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
         };
         auto multiply = [&](auto st_tag) {
             constexpr int st = decltype(st_tag)::value;
-            if (2 * st + 1 >= G::NRUNS && half) {
+            if constexpr (G::STRIDE == 4) {
+                if (2 * st + 1 >= G::NRUNS && half) {
 #pragma unroll
-                for (int pl = 0; pl < 3; ++pl) oa[st & 1][pl] = make_uint4(0u, 0u, 0u, 0u);
+                    for (int pl = 0; pl < 3; ++pl) oa[st & 1][pl] = make_uint4(0u, 0u, 0u, 0u);
+                }
+            } else {
+                // What a row's last run reads past the filter becomes zero here too, not only in the weights: a pixel that is not finite then
+                // touches no output whose window does not cover it, as in the direct kernel.
+                constexpr int v0 = (2 * st) % G::RPR == G::RPR - 1 ? G::LAST : 8;              // values of the run each half-wave multiplies
+                constexpr int v1 = 2 * st + 1 >= G::NRUNS ? 0 : (2 * st + 1) % G::RPR == G::RPR - 1 ? G::LAST : 8;
+                auto keep = [&](uint32_t v, int i) {
+                    const uint32_t m0 = (2 * i < v0 ? 0xFFFFu : 0u) | (2 * i + 1 < v0 ? 0xFFFF0000u : 0u);
+                    const uint32_t m1 = (2 * i < v1 ? 0xFFFFu : 0u) | (2 * i + 1 < v1 ? 0xFFFF0000u : 0u);
+                    return m0 == 0xFFFFFFFFu && m1 == 0xFFFFFFFFu ? v : v & (half ? m1 : m0);
+                };
+                if constexpr (v0 < 8 || v1 < 8)
+#pragma unroll
+                    for (int pl = 0; pl < 3; ++pl) {
+                        uint4& a = oa[st & 1][pl];
+                        a = make_uint4(keep(a.x, 0), keep(a.y, 1), keep(a.z, 2), keep(a.w, 3));
+                    }
             }
             // smallest terms first: (input term, weight term) pairs in order of decreasing index sum
 #pragma unroll
@@ -1037,7 +1062,9 @@ int launch_conv_f32_wave_v(const float* x, const float* w, const float* thr, flo
     // This kernel splits the weights itself while it stages them; the workspace the entry point asks for (the other
     // first-layer kernels keep their expanded weights there) is checked all the same, so that the call's contract does
     // not depend on which kernel serves a shape.
-    if (workspace == nullptr || workspace_bytes < (size_t)G::WPL * 2 * G::NSTEPS * 64 * 16 * col_tiles) return BNN_ERR_WORKSPACE;
+    // (stride 2: what the direct kernel asks, whose step count is a multiple of three)
+    constexpr int KEPT = G::STRIDE == 4 ? G::NSTEPS : (G::NSTEPS + 2) / 3 * 3;
+    if (workspace == nullptr || workspace_bytes < (size_t)G::WPL * 2 * KEPT * 64 * 16 * col_tiles) return BNN_ERR_WORKSPACE;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_f32_wave_kernel<G, TERMS, WANT_Y>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)LDS_MAX);
     if (attr != hipSuccess) return BNN_ERR_DEVICE;
@@ -1050,22 +1077,31 @@ int launch_conv_f32_wave_v(const float* x, const float* w, const float* thr, flo
     return check_launch();
 }
 
-// The geometries the wave-private kernel is built for.  true: launched (rc receives the status).
+template <int KS, int STRIDE, int FQ>
+int launch_conv_f32_wave(const float* x, const float* w, const float* thr, float* y, uint32_t* bits, int N, int H, int W, int O, int pad, int P,
+                         int Q, int products, void* workspace, size_t workspace_bytes, hipStream_t s) {
+    typedef WaveGeom<KS, STRIDE, 3, 32 / FQ, FQ> G;
+    static_assert(G::LDS <= LDS_MAX, "weights and eight patches fit LDS");
+    if (y != nullptr)
+        return products == 6 ? launch_conv_f32_wave_v<G, 6, true>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, workspace, workspace_bytes, s)
+                             : launch_conv_f32_wave_v<G, 9, true>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, workspace, workspace_bytes, s);
+    return products == 6 ? launch_conv_f32_wave_v<G, 6, false>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, workspace, workspace_bytes, s)
+                         : launch_conv_f32_wave_v<G, 9, false>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, workspace, workspace_bytes, s);
+}
+
+// The geometries the wave-private kernel is built for.  true: launched (rc receives the status).  Nine products, direct kernel with its expansion
+// launch -> this one, us, 1 and 32 x 224x224x3 -> 64: 3x3 stride 2 15.0 -> 6.0 and 41 -> 23, 5x5 19.0 -> 7.3 and 58 -> 32, 7x7 29.8 -> 11.1 and
+// 101 -> 62 (-> 128: 160 -> 114); six products alike.  Errors against 64 bits are the same to three digits.
 bool try_conv_f32_wave(const float* x, const float* w, const float* thr, float* y, uint32_t* bits, int N, int H, int W, int C, int O,
                        int k, int stride, int pad, int P, int Q, int products, void* workspace, size_t workspace_bytes, hipStream_t s,
                        int* rc) {
-    if (!(k == 7 && stride == 4 && C == 3)) return false;
+    if (C != 3 || !(stride == 4 ? k == 7 : stride == 2 && (k == 3 || k == 5 || k == 7))) return false;
     if ((long long)W * C < 2 || (long long)H * W * C >= (1LL << 31)) return false;
-    constexpr int FP = 4, FQ = 8;
-    typedef WaveGeom<7, 4, 3, FP, FQ> G;
-    static_assert(G::LDS <= LDS_MAX, "weights and eight patches fit LDS");
-    if ((long long)N * cdiv(P, FP) * cdiv(Q, FQ) >= (1LL << 31) - 65536) return false;
-    if (y != nullptr)
-        *rc = products == 6 ? launch_conv_f32_wave_v<G, 6, true>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, workspace, workspace_bytes, s)
-                            : launch_conv_f32_wave_v<G, 9, true>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, workspace, workspace_bytes, s);
-    else
-        *rc = products == 6 ? launch_conv_f32_wave_v<G, 6, false>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, workspace, workspace_bytes, s)
-                            : launch_conv_f32_wave_v<G, 9, false>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, workspace, workspace_bytes, s);
+    if ((long long)N * cdiv(P, stride) * cdiv(Q, 8) >= (1LL << 31) - 65536) return false;      // no fewer than the rectangles
+    *rc = stride == 4 ? launch_conv_f32_wave<7, 4, 8>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, products, workspace, workspace_bytes, s)
+        : k == 7 ? launch_conv_f32_wave<7, 2, 16>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, products, workspace, workspace_bytes, s)
+        : k == 5 ? launch_conv_f32_wave<5, 2, 16>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, products, workspace, workspace_bytes, s)
+                 : launch_conv_f32_wave<3, 2, 16>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, products, workspace, workspace_bytes, s);
     return true;
 }
 

@@ -549,6 +549,35 @@ def test_bwn_first_layer_strided_windows(bnn, orc, shape):
         assert np.array_equal(got[~covers], only[~covers]) and not got[covers].any(), bad
 
 
+# first layers with real weights, stride 2, on the kernel with wave-private patches: ragged rectangles, one output, no, odd and large
+# padding, ragged and several 64-channel tiles, several rectangles per wave; with integers below 2^12 every product is exact, in three terms
+# or in the largest two of each, and so is every sum; a pixel that is not finite touches no output that does not cover it
+@pytest.mark.parametrize("products", [9, 6])
+@pytest.mark.parametrize("shape", [(1, 3, 3, 1, 3, 0), (2, 37, 64, 65, 3, 1), (60, 130, 65, 40, 3, 1), (1, 5, 5, 64, 5, 0), (3, 40, 33, 130, 5, 2),
+                                   (30, 90, 131, 64, 5, 3), (1, 7, 7, 3, 7, 0), (2, 61, 70, 128, 7, 3), (20, 129, 112, 33, 7, 5)])
+def test_stem_split_stride_2(bnn, orc, shape, products):
+    N, H, W, O, k, pad = shape
+    rng = np.random.default_rng(sum(shape) + products)
+    x = rng.integers(-900, 901, size=(N, H, W, 3)).astype(np.float32)
+    w = rng.integers(-30, 31, size=(O, k, k, 3)).astype(np.float32)
+    thr = rng.integers(-50000, 50001, size=O).astype(np.float32)
+    print(shape, products, flush=True)
+    ref = orc.conv_f32(x, w, 2, pad)
+    bits, y = bnn.conv_f32_split_thr(to_dev(x), to_dev(w), to_dev(thr), 2, pad, want_f32=True, products=products)
+    assert np.array_equal(host(y), ref) and np.array_equal(words(bits), orc.pack_f32(ref, thr))
+    only = words(bnn.conv_f32_split_thr(to_dev(x), to_dev(w), to_dev(thr), 2, pad, products=products))
+    assert np.array_equal(only, words(bits))
+    h, q0 = H // 2, W // 2
+    P, Q = only.shape[1:3]
+    covers = np.zeros((N, P, Q), bool)
+    for p in range(P):
+        for q in range(Q):
+            covers[0, p, q] = 0 <= h - (p * 2 - pad) < k and 0 <= q0 - (q * 2 - pad) < k
+    x[0, h, q0, 0] = np.nan
+    got = words(bnn.conv_f32_split_thr(to_dev(x), to_dev(w), to_dev(thr), 2, pad, products=products))
+    assert np.array_equal(got[~covers], only[~covers]) and not got[covers].any()
+
+
 # weights and thresholds of 64 channels at a time go through LDS: groups one channel short, whole and one over, for workgroups of one
 # and of two groups
 @pytest.mark.parametrize("k,st", [(3, 1), (3, 2), (5, 1), (5, 2)])
