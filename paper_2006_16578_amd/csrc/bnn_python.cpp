@@ -78,24 +78,24 @@ Tensor empty(const Tensor& like, at::IntArrayRef sizes, at::ScalarType type) {
 inline int words(int bits) { return (int)(((long long)bits + 31) / 32); }
 template <class T> T* ptr(const Tensor& t) { return static_cast<T*>(t.data_ptr()); }
 
-// Runs f (the library's call) without the GIL; the result of the Python call.
-template <class F>
-PyObject* run(const Call& c, const char* what, PyObject* result, F f) {
+// The library's call, without the GIL; false: a Python error is set.  The arguments come by value: whatever reading them may throw (a tensor whose storage was freed
+// has no pointer) it throws in the caller, with the GIL held.
+template <class F, class... Args>
+bool run(const Call& c, const char* what, F f, Args... args) {
     void* s = nullptr;
     int status = 0;
-    if (!result || !c.stream(&s)) { Py_XDECREF(result); return nullptr; }
+    if (!c.stream(&s)) return false;
     Py_BEGIN_ALLOW_THREADS
-    status = f(s);
+    status = f(args..., s);
     Py_END_ALLOW_THREADS
-    if (status == 0) return result;
-    Py_DECREF(result);
+    if (status == 0) return true;
     PyObject* r = PyObject_CallFunction(check, "is", status, what);
     Py_XDECREF(r);
     if (r) PyErr_SetString(PyExc_RuntimeError, what);
-    return nullptr;
+    return false;
 }
 
-// C++ exceptions (an allocation that fails) become Python's.
+// C++ exceptions (an allocation that fails, a tensor without memory) become Python's.
 template <class F>
 PyObject* guarded(F f) {
     HANDLE_TH_ERRORS
@@ -122,9 +122,8 @@ PyObject* bmm(PyObject*, PyObject* const* a, Py_ssize_t nargs) {          // A, 
         PLAIN(c);
         const int M = (int)A.size(0), N = (int)B.size(0);
         const Tensor out = empty(A, {M, N}, at::kInt);
-        return run(c, "bnn_bmm", THPVariable_Wrap(out), [&](void* s) {
-            return p_bnn_bmm_ex(ptr<uint32_t>(A), ptr<uint32_t>(B), ptr<int32_t>(out), M, N, K, (int)A.size(1), (int)B.size(1), N, path, s);
-        });
+        const bool done = run(c, "bnn_bmm", p_bnn_bmm_ex, ptr<uint32_t>(A), ptr<uint32_t>(B), ptr<int32_t>(out), M, N, K, (int)A.size(1), (int)B.size(1), N, path);
+        return done ? THPVariable_Wrap(out) : nullptr;
     });
 }
 
@@ -139,9 +138,9 @@ PyObject* bmm_thr(PyObject*, PyObject* const* a, Py_ssize_t nargs) {      // A, 
         if (thr.size(0) != N) Py_RETURN_NONE;
         const int ld = (words(N) + 3) / 4 * 4;
         const Tensor out = empty(A, {M, ld}, BITS);
-        return run(c, "bnn_bmm_thr", THPVariable_Wrap(out), [&](void* s) {
-            return p_bnn_bmm_thr_ex(ptr<uint32_t>(A), ptr<uint32_t>(B), ptr<int32_t>(thr), ptr<uint32_t>(out), M, N, K, (int)A.size(1), (int)B.size(1), ld, path, s);
-        });
+        const bool done = run(c, "bnn_bmm_thr", p_bnn_bmm_thr_ex, ptr<uint32_t>(A), ptr<uint32_t>(B), ptr<int32_t>(thr), ptr<uint32_t>(out), M, N, K, (int)A.size(1),
+                              (int)B.size(1), ld, path);
+        return done ? THPVariable_Wrap(out) : nullptr;
     });
 }
 
@@ -168,9 +167,8 @@ PyObject* bconv(PyObject*, PyObject* const* a, Py_ssize_t nargs) {        // x, 
         Conv v;
         if (C < 1 || x.size(3) != words(C) || f.size(3) != x.size(3) || !v.set(x, f, stride, pad)) Py_RETURN_NONE;
         const Tensor y = empty(x, {v.N, v.P, v.Q, v.O}, at::kInt);
-        return run(c, "bnn_bconv", THPVariable_Wrap(y), [&](void* s) {
-            return p_bnn_bconv_ex(ptr<uint32_t>(x), ptr<uint32_t>(f), ptr<int32_t>(y), v.N, v.H, v.W, C, v.O, v.k, stride, pad, mode, path, s);
-        });
+        const bool done = run(c, "bnn_bconv", p_bnn_bconv_ex, ptr<uint32_t>(x), ptr<uint32_t>(f), ptr<int32_t>(y), v.N, v.H, v.W, C, v.O, v.k, stride, pad, mode, path);
+        return done ? THPVariable_Wrap(y) : nullptr;
     });
 }
 
@@ -190,15 +188,15 @@ PyObject* bconv_thr(PyObject*, PyObject* const* a, Py_ssize_t nargs) {    // x, 
         Tensor y;
         if (sum) y = empty(x, {v.N, v.P, v.Q, v.O}, at::kInt);
         const Tensor bits = empty(x, {v.N, v.P, v.Q, words(v.O)}, BITS);
-        PyObject* result = sum ? PyTuple_New(2) : THPVariable_Wrap(bits);
-        if (sum && result) {
-            PyTuple_SET_ITEM(result, 0, THPVariable_Wrap(bits));
-            PyTuple_SET_ITEM(result, 1, THPVariable_Wrap(y));
-        }
-        return run(c, "bnn_bconv_thr", result, [&](void* s) {
-            return p_bnn_bconv_thr_ex(ptr<uint32_t>(x), ptr<uint32_t>(f), add ? ptr<int32_t>(r) : nullptr, sum ? ptr<int32_t>(y) : nullptr, ptr<int32_t>(thr),
-                                      ptr<uint32_t>(bits), v.N, v.H, v.W, C, v.O, v.k, stride, pad, mode, path, s);
-        });
+        if (!run(c, "bnn_bconv_thr", p_bnn_bconv_thr_ex, ptr<uint32_t>(x), ptr<uint32_t>(f), add ? ptr<int32_t>(r) : nullptr, sum ? ptr<int32_t>(y) : nullptr,
+                 ptr<int32_t>(thr), ptr<uint32_t>(bits), v.N, v.H, v.W, C, v.O, v.k, stride, pad, mode, path))
+            return nullptr;
+        if (!sum) return THPVariable_Wrap(bits);
+        PyObject* result = PyTuple_New(2);
+        if (!result) return nullptr;
+        PyTuple_SET_ITEM(result, 0, THPVariable_Wrap(bits));
+        PyTuple_SET_ITEM(result, 1, THPVariable_Wrap(y));
+        return result;
     });
 }
 
@@ -214,8 +212,8 @@ PyObject* threshold_pack(PyObject*, PyObject* const* a, Py_ssize_t nargs) {   //
         std::vector<int64_t> sizes = X.sizes().vec();
         sizes.back() = ld;
         const Tensor bits = empty(X, sizes, BITS);
-        return run(c, "bnn_threshold_pack", THPVariable_Wrap(bits),
-                   [&](void* s) { return p_bnn_threshold_pack(ptr<int32_t>(X), ptr<int32_t>(thr), ptr<uint32_t>(bits), rows, cols, cols, ld, s); });
+        const bool done = run(c, "bnn_threshold_pack", p_bnn_threshold_pack, ptr<int32_t>(X), ptr<int32_t>(thr), ptr<uint32_t>(bits), rows, cols, cols, ld);
+        return done ? THPVariable_Wrap(bits) : nullptr;
     });
 }
 
@@ -229,8 +227,8 @@ PyObject* maxpool_or(PyObject*, PyObject* const* a, Py_ssize_t nargs) {   // bit
         const int N = (int)x.size(0), H = (int)x.size(1), W = (int)x.size(2);
         if (stride < 1 || win < 1 || win > H || win > W) Py_RETURN_NONE;
         const Tensor out = empty(x, {N, (H - win) / stride + 1, (W - win) / stride + 1, x.size(3)}, BITS);
-        return run(c, "bnn_maxpool_or", THPVariable_Wrap(out),
-                   [&](void* s) { return p_bnn_maxpool_or(ptr<uint32_t>(x), ptr<uint32_t>(out), N, H, W, C, win, stride, s); });
+        const bool done = run(c, "bnn_maxpool_or", p_bnn_maxpool_or, ptr<uint32_t>(x), ptr<uint32_t>(out), N, H, W, C, win, stride);
+        return done ? THPVariable_Wrap(out) : nullptr;
     });
 }
 
@@ -244,9 +242,9 @@ PyObject* bmm_general_f32(PyObject*, PyObject* const* a, Py_ssize_t nargs) {  //
         if (B.size(1) != K) Py_RETURN_NONE;
         const Tensor out = empty(A, {M, N}, at::kFloat);
         const Tensor work = empty(A, {std::max<int64_t>((int64_t)p_bnn_bmm_general_workspace_bytes(M, N, K), 256)}, at::kByte);
-        return run(c, "bnn_bmm_general_f32", THPVariable_Wrap(out), [&](void* s) {
-            return p_bnn_bmm_general_f32(ptr<float>(A), ptr<float>(B), ptr<float>(out), M, N, K, K, K, N, ptr<void>(work), (size_t)work.numel(), s);
-        });
+        const bool done = run(c, "bnn_bmm_general_f32", p_bnn_bmm_general_f32, ptr<float>(A), ptr<float>(B), ptr<float>(out), M, N, K, K, K, N, ptr<void>(work),
+                              (size_t)work.numel());
+        return done ? THPVariable_Wrap(out) : nullptr;
     });
 }
 
@@ -261,10 +259,9 @@ PyObject* bwn_conv_thr(PyObject*, PyObject* const* a, Py_ssize_t nargs) {     //
         if (C < 1 || x.size(3) != C || w.size(3) != words(C) || !v.set(x, w, stride, pad)) Py_RETURN_NONE;
         const Tensor bits = empty(x, {v.N, v.P, v.Q, words(v.O)}, BITS);
         const Tensor work = empty(x, {std::max<int64_t>((int64_t)p_bnn_bwn_workspace_bytes(C, v.O, v.k), 16)}, at::kByte);
-        return run(c, "bnn_bwn_conv_thr", THPVariable_Wrap(bits), [&](void* s) {
-            return p_bnn_bwn_conv_thr(ptr<float>(x), ptr<uint32_t>(w), ptr<float>(thr), nullptr, ptr<uint32_t>(bits), v.N, v.H, v.W, C, v.O, v.k, stride, pad,
-                                      ptr<void>(work), (size_t)work.numel(), s);
-        });
+        const bool done = run(c, "bnn_bwn_conv_thr", p_bnn_bwn_conv_thr, ptr<float>(x), ptr<uint32_t>(w), ptr<float>(thr), nullptr, ptr<uint32_t>(bits), v.N, v.H, v.W, C,
+                              v.O, v.k, stride, pad, ptr<void>(work), (size_t)work.numel());
+        return done ? THPVariable_Wrap(bits) : nullptr;
     });
 }
 
@@ -280,10 +277,9 @@ PyObject* conv_f32_split_thr(PyObject*, PyObject* const* a, Py_ssize_t nargs) { 
         if (w.size(3) != C || !v.set(x, w, stride, pad)) Py_RETURN_NONE;
         const Tensor bits = empty(x, {v.N, v.P, v.Q, words(v.O)}, BITS);
         const Tensor work = empty(x, {std::max<int64_t>((int64_t)p_bnn_conv_f32_split_workspace_bytes(C, v.O, v.k), 16)}, at::kByte);
-        return run(c, "bnn_conv_f32_split_thr_ex", THPVariable_Wrap(bits), [&](void* s) {
-            return p_bnn_conv_f32_split_thr_ex(ptr<float>(x), ptr<float>(w), ptr<float>(thr), nullptr, ptr<uint32_t>(bits), v.N, v.H, v.W, C, v.O, v.k, stride, pad,
-                                               products, ptr<void>(work), (size_t)work.numel(), s);
-        });
+        const bool done = run(c, "bnn_conv_f32_split_thr_ex", p_bnn_conv_f32_split_thr_ex, ptr<float>(x), ptr<float>(w), ptr<float>(thr), nullptr, ptr<uint32_t>(bits),
+                              v.N, v.H, v.W, C, v.O, v.k, stride, pad, products, ptr<void>(work), (size_t)work.numel());
+        return done ? THPVariable_Wrap(bits) : nullptr;
     });
 }
 
@@ -305,8 +301,8 @@ PyObject* net_forward(PyObject*, PyObject* const* a, Py_ssize_t nargs) {
         size_t need = 0;
         if (p_bnn_net_workspace_bytes(net, batch, &need) != 0 || (size_t)work.numel() < need) Py_RETURN_NONE;
         const Tensor out = empty(x, {batch, cols}, TYPES[kind]);
-        return run(c, "bnn_net_forward", THPVariable_Wrap(out),
-                   [&](void* s) { return p_bnn_net_forward(net, x.data_ptr(), out.data_ptr(), batch, work.data_ptr(), (size_t)work.numel(), path, s); });
+        const bool done = run(c, "bnn_net_forward", p_bnn_net_forward, net, x.data_ptr(), out.data_ptr(), batch, work.data_ptr(), (size_t)work.numel(), path);
+        return done ? THPVariable_Wrap(out) : nullptr;
     });
 }
 

@@ -100,6 +100,27 @@ def test_same_results_and_the_same_refusals(bnn, monkeypatch):
         del binding._load_native_module
 
 
+def test_a_tensor_without_a_pointer_raises(bnn):
+    # torch refuses the data pointer of such a tensor (one that is being traced, or copied on first write when memory has run out) by a C++ exception: it has to be raised
+    # before the interpreter lock is given up, where it would end the process.
+    for name, args in calls(bnn):
+        fn = getattr(bnn, name)
+        for i in [i for i, a in enumerate(args) if torch.is_tensor(a)]:
+            bad = args[i].clone()
+            torch._C._set_throw_on_mutable_data_ptr(bad)
+            with pytest.raises(RuntimeError, match="data pointer"):
+                fn(*args[:i], bad, *args[i + 1:])
+        fn(*args)
+    net = bnn.Net()
+    net.input_bits(128)
+    net.add_fc(torch.zeros((10, 4), dtype=torch.int32, device="cuda"), None, 128)
+    x = torch.zeros((3, 4), dtype=torch.int32, device="cuda")
+    net.forward(x)
+    torch._C._set_throw_on_mutable_data_ptr(x)
+    with pytest.raises(RuntimeError, match="data pointer"):
+        net.forward(x)
+
+
 def test_net_forward(bnn):
     g = torch.Generator(device="cuda").manual_seed(3)
     net = bnn.Net()
