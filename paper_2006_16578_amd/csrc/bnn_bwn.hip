@@ -959,28 +959,21 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
         };
         auto multiply = [&](auto st_tag) {
             constexpr int st = decltype(st_tag)::value;
-            if constexpr (G::STRIDE == 4) {
-                if (2 * st + 1 >= G::NRUNS && half) {
+            // What a row's last run reads past the filter becomes zero here too, not only in the weights: a pixel that is not finite then
+            // touches no output whose window does not cover it, as in the direct kernel.  (256 x 224x224x3 -> 64, 7x7 stride 4: 1 to 2 % of the time.)
+            constexpr int v0 = (2 * st) % G::RPR == G::RPR - 1 ? G::LAST : 8;                  // values of the run each half-wave multiplies
+            constexpr int v1 = 2 * st + 1 >= G::NRUNS ? 0 : (2 * st + 1) % G::RPR == G::RPR - 1 ? G::LAST : 8;
+            auto keep = [&](uint32_t v, int i) {
+                const uint32_t m0 = (2 * i < v0 ? 0xFFFFu : 0u) | (2 * i + 1 < v0 ? 0xFFFF0000u : 0u);
+                const uint32_t m1 = (2 * i < v1 ? 0xFFFFu : 0u) | (2 * i + 1 < v1 ? 0xFFFF0000u : 0u);
+                return m0 == 0xFFFFFFFFu && m1 == 0xFFFFFFFFu ? v : v & (half ? m1 : m0);
+            };
+            if constexpr (v0 < 8 || v1 < 8)
 #pragma unroll
-                    for (int pl = 0; pl < 3; ++pl) oa[st & 1][pl] = make_uint4(0u, 0u, 0u, 0u);
+                for (int pl = 0; pl < 3; ++pl) {
+                    uint4& a = oa[st & 1][pl];
+                    a = make_uint4(keep(a.x, 0), keep(a.y, 1), keep(a.z, 2), keep(a.w, 3));
                 }
-            } else {
-                // What a row's last run reads past the filter becomes zero here too, not only in the weights: a pixel that is not finite then
-                // touches no output whose window does not cover it, as in the direct kernel.
-                constexpr int v0 = (2 * st) % G::RPR == G::RPR - 1 ? G::LAST : 8;              // values of the run each half-wave multiplies
-                constexpr int v1 = 2 * st + 1 >= G::NRUNS ? 0 : (2 * st + 1) % G::RPR == G::RPR - 1 ? G::LAST : 8;
-                auto keep = [&](uint32_t v, int i) {
-                    const uint32_t m0 = (2 * i < v0 ? 0xFFFFu : 0u) | (2 * i + 1 < v0 ? 0xFFFF0000u : 0u);
-                    const uint32_t m1 = (2 * i < v1 ? 0xFFFFu : 0u) | (2 * i + 1 < v1 ? 0xFFFF0000u : 0u);
-                    return m0 == 0xFFFFFFFFu && m1 == 0xFFFFFFFFu ? v : v & (half ? m1 : m0);
-                };
-                if constexpr (v0 < 8 || v1 < 8)
-#pragma unroll
-                    for (int pl = 0; pl < 3; ++pl) {
-                        uint4& a = oa[st & 1][pl];
-                        a = make_uint4(keep(a.x, 0), keep(a.y, 1), keep(a.z, 2), keep(a.w, 3));
-                    }
-            }
             // smallest terms first: (input term, weight term) pairs in order of decreasing index sum
 #pragma unroll
             for (int sum = (TERMS == 9 ? 4 : 2); sum >= 0; --sum)

@@ -578,6 +578,33 @@ def test_stem_split_stride_2(bnn, orc, shape, products):
     assert np.array_equal(got[~covers], only[~covers]) and not got[covers].any()
 
 
+# the 7x7 stride-4 stem likewise: a filter row's last run reads one pixel beyond the window, whose zero weights a pixel that is not finite would turn into NaN
+@pytest.mark.parametrize("products", [9, 6])
+@pytest.mark.parametrize("shape", [(1, 7, 11, 1, 0), (2, 33, 40, 65, 3), (40, 60, 61, 64, 3)])
+def test_stem_split_not_finite(bnn, orc, shape, products):
+    N, H, W, O, pad = shape
+    rng = np.random.default_rng(sum(shape) + products)
+    x = rng.integers(-900, 901, size=(N, H, W, 3)).astype(np.float32)
+    w = rng.integers(-30, 31, size=(O, 7, 7, 3)).astype(np.float32)
+    thr = rng.integers(-50000, 50001, size=O).astype(np.float32)
+    only = words(bnn.conv_f32_split_thr(to_dev(x), to_dev(w), to_dev(thr), 4, pad, products=products))
+    assert np.array_equal(only, orc.pack_f32(orc.conv_f32(x, w, 4, pad), thr))
+    P, Q = only.shape[1:3]
+    h, q0 = H // 2, Q // 2
+    for col in (q0 * 4 - pad + 6, q0 * 4 - pad + 7):        # the last pixel of a window's rows, and the one behind it
+        if col >= W:
+            continue
+        covers = np.zeros((N, P, Q), bool)
+        for p in range(P):
+            for q in range(Q):
+                covers[N - 1, p, q] = 0 <= h - (p * 4 - pad) < 7 and 0 <= col - (q * 4 - pad) < 7
+        for bad in (np.inf, np.nan):
+            xb = x.copy()
+            xb[N - 1, h, col, 1] = bad
+            got = words(bnn.conv_f32_split_thr(to_dev(xb), to_dev(w), to_dev(thr), 4, pad, products=products))
+            assert np.array_equal(got[~covers], only[~covers]) and not got[covers].any(), (col, bad)
+
+
 # weights and thresholds of 64 channels at a time go through LDS: groups one channel short, whole and one over, for workgroups of one
 # and of two groups
 @pytest.mark.parametrize("k,st", [(3, 1), (3, 2), (5, 1), (5, 2)])
