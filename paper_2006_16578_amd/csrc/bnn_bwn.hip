@@ -586,6 +586,15 @@ __global__ __launch_bounds__(WAVES * 64) void bwn_conv_kernel(const float* __res
     }
 }
 
+int compute_units() {       // of the current device; 0: not known
+    int dev = 0, cus = 0;
+    return hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess ? cus : 0;
+}
+
+// The direct kernel's workgroups (of eight waves) per channel tile, and the groups of 32 MT outputs that its busiest wave takes.
+long long direct_workgroups(long long npix, int MT, int col_tiles, int cus) { return min((int)cdiv(npix, 32 * 8 * MT), max(1, cus / col_tiles)); }
+long long direct_rounds(long long npix, int MT, long long wgs) { return cdiv(cdiv(npix, 32 * MT), 8 * wgs); }
+
 template <int MT, int NT, int WAVES, int NPL, int TERMS = 3 * NPL>
 int launch_bwn_direct(const float* x, const void* weights, const float* thr, float* y, uint32_t* bits, int N, int H, int W,
                       int C, int O, int k, int stride, int pad, int P, int Q, void* workspace, size_t workspace_bytes,
@@ -594,12 +603,20 @@ int launch_bwn_direct(const float* x, const void* weights, const float* thr, flo
     const long long npix = (long long)N * P * Q;
     const int seg = k * C, nruns = k * ((seg + 7) / 8), nsteps = ((nruns + 1) / 2 + 2) / 3 * 3;
     const int col_tiles = (int)cdiv(O, COLS);
+    static_assert(WAVES == 8, "direct_workgroups counts on it");
     const size_t lds_bytes = (size_t)NPL * 2 * nsteps * COLS * 16;
     if (lds_bytes > 160 * 1024) return BNN_ERR_UNSUPPORTED;
     if (workspace_bytes < lds_bytes * col_tiles) return BNN_ERR_WORKSPACE;
+    // one workgroup per CU (registers allow no more), resident for the whole call: two waves per SIMD
+    const int cus = compute_units();
+    if (cus < 1) return BNN_ERR_DEVICE;
+    const long long wgs = direct_workgroups(npix, MT, col_tiles, cus);
     if constexpr (NPL == 1) {
+        const long long simd_products = direct_rounds(npix, MT, wgs) * MT * NT;
         int rc = BNN_OK;
-        if (try_bwn_rect(x, static_cast<const uint32_t*>(weights), thr, y, bits, N, H, W, C, O, k, stride, pad, P, Q, s, &rc)) return rc;
+        // 450 calls of narrow and of flat images, 7x7 stride 4: 4.6 of the rectangle kernel's units for 32 pixels x 64 channels as 64 x 64, 3.6 as 32 x 128
+        const double other = (NT == 2 ? 4.6 : 3.6) * (double)simd_products + (NT == 2 ? 1.6 : 4.);
+        if (try_bwn_rect(x, static_cast<const uint32_t*>(weights), thr, y, bits, N, H, W, C, O, k, stride, pad, P, Q, other, s, &rc)) return rc;
     }
     if (lds_bytes > 64 * 1024) {
         static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bwn_conv_kernel<MT, NT, WAVES, NPL, TERMS>),
@@ -614,16 +631,6 @@ int launch_bwn_direct(const float* x, const void* weights, const float* thr, flo
     else
         launch(conv_f32_expand_kernel, dim3((unsigned)cdiv(nunits, 256)), dim3(256), 0, s,
                            static_cast<const float*>(weights), wexp, C, O, k, COLS, nsteps, nunits, 1);
-    // one workgroup per CU (registers allow no more), resident for the whole call
-    const long long groups = cdiv(npix, MT * 32);
-    static int cus = 0;
-    if (cus == 0) {
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-            cus < 1)
-            return BNN_ERR_DEVICE;
-    }
-    const long long wgs = min(cdiv(groups, WAVES), (long long)max(1, cus / col_tiles));
     dim3 grid((unsigned)wgs, (unsigned)col_tiles);
     launch((bwn_conv_kernel<MT, NT, WAVES, NPL, TERMS>), grid, dim3(WAVES * 64), lds_bytes, s, x, wexp, thr, y, bits, N, H, W, C, O, k, stride,
                        pad, P, Q, make_fastdiv(P * Q), make_fastdiv(Q));
@@ -690,7 +697,7 @@ int launch_bwn_staged(const float* x, const uint32_t* wbits, const float* thr, f
     if (workspace_bytes < (size_t)g.wbytes * cdiv(O, NT * 32)) return BNN_ERR_WORKSPACE;
     int rc = BNN_OK;
     if (try_bwn_pixel(x, wbits, thr, y, bits, N, g.H, g.W, C, O, k, g.stride, g.pad, g.P, g.Q, s, &rc)) return rc;
-    if (try_bwn_rect(x, wbits, thr, y, bits, N, g.H, g.W, C, O, k, g.stride, g.pad, g.P, g.Q, s, &rc)) return rc;
+    if (try_bwn_rect(x, wbits, thr, y, bits, N, g.H, g.W, C, O, k, g.stride, g.pad, g.P, g.Q, BWN_RECT_ANY, s, &rc)) return rc;
     // the fp32 sums are a test / debugging output: only the generic-channel variant carries them
     if (y != nullptr)
         return launch_bwn_staged_v<MT, NT, WAVES, 0, true>(x, wbits, thr, y, bits, N, C, O, k, g, lds_bytes, workspace, s);
@@ -715,7 +722,7 @@ int launch_bwn_conv_thr(const float* x, const uint32_t* wbits, const float* thr,
     int rc = BNN_OK;
     if (k == 11 && stride == 4 && C == 3 && (long long)N * cdiv(P, 4) * cdiv(Q, 8) >= 4096) {
         if (workspace == nullptr || workspace_bytes < (size_t)2 * 28 * 64 * 16 * cdiv(O, 64)) return BNN_ERR_WORKSPACE;
-        if (try_bwn_rect(x, wbits, thr, y, bits, N, H, W, C, O, k, stride, pad, P, Q, s, &rc)) return rc;
+        if (try_bwn_rect(x, wbits, thr, y, bits, N, H, W, C, O, k, stride, pad, P, Q, BWN_RECT_ANY, s, &rc)) return rc;
     }
     BwnTile g;
     size_t lds = 0;
@@ -1085,12 +1092,24 @@ int launch_conv_f32_wave(const float* x, const float* w, const float* thr, float
 // The geometries the wave-private kernel is built for.  true: launched (rc receives the status).  Nine products, direct kernel with its expansion
 // launch -> this one, us, 1 and 32 x 224x224x3 -> 64: 3x3 stride 2 15.0 -> 6.0 and 41 -> 23, 5x5 19.0 -> 7.3 and 58 -> 32, 7x7 29.8 -> 11.1 and
 // 101 -> 62 (-> 128: 160 -> 114); six products alike.  Errors against 64 bits are the same to three digits.
+// Not, at stride 2, where its rectangles of 2 x 16 outputs are mostly empty and there are many: the direct kernel packs 64 consecutive outputs.  561 images
+// of 76 x 1 outputs -> 192, 5x5, 104 us here, 20 there; 456 of 49 x 17 -> 64, 7x7, 91 and 79.  The estimate, in 64 outputs of the direct kernel: 1760 calls of narrow and
+// of flat images, up to 40000 rectangles, 9 of ten within 12 % here and 9 % there.
 bool try_conv_f32_wave(const float* x, const float* w, const float* thr, float* y, uint32_t* bits, int N, int H, int W, int C, int O,
                        int k, int stride, int pad, int P, int Q, int products, void* workspace, size_t workspace_bytes, hipStream_t s,
                        int* rc) {
     if (C != 3 || !(stride == 4 ? k == 7 : stride == 2 && (k == 3 || k == 5 || k == 7))) return false;
     if ((long long)W * C < 2 || (long long)H * W * C >= (1LL << 31)) return false;
     if ((long long)N * cdiv(P, stride) * cdiv(Q, 8) >= (1LL << 31) - 65536) return false;      // no fewer than the rectangles
+    if (stride == 2) {
+        const int cus = compute_units(), col_tiles = (int)cdiv(O, 64);
+        if (cus < 1) { *rc = BNN_ERR_DEVICE; return true; }
+        const long long npix = (long long)N * P * Q, rects = (long long)N * cdiv(P, 2) * cdiv(Q, 16);
+        const long long here = cdiv(rects, 4 * min((int)cdiv(rects, 8), max(1, cus / col_tiles)));              // rectangles, 64 outputs of the busiest SIMD
+        const long long there = 2 * direct_rounds(npix, 2, direct_workgroups(npix, 2, col_tiles, cus));
+        const double share = (k == 3 ? 0.29 : k == 5 ? 0.275 : 0.31) * (products == 6 ? 0.92 : 1.), later = k == 3 ? 0.7 : 0.45;
+        if (share * (double)here > (double)there + later) return false;
+    }
     *rc = stride == 4 ? launch_conv_f32_wave<7, 4, 8>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, products, workspace, workspace_bytes, s)
         : k == 7 ? launch_conv_f32_wave<7, 2, 16>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, products, workspace, workspace_bytes, s)
         : k == 5 ? launch_conv_f32_wave<5, 2, 16>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, products, workspace, workspace_bytes, s)

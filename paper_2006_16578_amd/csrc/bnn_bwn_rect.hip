@@ -332,6 +332,7 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void bwn_rect_kernel(const float*
 
 struct RectCall {
     const float* x; const uint32_t* wbits; const float* thr; float* y; uint32_t* bits;
+    double other;                              // what the caller's own kernel would take (launch_rect)
     int cus;
     hipStream_t s;
 };
@@ -353,8 +354,9 @@ int launch_rect_nt(const RectCall& c, const RectArgs& g) {
     return c.y != nullptr ? launch_rect_v<G, NT, true>(c, g) : launch_rect_v<G, NT, false>(c, g);
 }
 
+// false: the caller's own kernel is the faster one.
 template <class G>
-int launch_rect(const RectCall& c, RectArgs g, int N) {
+bool launch_rect(const RectCall& c, RectArgs g, int N, int* rc) {
     g.tiles_p = (int)cdiv(g.P, G::FP); g.tiles_q = (int)cdiv(g.Q, G::FQ);
     g.ntiles = N * g.tiles_p * g.tiles_q;
     g.div_tiles = make_fastdiv((uint32_t)(g.tiles_p * g.tiles_q));
@@ -370,13 +372,17 @@ int launch_rect(const RectCall& c, RectArgs g, int N) {
         const double cost = (double)per_simd * (n + 0.5) + (per_simd == 1 ? 0.7 : 0.);
         if (n == 2 || cost < best) { best = cost; nt = n; }
     }
-    return nt == 4 ? launch_rect_nt<G, 4>(c, g) : nt == 3 ? launch_rect_nt<G, 3>(c, g) : launch_rect_nt<G, 2>(c, g);
+    // Many rectangles that the image leaves mostly empty: the direct kernel packs 32 consecutive outputs.  16977 images of 6 x 1 outputs -> 64, 7x7 stride 4, 76 us
+    // here, 21 there; 16668 of 1 x 3 -> 128 58 and 18; 1642 of 41 x 3 -> 128 63 and 53; of 26 x 5 51 and 54.
+    if (best > c.other) return false;
+    *rc = nt == 4 ? launch_rect_nt<G, 4>(c, g) : nt == 3 ? launch_rect_nt<G, 3>(c, g) : launch_rect_nt<G, 2>(c, g);
+    return true;
 }
 
 }  // namespace
 
 bool try_bwn_rect(const float* x, const uint32_t* wbits, const float* thr, float* y, uint32_t* bits, int N, int H, int W, int C, int O,
-                  int k, int stride, int pad, int P, int Q, hipStream_t s, int* rc) {
+                  int k, int stride, int pad, int P, int Q, double other, hipStream_t s, int* rc) {
     if (C != 3 || !(k == 7 ? stride == 2 || stride == 4 : k == 11 && stride == 4)) return false;
     if ((long long)H * W * C >= (1LL << 31)) return false;
     if ((long long)N * cdiv(P, 2) * cdiv(Q, 8) >= (1LL << 31) - 65536) return false;
@@ -387,10 +393,14 @@ bool try_bwn_rect(const float* x, const uint32_t* wbits, const float* thr, float
     }
     RectArgs g = {};
     g.H = H; g.W = W; g.O = O; g.pad = pad; g.P = P; g.Q = Q;
-    const RectCall c = {x, wbits, thr, y, bits, cus, s};
-    *rc = k == 11 ? launch_rect<RectGeom<11, 4, 8>>(c, g, N)
-        : stride == 4 ? launch_rect<RectGeom<7, 4, 8>>(c, g, N) : launch_rect<RectGeom<7, 2, 16>>(c, g, N);
-    return true;
+    const RectCall c = {x, wbits, thr, y, bits, other, cus, s};
+    if (k == 11) return launch_rect<RectGeom<11, 4, 8>>(c, g, N, rc);
+    if (stride == 4) return launch_rect<RectGeom<7, 4, 8>>(c, g, N, rc);
+    // 2 x 16 outputs, or 4 x 8 where the busiest SIMD then has fewer rectangles: 491 images of 79 x 3 outputs -> 192 99 -> 56 us (the kernel for staged patches 86), 426 of
+    // 90 x 8 -> 64 37 -> 24 (34).  With as many it is the slower one by 3 to 5 %, four patch rows more: 12 images of 94 x 38 -> 32 6.6 -> 6.95.
+    const long long col_tiles = cdiv(O, 64), wide = N * cdiv(P, 2) * cdiv(Q, 16), tall = N * cdiv(P, 4) * cdiv(Q, 8);
+    if (cdiv(tall * col_tiles, 4LL * cus) < cdiv(wide * col_tiles, 4LL * cus)) return launch_rect<RectGeom<7, 2, 8>>(c, g, N, rc);
+    return launch_rect<RectGeom<7, 2, 16>>(c, g, N, rc);
 }
 
 }  // namespace bnn

@@ -226,9 +226,11 @@ int launch_bwn_conv_thr(const float* x, const uint32_t* wbits, const float* thr,
 // 3x3 and 5x5 windows of 3-channel images, stride 1 or 2 (no workspace).  true: launched, rc receives the status.
 bool try_bwn_pixel(const float* x, const uint32_t* wbits, const float* thr, float* y, uint32_t* bits, int N, int H, int W, int C,
                    int O, int k, int stride, int pad, int P, int Q, hipStream_t s, int* rc);
-// 11x11 windows of 3-channel images, stride 4, and 7x7 ones, stride 2 or 4, likewise.
+// 11x11 windows of 3-channel images, stride 4, and 7x7 ones, stride 2 or 4, likewise, unless the caller's own kernel is estimated to be faster.  other: what
+// that takes, in the time of a SIMD's products of 32 pixels x 32 channels here (BWN_RECT_ANY: it is not asked).
+constexpr double BWN_RECT_ANY = 1e30;
 bool try_bwn_rect(const float* x, const uint32_t* wbits, const float* thr, float* y, uint32_t* bits, int N, int H, int W, int C,
-                  int O, int k, int stride, int pad, int P, int Q, hipStream_t s, int* rc);
+                  int O, int k, int stride, int pad, int P, int Q, double other, hipStream_t s, int* rc);
 int launch_head_f32(const uint32_t* bits, const float* w, float* y, int32_t* pooled, int N, int HW, int C, int J,
                     hipStream_t s);
 

@@ -605,6 +605,30 @@ def test_stem_split_not_finite(bnn, orc, shape, products):
             assert np.array_equal(got[~covers], only[~covers]) and not got[covers].any(), (col, bad)
 
 
+# Narrow and flat images, where a rectangle of outputs is mostly empty: few of them (one kernel), and so many that the kernel which packs consecutive outputs, or
+# rectangles of another shape, serve the call.  Integers are exact in any order; a few images are compared, the others repeat them.
+@pytest.mark.parametrize("weights,k,st,H,W", [("bits", 7, 4, 22, 2), ("bits", 7, 4, 3, 33), ("bits", 7, 2, 31, 2), ("bits", 7, 2, 93, 15), ("bits", 7, 2, 12, 33), ("bits", 11, 4, 9, 12),
+                                              ("f32", 3, 2, 26, 2), ("f32", 5, 2, 37, 35), ("f32", 7, 2, 19, 4), ("f32", 7, 2, 2, 40)])
+@pytest.mark.parametrize("O", [64, 70])
+@pytest.mark.parametrize("images", [3, 4099])
+def test_first_layers_of_narrow_images(bnn, orc, weights, k, st, H, W, O, images):
+    rng = np.random.default_rng(k + st + H + W + O)
+    pad = 2 if k == 11 else k // 2
+    x = rng.integers(-500, 501, size=(5, H, W, 3)).astype(np.float32)
+    many = to_dev(x[np.arange(images) % 5])
+    thr = rng.integers(-4000, 4001, size=O).astype(np.float32)
+    print(weights, k, st, H, W, O, images, flush=True)
+    if weights == "bits":
+        w = wl.random_bits(rng, (O, k, k), 3)
+        ref = orc.bwn_conv_f32(x, w, 3, st, pad)
+        got = words(bnn.bwn_conv_thr(many, to_dev(w), to_dev(thr), 3, st, pad))
+    else:
+        w = rng.integers(-30, 31, size=(O, k, k, 3)).astype(np.float32)
+        ref = orc.conv_f32(x, w, st, pad)
+        got = words(bnn.conv_f32_split_thr(many, to_dev(w), to_dev(thr), st, pad))
+    assert np.array_equal(got, orc.pack_f32(ref, thr)[np.arange(images) % 5])
+
+
 # weights and thresholds of 64 channels at a time go through LDS: groups one channel short, whole and one over, for workgroups of one
 # and of two groups
 @pytest.mark.parametrize("k,st", [(3, 1), (3, 2), (5, 1), (5, 2)])
