@@ -402,32 +402,6 @@ __global__ __launch_bounds__(TL::THREADS, TL::MINW) void mfma_ksplit_kernel(cons
     }
 }
 
-template <class TL>
-int launch_ksplit(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
-    const int col_span = (e.bits != nullptr) ? max(g.cols, e.ldbits_w * 32) : g.cols;
-    const int gx = (int)cdiv(g.rows, TL::ROWS), gy = (int)cdiv(col_span, TL::COLS);
-    const unsigned nwg = (unsigned)(cdiv((long long)gx * gy, 8) * 8);
-    constexpr size_t lds_bytes = TL::LDS_BYTES;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma_ksplit_kernel<TL>),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-    if (attr != hipSuccess) return BNN_ERR_DEVICE;
-    launch((mfma_ksplit_kernel<TL>), dim3(nwg), dim3(TL::THREADS), lds_bytes, s, A, B, g, e, gx, gy);
-    return check_launch();
-}
-
-template <class TL, bool PANELS>
-int launch_bits(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
-    const int col_span = (e.bits != nullptr) ? max(g.cols, e.ldbits_w * 32) : g.cols;
-    const int gx = (int)cdiv(g.rows, TL::ROWS), gy = (int)cdiv(col_span, TL::COLS);
-    const unsigned nwg = (unsigned)(cdiv((long long)gx * gy, 8) * 8);
-    constexpr size_t lds_bytes = TL::LDS_BYTES;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma_bits_kernel<TL, PANELS>),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-    if (attr != hipSuccess) return BNN_ERR_DEVICE;
-    launch((mfma_bits_kernel<TL, PANELS>), dim3(nwg), dim3(TL::THREADS), lds_bytes, s, A, B, g, e, gx, gy);
-    return check_launch();
-}
-
 }  // namespace mfma
 }  // namespace bnn
 #endif
