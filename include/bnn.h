@@ -66,6 +66,10 @@ const char* bnn_bconv_kernel_name(int N, int H, int W, int C, int O, int k, int 
  * can make the library choose a smaller wave tile. */
 #define BNN_OUT_BITS 0
 #define BNN_OUT_INT32 1
+/* Added to out_kind of bnn_bmm_kernel_name_out: the name also tells the program where several share a wave tile -- products of
+ * signs ("_signs") or counts of set bits ("_01", with "_w4" / "_w8" waves or K split over waves, "_ksplit"), and the columns of a
+ * workgroup for few rows ("_c16", "_c32").  Such a name may live until the thread's next call only. */
+#define BNN_NAME_PROGRAM 2
 const char* bnn_bmm_kernel_name_out(int M, int N, int K, int path, int out_kind);
 const char* bnn_bconv_kernel_name_out(int N, int H, int W, int C, int O, int k, int stride, int pad, int path,
                                       int out_kind);

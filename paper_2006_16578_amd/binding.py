@@ -103,8 +103,9 @@ def _check(status: int, what: str) -> None:
         raise BnnError(status, what)
 
 
-def bmm_kernel_name(M: int, N: int, K: int, path: int = PATH_AUTO, int32_out: bool = False) -> str:
-    return load().bnn_bmm_kernel_name_out(int(M), int(N), int(K), int(path), int(bool(int32_out))).decode()
+def bmm_kernel_name(M: int, N: int, K: int, path: int = PATH_AUTO, int32_out: bool = False, program: bool = False) -> str:
+    """program: the name also tells which of the kernels with this wave tile it is (BNN_NAME_PROGRAM)."""
+    return load().bnn_bmm_kernel_name_out(int(M), int(N), int(K), int(path), int(bool(int32_out)) | 2 * int(bool(program))).decode()
 
 
 def bconv_kernel_name(N, H, W, C, O, k, stride, pad, path: int = PATH_AUTO, int32_out: bool = False,

@@ -294,10 +294,12 @@ const char* bnn_bconv_kernel_name(int N, int H, int W, int C, int O, int k, int 
     return bnn_bconv_kernel_name_out(N, H, W, C, O, k, stride, pad, path, BNN_OUT_BITS);
 }
 const char* bnn_bmm_kernel_name_out(int M, int N, int K, int path, int out_kind) {
+    const int program = out_kind & BNN_NAME_PROGRAM;
+    out_kind &= ~BNN_NAME_PROGRAM;
     if (M < 1 || N < 1 || K < 1 || K > BNN_MAX_K || (out_kind != BNN_OUT_BITS && out_kind != BNN_OUT_INT32)) return "invalid";
     Geom g = {};
     g.rows = M; g.cols = N; g.conv = 0; g.taps = 1; g.tw = round4(words(K)); g.bits_tap = K;
-    return path == BNN_PATH_VALU ? describe_valu(g) : describe_mfma(g, out_kind == BNN_OUT_INT32);
+    return path == BNN_PATH_VALU ? describe_valu(g) : describe_mfma(g, out_kind == BNN_OUT_INT32, program ? NAME_PROGRAM : 0);
 }
 const char* bnn_bconv_kernel_name_out(int N, int H, int W, int C, int O, int k, int stride, int pad, int path,
                                       int out_kind) {

@@ -164,13 +164,13 @@ int launch_valu(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
 int launch_mfma(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 // Skinny matrix products (at most 128 rows): workgroups of 16 or 32 columns x all rows whose waves split K.
 bool mfma_skinny_takes(const Geom& g);
-const char* describe_mfma_skinny(const Geom& g);
+const char* describe_mfma_skinny(const Geom& g, bool program);
 int launch_mfma_skinny(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 // Matrix products on bits as {0, 1}: the tile for a product (BITS_NONE: another kernel serves it).
 enum BitsChoice { BITS_NONE = 0, BITS_256x256, BITS_256x128, BITS_192x128, BITS_128x128, BITS_128x128W8, BITS_128x64, BITS_K64x64, BITS_K32x32 };
 BitsChoice mfma_bits_choice(const Geom& g, const Epi& e, int tile);       // tile: pick_tile's
 int launch_mfma_bits(BitsChoice tile, const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
-const char* describe_mfma_bits(BitsChoice tile);
+const char* describe_mfma_bits(BitsChoice tile, bool program);
 int launch_mfma_bits_panels(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 // 3x3 stride-1 pad-1 convolutions with at most 128 channels in and out: filters resident in LDS, wave-private input patches.
 bool mfma_conv_patch_takes(const Geom& g, const Epi& e);
@@ -196,6 +196,7 @@ int launch_mfma_conv_v1(const uint32_t* A, const uint32_t* B, const Geom& g, con
 int launch_mfma_conv_v1_stream(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 // Name of the kernel variant launch_mfma / launch_valu would pick for this geometry.
 // (flags: those of bnn_bconv_kernel_name_ex.)
+constexpr int NAME_PROGRAM = 1 << 16;      // a flag beside BNN_CONV_*: see BNN_NAME_PROGRAM
 const char* describe_mfma(const Geom& g, bool int32_out = false, int flags = 0);
 const char* describe_valu(const Geom& g);
 

@@ -66,7 +66,8 @@ int launch_mfma(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
 }
 
 const char* describe_mfma(const Geom& g, bool int32_out, int flags) {
-    if (mfma_skinny_takes(g)) return describe_mfma_skinny(g);
+    const bool program = (flags & NAME_PROGRAM) != 0;
+    if (mfma_skinny_takes(g)) return describe_mfma_skinny(g, program);
     static int32_t some_output;
     static uint32_t some_bits;
     Epi e = {};                                   // the choice only asks which outputs there are, never touches them
@@ -85,7 +86,7 @@ const char* describe_mfma(const Geom& g, bool int32_out, int flags) {
     };
     e.sums_tiled = (flags & (BNN_CONV_RESIDUAL | BNN_CONV_KEEP_SUM)) && g.cols % 32 == 0 ? 1 : 0;
     const int tile = mfma::pick_tile(g, &e);
-    if (const BitsChoice bt = mfma_bits_choice(g, e, tile)) return describe_mfma_bits(bt);
+    if (const BitsChoice bt = mfma_bits_choice(g, e, tile)) return describe_mfma_bits(bt, program);
     const bool pools = (flags & BNN_CONV_POOL2) && mfma_conv_pools(g, e);
     if (!pools && mfma_conv_band_takes(g, e)) return "mfma_fp4_conv3x3_band_wg64";
     if (mfma_conv_patch_takes(g, e)) return describe_mfma_conv_patch(g);
@@ -94,14 +95,15 @@ const char* describe_mfma(const Geom& g, bool int32_out, int flags) {
     const char* suffix = pools ? "_pool2" : mfma::streams_residual(g, e) ? "_stream" : "";
     if (tile == 3 && mfma_conv_taps_takes(g, e, pools)) return with_suffix("mfma_fp4_conv_taps_wg32x32", suffix);
     const bool st = !g.b_tiled && !e.sums_tiled && staged_ok(g, tile);
+    auto product = [&](const char* base) { return program ? with_suffix(base, "_signs") : base; };
     switch (tile) {
         case 0: return g.conv ? with_suffix(st ? "mfma_fp4_conv_lds_wg256x128" : "mfma_fp4_conv_wg256x128", suffix)
-                              : (st ? "mfma_fp4_bmm_lds_wg256x128" : "mfma_fp4_bmm_wg256x128");
+                              : product(st ? "mfma_fp4_bmm_lds_wg256x128" : "mfma_fp4_bmm_wg256x128");
         case 1: return g.conv ? with_suffix(st ? "mfma_fp4_conv_lds_wg512x64" : "mfma_fp4_conv_wg512x64", suffix)
-                              : (st ? "mfma_fp4_bmm_lds_wg512x64" : "mfma_fp4_bmm_wg512x64");
+                              : product(st ? "mfma_fp4_bmm_lds_wg512x64" : "mfma_fp4_bmm_wg512x64");
         case 2: return g.conv ? with_suffix(st ? "mfma_fp4_conv_lds_wg128x128" : "mfma_fp4_conv_wg128x128", suffix)
-                              : (st ? "mfma_fp4_bmm_lds_wg128x128" : "mfma_fp4_bmm_wg128x128");
-        default: return g.conv ? with_suffix("mfma_fp4_conv_wg64x64", suffix) : "mfma_fp4_bmm_wg64x64";
+                              : product(st ? "mfma_fp4_bmm_lds_wg128x128" : "mfma_fp4_bmm_wg128x128");
+        default: return g.conv ? with_suffix("mfma_fp4_conv_wg64x64", suffix) : product("mfma_fp4_bmm_wg64x64");
     }
 }
 

@@ -113,15 +113,16 @@ int launch_mfma_bits(BitsChoice tile, const uint32_t* A, const uint32_t* B, cons
     }
 }
 
-const char* describe_mfma_bits(BitsChoice tile) {
+const char* describe_mfma_bits(BitsChoice tile, bool program) {
     switch (tile) {
-        case BITS_256x256: return "mfma_fp4_bmm_xlds_wg256x256";
-        case BITS_256x128: return "mfma_fp4_bmm_lds_wg256x128";
-        case BITS_192x128: return "mfma_fp4_bmm_lds_wg192x128";
-        case BITS_128x128: case BITS_128x128W8: return "mfma_fp4_bmm_lds_wg128x128";
-        case BITS_128x64: return "mfma_fp4_bmm_lds_wg128x64";
-        case BITS_K64x64: return "mfma_fp4_bmm_wg64x64";
-        default: return "mfma_fp4_bmm_wg32x32";
+        case BITS_256x256: return program ? "mfma_fp4_bmm_xlds_wg256x256_01" : "mfma_fp4_bmm_xlds_wg256x256";
+        case BITS_256x128: return program ? "mfma_fp4_bmm_lds_wg256x128_01" : "mfma_fp4_bmm_lds_wg256x128";
+        case BITS_192x128: return program ? "mfma_fp4_bmm_lds_wg192x128_01" : "mfma_fp4_bmm_lds_wg192x128";
+        case BITS_128x128: return program ? "mfma_fp4_bmm_lds_wg128x128_01_w4" : "mfma_fp4_bmm_lds_wg128x128";
+        case BITS_128x128W8: return program ? "mfma_fp4_bmm_lds_wg128x128_01_w8" : "mfma_fp4_bmm_lds_wg128x128";
+        case BITS_128x64: return program ? "mfma_fp4_bmm_lds_wg128x64_01" : "mfma_fp4_bmm_lds_wg128x64";
+        case BITS_K64x64: return program ? "mfma_fp4_bmm_wg64x64_01_ksplit" : "mfma_fp4_bmm_wg64x64";
+        default: return program ? "mfma_fp4_bmm_wg32x32_01_ksplit" : "mfma_fp4_bmm_wg32x32";
     }
 }
 

@@ -234,9 +234,12 @@ bool columns16(const Geom& g, int col_span) { return g.rows <= 16 || cdiv(col_sp
 
 bool mfma_skinny_takes(const Geom& g) { return !g.conv && !g.b_tiled && g.rows <= 128; }
 
-const char* describe_mfma_skinny(const Geom& g) {
-    if (takes16(g)) return "mfma_fp4_bmm_skinny_m16";
-    return g.rows <= 32 ? "mfma_fp4_bmm_skinny_m32" : g.rows <= 64 ? "mfma_fp4_bmm_skinny_m64" : "mfma_fp4_bmm_skinny_m128";
+const char* describe_mfma_skinny(const Geom& g, bool program) {
+    if (takes16(g)) return program ? "mfma_fp4_bmm_skinny_m16_c16" : "mfma_fp4_bmm_skinny_m16";
+    const bool c16 = program && columns16(g, (int)cdiv(g.cols, 128) * 128), c32 = program && !c16;       // (output rows of packed words are padded to four)
+    if (g.rows <= 32) return c16 ? "mfma_fp4_bmm_skinny_m32_c16" : c32 ? "mfma_fp4_bmm_skinny_m32_c32" : "mfma_fp4_bmm_skinny_m32";
+    if (g.rows <= 64) return c16 ? "mfma_fp4_bmm_skinny_m64_c16" : c32 ? "mfma_fp4_bmm_skinny_m64_c32" : "mfma_fp4_bmm_skinny_m64";
+    return c16 ? "mfma_fp4_bmm_skinny_m128_c16" : c32 ? "mfma_fp4_bmm_skinny_m128_c32" : "mfma_fp4_bmm_skinny_m128";
 }
 
 int launch_mfma_skinny(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
