@@ -166,11 +166,12 @@ int launch_mfma(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& 
 bool mfma_skinny_takes(const Geom& g);
 const char* describe_mfma_skinny(const Geom& g, bool program);
 int launch_mfma_skinny(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
-// Matrix products on bits as {0, 1}: the tile for a product (BITS_NONE: another kernel serves it).
-enum BitsChoice { BITS_NONE = 0, BITS_256x256, BITS_256x128, BITS_192x128, BITS_128x128, BITS_128x128W8, BITS_128x64, BITS_K64x64, BITS_K32x32 };
+// Matrix products on bits as {0, 1}: the tile for a product (BITS_SIGNS256x256: the kernel for signs of that tile; BITS_NONE: another kernel serves it).
+enum BitsChoice { BITS_NONE = 0, BITS_256x256, BITS_256x128, BITS_192x128, BITS_128x128, BITS_128x128W8, BITS_128x64, BITS_K64x64, BITS_K32x32, BITS_SIGNS256x256 };
 BitsChoice mfma_bits_choice(const Geom& g, const Epi& e, int tile);       // tile: pick_tile's
 int launch_mfma_bits(BitsChoice tile, const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 const char* describe_mfma_bits(BitsChoice tile, bool program);
+int launch_mfma_signs(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma_bits_panels(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 // 3x3 stride-1 pad-1 convolutions with at most 128 channels in and out: filters resident in LDS, wave-private input patches.
 bool mfma_conv_patch_takes(const Geom& g, const Epi& e);

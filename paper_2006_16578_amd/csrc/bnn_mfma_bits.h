@@ -15,8 +15,8 @@
 // room for slabs of 512 bits -- four lanes of a load cover 64 neighbouring bytes of a row, half as many lines per instruction as with 256 -- and one
 // barrier for eight K-steps.
 //
-// Measured, us, the kernel that expanded into LDS -> this one: bits of 16384^3 1427 -> 1219 (7.2 P binary op/s), of 8192^3 183 -> 160, of 4096^3 24.9 -> 22.8, of
-// 4096x4096x1024 10.7 -> 10.4; sums of 8192^3 197 -> 182.  On the way, 16384^3: signs as {0, 1} with the row operand still expanded in LDS 1336, both packed 1275, operands
+// Measured, us, the kernel that expanded into LDS -> this one: bits of 16384^3 1414 -> 1195 (7.4 P binary op/s), of 8192^3 182 -> 160, of 4096^3 24.8 -> 23.0, of
+// 4096x4096x2048 14.1 -> 14.0 (x1024 9.5 -> 10.0: left to that kernel, bnn_mfma_signs.hip); sums of 8192^3 197 -> 182.  On the way, 16384^3: signs as {0, 1} with the row operand still expanded in LDS 1336, both packed 1275, operands
 // made one row tile ahead of their MFMAs with an even mix of instructions 1228, no masks where K is whole slabs (FULL) 1219.  Tried: four waves of 128 x 128 (one per
 // SIMD, 256 accumulators) 1234, and slower below (4096^3 25.5).
 #ifndef BNN_MFMA_BITS_H
@@ -203,12 +203,15 @@ __global__ __launch_bounds__(TL::THREADS, TL::MINW) void mfma_bits_kernel(const 
 #pragma unroll
     for (int j = 0; j < NT; ++j) col_set[j] = set_lds[RA + wn * (NT * 32) + 32 * j + l32];
     const float* row_lds = set_lds + wm * (MT * 32) + 4 * half;
-    auto subtract_set = [&](int i) {
+    auto subtract_set = [&](int i, auto columns) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const float row_set = row_lds[32 * i + 8 * (r >> 2) + (r & 3)];
+        for (int q = 0; q < 4; ++q) {
+            const float4 row_set = *reinterpret_cast<const float4*>(row_lds + 32 * i + 8 * q);
+            const float rs[4] = {row_set.x, row_set.y, row_set.z, row_set.w};
 #pragma unroll
-            for (int j = 0; j < NT; ++j) acc[i][j][r] += row_set + col_set[j];
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[i][j][4 * q + r] += decltype(columns)::value ? rs[r] + col_set[j] : rs[r];
         }
     };
     const long long m0 = m_base + (long long)wm * (MT * 32);
@@ -217,9 +220,10 @@ __global__ __launch_bounds__(TL::THREADS, TL::MINW) void mfma_bits_kernel(const 
         int thi[NT];
         bool cok[NT];
         column_thresholds<NT>(thi, cok, n0, l32, g, e);
-        epilogue_bits<MT, NT, PANELS>(acc, m0, n0, lane, g, e, -g.bits_tap, thi, cok, subtract_set);
+        // the column's count goes to the threshold instead: one addition to a sum (4096 x 4096 bits out, K = 1024 10.3 -> 10.0 us, 4096 23.3 -> 23.0)
+        epilogue_bits<MT, NT, PANELS>(acc, m0, n0, lane, g, e, -g.bits_tap, thi, cok, [&](int i) { subtract_set(i, std::false_type{}); }, col_set);
     } else {
-        epilogue_sums<MT, NT>(acc, m0, n0, lane, g, e, -g.bits_tap, subtract_set);
+        epilogue_sums<MT, NT>(acc, m0, n0, lane, g, e, -g.bits_tap, [&](int i) { subtract_set(i, std::true_type{}); });
     }
 }
 

@@ -403,15 +403,15 @@ __device__ __forceinline__ void column_thresholds(int (&thi)[NT], bool (&cok)[NT
 // one v_cmp per accumulator register gives two packed words.
 // PANELS: the packed output is laid out in panels of 8 words (word wi of row `row` at ((wi / 8) * rows + row) * 8 + wi % 8).
 // POOL: rows in the order of Geom::pool2, the windows' bits are stored too.
-// before(i): called ahead of row tile i (a kernel whose sums are not finished until then).
+// before(i): called ahead of row tile i (a kernel whose sums are not finished until then); col: what is still missing from every sum of a column.
 struct Nothing { __device__ __forceinline__ void operator()(int) const {} };
 template <int MT, int NT, bool PANELS = false, bool POOL = false, class Before = Nothing>
 __device__ __forceinline__ void epilogue_bits(v16f (&acc)[MT][NT], const long long m0, const int n0, const int lane,
                                               const Geom& g, const Epi& e, const int corr_all, const int (&thi)[NT],
-                                              const bool (&cok)[NT], const Before& before = Before()) {
+                                              const bool (&cok)[NT], const Before& before = Before(), const float* col = nullptr) {
     float thf[NT];
 #pragma unroll
-    for (int j = 0; j < NT; ++j) thf[j] = cok[j] ? (float)thi[j] + (float)corr_all : __builtin_inff();
+    for (int j = 0; j < NT; ++j) thf[j] = cok[j] ? (float)thi[j] + (float)corr_all - (col != nullptr ? col[j] : 0.f) : __builtin_inff();
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
         const long long rbase = m0 + 32 * i;

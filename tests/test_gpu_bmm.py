@@ -50,7 +50,7 @@ def test_ragged_shapes(bnn, orc, pname, path):
 # ragged shapes large enough to select each LDS-staged tile of the matrix-core path
 STAGED = [(3000, 2500, 1000, "mfma_fp4_bmm_lds_wg128x128"), (5000, 5100, 1234, "mfma_fp4_bmm_xlds_wg256x256"),
           (131100, 50, 200, "mfma_fp4_bmm_lds_wg512x64"), (4097, 3001, 4100, "mfma_fp4_bmm_lds_wg256x128"),
-          # the 256 x 256 tile with operands expanded into LDS: ragged edges on both sides, a last slab that is
+          # the 256 x 256 tile for signs, its row operand expanded into LDS: ragged edges on both sides, a last slab that is
           # half empty (K words = 4 mod 8), a single slab pair, and a short K that keeps the 256 x 128 kernel
           (4097, 3700, 1100, "mfma_fp4_bmm_xlds_wg256x256"), (3850, 4200, 1024, "mfma_fp4_bmm_xlds_wg256x256"),
           (4000, 4000, 800, "mfma_fp4_bmm_lds_wg256x128")]
@@ -391,19 +391,27 @@ def test_skinny_16_rows(bnn, orc, M, N, K):
     assert np.array_equal(bits, want)
 
 
-# The kernels that multiply bits as {0, 1}, on each of their tiles: last row and column tiles of one row or column and one short of whole, K off every word, granule,
-# chunk and slab (an odd and an even number of 256-bit chunks, one slab, the last one partly filled), wider leading dimensions, and output words beyond the last
-# column -- whole tiles of them.
-BITS = [(129, 1, 2426, 0, "wg32x32"), (160, 505, 8310, 1, "wg32x32"), (191, 65, 1281, 1, "wg32x32"), (161, 31, 2049, 0, "wg64x64"), (142, 7, 1262, 0, "wg64x64"),
-        (4673, 40, 6064, 0, "wg64x64"), (197, 4133, 1285, 1, "lds_wg128x64"), (912, 4258, 523, 0, "lds_wg128x64"), (16001, 513, 3333, 0, "lds_wg128x64"),
-        (2738, 1117, 520, 0, "lds_wg128x128"), (1921, 2047, 2304, 1, "lds_wg128x128"), (3204, 1848, 1793, 0, "lds_wg192x128"), (3001, 2047, 3500, 1, "lds_wg192x128"),
-        (4097, 3001, 3620, 0, "lds_wg256x128"), (2700, 2218, 3876, 1, "lds_wg256x128"), (3841, 4000, 1300, 0, "xlds_wg256x256"),
-        (4353, 3001, 2070, 0, "xlds_wg256x256"), (4122, 3046, 517, 1, "xlds_wg256x256")]
+# The kernels that multiply bits as {0, 1}, on each of their tiles and for both outputs: last row and column tiles of one row or column and one short of whole, K off every word,
+# granule, chunk and slab (an odd and an even number of 256-bit chunks and of the K-split tiles' slabs, one slab, the last one partly filled) and in whole slabs (the form without
+# masks, which counts the last slab twice), wider leading dimensions, and output words beyond the last column -- whole tiles of them.  The kernel for signs of the
+# 256 x 256 tile and the direct one beside them.
+BITS = [(129, 1, 2426, 0, "wg32x32_01_ksplit"), (160, 505, 8310, 1, "wg32x32_01_ksplit"), (191, 65, 1281, 1, "wg32x32_01_ksplit"), (161, 31, 2049, 0, "wg32x32_01_ksplit"),
+        (161, 33, 8192, 0, "wg32x32_01_ksplit"), (129, 66, 4096, 1, "wg32x32_01_ksplit"), (142, 7, 1262, 0, "wg64x64_signs"), (133, 1, 512, 1, "wg64x64_signs"),
+        (4673, 40, 6064, 0, "wg64x64_01_ksplit"), (569, 917, 3967, 1, "wg64x64_01_ksplit"), (129, 3297, 4649, 1, "wg64x64_01_ksplit"), (4410, 1, 3903, 0, "wg64x64_01_ksplit"),
+        (5667, 65, 4744, 0, "wg64x64_01_ksplit"), (193, 2751, 5120, 1, "wg64x64_01_ksplit"), (197, 4133, 1285, 1, "wg64x64_signs"),
+        (912, 4258, 523, 0, "lds_wg128x64_01"), (4909, 162, 2048, 0, "lds_wg128x64_01"), (3001, 2047, 3500, 1, "lds_wg128x64_01"), (5441, 641, 1024, 1, "lds_wg128x64_01"),
+        (5432, 670, 825, 1, "lds_wg128x64_01"), (2738, 1117, 520, 0, "lds_wg128x128_01_w8"), (1921, 2047, 2304, 1, "lds_wg128x128_signs"), (1975, 1985, 628, 1, "lds_wg128x128_01_w8"), (4282, 412, 1024, 0, "lds_wg128x128_01_w8"),
+        (1336, 2325, 1283, 1, "lds_wg128x128_01_w8"), (4225, 1522, 1944, 0, "lds_wg128x128_01_w4"), (1817, 3303, 2646, 0, "lds_wg128x128_01_w4"), (2185, 2752, 2416, 0, "lds_wg128x128_01_w4"),
+        (3255, 2049, 1443, 1, "lds_wg128x128_01_w8"), (1921, 3320, 2048, 1, "lds_wg128x128_01_w4"), (2700, 2218, 3876, 1, "lds_wg128x128_01_w4"), (3204, 1848, 1793, 0, "lds_wg192x128_01"),
+        (1537, 2690, 2048, 0, "lds_wg192x128_01"), (16001, 513, 3333, 0, "lds_wg192x128_01"), (3402, 1181, 4530, 1, "lds_wg192x128_01"), (2056, 2049, 4834, 1, "lds_wg192x128_01"),
+        (4097, 3001, 3620, 0, "lds_wg256x128_01"), (4865, 4481, 2048, 0, "lds_wg256x128_01"), (3585, 4210, 2560, 1, "lds_wg256x128_01"), (5134, 3045, 2689, 1, "lds_wg256x128_01"),
+        (3841, 4000, 1300, 0, "xlds_wg256x256_signs"), (5522, 2757, 1024, 0, "xlds_wg256x256_signs"), (4353, 3001, 2070, 0, "xlds_wg256x256_01"), (4609, 2700, 1536, 0, "xlds_wg256x256_01"),
+        (4433, 3162, 1358, 0, "xlds_wg256x256_01"), (5455, 2242, 3283, 1, "xlds_wg256x256_01"), (2978, 4278, 11264, 1, "xlds_wg256x256_01"), (4122, 3046, 517, 1, "lds_wg128x64_01")]
 
 
 @pytest.mark.parametrize("M,N,K,int32_out,kernel", BITS)
 def test_bits_as_zero_and_one(bnn, orc, M, N, K, int32_out, kernel):
-    assert bnn.bmm_kernel_name(M, N, K, int32_out=bool(int32_out)) == "mfma_fp4_bmm_" + kernel
+    assert bnn.bmm_kernel_name(M, N, K, int32_out=bool(int32_out), program=True) == "mfma_fp4_bmm_" + kernel
     rng = np.random.default_rng(M + N + K)
     kw = bnn.nwords(K)
     A, B = (np.zeros((r, bnn.round_up(kw, 4) + x), np.uint32) for r, x in ((M, 0), (N, 8)))
@@ -434,5 +442,16 @@ def test_bits_as_zero_and_one(bnn, orc, M, N, K, int32_out, kernel):
 def test_skinny_columns(bnn, orc, M, N, K):
     name = "m16" if M <= 16 and N < 4096 else "m32" if M <= 32 else "m64" if M <= 64 else "m128"
     assert bnn.bmm_kernel_name(M, N, K) == "mfma_fp4_bmm_skinny_" + name
-    test_bits_as_zero_and_one(bnn, orc, M, N, K, 0, "skinny_" + name)
-    test_bits_as_zero_and_one(bnn, orc, M, N, K, 1, "skinny_" + name)
+    columns = "_c16" if M <= 16 or N <= 4096 else "_c32"
+    test_bits_as_zero_and_one(bnn, orc, M, N, K, 0, "skinny_" + name + columns)
+    test_bits_as_zero_and_one(bnn, orc, M, N, K, 1, "skinny_" + name + columns)
+
+
+# Real-valued operands, real-valued sums: what these kernels store as fp32 (edges of tiles; whole blocks and single elements), and the ones for few rows
+@pytest.mark.parametrize("M,N,K", [(3001, 2047, 3500), (161, 31, 2049), (4673, 2000, 2048), (129, 66, 600), (40, 5000, 700), (5249, 2300, 3283)])
+def test_general_product_ragged(bnn, orc, M, N, K):
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A, B = (torch.randn((r, K), device="cuda", generator=g) for r in (M, N))
+    A[0, :5], B[N - 1, :5] = 0.0, -0.0
+    sign = lambda X: torch.where(X >= 0, 1.0, -1.0)
+    assert torch.equal(bnn.bmm_general_f32(A, B), sign(A) @ sign(B).t().contiguous())          # exact: whole numbers below 2^24
