@@ -172,6 +172,7 @@ BitsChoice mfma_bits_choice(const Geom& g, const Epi& e, int tile);       // til
 int launch_mfma_bits(BitsChoice tile, const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 const char* describe_mfma_bits(BitsChoice tile, bool program);
 int launch_mfma_signs(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
+int launch_mfma_signs_panels(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 int launch_mfma_bits_panels(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s);
 // 3x3 stride-1 pad-1 convolutions with at most 128 channels in and out: filters resident in LDS, wave-private input patches.
 bool mfma_conv_patch_takes(const Geom& g, const Epi& e);

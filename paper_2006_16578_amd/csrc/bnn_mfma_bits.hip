@@ -162,12 +162,15 @@ const char* describe_mfma_bits(BitsChoice tile, bool program) {
 }
 
 // Operands in K panels (g.tw a multiple of 8, lda_w / ldb_w unused); e.bits, if set, receives panels too
-// (e.ldbits_w = 8 * number of output panels).  Any shape; the tile is sized for large ones.
+// (e.ldbits_w = 8 * number of output panels).  Any shape; the tile is sized for large ones.  On {0, 1} where tiles fill the chip and K is long enough for its cheaper
+// K-steps, else as products of signs.  Bits / sums, signs -> {0, 1}, us: 4096 x 4096, K = 1024 8.8 -> 10.0 / 16.4 -> 18.1, 4096 23.1 -> 23.2 / 30.7 -> 31.2, 8192 42.7 -> 41.4 / 50.7 ->
+// 48.8; 20000 x 20000 sums, K = 2048 458 -> 481, 4096 705 -> 715; 2048 x 2048 x 16384 68 -> 72 / 71 -> 75.  (Sums of 16384 columns are the exception, 0.93 to 0.97 of the time from K = 1024 on.)
 int launch_mfma_bits_panels(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
     if (g.conv || g.b_tiled || (g.tw & 7) || g.rows >= (1LL << 31)) return BNN_ERR_UNSUPPORTED;
     if (e.bits != nullptr && (e.out != nullptr || e.out16 != nullptr || e.resid != nullptr || e.resid16 != nullptr ||
                               e.resid_bits != nullptr || (e.ldbits_w & 7)))
         return BNN_ERR_UNSUPPORTED;
+    if (cdiv(g.rows, 256) * cdiv(g.cols, 256) < 208 || g.tw <= 128) return launch_mfma_signs_panels(A, B, g, e, s);
     return launch_bits<T256x256, true>(A, B, g, e, s);
 }
 

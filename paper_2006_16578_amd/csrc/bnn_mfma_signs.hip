@@ -1,9 +1,11 @@
-// Bits of large matrix products with a K of 1024 to 1280: operands are signs, the row operand is expanded to E2M1 ONCE per workgroup, on its way into LDS, and
-// the waves read finished MFMA operands; the column operand travels through LDS packed and every wave expands its own two column fragments a K-step ahead.
+// Large matrix products as products of signs: bits with a K of 1024 to 1280, and operands in K panels unless K is long.  The row operand is expanded to E2M1 ONCE per
+// workgroup, on its way into LDS, and the waves read finished MFMA operands; the column operand travels through LDS packed and every wave expands its own two column fragments a
+// K-step ahead.
 //
 // Beyond, the kernel that counts on {0, 1} (bnn_mfma_bits.h) has the cheaper K-steps; what it begins and ends with -- 512 bits to load ahead of the first
 // product, a row's and a column's count to subtract from every sum -- costs about 0.6 us more.  4096 x 4096 bits out, this kernel / that one (graph replays): K = 1024 9.5 / 10.0
-// us, 1280 10.7 / 11.7, 2048 14.1 / 14.0, 4096 24.8 / 23.0; 8192 x 8192 x 1024 34.9 / 37.2.
+// us, 1280 10.7 / 11.7, 2048 14.1 / 14.0, 4096 24.8 / 23.0; 8192 x 8192 x 1024 34.9 / 37.2.  In panels: K = 1024 8.8 / 10.0, 2048 13.2 / 14.6, 4096 23.1 / 23.2, 8192 42.7 / 41.4;
+// 2048 x 2048, whose 64 tiles leave the chip's power to spare, 8.4 / 9.6 and, K = 16384, 68 / 72.
 //
 // A workgroup of 8 waves owns a 256 x 256 tile (a wave: 128 x 64, 4 x 2 accumulators).  A row fragment is shared by 4 waves: it is expanded once, by the thread that fetched
 // it from global memory.  A column fragment is shared by only 2: its packed words are written once and each wave expands the two of its next K-step itself.  One
@@ -40,6 +42,9 @@ constexpr int BP = TILE + 4;                        // units between the two pla
 constexpr int A_UNITS = 8 * WS;
 constexpr int BUF_UNITS = A_UNITS + 2 * BP;         // A expanded: 8 words x 257 units; B packed: 2 planes of 4 words per row
 
+// PANELS: both operands (and the packed output, if there is one) are in the K-panel layout of bnn.h -- panel p holds words 8p .. 8p+7 of every row back to
+// back -- so that a loader wave's 16-byte loads of one slab cover 1 KB of contiguous memory (8 lines of 128 bytes) instead of 32 bytes in each of 32 lines.
+template <bool PANELS>
 __global__ __launch_bounds__(NTHREADS, 1) void mfma_signs_kernel(const uint32_t* __restrict__ A, const uint32_t* __restrict__ B,
                                                              Geom g, Epi e, int gx, int gy) {
     extern __shared__ uint4 lds[];                  // 2 * BUF_UNITS
@@ -58,16 +63,17 @@ __global__ __launch_bounds__(NTHREADS, 1) void mfma_signs_kernel(const uint32_t*
     // loader: thread -> row tid / 2 of A and of B, words 4 * (tid % 2) .. + 3 of every slab.  K-step v of a slab multiplies
     // word v of the lower half-wave's four words and word v of the upper one's: word v + 4 * half, in both operands.
     const int lrow = tid >> 1, lpart = tid & 1;
-    const uint32_t* ap = A + min(m_base + lrow, g.rows - 1) * (long long)g.lda_w + 4 * lpart;
-    const uint32_t* bp = B + (long long)min(n_base + lrow, g.cols - 1) * g.ldb_w + 4 * lpart;
-    const int kwords = g.tw;
+    const uint32_t* ap = A + min(m_base + lrow, g.rows - 1) * (long long)(PANELS ? 8 : g.lda_w) + 4 * lpart;
+    const uint32_t* bp = B + (long long)min(n_base + lrow, g.cols - 1) * (PANELS ? 8 : g.ldb_w) + 4 * lpart;
+    const int kwords = g.tw;                        // PANELS: a multiple of 8 (whole panels, pad bits 0)
     const int nslabs = (kwords + 7) / 8;
+    const long long a_slab = PANELS ? g.rows * 8 : 8, b_slab = PANELS ? (long long)g.cols * 8 : 8;   // words from slab to slab
 
     uint4 ga, gb;
-    // a slab part past the end of K reads the start of the row instead: a valid address, and the store masks it
-    auto slab_offset = [&](int s) { return s * 8 + 4 * lpart < kwords ? s * 8 : -4 * lpart; };
-    auto load_a = [&](int s) { ga = *reinterpret_cast<const uint4*>(ap + slab_offset(s)); };
-    auto load_b = [&](int s) { gb = *reinterpret_cast<const uint4*>(bp + slab_offset(s)); };
+    // a slab part past the end of K (row-major operands only) reads the start of the row instead: a valid address, and the store masks it
+    auto slab_offset = [&](int s, long long step) { return (PANELS || s * 8 + 4 * lpart < kwords) ? s * step : (long long)(-4 * lpart); };
+    auto load_a = [&](int s) { ga = *reinterpret_cast<const uint4*>(ap + slab_offset(s, a_slab)); };
+    auto load_b = [&](int s) { gb = *reinterpret_cast<const uint4*>(bp + slab_offset(s, b_slab)); };
     auto store_a = [&](int buf, int s, auto masked) {
         const uint32_t keep = (!decltype(masked)::value || s * 8 + 4 * lpart < kwords) ? 0xFFFFFFFFu : 0u;
         uint4* base = lds + buf * BUF_UNITS + (4 * lpart) * WS + lrow;
@@ -160,23 +166,33 @@ __global__ __launch_bounds__(NTHREADS, 1) void mfma_signs_kernel(const uint32_t*
     const long long m0 = m_base + (long long)wm * (MT * 32);
     const int n0 = n_base + wn * (NT * 32);
     const int corr_all = nslabs * 256 - g.bits_tap;
-    int thi[NT];
-    bool cok[NT];
-    mfma::column_thresholds<NT>(thi, cok, n0, l32, g, e);
-    mfma::epilogue_bits<MT, NT>(acc, m0, n0, lane, g, e, corr_all, thi, cok);
+    if (!PANELS || e.bits != nullptr) {             // uniform
+        int thi[NT];
+        bool cok[NT];
+        mfma::column_thresholds<NT>(thi, cok, n0, l32, g, e);
+        mfma::epilogue_bits<MT, NT, PANELS>(acc, m0, n0, lane, g, e, corr_all, thi, cok);
+    } else {
+        mfma::epilogue_sums<MT, NT>(acc, m0, n0, lane, g, e, corr_all);
+    }
+}
+
+template <bool PANELS>
+int launch_signs(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
+    const int gx = (int)cdiv(g.rows, TILE), gy = (int)cdiv(e.bits != nullptr ? max(g.cols, e.ldbits_w * 32) : g.cols, TILE);
+    const unsigned nwg = (unsigned)(cdiv((long long)gx * gy, 8) * 8);
+    constexpr size_t lds_bytes = (size_t)2 * BUF_UNITS * 16;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma_signs_kernel<PANELS>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
+    if (attr != hipSuccess) return BNN_ERR_DEVICE;
+    launch(mfma_signs_kernel<PANELS>, dim3(nwg), dim3(NTHREADS), lds_bytes, s, A, B, g, e, gx, gy);
+    return check_launch();
 }
 
 }  // namespace
 
-int launch_mfma_signs(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
-    const int gx = (int)cdiv(g.rows, TILE), gy = (int)cdiv(max(g.cols, e.ldbits_w * 32), TILE);
-    const unsigned nwg = (unsigned)(cdiv((long long)gx * gy, 8) * 8);
-    constexpr size_t lds_bytes = (size_t)2 * BUF_UNITS * 16;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma_signs_kernel),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-    if (attr != hipSuccess) return BNN_ERR_DEVICE;
-    launch(mfma_signs_kernel, dim3(nwg), dim3(NTHREADS), lds_bytes, s, A, B, g, e, gx, gy);
-    return check_launch();
-}
+// Bits, row-major operands
+int launch_mfma_signs(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) { return launch_signs<false>(A, B, g, e, s); }
+// Bits or sums, everything but sums in K panels
+int launch_mfma_signs_panels(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) { return launch_signs<true>(A, B, g, e, s); }
 
 }  // namespace bnn

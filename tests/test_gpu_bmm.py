@@ -435,6 +435,25 @@ def test_bits_as_zero_and_one(bnn, orc, M, N, K, int32_out, kernel):
         assert np.array_equal(bits, want)
 
 
+# Operands in K panels: products of signs, and counts on {0, 1} from 208 tiles of 256 x 256 and more than 4096 bits on (two K around that; ragged rows, columns and last panel)
+@pytest.mark.parametrize("M,N,K", [(3585, 3801, 4096), (3585, 3801, 4097), (3585, 3801, 4700), (3329, 3800, 5120), (3328, 3073, 4700), (257, 255, 4700)])
+def test_panels_on_both_kernels(bnn, orc, M, N, K):
+    rng = np.random.default_rng(M + N + K)
+    kw = bnn.nwords(K)
+    A, B = (wl.random_bits(rng, (r,), K, ldw=bnn.round_up(kw, 4)) for r in (M, N))
+    A[0], B[0, :kw] = A[M - 1], 0
+    tau = rng.integers(-60, 61, size=N).astype(np.int32)
+    tau[::7], tau[3::5] = -2 ** 31, 2 ** 31 - 1
+    pm = lambda X: torch.from_numpy(np.unpackbits(X[:, :kw].copy().view(np.uint8), axis=1, bitorder="little")[:, :K].astype(np.float32) * 2 - 1).cuda()
+    ref = host(pm(A) @ pm(B).t().contiguous()).astype(np.int32)           # exact: whole numbers below 2^24
+    Ap, Bp = bnn.panels_from_rows(to_dev(A), K), bnn.panels_from_rows(to_dev(B), K)
+    assert np.array_equal(host(bnn.bmm_panels(Ap, Bp, K)), ref)
+    packed = np.packbits(ref >= tau, axis=1, bitorder="little")
+    want = np.zeros((M, bnn.round_up(bnn.nwords(N), 8)), np.uint32)
+    want.view(np.uint8)[:, :packed.shape[1]] = packed
+    assert np.array_equal(words(bnn.bmm_thr_panels(Ap, Bp, to_dev(tau), K)), orc.panels(want, N))
+
+
 # Few rows: 16 columns to a workgroup while that is at most a workgroup per compute unit (4096 columns), 32 beyond; up to 16 rows always 16.  Row counts around the row
 # tiles, columns around 4096, K off every group and chunk, less than one chunk per wave and several; thresholds beyond every sum, sums of wider leading dimensions.
 @pytest.mark.parametrize("M,N,K", [(16, 4096, 700), (1, 4097, 4100), (13, 9001, 129), (17, 4095, 513), (31, 4096, 8200), (32, 4097, 4096), (17, 5003, 31), (33, 4096, 1000),
