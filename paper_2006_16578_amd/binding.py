@@ -9,7 +9,10 @@ from __future__ import annotations
 
 import contextlib
 import ctypes
+import importlib
 import os
+import sys
+import warnings
 
 import torch
 
@@ -73,22 +76,43 @@ def load() -> ctypes.CDLL:
 
 # The native module behind the calls whose kernels are short (csrc/bnn_python.cpp): each function there does what its namesake here does with
 # its defaults, in a third of the host time, or returns None for whatever is out of the ordinary, and the code here goes on.
-# bmm_thr of 8 x 4096 x 4096, passes queued one after another: 7.4 -> 4.6 us (the launch itself is 3.3 us of host time, the kernel runs 3.7).
+# bmm_thr of 8 x 4096 x 4096, passes queued one after another: 7.4 -> 4.0 to 4.8 us (which, differs from process to process).
 _native = None
 
 
-def _load_native():
-    global _native
+class _PythonOnly:
+    """In the native module's place where it does not load: every call goes on in Python."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _native_stamp() -> str:
+    """What a build of the native module is good for: the torch and the interpreter it was compiled against."""
+    return "torch %s, Python %d.%d" % (torch.__version__, sys.version_info[0], sys.version_info[1])
+
+
+def _native_module():
+    """The native module, initialised; raises ImportError if it is not built, or built for another torch or interpreter."""
+    module = importlib.import_module("._native", __package__)
+    if module.built_for != _native_stamp():
+        raise ImportError("_native.so was built for %s, this is %s" % (module.built_for, _native_stamp()))
     lib = load()
-    try:
-        from . import _native as module
-    except ImportError as e:
-        raise ImportError("_native.so is not built: run `python -m paper_2006_16578_amd.build` "
-                          "(or __graft_entry__.build()) first") from e
     stream = _raw_stream if _raw_stream is not None else lambda index: torch.cuda.current_stream(index).cuda_stream
     module.init({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in EXPORTS}, stream, _check)
-    _native = module
     return module
+
+
+def _load_native():
+    """Sets _native: the module, or what makes every call go by ctypes if that does not load (said once)."""
+    global _native
+    load()
+    try:
+        _native = _native_module()
+    except ImportError as e:
+        warnings.warn("short calls take about 3 us longer: %s (run `python -m paper_2006_16578_amd.build`)" % e, RuntimeWarning, stacklevel=3)
+        _native = _PythonOnly()
+    return _native
 
 
 def _status_string(status: int) -> str:

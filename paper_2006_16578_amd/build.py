@@ -60,19 +60,26 @@ def _compile(src: str, force: bool) -> str:
 
 def _compile_native(force: bool) -> None:
     """The binding's native module: compiled against torch's headers, resolved against the torch that the process has loaded."""
-    src = os.path.join(CSRC, "bnn_python.cpp")
-    newest = max(os.path.getmtime(p) for p in [src] + _headers())
-    if not force and os.path.exists(NATIVE) and os.path.getmtime(NATIVE) >= newest:
-        return
     import sysconfig
 
     import torch
+
+    from .binding import _native_stamp
+    src = os.path.join(CSRC, "bnn_python.cpp")
     root = os.path.dirname(torch.__file__)
+    cmd = [CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(root, "include"),
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), '-DBNN_BUILT_FOR="%s"' % _native_stamp(), src,
+           "-L" + os.path.join(root, "lib"), "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    # rebuilt when a source is newer, and when the command differs: another torch or interpreter
+    made_by = os.path.join(OBJ, "_native.cmd")
+    newest = max(os.path.getmtime(p) for p in [src] + _headers())
+    if not force and os.path.exists(NATIVE) and os.path.getmtime(NATIVE) >= newest and os.path.exists(made_by) and open(made_by).read() == repr(cmd):
+        return
     tmp = NATIVE + ".tmp.%d" % os.getpid()
-    subprocess.check_call([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(root, "include"),
-                           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), src, "-o", tmp, "-L" + os.path.join(root, "lib"),
-                           "-lc10", "-ltorch_cpu", "-ltorch_python"])
+    subprocess.check_call(cmd + ["-o", tmp])
     os.replace(tmp, NATIVE)
+    with open(made_by, "w") as f:
+        f.write(repr(cmd))
 
 
 def build(force: bool = False, jobs: int = 8) -> str:

@@ -3,6 +3,9 @@ declares; argument validation that needs no GPU returns the documented codes."""
 import ctypes
 import os
 import re
+import sys
+
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -41,6 +44,34 @@ def test_status_strings_and_null_checks():
     n = ctypes.c_size_t()
     assert lib.bnn_net_workspace_bytes(net, 8, ctypes.byref(n)) == 0 and n.value > 0
     assert lib.bnn_net_destroy(net) == 0
+
+
+@pytest.mark.parametrize("there", ["missing", "of another torch"])
+def test_without_the_native_module(monkeypatch, there):
+    # the module only shortens calls: without it, or with one built for another torch, they go by ctypes as ever, and that is said once
+    import types
+    import warnings
+
+    import torch
+    from paper_2006_16578_amd import binding
+    name = "paper_2006_16578_amd._native"
+    if there == "missing":
+        monkeypatch.setitem(sys.modules, name, None)
+    else:
+        monkeypatch.setitem(sys.modules, name, types.SimpleNamespace(built_for="torch 1.0, Python 3.0", init=lambda *a: pytest.fail("taken")))
+    monkeypatch.setattr(binding, "_native", None)
+    x = torch.zeros((4, 4), dtype=torch.int32)
+    with pytest.warns(RuntimeWarning, match="short calls"), pytest.raises(TypeError, match="device tensor"):
+        binding.bmm(x, x, 128)
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        with pytest.raises(TypeError, match="device tensor"):
+            binding.maxpool_or(x, 32, 2, 2)
+
+
+def test_the_native_module_is_of_this_torch():
+    from paper_2006_16578_amd import binding
+    assert binding._native_module().built_for == binding._native_stamp()
 
 
 def test_kernel_choice_is_host_logic():
