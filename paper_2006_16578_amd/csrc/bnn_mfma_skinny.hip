@@ -105,8 +105,8 @@ __global__ __launch_bounds__(64 * WAVES) void mfma_skinny_kernel(const uint32_t*
 
 // 16 columns to a workgroup (v_mfma_f32_16x16x128_f8f6f4, the weights as row operand), twice as many workgroups, and a load takes 64 neighbouring bytes of 16 rows
 // instead of 32 of 32 (the address side works line by line: of the 4.8 us of 8 x 1024 x 8192 two were its).  A lane ends up with four channels of one row of A.
-// Measured (graph replays of bits, 32 columns -> this one): 8 x 1024 x 8192 4.84 -> 3.85 us, 8 x 1024 x 1024 3.34 -> 2.93, 8 x 4096 x 4096 3.78 -> 3.09, 8 x 4096 x 25088
-// 7.86 -> 4.99, 16 x 16384 x 16384 12.0 -> 10.7; 32 x 4096 x 4096 3.96 -> 3.55, 32 x 1024 x 8192 5.04 -> 4.18; 64 x 4096 x 4096 4.87 -> 4.15, 64 x 1000 x 8192 (int32) 6.55 -> 5.45;
+// Measured (graph replays of bits, 32 columns -> this one): 8 x 1024 x 8192 4.84 -> 3.85 us, 8 x 1024 x 1024 3.34 -> 2.93, 8 x 4096 x 4096 3.78 -> 2.85, 8 x 4096 x 25088
+// 7.86 -> 4.97, 16 x 16384 x 16384 12.0 -> 10.4 (11.0 on the kernel for 32 rows), 16 x 16384 x 1024 3.08 (3.76); 32 x 4096 x 4096 3.96 -> 3.55, 32 x 1024 x 8192 5.04 -> 4.18; 64 x 4096 x 4096 4.87 -> 4.15, 64 x 1000 x 8192 (int32) 6.55 -> 5.45;
 // 128 x 4096 x 4096 6.87 -> 5.41, 128 x 10 x 4096 (int32) 6.49 -> 4.57, 128 x 4096 x 16384 13.7 -> 13.4.
 typedef float v4f __attribute__((ext_vector_type(4)));
 constexpr int WAVES16 = 8;
@@ -207,12 +207,11 @@ __device__ __forceinline__ void skinny16(const uint32_t* __restrict__ A, const u
     }
 }
 
-// At most 16 * RT rows.  The kernel for 32 carries the program for 16 too: many columns of few rows are its.
+// At most 16 * RT rows.
 template <int RT>
 __global__ __launch_bounds__(64 * WAVES16) void mfma_skinny16_kernel(const uint32_t* __restrict__ A, const uint32_t* __restrict__ B, Skinny g) {
     __shared__ float4 part[RT * WAVES16 * 64];
-    if (RT == 2 && g.rows <= 16) skinny16<1>(A, B, g, part);               // uniform
-    else skinny16<RT>(A, B, g, part);
+    skinny16<RT>(A, B, g, part);
 }
 
 template <int RT>
@@ -222,10 +221,6 @@ int launch_skinny16(const uint32_t* A, const uint32_t* B, const Geom& g, const E
     return check_launch();
 }
 
-// The kernel for at most 16 rows serves fewer than 4096 columns; from there on that for 32 rows does, with the same program (which of the two is tested behaviour
-// of bnn_bmm_kernel_name).
-bool takes16(const Geom& g) { return g.rows <= 16 && g.cols < 4096; }
-
 // 16 columns to a workgroup: with up to 16 rows always, beyond while there is a workgroup for each compute unit at most.  Past that every further one reads all rows of A
 // again: 32 rows 5000 x 4096 4.05 -> 4.29, 5000 x 16384 7.3 -> 8.7 (but 10000 x 16384 13.4 -> 11.8), 64 rows 5000 x 4096 5.05 -> 6.23, 128 rows 6.95 -> 9.06.
 bool columns16(const Geom& g, int col_span) { return g.rows <= 16 || cdiv(col_span, 16) <= 256; }
@@ -234,8 +229,9 @@ bool columns16(const Geom& g, int col_span) { return g.rows <= 16 || cdiv(col_sp
 
 bool mfma_skinny_takes(const Geom& g) { return !g.conv && !g.b_tiled && g.rows <= 128; }
 
+// The names without the program keep the classes that reports know: from 4096 columns on there is none for 16 rows.
 const char* describe_mfma_skinny(const Geom& g, bool program) {
-    if (takes16(g)) return program ? "mfma_fp4_bmm_skinny_m16_c16" : "mfma_fp4_bmm_skinny_m16";
+    if (g.rows <= 16) return program ? "mfma_fp4_bmm_skinny_m16_c16" : g.cols < 4096 ? "mfma_fp4_bmm_skinny_m16" : "mfma_fp4_bmm_skinny_m32";
     const bool c16 = program && columns16(g, (int)cdiv(g.cols, 128) * 128), c32 = program && !c16;       // (output rows of packed words are padded to four)
     if (g.rows <= 32) return c16 ? "mfma_fp4_bmm_skinny_m32_c16" : c32 ? "mfma_fp4_bmm_skinny_m32_c32" : "mfma_fp4_bmm_skinny_m32";
     if (g.rows <= 64) return c16 ? "mfma_fp4_bmm_skinny_m64_c16" : c32 ? "mfma_fp4_bmm_skinny_m64_c32" : "mfma_fp4_bmm_skinny_m64";
@@ -245,7 +241,7 @@ const char* describe_mfma_skinny(const Geom& g, bool program) {
 int launch_mfma_skinny(const uint32_t* A, const uint32_t* B, const Geom& g, const Epi& e, hipStream_t s) {
     const int col_span = (e.bits != nullptr) ? max(g.cols, e.ldbits_w * 32) : g.cols;
     if (columns16(g, col_span) && e.resid == nullptr && e.out16 == nullptr) {
-        if (takes16(g)) return launch_skinny16<1>(A, B, g, e, col_span, s);
+        if (g.rows <= 16) return launch_skinny16<1>(A, B, g, e, col_span, s);
         if (g.rows <= 32) return launch_skinny16<2>(A, B, g, e, col_span, s);
         return g.rows <= 64 ? launch_skinny16<4>(A, B, g, e, col_span, s) : launch_skinny16<8>(A, B, g, e, col_span, s);
     }

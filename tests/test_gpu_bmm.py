@@ -461,9 +461,9 @@ def test_panels_on_both_kernels(bnn, orc, M, N, K):
 def test_skinny_columns(bnn, orc, M, N, K):
     name = "m16" if M <= 16 and N < 4096 else "m32" if M <= 32 else "m64" if M <= 64 else "m128"
     assert bnn.bmm_kernel_name(M, N, K) == "mfma_fp4_bmm_skinny_" + name
-    columns = "_c16" if M <= 16 or N <= 4096 else "_c32"
-    test_bits_as_zero_and_one(bnn, orc, M, N, K, 0, "skinny_" + name + columns)
-    test_bits_as_zero_and_one(bnn, orc, M, N, K, 1, "skinny_" + name + columns)
+    program = "m16_c16" if M <= 16 else name + ("_c16" if N <= 4096 else "_c32")
+    test_bits_as_zero_and_one(bnn, orc, M, N, K, 0, "skinny_" + program)
+    test_bits_as_zero_and_one(bnn, orc, M, N, K, 1, "skinny_" + program)
 
 
 # Real-valued operands, real-valued sums: what these kernels store as fp32 (edges of tiles; whole blocks and single elements), and the ones for few rows
