@@ -28,7 +28,7 @@
 //    memory two K-steps ahead and splits them in registers.
 #include <type_traits>
 
-#include "bnn_internal.h"
+#include "bnn_bwn_wave.h"
 
 namespace bnn {
 namespace {
@@ -36,7 +36,6 @@ namespace {
 typedef float v16f_bwn __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf_bwn __attribute__((ext_vector_type(8)));
 typedef float float4_ub __attribute__((ext_vector_type(4), aligned(4)));
-typedef float float2_ub __attribute__((ext_vector_type(2), aligned(4)));
 extern "C" __device__ int bnn_bwn_writelane_i32(int val, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
 
 struct Split3 {
@@ -751,38 +750,18 @@ int launch_bwn_conv_thr(const float* x, const uint32_t* wbits, const float* thr,
 // waves of a workgroup share nothing but the weights (copied to LDS once: the workgroups are persistent) and drift
 // apart, so that on every SIMD one wave stages while the other multiplies.  No barrier after the weights are in.
 // WPL: weight planes (real-valued weights are split like the inputs).
-template <int KS_, int STRIDE_, int CIN_, int FP_, int FQ_>
-struct WaveGeom {
-    static constexpr int KS = KS_, STRIDE = STRIDE_, CIN = CIN_, FP = FP_, FQ = FQ_, WPL = 3;
-    static constexpr int PR = (FP - 1) * STRIDE + KS;                        // patch rows
-    static constexpr int ROW_ELEMS = ((FQ - 1) * STRIDE + KS) * CIN;         // input values of a patch row
-    static constexpr int SEG = KS * CIN;                                     // values of one filter row
-    static constexpr int RPR = (SEG + 7) / 8;                                // runs of 8 per filter row
-    static constexpr int NRUNS = KS * RPR;
-    static constexpr int NSTEPS = (NRUNS + 1) / 2;                           // MFMA K-steps (two runs each)
-    static constexpr int REACH = (FQ - 1) * STRIDE * CIN + 8 * RPR;          // farthest element a run reads from a patch row, + 1
-    static constexpr int PITCH = (2 * (REACH > ROW_ELEMS ? REACH : ROW_ELEMS) + 7) / 8 * 8;    // bytes between patch rows
-    static constexpr int PAIRS = PITCH / 4;                                  // 2-element units written per patch row (data + zeroed slack)
-    static constexpr int PLANE = PR * PITCH;                                 // bytes of one bf16 plane of a patch
-    static constexpr int WUNITS = NRUNS * 64;                                // 16-byte units of one weight plane in LDS
-    static constexpr int WAVES = 8;                                // what fits LDS beside the weights
-    static constexpr size_t LDS = (size_t)WPL * WUNITS * 16 + (size_t)WAVES * 3 * PLANE;
-    static constexpr int LAST = SEG - 8 * (RPR - 1);                         // values of a row's last run
-    static constexpr bool ALIGNED8 = (STRIDE * CIN * 2) % 8 == 0;            // of every run, else 4 bytes
-    static_assert(FP * FQ == 32 && PAIRS <= 64 && (STRIDE * CIN * 2) % 4 == 0, "one lane per pair; aligned runs");
-};
-
-struct WaveArgs {
-    int N, H, W, O, pad, P, Q;
-    int tiles_p, tiles_q;
-    int ntiles;              // N * tiles_p * tiles_q
-    FastDiv div_tiles, div_tq;
+template <int KS_, int STRIDE_, int FQ_>
+struct WaveGeom : wave::PatchGeom<KS_, STRIDE_, FQ_> {
+    typedef wave::PatchGeom<KS_, STRIDE_, FQ_> B;
+    static constexpr int WPL = 3;
+    static constexpr int WUNITS = B::NRUNS * 64;                             // 16-byte units of one weight plane in LDS
+    static constexpr size_t LDS = (size_t)WPL * WUNITS * 16 + (size_t)B::WAVES * 3 * B::PLANE;
 };
 
 template <class G, int TERMS, bool WANT_Y>
 __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const float* __restrict__ x, const float* __restrict__ wv,
                                                                         const float* __restrict__ thr, float* __restrict__ y,
-                                                                        uint32_t* __restrict__ bits, WaveArgs g) {
+                                                                        uint32_t* __restrict__ bits, wave::Args g) {
     constexpr int NT = 2, COLS = 64;
     extern __shared__ uint4 smem[];
     uint4* wlds = smem;                                                // [weight planes][NRUNS][64 columns] units of 8 bf16
@@ -794,13 +773,7 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
 
     float th[NT];
     bool cok[NT];
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-        const int col = n0 + 32 * j + l32;
-        cok[j] = col < g.O;
-        th[j] = ((!WANT_Y || bits != nullptr) && cok[j]) ? thr[col] : __builtin_inff();
-    }
-    const int ow = (g.O + 31) / 32;
+    wave::load_thresholds<NT, WANT_Y>(thr, bits, n0, l32, g.O, th, cok);
 
     // this lane's output pixel inside a rectangle; where its runs start in a patch plane; its column in a weight plane,
     // the upper half-wave one run further (its run index is 2 * step + 1)
@@ -809,72 +782,13 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
     const int dp = l32 % G::FP, dq = l32 / G::FP;
     const char* abase = patch + dp * (G::STRIDE * G::PITCH) + dq * (G::STRIDE * G::CIN * 2);
     const char* bbase = reinterpret_cast<const char*>(wlds + l32) + half * (COLS * 16);
-    const int rowlen = g.W * G::CIN;                                 // values per image row (H * W * C < 2^31: checked on the host)
 
-    // ---- patch prefetch: lane l holds elements 2l, 2l + 1 of every patch row.  A pair may hang over the left or right
-    // edge of the image row by one element (the padding is not a multiple of 2 elements): it is then loaded one element
-    // further in, and stage() picks the element that is image data.
-    float2_ub pre[G::PR];
-    auto tile_origin = [&](int t, int& n, int& p0, int& q0) {
-        n = fast_div(t, g.div_tiles);
-        const int rem = t - n * (g.tiles_p * g.tiles_q);
-        const int tp = fast_div(rem, g.div_tq);
-        p0 = tp * G::FP;
-        q0 = (rem - tp * g.tiles_q) * G::FQ;
-    };
-    auto request = [&](int t) {                // issues the loads of rectangle t's patch; nothing waits here
-        int n, p0, q0;
-        tile_origin(t, n, p0, q0);
-        const int y0 = p0 * G::STRIDE - g.pad;
-        const int e0 = (q0 * G::STRIDE - g.pad) * G::CIN + 2 * lane;                // first element of this lane's pair in the image row
-        const uint32_t lane_bytes = (uint32_t)min(max(e0, 0), rowlen - 2) * 4u;          // rowlen >= 2 (checked on the host)
-        const float* img = x + (long long)n * g.H * rowlen;                             // uniform
-#pragma unroll
-        for (int r = 0; r < G::PR; ++r) {
-            const int yy = min(max(y0 + r, 0), g.H - 1);                                // uniform: rows outside the image are zeroed in stage()
-            const char* rowp = reinterpret_cast<const char*>(img + yy * rowlen);        // uniform: scalar base + lane offset
-            pre[r] = *reinterpret_cast<const float2_ub*>(rowp + lane_bytes);            // 8 bytes, 4-byte aligned
-        }
-    };
-    auto stage = [&](int t) {                  // splits the prefetched patch of rectangle t into the wave's three planes
-        int n, p0, q0;
-        tile_origin(t, n, p0, q0);
-        const int y0 = p0 * G::STRIDE - g.pad;
-        const int e0 = (q0 * G::STRIDE - g.pad) * G::CIN + 2 * lane;
-        const bool shifted = min(max(e0, 0), rowlen - 2) != e0;
-        // element validity as bit masks: inside the image row and inside the patch row's data (beyond it the row's slack
-        // is zeroed); rows above / below the image are zeroed through a wave-uniform mask -- no branch in the loop
-        const uint32_t m0 = (e0 >= 0 && e0 < rowlen && 2 * lane < G::ROW_ELEMS) ? 0xFFFFFFFFu : 0u;
-        const uint32_t m1 = (e0 + 1 >= 0 && e0 + 1 < rowlen && 2 * lane + 1 < G::ROW_ELEMS) ? 0xFFFFFFFFu : 0u;
-        static_assert(2 * (G::PAIRS - 1) >= G::ROW_ELEMS, "the last pair is slack: the lanes past it repeat its stores of zeros");
-        char* dst = patch + 4 * min(lane, G::PAIRS - 1);
-#pragma unroll
-        for (int r = 0; r < G::PR; ++r) {
-            const uint32_t ym = (unsigned)(y0 + r) < (unsigned)g.H ? 0xFFFFFFFFu : 0u;     // uniform
-            // shifted by one element: the left-edge pair holds its second element first, the right-edge pair its first element second
-            const uint32_t ua = __float_as_uint(shifted ? pre[r][1] : pre[r][0]) & m0 & ym;
-            const uint32_t ub = __float_as_uint(shifted ? pre[r][0] : pre[r][1]) & m1 & ym;
-            const float a = __uint_as_float(ua), b = __uint_as_float(ub);
-            const float ra = a - __uint_as_float(ua & 0xffff0000u), rb = b - __uint_as_float(ub & 0xffff0000u);
-            const uint32_t va = __float_as_uint(ra), vb = __float_as_uint(rb);
-            const float la = ra - __uint_as_float(va & 0xffff0000u), lb = rb - __uint_as_float(vb & 0xffff0000u);
-            *reinterpret_cast<uint32_t*>(dst + r * G::PITCH) = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
-            *reinterpret_cast<uint32_t*>(dst + r * G::PITCH + G::PLANE) = __builtin_amdgcn_perm(vb, va, 0x07060302u);
-            *reinterpret_cast<uint32_t*>(dst + r * G::PITCH + 2 * G::PLANE) =
-                __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);
-        }
-    };
-
-    // Rectangle of this wave in round r: whole rounds give a workgroup's waves consecutive rectangles; the last, partial
-    // round is dealt across the workgroups (wave 0 of each first), so that no compute unit runs a full extra round.
-    const int step = (int)gridDim.x * G::WAVES;
-    const int whole = g.ntiles / step;
-    auto tile_of = [&](int r) {
-        if (r < whole) return r * step + (int)blockIdx.x * G::WAVES + wave;
-        return r == whole ? whole * step + wave * (int)gridDim.x + (int)blockIdx.x : g.ntiles;   // past the last round: no rectangle
-    };
-    int t = tile_of(0);
-    if (t < g.ntiles) request(t);              // the first patch is on its way while the weights are staged
+    wave::float2_ub pre[G::PR];                // the patch of the next rectangle, on its way
+    const int ow = (g.O + 31) / 32;
+    const int whole = g.ntiles / ((int)gridDim.x * G::WAVES);
+    int t = wave::tile_of<G>(g, whole, 0, wave);
+    if (t < g.ntiles) wave::request<G>(g, x, t, lane, pre);            // the first one while the weights are staged
+    else wave::no_request<G>(pre);
     {   // weights of this channel tile (w [O][k][k][C]) -> LDS in whole lines, into the patches' space, and from there, split on the way, to
         // their place: unit (plane, run, column) of wlds, a run being 8 consecutive values of one filter row, zero past the row's end; column =
         // output channel.  Each lane fetching its runs by itself (24 loads of 64 lines each) and splitting value by value: 1 x 224x224x3, nine
@@ -926,9 +840,9 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
     }
     __syncthreads();                                                   // the weights are in place and the patches' space is free: the last barrier
     for (int r = 0; t < g.ntiles; ++r) {
-        const int t_next = tile_of(r + 1);
-        stage(t);
-        if (t_next < g.ntiles) request(t_next);
+        const int t_next = wave::tile_of<G>(g, whole, r + 1, wave);
+        wave::stage<G>(g, t, lane, pre, patch);
+        if (t_next < g.ntiles) wave::request<G>(g, x, t_next, lane, pre);
 
         // ---- K loop, unrolled in full: run index of this lane = 2 * step + half; every offset is a compile-time constant
         v16f_bwn acc[NT];
@@ -950,14 +864,7 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
             const char* bsrc = upper_real ? bbase + rho0 * (COLS * 16) : bbase - half * (COLS * 16) + rho0 * (COLS * 16);
 #pragma unroll
             for (int pl = 0; pl < 3; ++pl) {
-                const char* run = asrc + pl * G::PLANE;
-                if constexpr (G::ALIGNED8) {
-                    const uint2 lo = *reinterpret_cast<const uint2*>(run), hi = *reinterpret_cast<const uint2*>(run + 8);
-                    oa[st & 1][pl] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-                } else {
-                    const uint32_t* w = reinterpret_cast<const uint32_t*>(run);
-                    oa[st & 1][pl] = make_uint4(w[0], w[1], w[2], w[3]);
-                }
+                oa[st & 1][pl] = wave::read_run<G>(asrc + pl * G::PLANE);
                 if (pl < G::WPL)
 #pragma unroll
                     for (int j = 0; j < NT; ++j)
@@ -966,21 +873,7 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
         };
         auto multiply = [&](auto st_tag) {
             constexpr int st = decltype(st_tag)::value;
-            // What a row's last run reads past the filter becomes zero here too, not only in the weights: a pixel that is not finite then
-            // touches no output whose window does not cover it, as in the direct kernel.  (256 x 224x224x3 -> 64, 7x7 stride 4: 1 to 2 % of the time.)
-            constexpr int v0 = (2 * st) % G::RPR == G::RPR - 1 ? G::LAST : 8;                  // values of the run each half-wave multiplies
-            constexpr int v1 = 2 * st + 1 >= G::NRUNS ? 0 : (2 * st + 1) % G::RPR == G::RPR - 1 ? G::LAST : 8;
-            auto keep = [&](uint32_t v, int i) {
-                const uint32_t m0 = (2 * i < v0 ? 0xFFFFu : 0u) | (2 * i + 1 < v0 ? 0xFFFF0000u : 0u);
-                const uint32_t m1 = (2 * i < v1 ? 0xFFFFu : 0u) | (2 * i + 1 < v1 ? 0xFFFF0000u : 0u);
-                return m0 == 0xFFFFFFFFu && m1 == 0xFFFFFFFFu ? v : v & (half ? m1 : m0);
-            };
-            if constexpr (v0 < 8 || v1 < 8)
-#pragma unroll
-                for (int pl = 0; pl < 3; ++pl) {
-                    uint4& a = oa[st & 1][pl];
-                    a = make_uint4(keep(a.x, 0), keep(a.y, 1), keep(a.z, 2), keep(a.w, 3));
-                }
+            wave::clear_past_row<G, st>(oa[st & 1], half);             // (256 x 224x224x3 -> 64, 7x7 stride 4: 1 to 2 % of the time)
             // smallest terms first: (input term, weight term) pairs in order of decreasing index sum
 #pragma unroll
             for (int sum = (TERMS == 9 ? 4 : 2); sum >= 0; --sum)
@@ -1011,40 +904,7 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void conv_f32_wave_kernel(const f
             __builtin_amdgcn_sched_barrier(0);
         });
 
-        // ---- epilogue: threshold -> packed bits (and / or the fp32 sums)
-        int n, p0, q0;
-        tile_origin(t, n, p0, q0);
-        const long long img_pix = (long long)n * g.P * g.Q;
-        uint32_t wout[NT];
-#pragma unroll
-        for (int j = 0; j < NT; ++j) wout[j] = 0u;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int lo_row = 8 * (r >> 2) + (r & 3);
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const float v = acc[j][r];
-                if (WANT_Y) {
-                    const int m = lo_row + 4 * half;                   // rectangle pixel of this register in this lane
-                    const int mp = m % G::FP, mq = m / G::FP;
-                    if (p0 + mp < g.P && q0 + mq < g.Q && cok[j])
-                        y[(img_pix + (long long)(p0 + mp) * g.Q + q0 + mq) * g.O + n0 + 32 * j + l32] = v;
-                }
-                if (!WANT_Y || bits != nullptr) {
-                    const unsigned long long ball = __builtin_amdgcn_ballot_w64(v >= th[j]);
-                    wout[j] = (uint32_t)bnn_bwn_writelane_i32((int)(uint32_t)ball, lo_row, (int)wout[j]);
-                    wout[j] = (uint32_t)bnn_bwn_writelane_i32((int)(uint32_t)(ball >> 32), lo_row + 4, (int)wout[j]);
-                }
-            }
-        }
-        if ((!WANT_Y || bits != nullptr) && lane < 32 && p0 + dp < g.P && q0 + dq < g.Q) {
-            const long long pix = img_pix + (long long)(p0 + dp) * g.Q + q0 + dq;
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const int wi = (n0 >> 5) + j;
-                if (wi < ow) bits[pix * ow + wi] = wout[j];
-            }
-        }
+        wave::store<G, NT, WANT_Y>(g, t, acc, th, cok, y, bits, n0, ow, lane);
         t = t_next;                            // every read of this rectangle's patch has been consumed by its MFMAs
     }
 }
@@ -1053,12 +913,9 @@ template <class G, int TERMS, bool WANT_Y>
 int launch_conv_f32_wave_v(const float* x, const float* w, const float* thr, float* y, uint32_t* bits, int N, int H, int W, int O,
                            int pad, int P, int Q, void* workspace, size_t workspace_bytes, hipStream_t s) {
     const int col_tiles = (int)cdiv(O, 64);
-    WaveArgs g;
-    g.N = N; g.H = H; g.W = W; g.O = O; g.pad = pad; g.P = P; g.Q = Q;
-    g.tiles_p = (int)cdiv(P, G::FP); g.tiles_q = (int)cdiv(Q, G::FQ);
-    g.ntiles = N * g.tiles_p * g.tiles_q;
-    g.div_tiles = make_fastdiv((uint32_t)(g.tiles_p * g.tiles_q));
-    g.div_tq = make_fastdiv((uint32_t)g.tiles_q);
+    wave::Args g;
+    g.H = H; g.W = W; g.O = O; g.pad = pad; g.P = P; g.Q = Q;
+    wave::set_tiles<G>(g, N);
     // This kernel splits the weights itself while it stages them; the workspace the entry point asks for (the other
     // first-layer kernels keep their expanded weights there) is checked all the same, so that the call's contract does
     // not depend on which kernel serves a shape.
@@ -1080,7 +937,7 @@ int launch_conv_f32_wave_v(const float* x, const float* w, const float* thr, flo
 template <int KS, int STRIDE, int FQ>
 int launch_conv_f32_wave(const float* x, const float* w, const float* thr, float* y, uint32_t* bits, int N, int H, int W, int O, int pad, int P,
                          int Q, int products, void* workspace, size_t workspace_bytes, hipStream_t s) {
-    typedef WaveGeom<KS, STRIDE, 3, 32 / FQ, FQ> G;
+    typedef WaveGeom<KS, STRIDE, FQ> G;
     static_assert(G::LDS <= LDS_MAX, "weights and eight patches fit LDS");
     if (y != nullptr)
         return products == 6 ? launch_conv_f32_wave_v<G, 6, true>(x, w, thr, y, bits, N, H, W, O, pad, P, Q, workspace, workspace_bytes, s)

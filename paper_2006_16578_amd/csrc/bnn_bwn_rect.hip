@@ -21,43 +21,21 @@
 // waves of a SIMD overlap the rest of each other in part (another wave priority for one of them changes nothing).
 #include <type_traits>
 
-#include "bnn_internal.h"
+#include "bnn_bwn_wave.h"
 
 namespace bnn {
 namespace {
 
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef float float2_ub __attribute__((ext_vector_type(2), aligned(4)));       // 8-byte load, 4-byte aligned
-extern "C" __device__ int bnn_rect_writelane_i32(int val, int lane, int old) __asm("llvm.amdgcn.writelane.i32");
+using wave::v16f;
+using wave::v8bf;
 
 template <int KS_, int STRIDE_, int FQ_>
-struct RectGeom {
-    static constexpr int KS = KS_, STRIDE = STRIDE_, CIN = 3, FQ = FQ_, FP = 32 / FQ_, WAVES = 8;
-    static constexpr int TAPS = KS * KS;
-    static constexpr int PR = (FP - 1) * STRIDE + KS;                        // patch rows
-    static constexpr int ROW_ELEMS = ((FQ - 1) * STRIDE + KS) * CIN;         // input values of a patch row
-    static constexpr int SEG = KS * CIN;                                     // values of one filter row
-    static constexpr int RPR = (SEG + 7) / 8;                                // runs of 8 per filter row
-    static constexpr int LAST = SEG - 8 * (RPR - 1);                         // values of a row's last run
-    static constexpr int NRUNS = KS * RPR;
-    static constexpr int NSTEPS = (NRUNS + 1) / 2;                           // MFMA K-steps (two runs each, one per half-wave)
-    static constexpr int WQ = (NSTEPS + 3) / 4;                              // sign words of a column
-    static constexpr int REACH = (FQ - 1) * STRIDE * CIN + 8 * RPR;          // farthest element a run reads from a patch row, + 1
-    static constexpr int PITCH = (2 * (REACH > ROW_ELEMS ? REACH : ROW_ELEMS) + 7) / 8 * 8;    // bytes between patch rows
-    static constexpr int PAIRS = PITCH / 4;                                  // 2-element units written per patch row (data + zeroed slack)
-    static constexpr int PLANE = PR * PITCH;                                 // bytes of one bf16 plane of a patch
-    static constexpr size_t LDS = (size_t)WAVES * 3 * PLANE;
-    static constexpr bool ALIGNED8 = (STRIDE * CIN * 2) % 8 == 0;            // of every run, else 4 bytes
-    static_assert(FP * FQ == 32 && PAIRS <= 64 && (STRIDE * CIN * 2) % 4 == 0, "one lane per pair; aligned runs");
-    static_assert(SEG <= 64 && LDS <= 160 * 1024, "a filter row of signs in two words; eight patches in LDS");
-};
-
-struct RectArgs {
-    int H, W, O, pad, P, Q;
-    int tiles_p, tiles_q;
-    int ntiles;              // images * tiles_p * tiles_q
-    FastDiv div_tiles, div_tq;
+struct RectGeom : wave::PatchGeom<KS_, STRIDE_, FQ_> {
+    typedef wave::PatchGeom<KS_, STRIDE_, FQ_> B;
+    static constexpr int TAPS = B::KS * B::KS;
+    static constexpr int WQ = (B::NSTEPS + 3) / 4;                           // sign words of a column
+    static constexpr size_t LDS = (size_t)B::WAVES * 3 * B::PLANE;
+    static_assert(B::SEG <= 64 && LDS <= 160 * 1024, "a filter row of signs in two words; eight patches in LDS");
 };
 
 // bits 0, 2, 4, ... of a word, packed
@@ -72,7 +50,7 @@ __device__ __forceinline__ uint32_t even_bits(uint32_t v) {
 template <class G, int NT, bool WANT_Y>
 __global__ __launch_bounds__(G::WAVES * 64, 1) void bwn_rect_kernel(const float* __restrict__ x, const uint32_t* __restrict__ wbits,
                                                                    const float* __restrict__ thr, float* __restrict__ y,
-                                                                   uint32_t* __restrict__ bits, RectArgs g) {
+                                                                   uint32_t* __restrict__ bits, wave::Args g) {
     constexpr int COLS = 32 * NT, NTHR = G::WAVES * 64;
     extern __shared__ uint4 smem[];
     const int tid = (int)threadIdx.x;
@@ -80,89 +58,23 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void bwn_rect_kernel(const float*
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);        // scalar: everything derived from the rectangle index stays scalar
     char* patch = reinterpret_cast<char*>(smem) + wave * (3 * G::PLANE);      // this wave's three planes
     const int n0 = (int)blockIdx.y * COLS;
-    const int ow = (g.O + 31) / 32;
 
     // this lane's output pixel inside a rectangle (rows vary fastest over the lanes: fewer bank conflicts of the 8-byte reads)
     const int dp = l32 % G::FP, dq = l32 / G::FP;
     const char* abase = patch + dp * (G::STRIDE * G::PITCH) + dq * (G::STRIDE * G::CIN * 2);
     const char* a_same = abase + half * 16;                                   // upper half-wave's run follows in the same filter row
     const char* a_next = abase + half * (G::PITCH - (G::RPR - 1) * 16);       // ... begins the next row
-    const int rowlen = g.W * G::CIN;                                          // values per image row (H * W * C < 2^31: checked on the host)
 
-    // ---- patch prefetch: lane l holds elements 2l, 2l + 1 of every patch row.  A pair may hang over the left or right
-    // edge of the image row by one element: it is then loaded one element further in, and stage() picks the element that is data.
-    float2_ub pre[G::PR];
-    auto tile_origin = [&](int t, int& n, int& p0, int& q0) {
-        n = fast_div(t, g.div_tiles);
-        const int rem = t - n * (g.tiles_p * g.tiles_q);
-        const int tp = fast_div(rem, g.div_tq);
-        p0 = tp * G::FP;
-        q0 = (rem - tp * g.tiles_q) * G::FQ;
-    };
-    auto request = [&](int t) {
-        int n, p0, q0;
-        tile_origin(t, n, p0, q0);
-        const int y0 = p0 * G::STRIDE - g.pad;
-        const int e0 = (q0 * G::STRIDE - g.pad) * G::CIN + 2 * lane;
-        const uint32_t lane_bytes = (uint32_t)min(max(e0, 0), rowlen - 2) * 4u;          // rowlen >= 2 (checked on the host)
-        const float* img = x + (long long)n * g.H * rowlen;                             // uniform
-#pragma unroll
-        for (int r = 0; r < G::PR; ++r) {
-            const int yy = min(max(y0 + r, 0), g.H - 1);                                // uniform: rows outside the image are zeroed in stage()
-            const char* rowp = reinterpret_cast<const char*>(img + yy * rowlen);
-            pre[r] = *reinterpret_cast<const float2_ub*>(rowp + lane_bytes);
-        }
-    };
-    auto stage = [&](int t) {                  // splits the prefetched patch of rectangle t into the wave's three planes
-        int n, p0, q0;
-        tile_origin(t, n, p0, q0);
-        const int y0 = p0 * G::STRIDE - g.pad;
-        const int e0 = (q0 * G::STRIDE - g.pad) * G::CIN + 2 * lane;
-        const bool shifted = min(max(e0, 0), rowlen - 2) != e0;
-        const uint32_t m0 = (e0 >= 0 && e0 < rowlen && 2 * lane < G::ROW_ELEMS) ? 0xFFFFFFFFu : 0u;
-        const uint32_t m1 = (e0 + 1 >= 0 && e0 + 1 < rowlen && 2 * lane + 1 < G::ROW_ELEMS) ? 0xFFFFFFFFu : 0u;
-        static_assert(2 * (G::PAIRS - 1) >= G::ROW_ELEMS, "the last pair is slack: the lanes past it repeat its stores of zeros");
-        char* dst = patch + 4 * min(lane, G::PAIRS - 1);
-#pragma unroll
-        for (int r = 0; r < G::PR; ++r) {
-            const uint32_t ym = (unsigned)(y0 + r) < (unsigned)g.H ? 0xFFFFFFFFu : 0u;     // uniform
-            const uint32_t ua = __float_as_uint(shifted ? pre[r][1] : pre[r][0]) & m0 & ym;
-            const uint32_t ub = __float_as_uint(shifted ? pre[r][0] : pre[r][1]) & m1 & ym;
-            const float a = __uint_as_float(ua), b = __uint_as_float(ub);
-            const float ra = a - __uint_as_float(ua & 0xffff0000u), rb = b - __uint_as_float(ub & 0xffff0000u);
-            const uint32_t va = __float_as_uint(ra), vb = __float_as_uint(rb);
-            const float la = ra - __uint_as_float(va & 0xffff0000u), lb = rb - __uint_as_float(vb & 0xffff0000u);
-            *reinterpret_cast<uint32_t*>(dst + r * G::PITCH) = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
-            *reinterpret_cast<uint32_t*>(dst + r * G::PITCH + G::PLANE) = __builtin_amdgcn_perm(vb, va, 0x07060302u);
-            *reinterpret_cast<uint32_t*>(dst + r * G::PITCH + 2 * G::PLANE) =
-                __builtin_amdgcn_perm(__float_as_uint(lb), __float_as_uint(la), 0x07060302u);
-        }
-    };
+    wave::float2_ub pre[G::PR];                // the patch of the next rectangle, on its way
+    const int ow = (g.O + 31) / 32;
+    const int whole = g.ntiles / ((int)gridDim.x * G::WAVES);
+    int t = wave::tile_of<G>(g, whole, 0, wave);
+    if (t < g.ntiles) wave::request<G>(g, x, t, lane, pre);            // the first one while the weights are prepared
+    else wave::no_request<G>(pre);
 
-    // Rectangle of this wave in round r: whole rounds give a workgroup's waves consecutive rectangles; the last, partial
-    // round is dealt across the workgroups (wave 0 of each first).
-    const int step = (int)gridDim.x * G::WAVES;
-    const int whole = g.ntiles / step;
-    auto tile_of = [&](int r) {
-        if (r < whole) return r * step + (int)blockIdx.x * G::WAVES + wave;
-        return r == whole ? whole * step + wave * (int)gridDim.x + (int)blockIdx.x : g.ntiles;   // past the last round: no rectangle
-    };
-    int t = tile_of(0);
-    if (t < g.ntiles) request(t);              // the first patch is on its way while the weights are prepared
-
-    // ---- thresholds (channels past the last: never reached) and sign words of this lane's NT columns
     float th[NT];
     bool cok[NT];
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-        const int col = n0 + 32 * j + l32;
-        cok[j] = col < g.O;
-        th[j] = __builtin_nanf("");
-        if (!WANT_Y || bits != nullptr) {
-            const float v = thr[min(col, g.O - 1)];
-            th[j] = cok[j] ? v : th[j];
-        }
-    }
+    wave::load_thresholds<NT, WANT_Y>(thr, bits, n0, l32, g.O, th, cok);
     uint32_t sw[G::WQ][NT];                    // step 4q + s, register i: element 2i at bit 4s + i, element 2i + 1 at bit 16 + 4s + i; set: -1
     {
         constexpr int RAW = COLS * G::TAPS, PER = (RAW + NTHR - 1) / NTHR;
@@ -210,9 +122,9 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void bwn_rect_kernel(const float*
     }
 
     for (int r = 0; t < g.ntiles; ++r) {
-        const int t_next = tile_of(r + 1);
-        stage(t);
-        if (t_next < g.ntiles) request(t_next);
+        const int t_next = wave::tile_of<G>(g, whole, r + 1, wave);
+        wave::stage<G>(g, t, lane, pre, patch);
+        if (t_next < g.ntiles) wave::request<G>(g, x, t_next, lane, pre);
 
         v16f acc[NT];
 #pragma unroll
@@ -234,16 +146,7 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void bwn_rect_kernel(const float*
             constexpr int off = (rho0 / G::RPR) * G::PITCH + (rho0 % G::RPR) * 16;
             const char* asrc = !upper ? abase : wraps ? a_next : a_same;
 #pragma unroll
-            for (int pl = 0; pl < 3; ++pl) {
-                const char* run = asrc + off + pl * G::PLANE;
-                if constexpr (G::ALIGNED8) {
-                    const uint2 lo = *reinterpret_cast<const uint2*>(run), hi = *reinterpret_cast<const uint2*>(run + 8);
-                    oa[st & 1][pl] = make_uint4(lo.x, lo.y, hi.x, hi.y);
-                } else {
-                    const uint32_t* w = reinterpret_cast<const uint32_t*>(run);
-                    oa[st & 1][pl] = make_uint4(w[0], w[1], w[2], w[3]);
-                }
-            }
+            for (int pl = 0; pl < 3; ++pl) oa[st & 1][pl] = wave::read_run<G>(asrc + off + pl * G::PLANE);
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 uint32_t reg[4];
@@ -254,21 +157,7 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void bwn_rect_kernel(const float*
         };
         auto multiply = [&](auto st_tag) {
             constexpr int st = decltype(st_tag)::value;
-            // What a row's last run reads past the filter becomes zero here, not in the weights: a pixel that is not finite then touches no
-            // output whose window does not cover it.  (As the values arrive, the masks wait for LDS a step early: 3 to 9 % slower.)
-            constexpr int v0 = (2 * st) % G::RPR == G::RPR - 1 ? G::LAST : 8;                  // values of the run each half-wave multiplies
-            constexpr int v1 = 2 * st + 1 >= G::NRUNS ? 0 : (2 * st + 1) % G::RPR == G::RPR - 1 ? G::LAST : 8;
-            auto keep = [&](uint32_t v, int i) {
-                const uint32_t m0 = (2 * i < v0 ? 0xFFFFu : 0u) | (2 * i + 1 < v0 ? 0xFFFF0000u : 0u);
-                const uint32_t m1 = (2 * i < v1 ? 0xFFFFu : 0u) | (2 * i + 1 < v1 ? 0xFFFF0000u : 0u);
-                return m0 == 0xFFFFFFFFu && m1 == 0xFFFFFFFFu ? v : v & (half ? m1 : m0);
-            };
-            if constexpr (v0 < 8 || v1 < 8)
-#pragma unroll
-                for (int pl = 0; pl < 3; ++pl) {
-                    uint4& a = oa[st & 1][pl];
-                    a = make_uint4(keep(a.x, 0), keep(a.y, 1), keep(a.z, 2), keep(a.w, 3));
-                }
+            wave::clear_past_row<G, st>(oa[st & 1], half);             // (2 to 4 % of the time; as the values arrive 3 to 9)
 #pragma unroll
             for (int pl = 2; pl >= 0; --pl)                            // smallest terms first
 #pragma unroll
@@ -292,40 +181,7 @@ __global__ __launch_bounds__(G::WAVES * 64, 1) void bwn_rect_kernel(const float*
             __builtin_amdgcn_sched_barrier(0);
         });
 
-        // ---- epilogue: threshold -> packed bits (and / or the fp32 sums)
-        int n, p0, q0;
-        tile_origin(t, n, p0, q0);
-        const long long img_pix = (long long)n * g.P * g.Q;
-        uint32_t wout[NT];
-#pragma unroll
-        for (int j = 0; j < NT; ++j) wout[j] = 0u;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int lo_row = 8 * (i >> 2) + (i & 3);
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const float v = acc[j][i];
-                if (WANT_Y) {
-                    const int m = lo_row + 4 * half;                   // rectangle pixel of this register in this lane
-                    const int mp = m % G::FP, mq = m / G::FP;
-                    if (p0 + mp < g.P && q0 + mq < g.Q && cok[j])
-                        y[(img_pix + (long long)(p0 + mp) * g.Q + q0 + mq) * g.O + n0 + 32 * j + l32] = v;
-                }
-                if (!WANT_Y || bits != nullptr) {
-                    const unsigned long long ball = __builtin_amdgcn_ballot_w64(v >= th[j]);
-                    wout[j] = (uint32_t)bnn_rect_writelane_i32((int)(uint32_t)ball, lo_row, (int)wout[j]);
-                    wout[j] = (uint32_t)bnn_rect_writelane_i32((int)(uint32_t)(ball >> 32), lo_row + 4, (int)wout[j]);
-                }
-            }
-        }
-        if ((!WANT_Y || bits != nullptr) && lane < 32 && p0 + dp < g.P && q0 + dq < g.Q) {
-            const long long pix = img_pix + (long long)(p0 + dp) * g.Q + q0 + dq;
-#pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                const int wi = (n0 >> 5) + j;
-                if (wi < ow) bits[pix * ow + wi] = wout[j];
-            }
-        }
+        wave::store<G, NT, WANT_Y>(g, t, acc, th, cok, y, bits, n0, ow, lane);
         t = t_next;                            // every read of this rectangle's patch has been consumed by its MFMAs
     }
 }
@@ -338,7 +194,7 @@ struct RectCall {
 };
 
 template <class G, int NT, bool WANT_Y>
-int launch_rect_v(const RectCall& c, const RectArgs& g) {
+int launch_rect_v(const RectCall& c, const wave::Args& g) {
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bwn_rect_kernel<G, NT, WANT_Y>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)G::LDS);
     if (attr != hipSuccess) return BNN_ERR_DEVICE;
@@ -350,17 +206,14 @@ int launch_rect_v(const RectCall& c, const RectArgs& g) {
 }
 
 template <class G, int NT>
-int launch_rect_nt(const RectCall& c, const RectArgs& g) {
+int launch_rect_nt(const RectCall& c, const wave::Args& g) {
     return c.y != nullptr ? launch_rect_v<G, NT, true>(c, g) : launch_rect_v<G, NT, false>(c, g);
 }
 
 // false: the caller's own kernel is the faster one.
 template <class G>
-bool launch_rect(const RectCall& c, RectArgs g, int N, int* rc) {
-    g.tiles_p = (int)cdiv(g.P, G::FP); g.tiles_q = (int)cdiv(g.Q, G::FQ);
-    g.ntiles = N * g.tiles_p * g.tiles_q;
-    g.div_tiles = make_fastdiv((uint32_t)(g.tiles_p * g.tiles_q));
-    g.div_tq = make_fastdiv((uint32_t)g.tiles_q);
+bool launch_rect(const RectCall& c, wave::Args g, int N, int* rc) {
+    wave::set_tiles<G>(g, N);
     // Channels of a wave (32 NT): the least work for the SIMD with the most waves, the patch of a rectangle costing about as much as the
     // products of 16 channels and a wave that has its SIMD to itself, with nothing to overlap, a little more.  Measured, NT = 2 / 3 / 4, us:
     // n x 224x224x3 -> 128, 11x11: n = 4 8.6 / 10.5 / 12.1, 8 11.8 / 15.0 / 12.8, 12 15.2 / 19.7 / 18.2, 16 19.9 / 25.7 / 18.4, 64 53.7 / 69.5 / 51.5,
@@ -391,7 +244,7 @@ bool try_bwn_rect(const float* x, const uint32_t* wbits, const float* thr, float
         *rc = BNN_ERR_DEVICE;
         return true;
     }
-    RectArgs g = {};
+    wave::Args g = {};
     g.H = H; g.W = W; g.O = O; g.pad = pad; g.P = P; g.Q = Q;
     const RectCall c = {x, wbits, thr, y, bits, other, cus, s};
     if (k == 11) return launch_rect<RectGeom<11, 4, 8>>(c, g, N, rc);
