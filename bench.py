@@ -27,13 +27,14 @@ if ROOT not in sys.path:
 PEAK_FP4_MFMA_TFLOPS = 10.1e3      # 4-bit float matrix cores, TFLOP/s (2 flop per MAC)
 PEAK_HBM_GBS = 8000.0
 PAPER_RESNET18_IMG_S = 5.6e3       # the paper's ResNet-18 throughput on an RTX 2080 (context only)
-# Memory-side bytes per launch of the dominant kernel of the default sweep, from rocprofv3 FETCH_SIZE and
+# Memory-side bytes per launch of the dominant kernels of the default sweep, from rocprofv3 FETCH_SIZE and
 # WRITE_SIZE scaled by a plain copy (profiles/bmm_sweep_dominant_kernel_hbm_traffic.md); bench.py cannot
 # read hardware counters itself, so the measured figure is carried here and reported only for that kernel
 # in the default configuration.
-TRAFFIC_DEFAULT_SWEEP = {"mfma_fp4_bmm_xlds_wg256x256": 5.409e+08,
-                         # the same kernel on K-panel operands (profiles/bmm_sweep_k_panels_kernel_stats_and_counters.md)
-                         "mfma_fp4_bmm_xlds_wg256x256_kpanels": 5.411e+08}
+TRAFFIC_DEFAULT_SWEEP = {"mfma_fp4_bmm_lds_wg256x128": 9.627e+08,         # the int32 sums of the large squares
+                         "mfma_fp4_bmm_xlds_wg256x256": 3.046e+08,        # their bits
+                         # both on K-panel operands (profiles/bmm_sweep_k_panels_kernel_stats_and_counters.md)
+                         "mfma_fp4_bmm_xlds_wg256x256_kpanels": 5.496e+08}
 WIDE_KERNEL = "mfma_fp4_bmm_xlds_wg256x256"
 
 
@@ -125,7 +126,7 @@ def main() -> int:
             sh = {"name": name, "M": M, "N": N, "K": K, "A": A, "B": B, "tau": tau, "Cb": Cb, "C": C, "panels": False,
                   "kernel": bnn.bmm_kernel_name(M, N, K, path),
                   "kernel_i32": bnn.bmm_kernel_name(M, N, K, path, int32_out=True)}
-            if layout == "panels" and sh["kernel"] == WIDE_KERNEL and sh["kernel_i32"] == WIDE_KERNEL:
+            if layout == "panels" and sh["kernel"] == WIDE_KERNEL:
                 sh.update({"panels": True, "A": bnn.panels_from_rows(A, K), "B": bnn.panels_from_rows(B, K),
                            "Cb": torch.empty(((N + 255) // 256, M, 8), dtype=torch.int32, device=dev),
                            "kernel": WIDE_KERNEL + "_kpanels", "kernel_i32": WIDE_KERNEL + "_kpanels"})
