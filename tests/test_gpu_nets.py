@@ -621,12 +621,16 @@ def test_first_layers_of_narrow_images(bnn, orc, weights, k, st, H, W, O, images
     if weights == "bits":
         w = wl.random_bits(rng, (O, k, k), 3)
         ref = orc.bwn_conv_f32(x, w, 3, st, pad)
-        got = words(bnn.bwn_conv_thr(many, to_dev(w), to_dev(thr), 3, st, pad))
+        layer = lambda **kw: bnn.bwn_conv_thr(many, to_dev(w), to_dev(thr), 3, st, pad, **kw)
     else:
         w = rng.integers(-30, 31, size=(O, k, k, 3)).astype(np.float32)
         ref = orc.conv_f32(x, w, st, pad)
-        got = words(bnn.conv_f32_split_thr(many, to_dev(w), to_dev(thr), st, pad))
-    assert np.array_equal(got, orc.pack_f32(ref, thr)[np.arange(images) % 5])
+        layer = lambda **kw: bnn.conv_f32_split_thr(many, to_dev(w), to_dev(thr), st, pad, **kw)
+    packed = orc.pack_f32(ref, thr)[np.arange(images) % 5]
+    assert np.array_equal(words(layer()), packed)
+    bits, y = layer(want_f32=True)
+    assert np.array_equal(words(bits), packed)
+    assert torch.equal(y, to_dev(ref)[torch.arange(images, device="cuda") % 5])
 
 
 # weights and thresholds of 64 channels at a time go through LDS: groups one channel short, whole and one over, for workgroups of one
