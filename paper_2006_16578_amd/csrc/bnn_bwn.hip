@@ -613,8 +613,9 @@ int launch_bwn_direct(const float* x, const void* weights, const float* thr, flo
     if constexpr (NPL == 1) {
         const long long simd_products = direct_rounds(npix, MT, wgs) * MT * NT;
         int rc = BNN_OK;
-        // 450 calls of narrow and of flat images, 7x7 stride 4: 4.6 of the rectangle kernel's units for 32 pixels x 64 channels as 64 x 64, 3.6 as 32 x 128
-        const double other = (NT == 2 ? 4.6 : 3.6) * (double)simd_products + (NT == 2 ? 1.6 : 4.);
+        // 680 calls of narrow and of flat images: 4.6 (7x7 stride 4; 11x11 4.5) of the rectangle kernel's units for 32 pixels x 64 channels as 64 x 64, 3.6 (3.0) as 32 x 128
+        const double per = NT == 2 ? 4.6 : k == 11 ? 3.0 : 3.6, start = NT == 2 ? 1.6 : k == 11 ? 3.3 : 4.;
+        const double other = per * (double)simd_products + start;
         if (try_bwn_rect(x, static_cast<const uint32_t*>(weights), thr, y, bits, N, H, W, C, O, k, stride, pad, P, Q, other, s, &rc)) return rc;
     }
     if (lds_bytes > 64 * 1024) {
